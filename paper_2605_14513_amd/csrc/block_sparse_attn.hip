@@ -101,8 +101,9 @@ constexpr int kPlanMaxHeads = 1024; // beyond this heads are dealt to the XCDs r
 // (i / Nb)-th head.
 
 // One workgroup, after attn_order_kernel: heads ranked by total kept count, greedy
-// assignment of heads (heaviest first) to the least loaded XCD, head table, cursors reset.
-__global__ __launch_bounds__(256) void attn_plan_kernel(int BH, int Nb, int *__restrict__ plan) {
+// assignment of heads (heaviest first) to the least loaded XCD, head table, cursors reset to
+// the number of attention workgroups of their XCD (n_wg in all; those take the first items).
+__global__ __launch_bounds__(256) void attn_plan_kernel(int BH, int Nb, int n_wg, int *__restrict__ plan) {
   __shared__ int w_head[kPlanMaxHeads];
   __shared__ int sorted[kPlanMaxHeads];
   __shared__ int xcd_of[kPlanMaxHeads], rank_of[kPlanMaxHeads];
@@ -156,7 +157,7 @@ __global__ __launch_bounds__(256) void attn_plan_kernel(int BH, int Nb, int *__r
   }
   __syncthreads();
   if (t < kNumXcd) {
-    plan[t] = 0;
+    plan[t] = n_wg / kNumXcd + (t < n_wg % kNumXcd ? 1 : 0);
     plan[kNumXcd + t] = n_heads[t] * Nb;
     plan[2 * kNumXcd + t] = off[t];
   }
@@ -606,14 +607,16 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
 
   // ---- work loop --------------------------------------------------------------------------
   // With a plan the workgroups are persistent (two per CU): each takes items from the list
-  // of its XCD (workgroup ids are dealt round-robin to the XCDs) with an atomic cursor and,
-  // once that list is empty, from the other XCDs' lists.  Without a plan a workgroup
-  // processes the one item its id maps to.
+  // of its XCD (workgroup ids are dealt round-robin to the XCDs) and, once that list is
+  // empty, from the other XCDs' lists.  The first item of a workgroup is the one its number
+  // among the workgroups of its XCD names; the plan starts the cursors behind those, so the
+  // launch does not begin with hundreds of atomics on one cache line.  Without a plan a
+  // workgroup processes the one item its id maps to.
   __shared__ int s_item;
   const int x0 = (int)(blockIdx.x % kNumXcd);
   const int len0 = plan ? plan[kNumXcd + x0] : 0;
   const int off0 = plan ? plan[2 * kNumXcd + x0] : 0;
-  // (thread 0) entry i of XCD x's list: item p = i % Nb of its (i / Nb)-th head
+  // entry i of XCD x's list: item p = i % Nb of its (i / Nb)-th head
   const int *head_tbl = plan + kPlanHdr, *seq = plan + kPlanHdr + 2 * BH;
   int cached_r = -1, cached_head = 0;  // the own list's head currently being walked
   auto entry = [&](int x, int off_x, int i) -> int {
@@ -627,23 +630,42 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     }
     return seq[head * Nb + p];
   };
-  // (thread 0) item for cursor value i_own of the own list, else from another list, else -1
-  auto take = [&](int i_own) -> int {
-    if (i_own >= 0 && i_own < len0) return entry(x0, off0, i_own);
-    for (int k2 = 1; k2 < kNumXcd; ++k2) {
-      const int x = (x0 + k2) % kNumXcd;
-      const int len = plan[kNumXcd + x];
-      if (len <= 0) continue;
-      const int i = atomicAdd(&plan[x], 1);
-      if (i < len) return entry(x, plan[2 * kNumXcd + x], i);
+  // (wavefront 0) an item of another XCD's list, or -1.  Lanes 0..7 look at the eight cursors
+  // at once and an atomic goes only to a list that still has items: same-address atomics of
+  // all XCDs are served one after another (about 40 ns each), and a workgroup that asked every
+  // empty list before it ended made the end of each launch a queue of 8 atomics per workgroup --
+  // 300 us at 1024 workgroups (D = 64, block 64, N = 6417, 20 heads: 406 -> 90 us), 150 us at 512.
+  auto steal = [&]() -> int {
+    const int x = (x0 + 1 + lane) % kNumXcd;  // lane order = the order in which lists are asked
+    const int len = lane < kNumXcd - 1 ? plan[kNumXcd + x] : 0;
+    unsigned long long asked = 0;
+    for (;;) {
+      int cur = 0x7fffffff;
+      if (lane < kNumXcd - 1) cur = __hip_atomic_load(&plan[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const unsigned long long open = __ballot(cur < len) & ~asked;
+      if (!open) return -1;
+      const int l = __ffsll((long long)open) - 1;
+      asked |= 1ull << l;  // (a list that turns out to be empty is not asked again)
+      const int xs = (x0 + 1 + l) % kNumXcd;
+      int i = 0;
+      if (lane == 0) i = atomicAdd(&plan[xs], 1);
+      i = __builtin_amdgcn_readfirstlane(i);
+      if (i < plan[kNumXcd + xs]) return entry(xs, plan[2 * kNumXcd + xs], i);
     }
-    return -1;
   };
   int item = -1;
   if (plan) {
-    if (t == 0) s_item = take(len0 > 0 ? atomicAdd(&plan[x0], 1) : -1);
-    __syncthreads();
-    item = __builtin_amdgcn_readfirstlane(s_item);
+    const int i0 = (int)(blockIdx.x / kNumXcd);
+    if (i0 < len0) {
+      item = __builtin_amdgcn_readfirstlane(entry(x0, off0, i0));
+    } else {
+      if (wave == 0) {
+        const int it = steal();
+        if (lane == 0) s_item = it;
+      }
+      __syncthreads();
+      item = __builtin_amdgcn_readfirstlane(s_item);
+    }
   } else {
     // XCD x takes the x-th eighth of the query blocks of every head, heads in order
     const int per = (Nb + kNumXcd - 1) / kNumXcd;  // query blocks per XCD and head
@@ -651,6 +673,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     const int qb0 = x0 * per + (int)(slot % per);
     if (qb0 < Nb) item = (int)(slot / per) * Nb + qb0;  // else: padding of the last eighth
   }
+  bool own_left = len0 > 0;  // the own list may still have items
   while (item >= 0 && item < BH * Nb) {
   begin_item(item);
   // (thread 0) cursor value and item id of the NEXT item.  The cursor is advanced only in
@@ -658,6 +681,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   // microsecond, and neighbouring rows of a head, whose kept lists overlap, walk through
   // K/V together (reserving the next item a whole row ahead costs a third of the L2 hits).
   int i_next = -1, item_next = -1;
+  const bool own_open = plan && own_left;
 
   if (cnt > 0) {
     // ---- prologue: stages 0 and 1 in flight, S^T and maximum of slice 0 --------------------
@@ -713,7 +737,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
       wait_loads_and_barrier();
 #pragma unroll
       for (int i = 0; i < EPB; ++i) asm volatile("" : "+s"(jn[i]));  // loaded before the barrier
-      if (plan && t == 0 && st + 2 >= T && len0 > 0) i_next = atomicAdd(&plan[x0], 1);
+      if (own_open && t == 0 && st + 2 >= T) i_next = atomicAdd(&plan[x0], 1);
       refill(G_B0);
       // ---- slice s0+1; stage st+2 -> buffers 0 ----
       {
@@ -771,9 +795,11 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     // loads of stages past the end may still be in flight towards LDS
     wait_loads_and_barrier();
   }
-  if (plan && t == 0) {
-    if (i_next < 0 && len0 > 0) i_next = atomicAdd(&plan[x0], 1);  // (row without kept blocks)
-    if (i_next >= 0 && i_next < len0) item_next = entry(x0, off0, i_next);
+  if (own_open && wave == 0) {
+    if (lane == 0 && i_next < 0) i_next = atomicAdd(&plan[x0], 1);  // (row without kept blocks)
+    i_next = __builtin_amdgcn_readfirstlane(i_next);
+    own_left = i_next < len0;
+    if (own_left) item_next = entry(x0, off0, i_next);
   }
 
   // ---- epilogue: normalise, stage through LDS, coalesced bf16 store -----------------------
@@ -806,7 +832,10 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
           *reinterpret_cast<const u32x4_t *>(sO + r * SO + o_c);
   }
   if (!plan) break;
-  if (t == 0) s_item = item_next >= 0 ? item_next : take(-1);
+  if (wave == 0) {
+    if (item_next < 0) item_next = steal();
+    if (lane == 0) s_item = item_next;
+  }
   __syncthreads();  // also: everyone has read the output staging before the next item's loads
   item = __builtin_amdgcn_readfirstlane(s_item);
   }  // work loop
@@ -853,7 +882,7 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
                          BH, Nb, mult, order);
     }
     if (int rc = check_launch("attn_order_kernel")) return rc;
-    hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(256), 0, st, BH, Nb, order);
+    hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(256), 0, st, BH, Nb, (int)grid, order);
     if (int rc = check_launch("attn_plan_kernel")) return rc;
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(BLK * 2), lds, st,
