@@ -92,6 +92,10 @@ constexpr int kNumXcd = 8;
 constexpr int kStageRows = 64;    // key rows per K / V stage buffer (two 32-key slices)
 constexpr int kOrderClasses = 32;   // count classes of the per-head sort
 constexpr int kPlanHdr = 24;        // plan header: 8 cursors, 8 list lengths, 8 list offsets
+#ifndef HEADS_IN_TURN
+#define HEADS_IN_TURN 2
+#endif
+constexpr int kHeadsInTurn = HEADS_IN_TURN;
 constexpr int kPlanMaxHeads = 1024; // beyond this heads are dealt to the XCDs round-robin
 // Plan layout (ints): [0,8) cursors, [8,16) items per XCD list, [16,24) offset of each
 // XCD's heads in the head table, [24, 24+BH) head table (the heads of XCD 0 in the order
@@ -616,51 +620,58 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   const int x0 = (int)(blockIdx.x % kNumXcd);
   const int len0 = plan ? plan[kNumXcd + x0] : 0;
   const int off0 = plan ? plan[2 * kNumXcd + x0] : 0;
-  // entry i of XCD x's list: item p = i % Nb of its (i / Nb)-th head
+  // entry i of a list of `len` items whose heads start at off_x in the head table: the heads one
+  // after the other, or, where a list has few of them, their rows in turn
   const int *head_tbl = plan + kPlanHdr, *seq = plan + kPlanHdr + 2 * BH;
-  int cached_r = -1, cached_head = 0;  // the own list's head currently being walked
-  auto entry = [&](int x, int off_x, int i) -> int {
-    const int r = i / Nb, p = i - r * Nb;
-    int head;
-    if (x == x0 && r == cached_r) {
-      head = cached_head;
-    } else {
-      head = head_tbl[off_x + r];
-      if (x == x0) cached_r = r, cached_head = head;
-    }
-    return seq[head * Nb + p];
+  auto entry = [&](int off_x, int len, int i) -> int {
+    const int nh = len / Nb;
+    const bool in_turn = nh <= kHeadsInTurn;
+    const int r = in_turn ? i % nh : i / Nb, p = in_turn ? i / nh : i - r * Nb;
+    return seq[head_tbl[off_x + r] * Nb + p];
   };
-  // (wavefront 0) an item of another XCD's list, or -1.  Lanes 0..7 look at the eight cursors
-  // at once and an atomic goes only to a list that still has items: same-address atomics of
-  // all XCDs are served one after another (about 40 ns each), and a workgroup that asked every
-  // empty list before it ended made the end of each launch a queue of 8 atomics per workgroup --
-  // 300 us at 1024 workgroups (D = 64, block 64, N = 6417, 20 heads: 406 -> 90 us), 150 us at 512.
-  auto steal = [&]() -> int {
-    const int x = (x0 + 1 + lane) % kNumXcd;  // lane order = the order in which lists are asked
-    const int len = lane < kNumXcd - 1 ? plan[kNumXcd + x] : 0;
+  const int n_own = ((int)gridDim.x - x0 + kNumXcd - 1) / kNumXcd;  // workgroups of this XCD
+  int i_own = (int)(blockIdx.x / kNumXcd);  // (wavefront 0) last entry taken from the own list
+  // (wavefront 0) an item of the own list, else of the list whose next item is the longest, else
+  // -1.  Lanes 0..7 look at the eight cursors at once and an atomic goes only to a list that still
+  // has items: same-address atomics of all XCDs are served one after another (about 40 ns each),
+  // and a workgroup that asked every empty list before it ended made the end of each launch a
+  // queue of 8 atomics per workgroup -- 300 us at 1024 workgroups (D = 64, block 64, N = 6417,
+  // 20 heads: 406 -> 90 us), 150 us at 512.
+  auto take = [&]() -> int {
+    const int x = (x0 + lane) % kNumXcd;
+    const int len = lane < kNumXcd ? plan[kNumXcd + x] : 0;
+    const int off = lane < kNumXcd ? plan[2 * kNumXcd + x] : 0;
     unsigned long long asked = 0;
     for (;;) {
-      int cur = 0x7fffffff;
-      if (lane < kNumXcd - 1) cur = __hip_atomic_load(&plan[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const unsigned long long open = __ballot(cur < len) & ~asked;
-      if (!open) return -1;
-      const int l = __ffsll((long long)open) - 1;
+      uint32_t key = 0;  // kept blocks of the list's next item (own list: first), lane; 0 = empty
+      if (lane < kNumXcd && !((asked >> lane) & 1)) {
+        const int cur = __hip_atomic_load(&plan[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (cur < len) {
+          const int n = lane == 0 ? Nb : min(max(kept_count[entry(off, len, cur)], 0), Nb);
+          key = (uint32_t)(n + 1) * kNumXcd + (uint32_t)(kNumXcd - 1 - lane);
+        }
+      }
+      HEART_WAVE_REDUCE(uint32_t, key, HEART_OP_UMAX);
+      if (key == 0) return -1;
+      const int l = kNumXcd - 1 - (int)(key % kNumXcd);
       asked |= 1ull << l;  // (a list that turns out to be empty is not asked again)
-      const int xs = (x0 + 1 + l) % kNumXcd;
+      const int xs = (x0 + l) % kNumXcd;
       int i = 0;
       if (lane == 0) i = atomicAdd(&plan[xs], 1);
       i = __builtin_amdgcn_readfirstlane(i);
-      if (i < plan[kNumXcd + xs]) return entry(xs, plan[2 * kNumXcd + xs], i);
+      if (i < plan[kNumXcd + xs]) {
+        if (l == 0) i_own = i;
+        return entry(plan[2 * kNumXcd + xs], plan[kNumXcd + xs], i);
+      }
     }
   };
   int item = -1;
   if (plan) {
-    const int i0 = (int)(blockIdx.x / kNumXcd);
-    if (i0 < len0) {
-      item = __builtin_amdgcn_readfirstlane(entry(x0, off0, i0));
+    if (i_own < len0) {
+      item = __builtin_amdgcn_readfirstlane(entry(off0, len0, i_own));
     } else {
       if (wave == 0) {
-        const int it = steal();
+        const int it = take();
         if (lane == 0) s_item = it;
       }
       __syncthreads();
@@ -673,7 +684,6 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     const int qb0 = x0 * per + (int)(slot % per);
     if (qb0 < Nb) item = (int)(slot / per) * Nb + qb0;  // else: padding of the last eighth
   }
-  bool own_left = len0 > 0;  // the own list may still have items
   while (item >= 0 && item < BH * Nb) {
   begin_item(item);
   // (thread 0) cursor value and item id of the NEXT item.  The cursor is advanced only in
@@ -681,7 +691,9 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   // microsecond, and neighbouring rows of a head, whose kept lists overlap, walk through
   // K/V together (reserving the next item a whole row ahead costs a third of the L2 hits).
   int i_next = -1, item_next = -1;
-  const bool own_open = plan && own_left;
+  // (only while every workgroup of the XCD can expect another item of the own list: the last
+  // round looks at the cursors first, so that it ends without a queue of failing atomics)
+  const bool ahead = plan && i_own + n_own < len0;
 
   if (cnt > 0) {
     // ---- prologue: stages 0 and 1 in flight, S^T and maximum of slice 0 --------------------
@@ -737,7 +749,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
       wait_loads_and_barrier();
 #pragma unroll
       for (int i = 0; i < EPB; ++i) asm volatile("" : "+s"(jn[i]));  // loaded before the barrier
-      if (own_open && t == 0 && st + 2 >= T) i_next = atomicAdd(&plan[x0], 1);
+      if (ahead && t == 0 && st + 2 >= T) i_next = atomicAdd(&plan[x0], 1);
       refill(G_B0);
       // ---- slice s0+1; stage st+2 -> buffers 0 ----
       {
@@ -795,11 +807,13 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     // loads of stages past the end may still be in flight towards LDS
     wait_loads_and_barrier();
   }
-  if (own_open && wave == 0) {
+  if (ahead && wave == 0) {
     if (lane == 0 && i_next < 0) i_next = atomicAdd(&plan[x0], 1);  // (row without kept blocks)
     i_next = __builtin_amdgcn_readfirstlane(i_next);
-    own_left = i_next < len0;
-    if (own_left) item_next = entry(x0, off0, i_next);
+    if (i_next < len0) {
+      i_own = i_next;
+      item_next = entry(off0, len0, i_next);
+    }
   }
 
   // ---- epilogue: normalise, stage through LDS, coalesced bf16 store -----------------------
@@ -833,7 +847,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   }
   if (!plan) break;
   if (wave == 0) {
-    if (item_next < 0) item_next = steal();
+    if (item_next < 0) item_next = take();
     if (lane == 0) s_item = item_next;
   }
   __syncthreads();  // also: everyone has read the output staging before the next item's loads
