@@ -495,7 +495,7 @@ def main():
     kidx = torch.zeros((B, H, Nb, Nb), dtype=torch.int32, device=dev)
     kcnt = torch.zeros((B, H, Nb), dtype=torch.int32, device=dev)
     out = torch.empty_like(steps_in[0][0])
-    attn_ws = torch.empty(heart.heart_workspace_bytes(B, H, Nb, D), dtype=torch.uint8, device=dev)
+    attn_ws = torch.empty(heart.heart_attn_workspace_bytes(out, blk), dtype=torch.uint8, device=dev)
     tickets = torch.zeros(heart.heart_pool_drift_workspace_bytes(B, H), dtype=torch.uint8, device=dev)
     # heart_mask_topp_ws (score stage on 8-bit slices: one launch more, pays for long rows)
     from paper_2605_14513_amd.tmr import SLICED_SCORES_MIN_NB

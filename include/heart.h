@@ -224,12 +224,14 @@ int heart_scores_antidiag(const heart_shape *shape, const void *q, const void *k
  * lse: fp32 [B,H,N] natural-log-sum-exp of the scaled logits over the kept keys,
  * or NULL.  A row with kept_count == 0 yields zeros (lse = -inf).
  * Supported: every (D, block) pair of heart_shape.
- * workspace: device memory of at least heart_attn_workspace_bytes(shape) bytes, 16-byte
- * aligned, or NULL.  With a workspace the call first builds a launch plan in it (whole
- * heads are assigned to the XCDs so that the workgroups of an XCD share one head's K/V
- * in its L2; inside a head the query blocks with the longest kept lists start first;
- * workgroups take items with atomic counters, which levels the load).  The results are
- * the same with and without it.  The contents need not be preserved between calls; two
+ * workspace: device memory of heart_attn_workspace_bytes(shape) bytes, 16-byte aligned, or
+ * NULL.  With a workspace the call first builds a launch plan in it (whole heads are
+ * assigned to the XCDs so that the workgroups of an XCD share one head's K/V in its L2;
+ * inside a head the query blocks run in batches of similar kept lists, which then find
+ * each other's K/V there; workgroups take items with atomic counters, which levels the
+ * load).  A workspace of heart_workspace_bytes(B, H, Nb, D) bytes is enough for a plan
+ * without the batches (longest kept lists first), a smaller one is an error.  The results
+ * are the same in all cases.  The contents need not be preserved between calls; two
  * calls that run concurrently must not share a workspace.
  */
 int heart_block_sparse_attn(const heart_shape *shape, const void *q_bf16, const void *k_bf16,
@@ -267,10 +269,11 @@ int heart_block_sparse_attn_static(const heart_shape *shape, const void *q_bf16,
 
 /*
  * Bytes of workspace the hot path can use for one call: only heart_block_sparse_attn takes one
- * (its launch plan: 24 + B*H*(Nb+2) ints); heart_pool_qk, heart_drift and heart_mask_topp
- * need none.  heart_workspace_bytes takes plain sizes (D does not enter; it is part of the
- * signature so that callers can size by the full shape), heart_attn_workspace_bytes a
- * heart_shape; both return 0 for an invalid shape.
+ * (its launch plan); heart_pool_qk, heart_drift and heart_mask_topp need none.
+ * heart_workspace_bytes takes plain sizes (D does not enter; it is part of the signature so that
+ * callers can size by the full shape) and gives the smallest plan, 24 + B*H*(Nb+2) ints;
+ * heart_attn_workspace_bytes takes a heart_shape and gives what the call can make use of: B*H*Nb
+ * ints more for 64 <= Nb <= 1024.  Both return 0 for an invalid shape.
  */
 size_t heart_workspace_bytes(int B, int H, int Nb, int D);
 size_t heart_attn_workspace_bytes(const heart_shape *shape);

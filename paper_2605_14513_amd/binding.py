@@ -307,7 +307,7 @@ HEART_ATTN_FOLD_SCALE = 1  # flag of heart_block_sparse_attn_flags (include/hear
 
 
 def heart_workspace_bytes(B: int, H: int, Nb: int, D: int) -> int:
-    """Bytes of workspace one call of the hot path can use (the attention launch plan)."""
+    """Bytes of the smallest attention launch plan (heart_attn_workspace_bytes: the full one)."""
     return int(load_library().heart_workspace_bytes(int(B), int(H), int(Nb), int(D)))
 
 
@@ -320,8 +320,8 @@ def heart_block_sparse_attn(q, k, v, block: int, kept_idx, kept_count, scale: fl
                             out=None, lse=None, workspace="auto", flags: int = 0):
     """Block-sparse attention over the kept key blocks; returns bf16 out like q.
 
-    workspace: a uint8/int32 GPU tensor of at least heart_attn_workspace_bytes, None (natural
-    launch order), or "auto" (a fresh tensor from torch's allocator).
+    workspace: a uint8/int32 GPU tensor of heart_attn_workspace_bytes (at least
+    heart_workspace_bytes), None (natural launch order), or "auto" (a fresh tensor from torch's allocator).
     flags: 0 (heart_block_sparse_attn) or HEART_ATTN_FOLD_SCALE (heart_block_sparse_attn_flags)."""
     lib = load_library()
     if q.shape != k.shape or q.shape != v.shape:

@@ -37,16 +37,16 @@
 // Scheduling.  Kept counts range from 1 to Nb per row and the densities of the heads
 // differ a lot, the K/V of one head (16.8 MB at N = 32760, D = 128) is far larger than
 // the 4 MB L2 of an XCD, and every query block re-reads its kept K/V blocks.  With a
-// caller-provided workspace the launch therefore follows a plan (attn_order_kernel,
-// attn_plan_kernel): whole heads are assigned to the 8 XCDs (greedily, heaviest head
-// first, by total kept count), each XCD walks through its heads one at a time -- all
-// its workgroups then share one head's K/V through that XCD's L2, and only 8 heads are
-// in flight in the memory-side cache -- and inside a head the rows with the longest
-// kept lists start first (stable counting sort on 32 count classes), so that no long
-// row starts late.  A workgroup takes the next item of its XCD's list with an atomic
-// counter; when that list is exhausted it takes from another XCD's list, which levels
-// whatever imbalance the head assignment left.  Without a workspace an XCD works on a
-// contiguous eighth of the query blocks of every head, in index order.
+// caller-provided workspace the launch therefore follows a plan (attn_plan.hip): whole
+// heads are assigned to the 8 XCDs (greedily, heaviest head first, by total kept count),
+// each XCD walks through its heads one at a time -- all its workgroups then share one
+// head's K/V through that XCD's L2, and only 8 heads are in flight in the memory-side
+// cache -- and inside a head the rows run in batches of similar kept lists (or, in a small
+// workspace, the rows with the longest kept lists first).  A workgroup takes the next item
+// of its XCD's list with an atomic counter; when that list is exhausted it takes from
+// another XCD's list, which levels whatever imbalance the head assignment left.  Without a
+// workspace an XCD works on a contiguous eighth of the query blocks of every head, in index
+// order.
 #include "heart_internal.h"
 
 namespace heart {
@@ -88,165 +88,12 @@ __device__ __forceinline__ u32x4_t head_rsrc_words(const uint16_t *base, uint32_
   return r;
 }
 
-constexpr int kNumXcd = 8;
 constexpr int kStageRows = 64;    // key rows per K / V stage buffer (two 32-key slices)
-constexpr int kOrderClasses = 32;   // count classes of the per-head sort
-constexpr int kPlanHdr = 24;        // plan header: 8 cursors, 8 list lengths, 8 list offsets
-#ifndef HEADS_IN_TURN
-#define HEADS_IN_TURN 2
-#endif
-constexpr int kHeadsInTurn = HEADS_IN_TURN;
-constexpr int kPlanMaxHeads = 1024; // beyond this heads are dealt to the XCDs round-robin
-// Plan layout (ints): [0,8) cursors, [8,16) items per XCD list, [16,24) offset of each
-// XCD's heads in the head table, [24, 24+BH) head table (the heads of XCD 0 in the order
-// it walks them, then those of XCD 1, ...), [24+BH, 24+2BH) total kept count per head,
-// then seq[BH*Nb], head-major: seq[head*Nb + p] = the head's p-th item in launch order
-// (item = head * Nb + query block).  Entry i of an XCD's list is item p = i % Nb of its
-// (i / Nb)-th head.
-
-// One workgroup, after attn_order_kernel: heads ranked by total kept count, greedy
-// assignment of heads (heaviest first) to the least loaded XCD, head table, cursors reset to
-// the number of attention workgroups of their XCD (n_wg in all; those take the first items).
-__global__ __launch_bounds__(256) void attn_plan_kernel(int BH, int Nb, int n_wg, int *__restrict__ plan) {
-  __shared__ int w_head[kPlanMaxHeads];
-  __shared__ int sorted[kPlanMaxHeads];
-  __shared__ int xcd_of[kPlanMaxHeads], rank_of[kPlanMaxHeads];
-  __shared__ int n_heads[kNumXcd], off[kNumXcd];
-  const int t = threadIdx.x;
-  if (BH <= kPlanMaxHeads) {
-    for (int bh = t; bh < BH; bh += 256) w_head[bh] = plan[kPlanHdr + BH + bh];
-    __syncthreads();
-    // rank by (work descending, index ascending)
-    for (int bh = t; bh < BH; bh += 256) {
-      const int w = w_head[bh];
-      int r = 0;
-      for (int j = 0; j < BH; ++j) {
-        const int wj = w_head[j];
-        r += (wj > w) || (wj == w && j < bh);
-      }
-      sorted[r] = bh;
-    }
-    __syncthreads();
-    if (t < 64) {
-      // greedy on one wavefront: lane x < 8 holds the load of XCD x (scaled to 32 bits;
-      // +Nb per head: a row costs about one key block of fixed work); the minimum is a
-      // register-only wave reduction, so a step costs no LDS round trips
-      int shift = 0;
-      while ((((long long)BH * Nb * (Nb + 1)) >> shift) > 0x3fffffffLL) ++shift;
-      uint32_t load = t < kNumXcd ? 0u : 0xffffffffu;
-      int nh = 0;
-      for (int r = 0; r < BH; ++r) {
-        const int bh = sorted[r];
-        const uint32_t m = wave_min_u32(load);
-        const unsigned long long is_min = __ballot(load == m);
-        const int best = __ffsll((long long)is_min) - 1;  // least loaded XCD, lowest id on ties
-        if (t == best) {
-          xcd_of[bh] = best;
-          rank_of[bh] = nh++;
-          load += (uint32_t)(((long long)w_head[bh] + Nb) >> shift);
-        }
-      }
-      if (t < kNumXcd) n_heads[t] = nh;
-    }
-  } else {
-    if (t < kNumXcd) n_heads[t] = BH / kNumXcd + (t < BH % kNumXcd ? 1 : 0);
-  }
-  __syncthreads();
-  if (t == 0) {
-    int run = 0;
-    for (int x = 0; x < kNumXcd; ++x) {
-      off[x] = run;
-      run += n_heads[x];
-    }
-  }
-  __syncthreads();
-  if (t < kNumXcd) {
-    plan[t] = n_wg / kNumXcd + (t < n_wg % kNumXcd ? 1 : 0);
-    plan[kNumXcd + t] = n_heads[t] * Nb;
-    plan[2 * kNumXcd + t] = off[t];
-  }
-  for (int bh = t; bh < BH; bh += 256) {
-    const int x = BH <= kPlanMaxHeads ? xcd_of[bh] : bh % kNumXcd;
-    const int r = BH <= kPlanMaxHeads ? rank_of[bh] : bh / kNumXcd;
-    plan[kPlanHdr + off[x] + r] = bh;
-  }
-}
-
-// One workgroup per head: the Nb items of the head, longest kept list first, into the
-// head's range of seq, and the head's total kept count.  Stable counting sort by count class (class 0 = the longest
-// rows): thread t owns a contiguous segment of the items and one column of the class
-// histogram, so that items of a class keep their natural order.  The counts are first
-// read once, coalesced and all in flight, and kept as class bytes in LDS when they fit
-// (kStaged); otherwise the segments are read from global memory.
-constexpr int kOrderStagedMax = 96 * 1024;  // items whose classes fit next to the histogram
-template <bool kStaged>
-__global__ __launch_bounds__(256) void attn_order_kernel(const int *__restrict__ kept_count, int BH,
-                                                         int Nb, uint32_t mult,
-                                                         int *__restrict__ plan) {
-  const int n = Nb;
-  const int item0 = blockIdx.x * Nb;
-  kept_count += item0;
-  int *order = plan + kPlanHdr + 2 * BH + item0;
-  __shared__ int total;
-  if (threadIdx.x == 0) total = 0;
-  __shared__ int hist[kOrderClasses][256];
-  __shared__ int scan[256];
-  extern __shared__ unsigned char cls_lds[];  // [n] when kStaged
-  const int t = threadIdx.x;
-  const int per = (n + 255) / 256;
-  const int i0 = min(n, t * per), i1 = min(n, i0 + per);
-  // class of a count c in [0, Nb]: (kOrderClasses-1) - floor(c * mult / 2^16) with
-  // mult = floor((kOrderClasses-1) * 2^16 / Nb) from the host (no integer division here)
-  auto cls = [&](int c) -> int {
-    c = min(max(c, 0), Nb);
-    return (kOrderClasses - 1) - (int)(((uint32_t)c * mult) >> 16);
-  };
-  auto cls_of = [&](int i) -> int { return kStaged ? (int)cls_lds[i] : cls(kept_count[i]); };
-#pragma unroll
-  for (int b = 0; b < kOrderClasses; ++b) hist[b][t] = 0;
-  __syncthreads();  // `total` is zero before any wavefront adds to it
-  if (kStaged) {
-#pragma unroll 16
-    for (int i = t; i < n; i += 256) cls_lds[i] = (unsigned char)cls(kept_count[i]);
-    __syncthreads();
-  }
-  for (int i = i0; i < i1; ++i) hist[cls_of(i)][t] += 1;
-  {
-    int w = 0;
-#pragma unroll 4
-    for (int i = t; i < n; i += 256) w += min(max(kept_count[i], 0), Nb);
-    w = wave_sum_i32(w);
-    if ((t & 63) == 0) atomicAdd(&total, w);
-  }
-  __syncthreads();
-  if (t == 0) plan[kPlanHdr + BH + blockIdx.x] = total;
-  // exclusive scan over the histogram flattened class-major (index = class * 256 + thread)
-  int *flat = &hist[0][0];
-  int sum = 0;
-  for (int j = 0; j < kOrderClasses; ++j) sum += flat[t * kOrderClasses + j];
-  scan[t] = sum;
-  __syncthreads();
-  for (int d = 1; d < 256; d <<= 1) {
-    const int add = t >= d ? scan[t - d] : 0;
-    __syncthreads();
-    scan[t] += add;
-    __syncthreads();
-  }
-  int run = scan[t] - sum;
-  for (int j = 0; j < kOrderClasses; ++j) {
-    const int x = flat[t * kOrderClasses + j];
-    flat[t * kOrderClasses + j] = run;
-    run += x;
-  }
-  __syncthreads();
-  for (int i = i0; i < i1; ++i) {
-    const int b = cls_of(i);
-    const int pos = hist[b][t];
-    hist[b][t] = pos + 1;
-    order[pos] = item0 + i;
-  }
-}
-
+// An XCD with no more heads than this walks their rows in turn: one after the other, the second
+// head's long rows would start late and their length decide when the launch ends (12 heads at
+// N = 32760: 1428 -> 1406 us for the whole step); with three heads the L2 sharing that this gives
+// up costs more than it gains (24 heads at N = 119056: 33.1 -> 38.6 ms).
+constexpr int kHeadsInTurn = 2;
 // kExact (the default of the ABI): Q stays as it is and every logit is scaled in fp32 (one more
 // multiply per logit); the error is then the bf16 rounding of the weights and of the output
 // for any input scale.  !kExact (HEART_ATTN_FOLD_SCALE): the softmax scale is folded into Q
@@ -266,7 +113,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     long long qsn, long long ksb, long long ksh, long long ksn, long long vsb, long long vsh,
     long long vsn, long long osb, long long osh, long long osn, int H, int BH, int N, int Nb,
     const int *__restrict__ kept_idx, const int *__restrict__ kept_count, float scale_log2e,
-    float *__restrict__ lse, int *__restrict__ plan) {
+    float *__restrict__ lse, int *__restrict__ plan, const int *__restrict__ seq) {
   constexpr int NT = BLK * 2;            // threads
   constexpr int NW = NT / 64;            // wavefronts
   constexpr int DT = D / 32;             // 32-wide d tiles of the output
@@ -622,7 +469,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   const int off0 = plan ? plan[2 * kNumXcd + x0] : 0;
   // entry i of a list of `len` items whose heads start at off_x in the head table: the heads one
   // after the other, or, where a list has few of them, their rows in turn
-  const int *head_tbl = plan + kPlanHdr, *seq = plan + kPlanHdr + 2 * BH;
+  const int *head_tbl = plan + kPlanHdr;
   auto entry = [&](int off_x, int len, int i) -> int {
     const int nh = len / Nb;
     const bool in_turn = nh <= kHeadsInTurn;
@@ -858,7 +705,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
 template <int D, int BLK, bool kExact>
 static int launch_attn_t(const heart_shape &s, const void *q, const void *k, const void *v,
                          const int *kept_idx, const int *kept_count, float scale, void *out,
-                         float *lse, int *order, hipStream_t st) {
+                         float *lse, int *order, size_t order_bytes, hipStream_t st) {
   const int Nb = (s.N + BLK - 1) / BLK;
   const int BH = s.B * s.H;
   const size_t lds = 4 * (size_t)kStageRows * D * 2;  // >= BLK * (D + 8) * 2 of the output staging
@@ -881,52 +728,39 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
     grid = n_items < resident ? n_items : resident;
   }
   if (grid > 0x7fffffffLL) return fail(HEART_EUNSUPPORTED, "heart_block_sparse_attn: grid too large");
+  const int *seq = nullptr;
   if (order) {
-    const uint32_t mult = (uint32_t)(((kOrderClasses - 1) << 16) / Nb);
-    if (Nb <= kOrderStagedMax) {
-      auto okern = attn_order_kernel<true>;
-      static DeviceFlags order_attr_set;
-      if (hipError_t e = set_max_lds_once(order_attr_set, dev, reinterpret_cast<const void *>(okern),
-                                          kOrderStagedMax))
-        return fail(HEART_EHIP, "hipFuncSetAttribute(order kernel LDS): %s", hipGetErrorString(e));
-      hipLaunchKernelGGL(okern, dim3((unsigned)BH), dim3(256), (size_t)((Nb + 15) / 16 * 16), st,
-                         kept_count, BH, Nb, mult, order);
-    } else {
-      hipLaunchKernelGGL(attn_order_kernel<false>, dim3((unsigned)BH), dim3(256), 0, st, kept_count,
-                         BH, Nb, mult, order);
-    }
-    if (int rc = check_launch("attn_order_kernel")) return rc;
-    hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(256), 0, st, BH, Nb, (int)grid, order);
-    if (int rc = check_launch("attn_plan_kernel")) return rc;
+    if (int rc = launch_attn_plan(BH, Nb, (int)grid, (int)n_items, kept_idx, kept_count, order, order_bytes, &seq, st))
+      return rc;
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(BLK * 2), lds, st,
                      (const uint16_t *)q, (const uint16_t *)k, (const uint16_t *)v,
                      (uint16_t *)out, s.q_stride[0], s.q_stride[1], s.q_stride[2], s.k_stride[0],
                      s.k_stride[1], s.k_stride[2], s.v_stride[0], s.v_stride[1], s.v_stride[2],
                      s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, BH, s.N, Nb, kept_idx,
-                     kept_count, scale_log2e, lse, order);
+                     kept_count, scale_log2e, lse, order, seq);
   return check_launch("attn_kernel");
 }
 
 template <bool kExact>
 static int launch_attn_e(const heart_shape &s, const void *q, const void *k, const void *v,
                          const int *kept_idx, const int *kept_count, float scale, void *out,
-                         float *lse, int *order, hipStream_t st) {
+                         float *lse, int *order, size_t order_bytes, hipStream_t st) {
   if (s.D == 128 && s.block == 128)
-    return launch_attn_t<128, 128, kExact>(s, q, k, v, kept_idx, kept_count, scale, out, lse, order, st);
+    return launch_attn_t<128, 128, kExact>(s, q, k, v, kept_idx, kept_count, scale, out, lse, order, order_bytes, st);
   if (s.D == 128 && s.block == 64)
-    return launch_attn_t<128, 64, kExact>(s, q, k, v, kept_idx, kept_count, scale, out, lse, order, st);
+    return launch_attn_t<128, 64, kExact>(s, q, k, v, kept_idx, kept_count, scale, out, lse, order, order_bytes, st);
   if (s.D == 64 && s.block == 128)
-    return launch_attn_t<64, 128, kExact>(s, q, k, v, kept_idx, kept_count, scale, out, lse, order, st);
+    return launch_attn_t<64, 128, kExact>(s, q, k, v, kept_idx, kept_count, scale, out, lse, order, order_bytes, st);
   if (s.D == 64 && s.block == 64)
-    return launch_attn_t<64, 64, kExact>(s, q, k, v, kept_idx, kept_count, scale, out, lse, order, st);
+    return launch_attn_t<64, 64, kExact>(s, q, k, v, kept_idx, kept_count, scale, out, lse, order, order_bytes, st);
   return fail(HEART_EUNSUPPORTED, "heart_block_sparse_attn: unsupported (D, block) = (%d, %d)",
               s.D, s.block);
 }
 
 int launch_attn(const heart_shape &s, const void *q, const void *k, const void *v,
                 const int *kept_idx, const int *kept_count, float scale, unsigned flags, void *out,
-                float *lse, int *order, hipStream_t st) {
+                float *lse, int *order, size_t order_bytes, hipStream_t st) {
   // the kernel addresses one head's rows through 32-bit buffer offsets
   const long long lim = 0xffffffffLL;
   const long long rows = (long long)s.N + 2 * s.block;  // staging may address a few rows past N
@@ -936,8 +770,8 @@ int launch_attn(const heart_shape &s, const void *q, const void *k, const void *
                 "heart_block_sparse_attn: (N + 2*block) * token stride * 2 bytes must stay "
                 "below 4 GiB");
   if (flags & HEART_ATTN_FOLD_SCALE)
-    return launch_attn_e<false>(s, q, k, v, kept_idx, kept_count, scale, out, lse, order, st);
-  return launch_attn_e<true>(s, q, k, v, kept_idx, kept_count, scale, out, lse, order, st);
+    return launch_attn_e<false>(s, q, k, v, kept_idx, kept_count, scale, out, lse, order, order_bytes, st);
+  return launch_attn_e<true>(s, q, k, v, kept_idx, kept_count, scale, out, lse, order, order_bytes, st);
 }
 
 // ---- launch plan in static device memory, for callers that cannot allocate --------------------

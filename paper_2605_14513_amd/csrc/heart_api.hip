@@ -209,12 +209,14 @@ static int attn_checked(const heart_shape *shape, const void *q, const void *k, 
   if (workspace) {
     if (!aligned16(workspace))
       return fail(HEART_EUNSUPPORTED, "heart_block_sparse_attn: workspace must be 16-byte aligned");
-    if (workspace_bytes < heart_attn_workspace_bytes(shape))
+    const int nb = (shape->N + shape->block - 1) / shape->block;
+    const size_t need = attn_plan_bytes((long long)shape->B * shape->H, nb);
+    if (workspace_bytes < need)
       return fail(HEART_EINVAL, "heart_block_sparse_attn: workspace of %zu bytes, need %zu",
-                  workspace_bytes, heart_attn_workspace_bytes(shape));
+                  workspace_bytes, need);
   }
   return launch_attn(*shape, q, k, v, kept_idx, kept_count, scale, flags, out, lse,
-                     (int *)workspace, (hipStream_t)stream);
+                     (int *)workspace, workspace_bytes, (hipStream_t)stream);
 }
 
 int heart_block_sparse_attn(const heart_shape *shape, const void *q, const void *k,
@@ -239,7 +241,8 @@ int heart_block_sparse_attn_static(const heart_shape *shape, const void *q, cons
                                    void *stream) {
   clear_error();
   if (int rc = check_shape(shape, "heart_block_sparse_attn_static")) return rc;
-  const size_t need = heart_attn_workspace_bytes(shape);
+  const int nb = (shape->N + shape->block - 1) / shape->block;
+  const size_t need = attn_plan_bytes((long long)shape->B * shape->H, nb);
   if (need > HEART_ATTN_STATIC_PLAN_BYTES)
     return fail(HEART_EUNSUPPORTED,
                 "heart_block_sparse_attn_static: the launch plan of this shape takes %zu bytes, the "
@@ -247,21 +250,21 @@ int heart_block_sparse_attn_static(const heart_shape *shape, const void *q, cons
                 need, HEART_ATTN_STATIC_PLAN_BYTES, HEART_ATTN_STATIC_PLAN_BYTES / 4u);
   int *plan = nullptr;
   if (int rc = attn_static_plan(&plan)) return rc;
-  return attn_checked(shape, q, k, v, kept_idx, kept_count, scale, flags, out, lse, plan, need,
-                      stream);
+  return attn_checked(shape, q, k, v, kept_idx, kept_count, scale, flags, out, lse, plan,
+                      HEART_ATTN_STATIC_PLAN_BYTES, stream);
 }
 
 size_t heart_workspace_bytes(int B, int H, int Nb, int D) {
   (void)D;
   if (B <= 0 || H <= 0 || Nb <= 0) return 0;
   // plan header (24 ints) + two entries per head + one entry per (head, query block)
-  return ((size_t)B * H * ((size_t)Nb + 2) + 24) * sizeof(int);
+  return attn_plan_bytes((long long)B * H, Nb);
 }
 
 size_t heart_attn_workspace_bytes(const heart_shape *s) {
   if (!s || s->B <= 0 || s->H <= 0 || s->N <= 0 || s->block <= 0) return 0;
   const long long nb = ((long long)s->N + s->block - 1) / s->block;
-  return heart_workspace_bytes(s->B, s->H, (int)nb, s->D);
+  return attn_plan_bytes((long long)s->B * s->H, nb) + attn_near_bytes((long long)s->B * s->H, nb);
 }
 
 static int check_antidiag(const heart_shape *s, int stride, const char *fn) {

@@ -204,7 +204,26 @@ int launch_mask_topp(int B, int H, int Nb, int D, const float *qblk, const float
 size_t mask_topp_workspace_bytes(int B, int H, int Nb, int D);
 int launch_attn(const heart_shape &s, const void *q, const void *k, const void *v,
                 const int *kept_idx, const int *kept_count, float scale, unsigned flags, void *out,
-                float *lse, int *order, hipStream_t st);
+                float *lse, int *order, size_t order_bytes, hipStream_t st);
+
+// Launch plan of heart_block_sparse_attn (attn_plan.hip).  Layout (ints): [0,8) cursors, [8,16)
+// items per XCD list, [16,24) offset of each XCD's heads in the head table, [24, 24+BH) head table
+// (the heads of XCD 0 in the order it walks them, then those of XCD 1, ...), [24+BH, 24+2BH) total
+// kept count per head, then seq[BH*Nb], head-major: seq[head*Nb + p] = the head's p-th item,
+// longest kept lists first (item = head * Nb + query block); then, in a workspace that has room
+// for it, a second such sequence with the items in batches of similar kept lists.
+constexpr int kNumXcd = 8;
+constexpr int kPlanHdr = 24;
+inline size_t attn_plan_bytes(long long BH, long long Nb) { return (size_t)(kPlanHdr + BH * (Nb + 2)) * sizeof(int); }
+// rows per head for which the second sequence exists (0 bytes otherwise)
+constexpr int kNearMinRows = 64, kNearMaxRows = 1024;
+inline size_t attn_near_bytes(long long BH, long long Nb) {
+  return Nb >= kNearMinRows && Nb <= kNearMaxRows ? (size_t)(BH * Nb) * sizeof(int) : 0;
+}
+// Enqueues the plan for a launch of n_wg attention workgroups over n_items items; *seq = the
+// sequence that launch follows.
+int launch_attn_plan(int BH, int Nb, int n_wg, int n_items, const int *kept_idx, const int *kept_count, int *plan,
+                     size_t plan_bytes, const int **seq, hipStream_t st);
 
 // Device address, on the current device, of the library's static launch-plan array
 // (HEART_ATTN_STATIC_PLAN_BYTES bytes).

@@ -1,0 +1,69 @@
+"""The launch plan of heart_block_sparse_attn at the edges of its per-head row orders: the batches of
+similar kept lists against a plain model of the rule, and the same output bits in every order."""
+import numpy as np
+import pytest
+import torch
+
+from heart_testlib import check_attn_plan, np_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def near_rows(idx, cnt, batch):
+    """Rows of one head in launch order: the longest left (lower index first) and the batch - 1 rows
+    nearest to it, in order of length; nearness = the list at eight evenly spaced ranks and four
+    times the length, sum of absolute differences."""
+    Nb = len(cnt)
+    sig = np.zeros((Nb, 9), np.int64)
+    for r in range(Nb):
+        if cnt[r] > 0:
+            sig[r, :8] = [idx[r, cnt[r] * (2 * k + 1) // 16] for k in range(8)]
+        sig[r, 8] = 4 * cnt[r]
+    left, out = np.argsort(-cnt.astype(np.int64), kind="stable"), []
+    while len(left):
+        d = np.abs(sig[left] - sig[left[0]]).sum(1)
+        take = np.zeros(len(left), bool)
+        take[np.argsort(d, kind="stable")[:batch]] = True
+        out += left[take].tolist()
+        left = left[~take]
+    return np.array(out)
+
+
+# rows per head at the ends of the range that has batches, around the register layouts (64 rows a
+# slot: 256 / 257, 640 / 641) and ragged; heads around the two per XCD that are walked in turn
+@pytest.mark.parametrize("H,Nb,block", [(17, 64, 64), (9, 63, 128), (16, 65, 64), (3, 256, 128), (5, 257, 64),
+                                        (2, 640, 64), (2, 641, 64), (2, 1024, 64), (1, 1023, 128)])
+def test_batches_of_similar_rows(H, Nb, block):
+    import paper_2605_14513_amd as heart
+
+    D = 64
+    N = Nb * block - 3
+    rng = np.random.default_rng(H * 10007 + Nb)
+    cnt = rng.integers(0, min(Nb, 12) + 1, size=(1, H, Nb)).astype(np.int32)
+    cnt[0, 0, :7] = Nb  # a few full rows, equal to each other
+    idx = np.zeros((1, H, Nb, Nb), np.int32)
+    for h in range(H):
+        for i in range(Nb):
+            idx[0, h, i, :cnt[0, h, i]] = np.sort(rng.permutation(Nb)[:cnt[0, h, i]])
+    g = torch.Generator(device="cuda").manual_seed(Nb)
+    q, k, v = (torch.randn((1, H, N, D), generator=g, device="cuda").bfloat16() for _ in range(3))
+    gi, gc = np_gpu(idx), np_gpu(cnt)
+    base = heart.heart_workspace_bytes(1, H, Nb, D) // 4
+    full = heart.heart_attn_workspace_bytes(q, block) // 4
+    assert full == base + (H * Nb if 64 <= Nb <= 1024 else 0)
+    print(f"H={H} Nb={Nb} block={block}", flush=True)
+    outs = []
+    for words in (full, base, None):
+        ws = None if words is None else torch.full((words + 5,), -7, dtype=torch.int32, device="cuda")[:words]
+        outs.append(heart.heart_block_sparse_attn(q, k, v, block, gi, gc, workspace=ws))
+        torch.cuda.synchronize()
+        if ws is None:
+            continue
+        check_attn_plan(ws.cpu().numpy(), cnt, Nb)
+        n_wg = torch.cuda.get_device_properties(0).multi_processor_count * 2 * 128 // block
+        if words > base and H * Nb > n_wg:
+            near = ws[base:].cpu().numpy().reshape(H, Nb)
+            batch = (n_wg + 7) // 8 * (2 if H <= 16 else 1)
+            for h in range(H):
+                assert np.array_equal(near[h], h * Nb + near_rows(idx[0, h], cnt[0, h], batch)), f"head {h}"
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
