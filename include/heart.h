@@ -273,7 +273,8 @@ int heart_block_sparse_attn_static(const heart_shape *shape, const void *q_bf16,
  * heart_workspace_bytes takes plain sizes (D does not enter; it is part of the signature so that
  * callers can size by the full shape) and gives the smallest plan, 24 + B*H*(Nb+2) ints;
  * heart_attn_workspace_bytes takes a heart_shape and gives what the call can make use of: B*H*Nb
- * ints more for 64 <= Nb <= 1024.  Both return 0 for an invalid shape.
+ * ints more for 64 <= Nb <= 1024, and 2304 bytes more (counters on cache lines of their own) for
+ * B*H*Nb > 512.  Both return 0 for an invalid shape.
  */
 size_t heart_workspace_bytes(int B, int H, int Nb, int D);
 size_t heart_attn_workspace_bytes(const heart_shape *shape);

@@ -19,6 +19,7 @@ constexpr int kOrderClasses = 32;   // count classes of the per-head sort
 constexpr int kPlanMaxHeads = 1024; // beyond this heads are dealt to the XCDs round-robin
 constexpr int kPlanThreads = 1024;
 constexpr int kOrderCols = 256;     // columns of the class histogram
+static_assert(kCursorSpread * kNumXcd * sizeof(int) + kCursorLine <= kCursorBytes, "room of the spread cursors");
 
 // kept count of a row as the attention kernel reads it
 __device__ __forceinline__ int row_count(const int *kept_count, int i, int Nb) {
@@ -26,10 +27,10 @@ __device__ __forceinline__ int row_count(const int *kept_count, int i, int Nb) {
 }
 
 // Heads ranked by total kept count, greedy assignment of heads (heaviest first) to the least
-// loaded XCD, head table, cursors reset to the number of attention workgroups of their XCD (n_wg
-// in all; those take the first items of its list).
+// loaded XCD, head table, cursors (`spread` if given, else the header's) reset to the number of
+// attention workgroups of their XCD (n_wg in all; those take the first items of its list).
 __device__ __forceinline__ void plan_heads(const int *__restrict__ kept_count, int BH, int Nb, int n_wg,
-                                           int *__restrict__ plan, unsigned char *lds) {
+                                           int *__restrict__ plan, int *__restrict__ spread, unsigned char *lds) {
   int *w_head = reinterpret_cast<int *>(lds);
   int *sorted = w_head + kPlanMaxHeads, *xcd_of = sorted + kPlanMaxHeads, *rank_of = xcd_of + kPlanMaxHeads;
   __shared__ int n_heads[kNumXcd], off[kNumXcd];
@@ -91,7 +92,9 @@ __device__ __forceinline__ void plan_heads(const int *__restrict__ kept_count, i
   }
   __syncthreads();
   if (t < kNumXcd) {
-    plan[t] = n_wg / kNumXcd + (t < n_wg % kNumXcd ? 1 : 0);
+    const int first = n_wg / kNumXcd + (t < n_wg % kNumXcd ? 1 : 0);
+    if (spread) spread[t * kCursorSpread] = first;
+    plan[t] = spread ? n_heads[t] * Nb : first;
     plan[kNumXcd + t] = n_heads[t] * Nb;
     plan[2 * kNumXcd + t] = off[t];
   }
@@ -286,7 +289,7 @@ template <bool kStaged>
 __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(const int *__restrict__ kept_idx,
                                                                  const int *__restrict__ kept_count, int BH,
                                                                  int Nb, int n_wg, uint32_t mult, int batch,
-                                                                 int *__restrict__ plan,
+                                                                 int *__restrict__ plan, int *__restrict__ spread,
                                                                  int *__restrict__ near_seq) {
   extern __shared__ __align__(16) unsigned char lds[];
   int id = blockIdx.x;
@@ -303,7 +306,7 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(const int *__re
     id -= BH;
   }
   if (id == 0)
-    plan_heads(kept_count, BH, Nb, n_wg, plan, lds);
+    plan_heads(kept_count, BH, Nb, n_wg, plan, spread, lds);
   else
     class_order<kStaged>(kept_count, id - 1, Nb, mult, plan + kPlanHdr + 2 * BH, lds);
 }
@@ -311,13 +314,20 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(const int *__re
 }  // namespace
 
 int launch_attn_plan(int BH, int Nb, int n_wg, int n_items, const int *kept_idx, const int *kept_count, int *plan,
-                     size_t plan_bytes, const int **seq, hipStream_t st) {
+                     size_t plan_bytes, const int **seq, int **cursors, hipStream_t st) {
   int *class_seq = plan + kPlanHdr + 2 * BH;
   int *near_seq = nullptr;
   // (with one row per workgroup there is nothing to order)
   const size_t near_bytes = attn_near_bytes(BH, Nb);
   if (near_bytes && n_items > n_wg && plan_bytes >= attn_plan_bytes(BH, Nb) + near_bytes) near_seq = class_seq + (size_t)BH * Nb;
   *seq = near_seq ? near_seq : class_seq;
+  int *spread = nullptr;
+  const size_t used = attn_plan_bytes(BH, Nb) + near_bytes;
+  if (n_items > n_wg && plan_bytes >= used + kCursorBytes) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(plan) + used;
+    spread = reinterpret_cast<int *>((a + kCursorLine - 1) / kCursorLine * kCursorLine);
+  }
+  *cursors = spread;
   // rows an XCD works on at a time; twice as many where it walks two heads in turn, so that their
   // long rows start early (12 heads, N = 32760: 1407 -> 1359 us)
   int batch = (n_wg + kNumXcd - 1) / kNumXcd;
@@ -339,7 +349,7 @@ int launch_attn_plan(int BH, int Nb, int n_wg, int n_items, const int *kept_idx,
   const uint32_t mult = (uint32_t)(((kOrderClasses - 1) << 16) / Nb);
   const unsigned grid = (unsigned)(1 + BH + (near_seq ? BH : 0));
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kPlanThreads), lds, st, kept_idx, kept_count, BH, Nb, n_wg, mult, batch,
-                     plan, near_seq);
+                     plan, spread, near_seq);
   return check_launch("attn_plan_kernel");
 }
 

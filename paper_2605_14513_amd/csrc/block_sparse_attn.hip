@@ -113,7 +113,8 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     long long qsn, long long ksb, long long ksh, long long ksn, long long vsb, long long vsh,
     long long vsn, long long osb, long long osh, long long osn, int H, int BH, int N, int Nb,
     const int *__restrict__ kept_idx, const int *__restrict__ kept_count, float scale_log2e,
-    float *__restrict__ lse, int *__restrict__ plan, const int *__restrict__ seq) {
+    float *__restrict__ lse, int *__restrict__ plan, const int *__restrict__ seq, int *__restrict__ cursors,
+    int cursor_step) {
   constexpr int NT = BLK * 2;            // threads
   constexpr int NW = NT / 64;            // wavefronts
   constexpr int DT = D / 32;             // 32-wide d tiles of the output
@@ -492,7 +493,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     for (;;) {
       uint32_t key = 0;  // kept blocks of the list's next item (own list: first), lane; 0 = empty
       if (lane < kNumXcd && !((asked >> lane) & 1)) {
-        const int cur = __hip_atomic_load(&plan[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int cur = __hip_atomic_load(&cursors[x * cursor_step], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (cur < len) {
           const int n = lane == 0 ? Nb : min(max(kept_count[entry(off, len, cur)], 0), Nb);
           key = (uint32_t)(n + 1) * kNumXcd + (uint32_t)(kNumXcd - 1 - lane);
@@ -504,7 +505,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
       asked |= 1ull << l;  // (a list that turns out to be empty is not asked again)
       const int xs = (x0 + l) % kNumXcd;
       int i = 0;
-      if (lane == 0) i = atomicAdd(&plan[xs], 1);
+      if (lane == 0) i = atomicAdd(&cursors[xs * cursor_step], 1);
       i = __builtin_amdgcn_readfirstlane(i);
       if (i < plan[kNumXcd + xs]) {
         if (l == 0) i_own = i;
@@ -596,7 +597,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
       wait_loads_and_barrier();
 #pragma unroll
       for (int i = 0; i < EPB; ++i) asm volatile("" : "+s"(jn[i]));  // loaded before the barrier
-      if (ahead && t == 0 && st + 2 >= T) i_next = atomicAdd(&plan[x0], 1);
+      if (ahead && t == 0 && st + 2 >= T) i_next = atomicAdd(&cursors[x0 * cursor_step], 1);
       refill(G_B0);
       // ---- slice s0+1; stage st+2 -> buffers 0 ----
       {
@@ -655,7 +656,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     wait_loads_and_barrier();
   }
   if (ahead && wave == 0) {
-    if (lane == 0 && i_next < 0) i_next = atomicAdd(&plan[x0], 1);  // (row without kept blocks)
+    if (lane == 0 && i_next < 0) i_next = atomicAdd(&cursors[x0 * cursor_step], 1);  // (row without kept blocks)
     i_next = __builtin_amdgcn_readfirstlane(i_next);
     if (i_next < len0) {
       i_own = i_next;
@@ -729,8 +730,9 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
   }
   if (grid > 0x7fffffffLL) return fail(HEART_EUNSUPPORTED, "heart_block_sparse_attn: grid too large");
   const int *seq = nullptr;
+  int *spread = nullptr;
   if (order) {
-    if (int rc = launch_attn_plan(BH, Nb, (int)grid, (int)n_items, kept_idx, kept_count, order, order_bytes, &seq, st))
+    if (int rc = launch_attn_plan(BH, Nb, (int)grid, (int)n_items, kept_idx, kept_count, order, order_bytes, &seq, &spread, st))
       return rc;
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(BLK * 2), lds, st,
@@ -738,7 +740,7 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
                      (uint16_t *)out, s.q_stride[0], s.q_stride[1], s.q_stride[2], s.k_stride[0],
                      s.k_stride[1], s.k_stride[2], s.v_stride[0], s.v_stride[1], s.v_stride[2],
                      s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, BH, s.N, Nb, kept_idx,
-                     kept_count, scale_log2e, lse, order, seq);
+                     kept_count, scale_log2e, lse, order, seq, spread ? spread : order, spread ? kCursorSpread : 1);
   return check_launch("attn_kernel");
 }
 

@@ -264,7 +264,8 @@ size_t heart_workspace_bytes(int B, int H, int Nb, int D) {
 size_t heart_attn_workspace_bytes(const heart_shape *s) {
   if (!s || s->B <= 0 || s->H <= 0 || s->N <= 0 || s->block <= 0) return 0;
   const long long nb = ((long long)s->N + s->block - 1) / s->block;
-  return attn_plan_bytes((long long)s->B * s->H, nb) + attn_near_bytes((long long)s->B * s->H, nb);
+  const long long BH = (long long)s->B * s->H;
+  return attn_plan_bytes(BH, nb) + attn_near_bytes(BH, nb) + (BH * nb > kCursorMinItems ? kCursorBytes : 0);
 }
 
 static int check_antidiag(const heart_shape *s, int stride, const char *fn) {

@@ -220,10 +220,21 @@ constexpr int kNearMinRows = 64, kNearMaxRows = 1024;
 inline size_t attn_near_bytes(long long BH, long long Nb) {
   return Nb >= kNearMinRows && Nb <= kNearMaxRows ? (size_t)(BH * Nb) * sizeof(int) : 0;
 }
+// In a workspace that has room for them the cursors in use are a second set behind all that, one per
+// 256 bytes (those of the header then say that every list is handed out).  Atomics on one cache line
+// are served one after another, about 40 ns each whatever XCD they come from: with the eight cursors
+// side by side, 1000 workgroups that ended their first rows together waited 40 us for the second
+// (B = 1, 20 heads of 101 rows, one kept block a row, D = 64, block 64: 59 -> 28 us; 30 kept blocks:
+// 130 -> 103 us; D = 128, block 128: 88 -> 55 and 516 -> 497 us).  Only where there can be more items
+// than workgroups (512 of them at block 128, the fewest).
+constexpr size_t kCursorLine = 256;
+constexpr int kCursorSpread = (int)(kCursorLine / sizeof(int));
+constexpr size_t kCursorBytes = (kNumXcd + 1) * kCursorLine;  // (the workspace is aligned to 16 bytes only)
+constexpr long long kCursorMinItems = 512;
 // Enqueues the plan for a launch of n_wg attention workgroups over n_items items; *seq = the
-// sequence that launch follows.
+// sequence that launch follows; *cursors = the spread cursors or null.
 int launch_attn_plan(int BH, int Nb, int n_wg, int n_items, const int *kept_idx, const int *kept_count, int *plan,
-                     size_t plan_bytes, const int **seq, hipStream_t st);
+                     size_t plan_bytes, const int **seq, int **cursors, hipStream_t st);
 
 // Device address, on the current device, of the library's static launch-plan array
 // (HEART_ATTN_STATIC_PLAN_BYTES bytes).
