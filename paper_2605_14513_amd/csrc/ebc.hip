@@ -4,17 +4,29 @@
 //  heart_ebc_band_error   the frequency-weighted velocity error of Eq. 6 on the GPU.
 //    The four bands of the appendix (after fftshift a frequency is low along an axis of
 //    length n when it lies within floor(n/4) of the centre) are products of per-axis
-//    low / high sets, and the low set {-r..r} is symmetric, so its indicator in the
-//    frequency domain is a real orthogonal projection P in the signal domain: a circular
-//    convolution with the Dirichlet kernel p[d] = (1/n)(1 + 2 sum_{f=1..r} cos(2 pi f d / n)).
-//    By Parseval, with n_tot = T*Y*X and the unnormalised transform of the definition,
-//        E_LL = n_tot |Pt Py Px e|^2            E_LH = n_tot (|Pt e|^2 - |Pt Py Px e|^2)
-//        E_HL = n_tot (|Py Px e|^2 - |Pt Py Px e|^2)
-//        E_HH = n_tot (|e|^2 - |Pt e|^2 - |Py Px e|^2 + |Pt Py Px e|^2)
-//    and the denominator is n_tot |dense|^2 + epsilon.  No transform is computed: three
-//    circular convolutions (n^2 work per line, n <= a few hundred) in fp64 and four
-//    deterministic reductions.  A calibration run evaluates this once per (head,
-//    candidate, prompt-step), off the serving path.
+//    low / high sets, and the low set {-r..r}, r = floor(n/4), is symmetric: the low part of
+//    a line is spanned by the 2r+1 real functions 1, cos(2 pi f j / n), sin(2 pi f j / n),
+//    f = 1..r, which are orthogonal.  With c_k the sums of a line against them,
+//        |P e|^2 = 1/n (c_0^2 + 2 sum_{k>0} c_k^2)
+//    so, with S_A the weighted sum of squares after contracting the axes in A (weight 2 per
+//    axis with k > 0, no rounding) and n_tot = T*Y*X, the unnormalised transform of the
+//    definition gives by Parseval
+//        n_tot |Pt e|^2 = Y X S_T    n_tot |Py Px e|^2 = T S_XY    n_tot |Pt Py Px e|^2 = S_XYT
+//        E_LL = S_XYT                E_LH = Y X S_T - S_XYT
+//        E_HL = T S_XY - S_XYT       E_HH = n_tot |e|^2 - Y X S_T - T S_XY + S_XYT
+//    and the denominator is n_tot |dense|^2 + epsilon.  About n/2 coefficients of an axis are
+//    all that is ever computed or stored of it: no transform, no projected tensor.
+//    The contractions run on the fp64 matrix cores (v_mfma_f64_16x16x4_f64: 16 coefficients
+//    of 16 lines, four elements of the lines a step); the sums of squares are taken from the
+//    accumulators and reduced in a fixed order.  Three launches:
+//      ebc_first   x coefficients of err with |err|^2, S_T of err, |dense|^2
+//      ebc_second  y coefficients of the x coefficients with S_XY
+//      ebc_third   S_XYT; its last workgroup adds everything up
+//    Bound by latency: at 128 x 21 x 30 x 52 the matrix instructions are 7 us of the chip and the
+//    100 MB moved (half of them in the caches) some 20 us; the launches take 21 + 10 + 12 us, of
+//    which a table, a first load and a last sum each about 1 us.  Whole call 257 -> 42 us against
+//    twelve launches that convolved in fp64 on the vector units (results equal to 1e-15).
+//    A calibration run evaluates this once per (head, candidate, prompt-step), off the serving path.
 //
 //  heart_ebc_select       the one-candidate-per-head selection of Eq. 5 (minimum summed
 //    error under a mean-sparsity budget), solved exactly on the host: linear relaxation of
@@ -31,95 +43,302 @@
 namespace heart {
 
 constexpr int kEbcThreads = 256;
-constexpr int kEbcMaxAxis = 1024;   // longest axis the convolution kernel stages in LDS
-constexpr int kEbcPartials = 1024;  // partial sums per reduction
+constexpr int kEbcWaves = kEbcThreads / 64;
+constexpr int kEbcMaxAxis = 1024;   // longest axis (the trigonometric table sits in LDS)
+constexpr int kEbcPartials = 1024;  // partial sums per reduction, one per workgroup
+constexpr int kEbcSums = 5;         // |e|^2, S_T, S_XY, S_XYT, |dense|^2
+constexpr int kEbcTileCols = 32;    // lines a wavefront contracts at a time (two matrix tiles)
+typedef __attribute__((ext_vector_type(4))) double ebc_f64x4;
 
-// p[d], d = 0..n-1, of the low-pass projection along an axis of length n
-__global__ void ebc_dirichlet_kernel(int n, double *__restrict__ p) {
-  const int r = n / 4;
-  for (int d = blockIdx.x * blockDim.x + threadIdx.x; d < n; d += gridDim.x * blockDim.x) {
-    double s = 1.0;
-    for (int f = 1; f <= r; ++f) {
-      // reduce f*d modulo n in integers so that the argument of cospi stays in [0, 2)
-      const long long m = ((long long)f * d) % n;
-      s += 2.0 * cospi(2.0 * (double)m / (double)n);
-    }
-    p[d] = s / (double)n;
+__host__ __device__ constexpr int ebc_coefs(int n) { return 2 * (n / 4) + 1; }
+
+// cos(2 pi m / n) in tab[m], sin(2 pi m / n) in tab[n + m], by the whole workgroup
+__device__ __forceinline__ void ebc_table(int n, double *tab) {
+  for (int m = threadIdx.x; m < n; m += kEbcThreads) {
+    double c, s;
+    sincospi(2.0 * (double)m / (double)n, &s, &c);
+    tab[m] = c;
+    tab[n + m] = s;
   }
-}
-
-// out[o, i, s] = sum_j p[(i - j) mod n] * in[o, j, s]   for a tensor viewed as [outer][n][inner]
-template <typename TIn>
-__global__ __launch_bounds__(kEbcThreads) void ebc_project_kernel(
-    const TIn *__restrict__ in, double *__restrict__ out, const double *__restrict__ p, int n,
-    long long inner, long long total) {
-  __shared__ double sp[kEbcMaxAxis];
-  for (int d = threadIdx.x; d < n; d += kEbcThreads) sp[d] = p[d];
   __syncthreads();
-  for (long long e = (long long)blockIdx.x * kEbcThreads + threadIdx.x; e < total;
-       e += (long long)gridDim.x * kEbcThreads) {
-    const long long s = e % inner;
-    const long long oi = e / inner;
-    const int i = (int)(oi % n);
-    const long long o = oi / n;
-    const TIn *line = in + o * n * inner + s;
-    double acc = 0.0;
-    int d = i;  // (i - j) mod n for j = 0
-    for (int j = 0; j < n; ++j) {
-      acc = fma(sp[d], (double)line[(long long)j * inner], acc);
-      d = d == 0 ? n - 1 : d - 1;
-    }
-    out[e] = acc;
-  }
 }
 
-// partial[b] = sum of squares of the elements block b owns (fixed assignment and order)
-template <typename TIn>
-__global__ __launch_bounds__(kEbcThreads) void ebc_sumsq_kernel(const TIn *__restrict__ x,
-                                                                long long total,
-                                                                double *__restrict__ partial) {
-  __shared__ double red[kEbcThreads];
-  double acc = 0.0;
-  for (long long e = (long long)blockIdx.x * kEbcThreads + threadIdx.x; e < total;
-       e += (long long)gridDim.x * kEbcThreads) {
-    const double v = (double)x[e];
-    acc = fma(v, v, acc);
-  }
-  red[threadIdx.x] = acc;
+// sum over the workgroup in a fixed order, valid in thread 0; red: kEbcWaves doubles of LDS
+__device__ __forceinline__ double ebc_block_sum(double v, double *red) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
   __syncthreads();
-  for (int s = kEbcThreads / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double s = red[0];
+#pragma unroll
+  for (int w = 1; w < kEbcWaves; ++w) s += red[w];
+  return s;
 }
 
-// sums[k] = sum of the kEbcPartials partials of reduction k (k = 0..4: |e|^2, |Pt e|^2,
-// |Py Px e|^2, |Pt Py Px e|^2, |dense|^2), then the band energies and the weighted error
-__global__ __launch_bounds__(kEbcThreads) void ebc_finish_kernel(const double *__restrict__ partials,
-                                                                 double n_tot, double w0, double w1,
-                                                                 double w2, double w3, double epsilon,
-                                                                 double *__restrict__ out) {
-  __shared__ double red[kEbcThreads];
-  __shared__ double sums[5];
-  for (int k = 0; k < 5; ++k) {
-    double acc = 0.0;
-    for (int i = threadIdx.x; i < kEbcPartials; i += kEbcThreads) acc += partials[k * kEbcPartials + i];
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    for (int s = kEbcThreads / 2; s > 0; s >>= 1) {
-      if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) sums[k] = red[0];
-    __syncthreads();
+// A tensor as lines of n elements: element j of line o * inner + s is in[(o * n + j) * inner + s].
+// Coefficient k of line c goes to out[k * lines + c] (the store is then coalesced, and the next
+// axis of the original tensor is the last one of the result).
+// Weight of a line in the sum of squares: 1, or 2 per earlier axis with k > 0.  With c = c1 * wdiv
+// + c0, c1 = ky * wmod + kx counts the coefficients of the earlier axes.
+struct EbcLines {
+  int n;
+  long long inner, lines;
+  long long wdiv;  // 0: all weights are 1
+  int wmod;
+};
+
+__device__ __forceinline__ long long ebc_div(long long a, long long b) {
+  if (((unsigned long long)(a | b) >> 32) == 0) return (long long)((uint32_t)a / (uint32_t)b);
+  return a / b;
+}
+
+// 32 lines as one wavefront contracts them: lane l16 = lane % 16 holds lines col0 + l16 and
+// col0 + 16 + l16, lane group g = lane / 16 their elements j = g mod 4.
+template <typename TIn>
+struct EbcTile {
+  long long col0;
+  const TIn *src[2];  // this lane's first elements
+  bool ok[2];         // the line exists (others count as zeros)
+};
+template <typename TIn, bool kUnit>
+__device__ __forceinline__ EbcTile<TIn> ebc_tile_at(const TIn *in, const EbcLines &L, long long tile) {
+  const int l16 = threadIdx.x & 15, g = (threadIdx.x & 63) >> 4;
+  EbcTile<TIn> t;
+  t.col0 = tile * kEbcTileCols;
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const long long col = t.col0 + 16 * c + l16;
+    t.ok[c] = col < L.lines;
+    const long long o = kUnit ? col : ebc_div(col, L.inner);
+    t.src[c] = in + (kUnit ? col * L.n + g : (o * L.n + g) * L.inner + (col - o * L.inner));
   }
+  return t;
+}
+
+constexpr int kEbcBatch = 4;  // contraction steps (of 4 elements) whose loads are issued together
+template <typename TIn>
+struct EbcBatch {
+  TIn v[kEbcBatch][2];
+};
+template <typename TIn, bool kUnit>
+__device__ __forceinline__ void ebc_load(EbcBatch<TIn> &d, const EbcTile<TIn> &t, const EbcLines &L, int j0) {
+  const long long inner = kUnit ? 1 : L.inner;
+  const int last = L.n - (int)((threadIdx.x & 63) >> 4);
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const TIn *p = t.src[c] + j0 * inner;
+#pragma unroll
+    for (int u = 0; u < kEbcBatch; ++u) d.v[u][c] = t.ok[c] && j0 + 4 * u < last ? p[4 * u * inner] : (TIn)0;
+  }
+}
+
+// M * 16 coefficients from kt * 16 on of a tile; `cur` holds its first batch, and that of `next` on return
+template <int M, typename TIn, bool kUnit, bool kStore, bool kSumIn>
+__device__ __forceinline__ void ebc_tile(EbcBatch<TIn> &cur, const EbcTile<TIn> &t, const EbcTile<TIn> &next,
+                                         double *__restrict__ out, const EbcLines &L, const double *tab, int kt,
+                                         int K, double &e_out, double &e_in) {
+  // operand layout (16x16x4 fp64): A lane = (row lane%16, k lane/16), B lane = (k lane/16, column
+  // lane%16), D lane register r = (row lane/16 + 4 r, column lane%16)
+  const int lane = threadIdx.x & 63, l16 = lane & 15, g = lane >> 4;
+  const int n = L.n;
+  ebc_f64x4 acc[M][2];
+  int idx[M], step[M], part[M];  // (f * j) mod n at this lane's j, its step for j + 4, table half
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    const int k = (kt + m) * 16 + l16;
+    const int f = k < K ? (k + 1) >> 1 : 0;  // (coefficients past K are computed and dropped)
+    part[m] = (k & 1) == 0 && k > 0 && k < K ? n : 0;
+    idx[m] = (int)((uint32_t)(f * g) % (uint32_t)n);
+    step[m] = (int)((uint32_t)(4 * f) % (uint32_t)n);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) acc[m][c] = ebc_f64x4{0.0, 0.0, 0.0, 0.0};
+  }
+  for (int j0 = 0; j0 < n; j0 += 4 * kEbcBatch) {
+    EbcBatch<TIn> nxt;
+    const bool more = j0 + 4 * kEbcBatch < n;
+    ebc_load<TIn, kUnit>(nxt, more ? t : next, L, more ? j0 + 4 * kEbcBatch : 0);
+#pragma unroll
+    for (int u = 0; u < kEbcBatch; ++u) {
+      if (j0 + 4 * u >= n) break;  // uniform
+      double b[2];
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        b[c] = (double)cur.v[u][c];
+        if constexpr (kSumIn) e_in = fma(b[c], b[c], e_in);
+      }
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const double a = tab[part[m] + idx[m]];
+        idx[m] += step[m];
+        if (idx[m] >= n) idx[m] -= n;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) acc[m][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b[c], acc[m][c], 0, 0, 0);
+      }
+    }
+    cur = nxt;
+  }
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const long long col = t.col0 + 16 * c + l16;
+    double w = 1.0;  // weight of the line
+    if (L.wdiv) {
+      const long long c1 = ebc_div(col, L.wdiv), ky = ebc_div(c1, L.wmod);
+      w = (ky > 0 ? 2.0 : 1.0) * (c1 - ky * L.wmod > 0 ? 2.0 : 1.0);
+    }
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int k = (kt + m) * 16 + g + 4 * r;
+        if (k < K && t.ok[c]) {
+          const double v = acc[m][c][r];
+          e_out = fma((k > 0 ? 2.0 : 1.0) * w * v, v, e_out);
+          if constexpr (kStore) out[(long long)k * L.lines + col] = v;
+        }
+      }
+  }
+}
+
+// All coefficients of the lines workgroup `blk` of `n_blk` owns; e_out += weighted sum of their
+// squares, e_in += sum of the squares of the elements (kSumIn).  The loads of the next 16 elements,
+// or of the next tile, are always in flight, those of the first while the table is made: a line is
+// short, and a wavefront that waited for every load would do nothing else.
+template <typename TIn, bool kUnit, bool kStore, bool kSumIn>
+__device__ __forceinline__ void ebc_contract(const TIn *__restrict__ in, double *__restrict__ out,
+                                             const EbcLines &L, int blk, int n_blk, double *tab,
+                                             double &e_out, double &e_in) {
+  const int wave = threadIdx.x >> 6;
+  const int K = ebc_coefs(L.n), KT = (K + 15) / 16;
+  const long long tiles = (L.lines + kEbcTileCols - 1) / kEbcTileCols;
+  const long long first = (long long)blk * kEbcWaves + wave, stride = (long long)n_blk * kEbcWaves;
+  EbcTile<TIn> t = ebc_tile_at<TIn, kUnit>(in, L, first);
+  EbcBatch<TIn> cur;
+  ebc_load<TIn, kUnit>(cur, t, L, 0);
+  ebc_table(L.n, tab);
+  for (long long tile = first; tile < tiles; tile += stride) {
+    const EbcTile<TIn> next = ebc_tile_at<TIn, kUnit>(in, L, tile + stride);  // (past the end: no line exists)
+    if (KT == 1) {
+      ebc_tile<1, TIn, kUnit, kStore, kSumIn>(cur, t, next, out, L, tab, 0, K, e_out, e_in);
+    } else {
+      ebc_tile<2, TIn, kUnit, kStore, kSumIn>(cur, t, KT > 2 ? t : next, out, L, tab, 0, K, e_out, e_in);
+      for (int kt = 2; kt < KT; kt += 2)  // (rows of the last pair past K are dropped)
+        ebc_tile<2, TIn, kUnit, kStore, false>(cur, t, kt + 2 < KT ? t : next, out, L, tab, kt, K, e_out, e_in);
+    }
+    t = next;
+  }
+}
+
+// Workgroups [0, gx): x coefficients of err -> cx, |err|^2.  [gx, gx + gt): S_T of err.  The rest:
+// |dense|^2.  ticket: zeroed for ebc_third.
+__global__ __launch_bounds__(kEbcThreads, 4) void ebc_first_kernel(
+    const float *__restrict__ err, const float *__restrict__ dense, long long total, EbcLines lx, EbcLines lt,
+    int gx, int gt, double *__restrict__ cx, double *__restrict__ partials, unsigned *__restrict__ ticket) {
+  __shared__ double tab[2 * kEbcMaxAxis];
+  __shared__ double red[kEbcWaves];
+  int blk = blockIdx.x;
+  double e_out = 0.0, e_in = 0.0;
+  if (blk < gx) {
+    ebc_contract<float, true, true, true>(err, cx, lx, blk, gx, tab, e_out, e_in);
+    // (e_in of a line is spread over the four lane groups, each element once)
+    const double s = ebc_block_sum(e_in, red);
+    if (threadIdx.x == 0) {
+      partials[0 * kEbcPartials + blk] = s;
+      if (blk == 0) *ticket = 0u;
+    }
+  } else if (blk < gx + gt) {
+    blk -= gx;
+    ebc_contract<float, false, false, false>(err, nullptr, lt, blk, gt, tab, e_out, e_in);
+    const double s = ebc_block_sum(e_out, red);
+    if (threadIdx.x == 0) partials[1 * kEbcPartials + blk] = s;
+  } else {
+    blk -= gx + gt;
+    const long long stride = (long long)(gridDim.x - gx - gt) * kEbcThreads, t0 = (long long)blk * kEbcThreads + threadIdx.x;
+    constexpr int U = 8;  // loads in flight
+    const bool wide = (reinterpret_cast<uintptr_t>(dense) & 15u) == 0;
+    const long long quads = wide ? total / 4 : 0;
+    const float4 *dense4 = reinterpret_cast<const float4 *>(dense);
+    for (long long e = t0; e < quads; e += U * stride) {
+      float4 v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = e + u * stride < quads ? dense4[e + u * stride] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        e_in = fma((double)v[u].w, (double)v[u].w,
+                   fma((double)v[u].z, (double)v[u].z, fma((double)v[u].y, (double)v[u].y, fma((double)v[u].x, (double)v[u].x, e_in))));
+    }
+    for (long long e = 4 * quads + t0; e < total; e += stride) e_in = fma((double)dense[e], (double)dense[e], e_in);
+    const double s = ebc_block_sum(e_in, red);
+    if (threadIdx.x == 0) partials[4 * kEbcPartials + blk] = s;
+  }
+}
+
+// y coefficients of the x coefficients -> cyx, S_XY
+__global__ __launch_bounds__(kEbcThreads, 3) void ebc_second_kernel(const double *__restrict__ cx, EbcLines ly,
+                                                                 double *__restrict__ cyx,
+                                                                 double *__restrict__ partials) {
+  __shared__ double tab[2 * kEbcMaxAxis];
+  __shared__ double red[kEbcWaves];
+  double e_out = 0.0, e_in = 0.0;
+  ebc_contract<double, true, true, false>(cx, cyx, ly, blockIdx.x, gridDim.x, tab, e_out, e_in);
+  const double s = ebc_block_sum(e_out, red);
+  if (threadIdx.x == 0) partials[2 * kEbcPartials + blockIdx.x] = s;
+}
+
+struct EbcFinish {
+  int count[kEbcSums];  // partial sums of each reduction
+  double n_t, n_yx, w[4], epsilon;
+};
+
+// S_XYT; the workgroup that draws the last ticket adds up the partial sums and writes the result.
+// The partial sums of this launch cross workgroups of different XCDs and therefore move with
+// device-scope stores and loads; a workgroup takes its ticket after its store is acknowledged.
+__global__ __launch_bounds__(kEbcThreads, 3) void ebc_third_kernel(const double *__restrict__ cyx, EbcLines lt,
+                                                                double *__restrict__ partials,
+                                                                unsigned *__restrict__ ticket, EbcFinish f,
+                                                                double *__restrict__ out) {
+  __shared__ double tab[2 * kEbcMaxAxis];
+  __shared__ double red[kEbcWaves];
+  __shared__ int s_last;
+  double e_out = 0.0, e_in = 0.0;
+  ebc_contract<double, true, false, false>(cyx, nullptr, lt, blockIdx.x, gridDim.x, tab, e_out, e_in);
+  const double s = ebc_block_sum(e_out, red);
   if (threadIdx.x == 0) {
-    const double tot = sums[0], a = sums[1], b = sums[2], c = sums[3];
-    const double ll = n_tot * c, lh = n_tot * (a - c), hl = n_tot * (b - c),
-                 hh = n_tot * (tot - a - b + c);
-    const double den = n_tot * sums[4] + epsilon;
-    out[0] = (w0 * ll + w1 * lh + w2 * hl + w3 * hh) / den;
+    __hip_atomic_store(&partials[3 * kEbcPartials + blockIdx.x], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    s_last = atomicAdd(ticket, 1u) == gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!s_last) return;
+  double v[kEbcSums][kEbcPartials / kEbcThreads];
+#pragma unroll
+  for (int k = 0; k < kEbcSums; ++k)
+#pragma unroll
+    for (int u = 0; u < kEbcPartials / kEbcThreads; ++u) {
+      const int i = threadIdx.x + u * kEbcThreads;
+      v[k][u] = i < f.count[k] ? __hip_atomic_load(&partials[k * kEbcPartials + i], __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT)
+                               : 0.0;
+    }
+  __shared__ double fin[kEbcSums][kEbcWaves];
+#pragma unroll
+  for (int k = 0; k < kEbcSums; ++k) {
+    double a = 0.0;
+#pragma unroll
+    for (int u = 0; u < kEbcPartials / kEbcThreads; ++u) a += v[k][u];
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) a += __shfl_xor(a, d, 64);
+    if ((threadIdx.x & 63) == 0) fin[k][threadIdx.x >> 6] = a;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double sums[kEbcSums];
+#pragma unroll
+    for (int k = 0; k < kEbcSums; ++k) sums[k] = (fin[k][0] + fin[k][1]) + (fin[k][2] + fin[k][3]);
+    const double n_tot = f.n_t * f.n_yx;
+    const double a = f.n_yx * sums[1], b = f.n_t * sums[2], ll = sums[3];
+    const double lh = a - ll, hl = b - ll, hh = n_tot * sums[0] - a - b + ll;
+    out[0] = (f.w[0] * ll + f.w[1] * lh + f.w[2] * hl + f.w[3] * hh) / (n_tot * sums[4] + f.epsilon);
     out[1] = ll;
     out[2] = lh;
     out[3] = hl;
@@ -128,45 +347,38 @@ __global__ __launch_bounds__(kEbcThreads) void ebc_finish_kernel(const double *_
   }
 }
 
+// the two coefficient arrays (neither larger than the tensor), the partial sums, the ticket
 static size_t ebc_workspace_doubles(long long total, int T, int Y, int X) {
-  return 2 * (size_t)total + (size_t)(T + Y + X) + 5 * (size_t)kEbcPartials;
+  return 2 * (size_t)total + (size_t)(T + Y + X) + kEbcSums * (size_t)kEbcPartials;
 }
 
 int launch_ebc_band_error(long long C, int T, int Y, int X, const float *err, const float *dense,
                           const double *w, double epsilon, double *ws, double *out,
                           hipStream_t st) {
   const long long total = C * T * Y * X;
-  double *bufa = ws, *bufb = ws + total;
-  double *pt = bufb + total, *py = pt + T, *px = py + Y;
-  double *partials = px + X;
-  const int grid = (int)std::min<long long>((total + kEbcThreads - 1) / kEbcThreads, 4096);
-  hipLaunchKernelGGL(ebc_dirichlet_kernel, dim3(1), dim3(256), 0, st, T, pt);
-  hipLaunchKernelGGL(ebc_dirichlet_kernel, dim3(1), dim3(256), 0, st, Y, py);
-  hipLaunchKernelGGL(ebc_dirichlet_kernel, dim3(1), dim3(256), 0, st, X, px);
-  // |e|^2 and |dense|^2
-  hipLaunchKernelGGL(ebc_sumsq_kernel<float>, dim3(kEbcPartials), dim3(kEbcThreads), 0, st, err,
-                     total, partials + 0 * kEbcPartials);
-  hipLaunchKernelGGL(ebc_sumsq_kernel<float>, dim3(kEbcPartials), dim3(kEbcThreads), 0, st, dense,
-                     total, partials + 4 * kEbcPartials);
-  // Pt e -> bufa
-  hipLaunchKernelGGL(ebc_project_kernel<float>, dim3(grid), dim3(kEbcThreads), 0, st, err, bufa, pt,
-                     T, (long long)Y * X, total);
-  hipLaunchKernelGGL(ebc_sumsq_kernel<double>, dim3(kEbcPartials), dim3(kEbcThreads), 0, st, bufa,
-                     total, partials + 1 * kEbcPartials);
-  // Px e -> bufa, Py Px e -> bufb
-  hipLaunchKernelGGL(ebc_project_kernel<float>, dim3(grid), dim3(kEbcThreads), 0, st, err, bufa, px,
-                     X, 1LL, total);
-  hipLaunchKernelGGL(ebc_project_kernel<double>, dim3(grid), dim3(kEbcThreads), 0, st, bufa, bufb,
-                     py, Y, (long long)X, total);
-  hipLaunchKernelGGL(ebc_sumsq_kernel<double>, dim3(kEbcPartials), dim3(kEbcThreads), 0, st, bufb,
-                     total, partials + 2 * kEbcPartials);
-  // Pt Py Px e -> bufa
-  hipLaunchKernelGGL(ebc_project_kernel<double>, dim3(grid), dim3(kEbcThreads), 0, st, bufb, bufa,
-                     pt, T, (long long)Y * X, total);
-  hipLaunchKernelGGL(ebc_sumsq_kernel<double>, dim3(kEbcPartials), dim3(kEbcThreads), 0, st, bufa,
-                     total, partials + 3 * kEbcPartials);
-  hipLaunchKernelGGL(ebc_finish_kernel, dim3(1), dim3(kEbcThreads), 0, st, partials,
-                     (double)T * Y * X, w[0], w[1], w[2], w[3], epsilon, out);
+  const int KX = ebc_coefs(X), KY = ebc_coefs(Y);
+  double *cx = ws, *cyx = cx + total, *partials = cyx + total;
+  unsigned *ticket = reinterpret_cast<unsigned *>(partials + kEbcSums * (size_t)kEbcPartials);
+  const EbcLines lx{X, 1, C * T * Y, 0, 1};
+  const EbcLines lt{T, (long long)Y * X, C * Y * X, 0, 1};
+  const EbcLines ly{Y, 1, (long long)KX * C * T, C * T, KX};
+  const EbcLines lyx{T, 1, (long long)KY * KX * C, C, KX};
+  // workgroups of a contraction: one tile per wavefront, or the fewest equal rounds that leave no
+  // more than `most`: the workgroups of a launch are resident at once (four wavefronts per SIMD in
+  // the first, where the three parts share them by their matrix work and bytes; three in the others)
+  auto groups = [](const EbcLines &l, long long most) -> int {
+    const long long g = (l.lines + kEbcTileCols * kEbcWaves - 1) / (kEbcTileCols * kEbcWaves);
+    const long long rounds = (g + most - 1) / most;
+    return (int)((g + rounds - 1) / rounds);
+  };
+  const int gx = groups(lx, 384), gt = groups(lt, 400), gy = groups(ly, 768), gyx = groups(lyx, 768);
+  const int gd = (int)std::min<long long>((total + 8 * kEbcThreads - 1) / (8 * kEbcThreads), 240);
+  const EbcFinish f{{gx, gt, gy, gyx, gd}, (double)T, (double)Y * X, {w[0], w[1], w[2], w[3]}, epsilon};
+  hipLaunchKernelGGL(ebc_first_kernel, dim3((unsigned)(gx + gt + gd)), dim3(kEbcThreads), 0, st, err, dense, total, lx,
+                     lt, gx, gt, cx, partials, ticket);
+  hipLaunchKernelGGL(ebc_second_kernel, dim3((unsigned)gy), dim3(kEbcThreads), 0, st, cx, ly, cyx, partials);
+  hipLaunchKernelGGL(ebc_third_kernel, dim3((unsigned)gyx), dim3(kEbcThreads), 0, st, cyx, lyx, partials, ticket, f,
+                     out);
   return check_launch("ebc kernels");
 }
 

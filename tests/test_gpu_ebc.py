@@ -40,6 +40,27 @@ def test_band_error_matches_fft_definition(shape):
     assert np.array_equal(again, got)
 
 
+# axes around the edges of the coefficient tiles (16 coefficients a tile, in pairs: 31 / 33 coefficients at
+# 63 / 64 elements, 49 at 96..99), the longest axis in each place, lines that do not fill a tile of 32
+@pytest.mark.parametrize("shape", [(1, 1, 1, 1), (3, 63, 2, 64), (1, 64, 65, 3), (2, 99, 5, 96), (1, 1024, 3, 5),
+                                   (2, 3, 1024, 1), (1, 2, 5, 1023), (33, 4, 4, 1), (700, 5, 6, 33)])
+def test_band_error_at_tile_edges(shape):
+    import paper_2605_14513_amd as heart
+
+    rng = np.random.default_rng(sum(shape))
+    err, dense = (rng.standard_normal(shape).astype(np.float32) for _ in range(2))
+    print("ebc", shape, flush=True)
+    got = heart.heart_ebc_band_error(np_gpu(err), np_gpu(dense)).cpu().numpy()
+    want = eo.band_energies(err)
+    n_tot = shape[1] * shape[2] * shape[3]
+    # each energy is a difference of sums no larger than the whole energy; both sides round each of
+    # them by some 1e-15 (64-bit sums of n terms in a tree, n <= 1e6)
+    assert np.abs(got[1:5] - want).max() <= 1e-13 * want.sum(), (got[1:5], want)
+    ref = n_tot * (dense.astype(np.float64) ** 2).sum()
+    assert abs(got[5] - ref) <= 1e-13 * ref
+    assert np.isclose(got[0], np.dot(eo.BAND_WEIGHTS, want) / (ref + 1e-10), rtol=1e-12)
+
+
 def test_band_error_single_frequencies_and_zero_reference():
     import paper_2605_14513_amd as heart
 
