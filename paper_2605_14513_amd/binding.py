@@ -116,37 +116,37 @@ def _check(fn: str, rc: int) -> None:
 
 
 def _dev(t: Optional[torch.Tensor], dtype, name: str, contiguous: bool = True):
+    # (addresses go to ctypes as plain ints: the argtypes make pointers of them, and a c_void_p
+    # object per tensor is a third of a call's time here)
     if t is None:
         return None
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a GPU tensor")
-    if t.dtype != dtype:
+    if t.dtype is not dtype:
         raise TypeError(f"{name} must have dtype {dtype}, got {t.dtype}")
     if contiguous and not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream() -> int:
+    """Handle of torch's current stream on the current device (without a Stream object)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _strides_bhn(t: torch.Tensor, name: str) -> Tuple[int, int, int]:
-    if t.dim() != 4 or t.stride(3) != 1:
+    st = t.stride()
+    if len(st) != 4 or st[3] != 1:
         raise ValueError(f"{name} must be [B,H,N,D] with a contiguous D axis")
-    return t.stride(0), t.stride(1), t.stride(2)
+    return st[:3]
 
 
 def make_shape(q: torch.Tensor, k: torch.Tensor, block: int, v: Optional[torch.Tensor] = None,
                o: Optional[torch.Tensor] = None) -> HeartShape:
     B, H, N, D = q.shape
-    s = HeartShape()
-    s.B, s.H, s.N, s.D, s.block = B, H, N, D, block
-    s.q_stride[:] = _strides_bhn(q, "q")
-    s.k_stride[:] = _strides_bhn(k, "k")
-    s.v_stride[:] = _strides_bhn(v if v is not None else k, "v")
-    s.o_stride[:] = _strides_bhn(o if o is not None else q, "out")
-    return s
+    qs, ks = _strides_bhn(q, "q"), _strides_bhn(k, "k")
+    return HeartShape(B, H, N, D, block, qs, ks, ks if v is None else _strides_bhn(v, "v"),
+                      qs if o is None else _strides_bhn(o, "out"))
 
 
 def heart_pool_qk(q: torch.Tensor, k: torch.Tensor, block: int, qblk=None, kblk=None, qmean=None,
@@ -181,9 +181,9 @@ def heart_drift(qmean, kmean, qanchor, kanchor, has_anchor, delta, gate_lo: floa
     if delta.numel() != H:
         raise ValueError("delta must have H entries")
     for t, n in ((kmean, "kmean"), (qanchor, "qanchor"), (kanchor, "kanchor")):
-        if tuple(t.shape) != (B, H, D):
+        if t.shape != (B, H, D):
             raise ValueError(f"{n} must be [B,H,D]")
-    if tuple(has_anchor.shape) != (B, H) or tuple(drift.shape) != (B, H) or tuple(refresh.shape) != (B, H):
+    if has_anchor.shape != (B, H) or drift.shape != (B, H) or refresh.shape != (B, H):
         raise ValueError("has_anchor, drift, refresh must be [B,H]")
     rc = lib.heart_drift(B, H, D, _dev(qmean, torch.float32, "qmean"),
                          _dev(kmean, torch.float32, "kmean"),
@@ -222,9 +222,9 @@ def heart_pool_drift(q, k, block: int, qanchor, kanchor, has_anchor, delta, work
     if delta.numel() != H:
         raise ValueError("delta must have H entries")
     for t, n in ((qanchor, "qanchor"), (kanchor, "kanchor"), (qmean, "qmean"), (kmean, "kmean")):
-        if tuple(t.shape) != (B, H, D):
+        if t.shape != (B, H, D):
             raise ValueError(f"{n} must be [B,H,D]")
-    if tuple(has_anchor.shape) != (B, H) or tuple(drift.shape) != (B, H) or tuple(refresh.shape) != (B, H):
+    if has_anchor.shape != (B, H) or drift.shape != (B, H) or refresh.shape != (B, H):
         raise ValueError("has_anchor, drift, refresh must be [B,H]")
     if not workspace.is_cuda or not workspace.is_contiguous():
         raise ValueError("workspace must be a contiguous GPU tensor")
@@ -236,8 +236,8 @@ def heart_pool_drift(q, k, block: int, qanchor, kanchor, has_anchor, delta, work
         _dev(qanchor, torch.float32, "qanchor"), _dev(kanchor, torch.float32, "kanchor"),
         _dev(has_anchor, torch.uint8, "has_anchor"), _dev(delta, torch.float32, "delta"),
         float(gate_lo), float(gate_hi), 1 if commit else 0, _dev(drift, torch.float32, "drift"),
-        _dev(refresh, torch.uint8, "refresh"), ctypes.c_void_p(workspace.data_ptr()),
-        workspace.numel() * workspace.element_size(), _stream())
+        _dev(refresh, torch.uint8, "refresh"), workspace.data_ptr(),
+        workspace.nbytes, _stream())
     _check("heart_pool_drift", rc)
     return qblk, kblk, qmean, kmean, drift, refresh
 
@@ -266,13 +266,13 @@ def heart_mask_topp(qblk, kblk, tau, refresh=None, scores_in=None, n_always_kv_b
         raise ValueError("tau must have H entries")
     for t, shp, n in ((mask, (B, H, Nb, Nb), "mask"), (kept_idx, (B, H, Nb, Nb), "kept_idx"),
                       (kept_count, (B, H, Nb), "kept_count")):
-        if tuple(t.shape) != shp:
+        if t.shape != shp:
             raise ValueError(f"{n} must have shape {shp}")
-    if scores_out is not None and tuple(scores_out.shape) != (B, H, Nb, Nb):
+    if scores_out is not None and scores_out.shape != (B, H, Nb, Nb):
         raise ValueError("scores_out must be [B,H,Nb,Nb]")
-    if refresh is not None and tuple(refresh.shape) != (B, H):
+    if refresh is not None and refresh.shape != (B, H):
         raise ValueError("refresh must be [B,H]")
-    if scores_in is None and tuple(kblk.shape) != (B, H, Nb, D):
+    if scores_in is None and kblk.shape != (B, H, Nb, D):
         raise ValueError("kblk must match qblk")
     args = (B, H, Nb, D, _dev(qblk, torch.float32, "qblk"), _dev(kblk, torch.float32, "kblk"),
             _dev(scores_in, torch.float32, "scores_in"), _dev(tau, torch.float32, "tau"),
@@ -285,8 +285,8 @@ def heart_mask_topp(qblk, kblk, tau, refresh=None, scores_in=None, n_always_kv_b
     else:
         if not workspace.is_contiguous():
             raise ValueError("workspace must be contiguous")
-        rc = lib.heart_mask_topp_ws(*args, ctypes.c_void_p(workspace.data_ptr()),
-                                    workspace.numel() * workspace.element_size(), _stream())
+        rc = lib.heart_mask_topp_ws(*args, workspace.data_ptr(),
+                                    workspace.nbytes, _stream())
         _check("heart_mask_topp_ws", rc)
     return mask, kept_idx, kept_count
 
@@ -330,9 +330,9 @@ def heart_block_sparse_attn(q, k, v, block: int, kept_idx, kept_count, scale: fl
     Nb = (N + block - 1) // block
     if out is None:
         out = torch.empty_like(q)
-    if tuple(kept_idx.shape) != (B, H, Nb, Nb) or tuple(kept_count.shape) != (B, H, Nb):
+    if kept_idx.shape != (B, H, Nb, Nb) or kept_count.shape != (B, H, Nb):
         raise ValueError("kept_idx must be [B,H,Nb,Nb] and kept_count [B,H,Nb]")
-    if lse is not None and tuple(lse.shape) != (B, H, N):
+    if lse is not None and lse.shape != (B, H, N):
         raise ValueError("lse must be [B,H,N]")
     shape = make_shape(q, k, block, v, out)
     if isinstance(workspace, str):
@@ -344,7 +344,7 @@ def heart_block_sparse_attn(q, k, v, block: int, kept_idx, kept_count, scale: fl
     if workspace is not None:
         if not workspace.is_cuda or not workspace.is_contiguous():
             raise ValueError("workspace must be a contiguous GPU tensor")
-        ws_ptr, ws_bytes = ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size()
+        ws_ptr, ws_bytes = workspace.data_ptr(), workspace.nbytes
     args = [ctypes.byref(shape), _dev(q, torch.bfloat16, "q", False),
             _dev(k, torch.bfloat16, "k", False), _dev(v, torch.bfloat16, "v", False),
             _dev(kept_idx, torch.int32, "kept_idx"), _dev(kept_count, torch.int32, "kept_count"),
@@ -375,9 +375,9 @@ def heart_block_sparse_attn_static(q, k, v, block: int, kept_idx, kept_count, ou
         raise ValueError("q, k, v, out must have the same shape")
     B, H, N, D = q.shape
     Nb = (N + block - 1) // block
-    if tuple(kept_idx.shape) != (B, H, Nb, Nb) or tuple(kept_count.shape) != (B, H, Nb):
+    if kept_idx.shape != (B, H, Nb, Nb) or kept_count.shape != (B, H, Nb):
         raise ValueError("kept_idx must be [B,H,Nb,Nb] and kept_count [B,H,Nb]")
-    if lse is not None and tuple(lse.shape) != (B, H, N):
+    if lse is not None and lse.shape != (B, H, N):
         raise ValueError("lse must be [B,H,N]")
     shape = make_shape(q, k, block, v, out)
     rc = lib.heart_block_sparse_attn_static(
@@ -442,7 +442,7 @@ def heart_scores_antidiag(q, k, block: int, stride: int, scores=None, workspace=
         raise ValueError("q and k must have the same shape")
     B, H, N, D = q.shape
     Nb = (N + block - 1) // block
-    if refresh is not None and tuple(refresh.shape) != (B, H):
+    if refresh is not None and refresh.shape != (B, H):
         raise ValueError("refresh must be [B,H]")
     shape = make_shape(q, k, block)
     need = int(lib.heart_scores_antidiag_workspace_bytes(ctypes.byref(shape), int(stride)))
@@ -452,14 +452,14 @@ def heart_scores_antidiag(q, k, block: int, stride: int, scores=None, workspace=
         raise ValueError("workspace must be a contiguous GPU tensor")
     if scores is None:
         scores = torch.empty((B, H, Nb, Nb), dtype=torch.float32, device=q.device)
-    elif tuple(scores.shape) != (B, H, Nb, Nb):
+    elif scores.shape != (B, H, Nb, Nb):
         raise ValueError("scores must be [B,H,Nb,Nb]")
     rc = lib.heart_scores_antidiag(ctypes.byref(shape), _dev(q, torch.bfloat16, "q", False),
                                    _dev(k, torch.bfloat16, "k", False), int(stride),
                                    _dev(refresh, torch.uint8, "refresh"),
                                    _dev(scores, torch.float32, "scores"),
-                                   ctypes.c_void_p(workspace.data_ptr()),
-                                   workspace.numel() * workspace.element_size(), _stream())
+                                   workspace.data_ptr(),
+                                   workspace.nbytes, _stream())
     _check("heart_scores_antidiag", rc)
     return scores
 
@@ -486,7 +486,7 @@ def heart_ebc_band_error(err, dense, weights=(1.0, 0.5, 0.01, 0.01), epsilon: fl
     rc = lib.heart_ebc_band_error(C, T, Y, X, _dev(err, torch.float32, "err"),
                                   _dev(dense, torch.float32, "dense"), w, float(epsilon),
                                   _dev(workspace, workspace.dtype, "workspace"),
-                                  workspace.numel() * workspace.element_size(),
+                                  workspace.nbytes,
                                   _dev(out, torch.float64, "out"), _stream())
     _check("heart_ebc_band_error", rc)
     return out
