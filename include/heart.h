@@ -231,8 +231,13 @@ int heart_scores_antidiag(const heart_shape *shape, const void *q, const void *k
  * each other's K/V there; workgroups take items with atomic counters, which levels the
  * load).  A workspace of heart_workspace_bytes(B, H, Nb, D) bytes is enough for a plan
  * without the batches (longest kept lists first), a smaller one is an error.  The results
- * are the same in all cases.  The contents need not be preserved between calls; two
- * calls that run concurrently must not share a workspace.
+ * are the same in all these cases.  Where the call has so few query blocks that the chip would
+ * be left partly idle (2 B H Nb <= 512, or 1024 at D = 64 and block = 64, and Nb >= 8),
+ * heart_attn_workspace_bytes is larger (35 MB at most); a workspace of that size then holds no
+ * plan but the partial results of up to 16 workgroups per query block, which each take a
+ * part of its kept list, and the results are those of the other cases up to rounding (fp32
+ * sums in another order, each part with its own reference exponent).  The contents need not
+ * be preserved between calls; two calls that run concurrently must not share a workspace.
  */
 int heart_block_sparse_attn(const heart_shape *shape, const void *q_bf16, const void *k_bf16,
                             const void *v_bf16, const int *kept_idx, const int *kept_count,
@@ -253,7 +258,7 @@ int heart_block_sparse_attn_flags(const heart_shape *shape, const void *q_bf16,
  * hipMalloc.  The launch plan lives in a static device array of the library
  * (HEART_ATTN_STATIC_PLAN_BYTES on every GPU the library runs on, held until the process
  * ends); the call allocates nothing and otherwise does what heart_block_sparse_attn_flags does
- * with a workspace, with the same results.  It needs heart_workspace_bytes(B, H, Nb, D) <=
+ * with a workspace of that size, with the same results.  It needs heart_workspace_bytes(B, H, Nb, D) <=
  * HEART_ATTN_STATIC_PLAN_BYTES, i.e. B*H*(Nb+2) + 24 <= 262144, and returns HEART_EUNSUPPORTED
  * beyond that.  Every call on a GPU shares that GPU's array (each call rebuilds the plan, so
  * nothing carries over from the previous one): calls that overlap on one GPU -- different
@@ -273,8 +278,9 @@ int heart_block_sparse_attn_static(const heart_shape *shape, const void *q_bf16,
  * heart_workspace_bytes takes plain sizes (D does not enter; it is part of the signature so that
  * callers can size by the full shape) and gives the smallest plan, 24 + B*H*(Nb+2) ints;
  * heart_attn_workspace_bytes takes a heart_shape and gives what the call can make use of: B*H*Nb
- * ints more for 64 <= Nb <= 1024, and 2304 bytes more (counters on cache lines of their own) for
- * B*H*Nb > 512.  Both return 0 for an invalid shape.
+ * ints more for 64 <= Nb <= 1024, 2304 bytes more (counters on cache lines of their own) for
+ * B*H*Nb > 512, and the room for partial results where there are few query blocks.  Both return 0
+ * for an invalid shape.
  */
 size_t heart_workspace_bytes(int B, int H, int Nb, int D);
 size_t heart_attn_workspace_bytes(const heart_shape *shape);

@@ -46,7 +46,8 @@
 // of its XCD's list with an atomic counter; when that list is exhausted it takes from
 // another XCD's list, which levels whatever imbalance the head assignment left.  Without a
 // workspace an XCD works on a contiguous eighth of the query blocks of every head, in index
-// order.
+// order.  With fewer query blocks than places for workgroups the lists themselves are split
+// (kSplit below).
 #include "heart_internal.h"
 
 namespace heart {
@@ -54,6 +55,7 @@ namespace heart {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 // Native vector types (not the HIP struct wrappers): loads and stores of these are
 // first-class values, so staging arrays of them always live in registers.
@@ -106,7 +108,108 @@ constexpr int kHeadsInTurn = 2;
 #define HEART_ATTN_OCC 2  // waves per SIMD the register budget is sized for
 #endif
 
-template <int D, int BLK, bool kExact>
+// Split rows.  A launch with fewer rows than the chip has places for workgroups (two per CU, four
+// of the small ones at D = 64, block 64) would leave the rest idle while each row walks its list
+// alone; there S workgroups take a part of each list and write their unnormalised outputs, and
+// attn_merge_kernel adds them up.  S is as many as there are places for, with at least kSplitMinBlocks
+// blocks a part where lists are full: a part costs about 10 us beside its blocks (launch, first
+// loads, 64 KB written and read again), a block 0.8 us (64 keys, D = 64) to 1.7 us (128 keys,
+// D = 128).  All parts start at once, so such a launch needs no plan.  A function of the sizes only.
+// Measured, whole call: dense 38 -> 19 us, a step at two heads of 16 rows 36 -> 31.5 us (which the
+// host now bounds), steps of 100 to 250 rows 67 -> 33, 88 -> 38, 88 -> 43 us.
+constexpr int kSplitCus = 256;        // CUs the places are counted for
+constexpr int kSplitMinBlocks = 4;
+constexpr int kSplitMax = 16;
+constexpr int kLdsPerCu = 160 * 1024;
+// floats of one wavefront's part: accumulators, reference exponent and row sum of every lane
+template <int D>
+constexpr int kPartFloats = 64 * (D / 2) + 128;
+
+int attn_split(long long BH, long long Nb, int D, int block) {
+  const int by_waves = HEART_ATTN_OCC * 4 / (block / 32), by_lds = kLdsPerCu / (4 * kStageRows * D * 2);
+  const long long places = (long long)kSplitCus * (by_waves < by_lds ? by_waves : by_lds);
+  long long s = places / (BH * Nb);
+  if (s > Nb / kSplitMinBlocks) s = Nb / kSplitMinBlocks;
+  if (s > kSplitMax) s = kSplitMax;
+  return s < 2 ? 1 : (int)s;
+}
+
+size_t attn_split_bytes(long long BH, long long Nb, int D, int block) {
+  const int s = attn_split(BH, Nb, D, block);
+  if (s == 1) return 0;
+  const size_t part = D == 128 ? kPartFloats<128> : kPartFloats<64>;
+  return (size_t)(BH * Nb) * s * (block / 32) * part * sizeof(float);
+}
+
+// Adds up the parts of every row: one wavefront per (32 query rows, 32 columns of the output), lanes
+// as in attn_kernel.  Bound by latency (the parts come from the L2s and the memory-side cache):
+// all softmax states are loaded at once, the accumulators of four parts at a time.
+template <int D, int BLK>
+__global__ __launch_bounds__(D * 2) void attn_merge_kernel(const float *__restrict__ part, int n_split,
+                                                           uint16_t *__restrict__ out, long long osb, long long osh,
+                                                           long long osn, int H, int N, int Nb,
+                                                           float *__restrict__ lse) {
+  constexpr int NW = BLK / 32;
+  const int lane = threadIdx.x & 63, dt = threadIdx.x >> 6, l32 = lane & 31, hf = lane >> 5;
+  const int item = (int)(blockIdx.x / NW), wave = (int)(blockIdx.x % NW);
+  const size_t step = (size_t)NW * kPartFloats<D>;  // from part to part of a row
+  const float *src = part + ((size_t)item * n_split * NW + wave) * kPartFloats<D>;
+  const float ninf = -__builtin_inff();
+  float ms[kSplitMax], ls[kSplitMax];
+#pragma unroll
+  for (int s = 0; s < kSplitMax; ++s) {
+    ms[s] = s < n_split ? src[s * step + 64 * (D / 2) + lane] : ninf;
+    ls[s] = s < n_split ? src[s * step + 64 * (D / 2) + 64 + lane] : 0.f;
+  }
+  float m = ninf, l = 0.f;
+#pragma unroll
+  for (int s = 0; s < kSplitMax; ++s) m = fmaxf(m, ms[s]);
+#pragma unroll
+  for (int s = 0; s < kSplitMax; ++s) {
+    // weight of a part; one without keys (reference exponent -inf, same for all lanes) has none
+    ms[s] = ms[s] == ninf ? 0.f : __builtin_amdgcn_exp2f(ms[s] - m);
+    l = fmaf(ls[s], ms[s], l);
+  }
+  f32x4_t o[4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) o[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s0 = 0; s0 < kSplitMax; s0 += 4) {
+    if (s0 < n_split) {
+      f32x4_t x[4][4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const f32x4_t *o4 = reinterpret_cast<const f32x4_t *>(src + min(s0 + s, n_split - 1) * step) + 4 * 64 * dt + lane;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) x[s][g] = o4[64 * g];
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)  // (accumulators of a part without keys are not written)
+            o[g][e] = ms[s0 + s] != 0.f ? fmaf(x[s][g][e], ms[s0 + s], o[g][e]) : o[g][e];
+    }
+  }
+  const int bh = item / Nb, qb = item % Nb, n = qb * BLK + wave * 32 + l32;
+  const float l_tot = l + __shfl_xor(l, 32, 64);
+  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+  if (n >= N) return;
+  if (lse && dt == 0 && hf == 0)
+    lse[(size_t)bh * N + n] = l_tot > 0.f ? (m + log2f(l_tot)) * 0.6931471805599453f : ninf;
+  uint16_t *dst = out + (bh / H) * osb + (bh % H) * osh + (long long)n * osn + 32 * dt + 4 * hf;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    u32x2_t pk;
+    pk.x = cvt_pk_bf16(o[g][0] * inv, o[g][1] * inv);
+    pk.y = cvt_pk_bf16(o[g][2] * inv, o[g][3] * inv);
+    *reinterpret_cast<u32x2_t *>(dst + 8 * g) = pk;
+  }
+}
+
+// kSplit: a workgroup takes part of a row's list and leaves it in `part` (no plan)
+template <int D, int BLK, bool kExact, bool kSplit>
 __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k,
     const uint16_t *__restrict__ v, uint16_t *__restrict__ out, long long qsb, long long qsh,
@@ -114,7 +217,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     long long vsn, long long osb, long long osh, long long osn, int H, int BH, int N, int Nb,
     const int *__restrict__ kept_idx, const int *__restrict__ kept_count, float scale_log2e,
     float *__restrict__ lse, int *__restrict__ plan, const int *__restrict__ seq, int *__restrict__ cursors,
-    int cursor_step) {
+    int cursor_step, float *__restrict__ part, int n_split) {
   constexpr int NT = BLK * 2;            // threads
   constexpr int NW = NT / 64;            // wavefronts
   constexpr int DT = D / 32;             // 32-wide d tiles of the output
@@ -227,6 +330,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   // the reference exponent and go into the exponential as they are
   f32x16_t cinit;
   float l_run = 0.f;  // running sum over this lane's keys, relative to m_ref
+  int split = 0;  // (split rows) which part of the kept list
   auto begin_item = [&](int item) __attribute__((always_inline)) {
     bh = item / Nb;
     qb = item % Nb;
@@ -260,6 +364,12 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     const size_t row = (size_t)bh * Nb + qb;
     cnt = min(kept_count[row], Nb);
     idx = kept_idx + row * Nb;
+    if constexpr (kSplit) {
+      cnt = max(cnt, 0);
+      const int per = (cnt + n_split - 1) / n_split, e0 = min(cnt, split * per);
+      cnt = min(per, cnt - e0);
+      idx += e0;
+    }
   };
 
   // The kept blocks are consumed as one sequence of 32-key slices.  Kept indices are
@@ -514,7 +624,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     }
   };
   int item = -1;
-  if (plan) {
+  if (!kSplit && plan) {
     if (i_own < len0) {
       item = __builtin_amdgcn_readfirstlane(entry(off0, len0, i_own));
     } else {
@@ -524,6 +634,15 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
       }
       __syncthreads();
       item = __builtin_amdgcn_readfirstlane(s_item);
+    }
+  } else if constexpr (kSplit) {
+    // XCD x takes the x-th eighth of the parts: by head, part of the list and query block, so that
+    // its workgroups share the K/V of one part of one head
+    const int n = BH * Nb * n_split, per = (n + kNumXcd - 1) / kNumXcd, slot = (int)(blockIdx.x / kNumXcd);
+    const int w = x0 * per + slot;
+    if (slot < per && w < n) {
+      split = w / Nb % n_split;
+      item = w / (Nb * n_split) * Nb + w % Nb;
     }
   } else {
     // XCD x takes the x-th eighth of the query blocks of every head, heads in order
@@ -541,7 +660,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   int i_next = -1, item_next = -1;
   // (only while every workgroup of the XCD can expect another item of the own list: the last
   // round looks at the cursors first, so that it ends without a queue of failing atomics)
-  const bool ahead = plan && i_own + n_own < len0;
+  const bool ahead = !kSplit && plan && i_own + n_own < len0;
 
   if (cnt > 0) {
     // ---- prologue: stages 0 and 1 in flight, S^T and maximum of slice 0 --------------------
@@ -664,6 +783,22 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     }
   }
 
+  if constexpr (kSplit) {
+    // ---- part of a row: unnormalised output and its softmax state, as the lanes hold them ----
+    float *dst = part + ((size_t)(item * n_split + split) * NW + wave) * kPartFloats<D>;
+    dst[64 * 16 * DT + lane] = m_ref;
+    dst[64 * 16 * DT + 64 + lane] = l_run;
+    if (cnt > 0) {
+      f32x4_t *o4 = reinterpret_cast<f32x4_t *>(dst);
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          o4[(4 * dt + g) * 64 + lane] = f32x4_t{o[dt][4 * g], o[dt][4 * g + 1], o[dt][4 * g + 2], o[dt][4 * g + 3]};
+    }
+    break;
+  }
+
   // ---- epilogue: normalise, stage through LDS, coalesced bf16 store -----------------------
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
@@ -709,17 +844,25 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
                          float *lse, int *order, size_t order_bytes, hipStream_t st) {
   const int Nb = (s.N + BLK - 1) / BLK;
   const int BH = s.B * s.H;
+  const int n_split = order ? attn_split(BH, Nb, D, BLK) : 1;
+  const bool split = n_split > 1 && order_bytes >= attn_split_bytes(BH, Nb, D, BLK);
   const size_t lds = 4 * (size_t)kStageRows * D * 2;  // >= BLK * (D + 8) * 2 of the output staging
-  auto kern = attn_kernel<D, BLK, kExact>;
+  auto kern = split ? attn_kernel<D, BLK, kExact, true> : attn_kernel<D, BLK, kExact, false>;
   const int dev = current_device();
   if (dev < 0) return fail(HEART_EHIP, "heart_block_sparse_attn: cannot identify the current device");
-  static DeviceFlags attr_set;  // per instantiation: the attribute is per function and device
-  if (hipError_t e = set_max_lds_once(attr_set, dev, reinterpret_cast<const void *>(kern), (int)lds))
+  static DeviceFlags attr_set[2];  // per instantiation: the attribute is per function and device
+  if (hipError_t e = set_max_lds_once(attr_set[split], dev, reinterpret_cast<const void *>(kern), (int)lds))
     return fail(HEART_EHIP, "hipFuncSetAttribute(max dynamic LDS %zu): %s", lds, hipGetErrorString(e));
   const float sc = scale > 0.f ? scale : 1.0f / sqrtf((float)D);
   const float scale_log2e = sc * 1.4426950408889634f;
   const long long n_items = (long long)BH * Nb;
   long long grid = (long long)BH * ((Nb + kNumXcd - 1) / kNumXcd) * kNumXcd;
+  float *part = nullptr;
+  if (split) {
+    part = reinterpret_cast<float *>(order);
+    order = nullptr;
+    grid = (n_items * n_split + kNumXcd - 1) / kNumXcd * kNumXcd;
+  }
   if (order) {
     // persistent workgroups: as many as are resident at once (HEART_ATTN_OCC per SIMD, i.e.
     // two workgroups of four wavefronts per CU)
@@ -740,8 +883,12 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
                      (uint16_t *)out, s.q_stride[0], s.q_stride[1], s.q_stride[2], s.k_stride[0],
                      s.k_stride[1], s.k_stride[2], s.v_stride[0], s.v_stride[1], s.v_stride[2],
                      s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, BH, s.N, Nb, kept_idx,
-                     kept_count, scale_log2e, lse, order, seq, spread ? spread : order, spread ? kCursorSpread : 1);
-  return check_launch("attn_kernel");
+                     kept_count, scale_log2e, lse, order, seq, spread ? spread : order, spread ? kCursorSpread : 1, part, n_split);
+  if (int rc = check_launch("attn_kernel")) return rc;
+  if (!split) return HEART_OK;
+  hipLaunchKernelGGL((attn_merge_kernel<D, BLK>), dim3((unsigned)(n_items * (BLK / 32))), dim3(D * 2), 0, st, part, n_split,
+                     (uint16_t *)out, s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, s.N, Nb, lse);
+  return check_launch("attn_merge_kernel");
 }
 
 template <bool kExact>

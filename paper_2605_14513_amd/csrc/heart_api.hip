@@ -265,7 +265,9 @@ size_t heart_attn_workspace_bytes(const heart_shape *s) {
   if (!s || s->B <= 0 || s->H <= 0 || s->N <= 0 || s->block <= 0) return 0;
   const long long nb = ((long long)s->N + s->block - 1) / s->block;
   const long long BH = (long long)s->B * s->H;
-  return attn_plan_bytes(BH, nb) + attn_near_bytes(BH, nb) + (BH * nb > kCursorMinItems ? kCursorBytes : 0);
+  const size_t plan = attn_plan_bytes(BH, nb) + attn_near_bytes(BH, nb) + (BH * nb > kCursorMinItems ? kCursorBytes : 0);
+  const size_t parts = (s->D == 64 || s->D == 128) && (s->block == 64 || s->block == 128) ? attn_split_bytes(BH, nb, s->D, s->block) : 0;
+  return plan > parts ? plan : parts;
 }
 
 static int check_antidiag(const heart_shape *s, int stride, const char *fn) {

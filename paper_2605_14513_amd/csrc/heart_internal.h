@@ -236,6 +236,11 @@ constexpr long long kCursorMinItems = 512;
 int launch_attn_plan(int BH, int Nb, int n_wg, int n_items, const int *kept_idx, const int *kept_count, int *plan,
                      size_t plan_bytes, const int **seq, int **cursors, hipStream_t st);
 
+// Parts that the kept list of every row is split into, 1 = not (a function of the sizes alone), and the
+// workspace bytes the parts take (instead of a plan; 0 if rows are not split).
+int attn_split(long long BH, long long Nb, int D, int block);
+size_t attn_split_bytes(long long BH, long long Nb, int D, int block);
+
 // Device address, on the current device, of the library's static launch-plan array
 // (HEART_ATTN_STATIC_PLAN_BYTES bytes).
 int attn_static_plan(int **ptr);

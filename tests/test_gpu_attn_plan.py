@@ -1,10 +1,12 @@
 """The launch plan of heart_block_sparse_attn at the edges of its per-head row orders: the batches of
-similar kept lists against a plain model of the rule, and the same output bits in every order."""
+similar kept lists against a plain model of the rule, and the same output bits in every order.  Launches
+of few rows, whose lists are split over several workgroups, against the oracle and the unsplit launch."""
 import numpy as np
 import pytest
 import torch
 
-from heart_testlib import check_attn_plan, np_gpu
+import oracle
+from heart_testlib import attn_atol, check_attn_plan, np_gpu, u16
 
 pytestmark = pytest.mark.gpu
 
@@ -68,3 +70,49 @@ def test_batches_of_similar_rows(H, Nb, block):
             for h in range(H):
                 assert np.array_equal(near[h], h * Nb + near_rows(idx[0, h], cnt[0, h], batch)), f"head {h}"
     assert all(torch.equal(outs[0], o) for o in outs[1:])
+
+
+# parts per row: 2, 8, 7, 3 (two workgroups per CU); 16, 6, 2 (four); one head's places not divisible by the
+# rows; both block sizes; token-major tensors; short last blocks
+@pytest.mark.parametrize("H,Nb,D,block,tail,parts", [(1, 8, 128, 128, 0, 2), (1, 64, 128, 128, 5, 8), (1, 67, 128, 64, 63, 7),
+                                                     (3, 50, 128, 128, 127, 3), (1, 64, 64, 64, 1, 16), (3, 50, 64, 64, 0, 6),
+                                                     (4, 9, 64, 128, 100, 2)])
+def test_split_rows(H, Nb, D, block, tail, parts):
+    import paper_2605_14513_amd as heart
+
+    N = Nb * block - tail
+    rng = np.random.default_rng(Nb * 131 + D)
+    cnt = rng.integers(0, Nb + 1, size=(1, H, Nb)).astype(np.int32)
+    cnt[0, 0, :4] = (0, 1, parts - 1, Nb)  # no, one, almost one key block a part, all
+    idx = np.zeros((1, H, Nb, Nb), np.int32)
+    for h in range(H):
+        for i in range(Nb):
+            idx[0, h, i, :cnt[0, h, i]] = np.sort(rng.permutation(Nb)[:cnt[0, h, i]])
+    idx[0, 0, 1, 0] = Nb - 1  # the short last block alone
+    g = torch.Generator(device="cuda").manual_seed(Nb)
+    q, k, v = (torch.randn((1, N, H, D), generator=g, device="cuda").bfloat16().transpose(1, 2) for _ in range(3))
+    gi, gc = np_gpu(idx), np_gpu(cnt)
+    n_bytes = heart.heart_attn_workspace_bytes(q, block)
+    # per part and 32 query rows: 32 x D accumulators and 64 lanes' softmax states, 4 bytes each
+    assert n_bytes == 4 * parts * H * Nb * (block // 32) * (32 * D + 128)
+    print(f"H={H} Nb={Nb} D={D} block={block} parts={parts}", flush=True)
+    want = None
+    for flags in (0, heart.HEART_ATTN_FOLD_SCALE):
+        ws = torch.full((n_bytes + 64,), 255, dtype=torch.uint8, device="cuda")  # (NaN where nothing is written)
+        lse, lse0 = (torch.full((1, H, N), float("nan"), device="cuda") for _ in range(2))
+        out = heart.heart_block_sparse_attn(q, k, v, block, gi, gc, workspace=ws[:n_bytes], flags=flags, lse=lse)
+        one = heart.heart_block_sparse_attn(q, k, v, block, gi, gc, workspace=None, flags=flags, lse=lse0)
+        small = heart.heart_block_sparse_attn(q, k, v, block, gi, gc, workspace=ws[:n_bytes - 16], flags=flags)
+        torch.cuda.synchronize()
+        assert (ws[n_bytes:] == 255).all()
+        assert torch.equal(small, one)  # no room for the parts: the unsplit launch
+        # either side rounds every weight to bf16, relative to its own reference exponent: 2^-9 of each
+        # weight, at most 2^-9 max|v| of the output; and its output: 2^-9 of the value
+        a, b = out.float(), one.float()
+        assert ((a - b).abs() <= 2.0 ** -8 * (v.float().abs().max() + b.abs())).all(), (a - b).abs().max().item()
+        empty = torch.isinf(lse0)
+        assert torch.equal(torch.isinf(lse), empty) and (lse - lse0)[~empty].abs().max() <= 2e-5 * lse0[~empty].abs().max()
+        if want is None:
+            want = oracle.attn(u16(q.contiguous()), u16(k.contiguous()), u16(v.contiguous()), block, idx, cnt)
+            want = np.nan_to_num(want)  # (the oracle has no value for a row without blocks, the kernel zeros)
+        assert np.abs(out.float().cpu().numpy() - want).max() <= attn_atol(want)
