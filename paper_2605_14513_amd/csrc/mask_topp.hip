@@ -102,7 +102,7 @@ struct BlockSlices {
 };
 template <int CMAX, int NF4T, bool kInt8>
 __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
-    int H, int Nb, int D, const float *__restrict__ qblk, const float *__restrict__ kblk,
+    int BH, int H, int Nb, int D, const float *__restrict__ qblk, const float *__restrict__ kblk,
     const float *__restrict__ scores_in, const float *__restrict__ tau,
     const unsigned char *__restrict__ refresh, int n_always_kv, int n_dense_q, int min_keep,
     unsigned char *__restrict__ mask, int *__restrict__ kept_idx, int *__restrict__ kept_count,
@@ -114,13 +114,47 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
   double *sQ = reinterpret_cast<double *>(smem_raw + (size_t)kRows * NBP * 4);  // [kRows][D + 2]
 
   if (NF4T) D = 16 * NF4T;  // (a compile-time constant from here on)
-  const int groups = (Nb + kRows - 1) / kRows;
-  const long long bh = blockIdx.x / groups;
-  const int i0 = (int)(blockIdx.x % groups) * kRows;
-  const int h = (int)(bh % H);
-  if (refresh && !refresh[bh]) return;  // reused head: cached mask persists
-
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // Workgroup -> (refreshed head, row group): the work items of the refreshed heads (reused heads keep
+  // their masks and have none), in order, cut into eighths, one per XCD (workgroup ids are dealt to
+  // them round-robin).  Every row group reads all block means of its head; this way an XCD reads
+  // those of two or three heads, one or two at a time, instead of all heads' (13 of 24 heads refreshed,
+  // Nb = 931, slices: 114 -> 97 us, 0.48 MB of slices a head against 4 MB of L2; at Nb = 256, where
+  // all heads' means fit, no change).
+  const int groups = (Nb + kRows - 1) / kRows;
+  long long bh;
+  int i0;
+  {
+    int n_heads = BH;
+    unsigned long long set = ~0ull;  // refreshed heads among the first 64
+    if (refresh) {
+      n_heads = 0;
+      for (int h0 = 0; h0 < BH; h0 += 64) {
+        const unsigned long long b = __ballot(h0 + lane < BH && refresh[min(h0 + lane, BH - 1)] != 0);
+        if (h0 == 0) set = b;
+        n_heads += __popcll(b);
+      }
+    }
+    const long long items = (long long)n_heads * groups;
+    const int x = (int)(blockIdx.x % kNumXcd);
+    const long long w = items * x / kNumXcd + blockIdx.x / kNumXcd;
+    if (w >= items * (x + 1) / kNumXcd) return;
+    int rank = (int)(w / groups);
+    i0 = (int)(w - (long long)rank * groups) * kRows;
+    if (refresh) {
+      int h0 = 0;
+      while (rank >= __popcll(set)) {  // (ends: rank < n_heads)
+        rank -= __popcll(set);
+        h0 += 64;
+        set = __ballot(h0 + lane < BH && refresh[min(h0 + lane, BH - 1)] != 0);
+      }
+      const bool mine = ((set >> lane) & 1) && __popcll(set & ((1ull << lane) - 1ull)) == rank;
+      bh = h0 + __ffsll((long long)__ballot(mine)) - 1;
+    } else {
+      bh = rank;
+    }
+  }
+  const int h = (int)(bh % H);
 
   if constexpr (kInt8) {
     // ---- Phase A on the int8 matrix cores (launched only without scores_in) -------- -----------------------------------------
@@ -618,7 +652,8 @@ static int launch_cmax_d(int B, int H, int Nb, int D, const float *qblk, const f
   int groups = (Nb + kRows - 1) / kRows;
   // logits of the row group; the fp64 score stage also keeps its query rows there
   size_t lds = scores_in ? 0 : (size_t)kRows * 64 * CMAX * 4 + (kInt8 ? 0 : (size_t)kRows * (D + 2) * 8);
-  long long nwg = (long long)B * H * groups;
+  // (eight XCDs with a place for an eighth of all items, rounded up)
+  long long nwg = ((long long)B * H * groups + kNumXcd - 1) / kNumXcd * kNumXcd;
   auto kern = mask_topp_kernel<CMAX, NF4T, kInt8>;
   if (lds > 64 * 1024) {
     const int dev = current_device();
@@ -627,7 +662,7 @@ static int launch_cmax_d(int B, int H, int Nb, int D, const float *qblk, const f
     if (hipError_t e = set_max_lds_once(attr_set, dev, reinterpret_cast<const void *>(kern), 96 * 1024))
       return fail(HEART_EHIP, "hipFuncSetAttribute(mask kernel LDS): %s", hipGetErrorString(e));
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)nwg), dim3(64 * kWaves), lds, st, H, Nb, D, qblk, kblk,
+  hipLaunchKernelGGL(kern, dim3((unsigned)nwg), dim3(64 * kWaves), lds, st, B * H, H, Nb, D, qblk, kblk,
                      scores_in, tau, refresh, n_always_kv, n_dense_q, min_keep, mask, kept_idx,
                      kept_count, scores_out, sl);
   return check_launch("mask_topp_kernel");

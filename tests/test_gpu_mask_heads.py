@@ -1,0 +1,51 @@
+"""heart_mask_topp: the work of the refreshed heads is dealt out over the chip by their rank among all
+heads.  At the edges of that dealing every refreshed head gets what it gets when all heads are
+refreshed, bit for bit, and every other head keeps its mask, lists and counts."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from heart_testlib import np_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+# heads around the 64 that one look at the flags covers; row groups of 16 rows: one short one, an exact
+# one, several; less and more work than the eight XCDs
+@pytest.mark.parametrize("B,H,Nb", [(1, 1, 5), (2, 32, 16), (1, 65, 33), (3, 43, 7), (1, 13, 70)])
+@pytest.mark.parametrize("which", ["none", "first", "last", "some", "all"])
+@pytest.mark.parametrize("slices", [False, True])
+def test_refreshed_heads_only(B, H, Nb, which, slices):
+    import paper_2605_14513_amd as heart
+
+    D, BH = 64, B * H
+    rng = np.random.default_rng(BH * 100 + Nb)
+    qblk, kblk = (rng.standard_normal((B, H, Nb, D)).astype(np.float32) for _ in range(2))
+    tau = rng.uniform(0.5, 0.95, H).astype(np.float32)
+    flags = np.zeros(BH, np.uint8)
+    if which == "first":
+        flags[0] = 1
+    elif which == "last":
+        flags[-1] = 7  # (any value but 0)
+    elif which == "some":
+        flags[rng.permutation(BH)[:(BH + 1) // 2]] = 1
+    elif which == "all":
+        flags[:] = 1
+    print(f"B={B} H={H} Nb={Nb} {which} slices={slices}", flush=True)
+    gq, gk, gt = np_gpu(qblk), np_gpu(kblk), np_gpu(tau)
+    ws = None
+    if slices:
+        ws = torch.empty(heart.heart_mask_topp_workspace_bytes(B, H, Nb, D), dtype=torch.uint8, device="cuda")
+    full = heart.heart_mask_topp(gq, gk, gt, workspace=ws)
+    assert np.array_equal(full[0].cpu().numpy(), oracle.topp(oracle.scores(qblk, kblk), tau)[0])
+    mask = torch.full((B, H, Nb, Nb), 9, dtype=torch.uint8, device="cuda")
+    idx = torch.full((B, H, Nb, Nb), -1, dtype=torch.int32, device="cuda")
+    cnt = torch.full((B, H, Nb), -5, dtype=torch.int32, device="cuda")
+    heart.heart_mask_topp(gq, gk, gt, refresh=np_gpu(flags.reshape(B, H)), mask=mask, kept_idx=idx, kept_count=cnt,
+                          workspace=ws)
+    torch.cuda.synchronize()
+    on = torch.from_numpy(flags.reshape(B, H) != 0).cuda()
+    for got, want, untouched in ((mask, full[0], 9), (idx, full[1], -1), (cnt, full[2], -5)):
+        assert torch.equal(got[on], want[on])
+        assert (got[~on] == untouched).all()
