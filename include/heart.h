@@ -232,7 +232,7 @@ int heart_scores_antidiag(const heart_shape *shape, const void *q, const void *k
  * load).  A workspace of heart_workspace_bytes(B, H, Nb, D) bytes is enough for a plan
  * without the batches (longest kept lists first), a smaller one is an error.  The results
  * are the same in all these cases.  Where the call has so few query blocks that the chip would
- * be left partly idle (2 B H Nb <= 512, or 1024 at D = 64 and block = 64, and Nb >= 8),
+ * be left partly idle (2 B H Nb <= 512, or 1024 at block = 64, and Nb >= 8),
  * heart_attn_workspace_bytes is larger (35 MB at most); a workspace of that size then holds no
  * plan but the partial results of up to 16 workgroups per query block, which each take a
  * part of its kept list, and the results are those of the other cases up to rounding (fp32

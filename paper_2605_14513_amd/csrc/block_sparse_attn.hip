@@ -30,7 +30,7 @@
 // The kept key blocks are consumed as one stream of 32-key slices.  K and V arrive in
 // double-buffered stages of 64 rows, loaded two slices ahead; V stages are skewed by one
 // slice against K stages so that one workgroup barrier per 64 keys retires both (see
-// the comment at the loop).  The softmax scale and log2(e) are folded into Q once, and
+// the comment at the loop; D = 128 with blocks of 64 has stages of one slice, kStageRows).  The softmax scale and log2(e) are folded into Q once, and
 // the S^T accumulators start from minus the running reference exponent, so an
 // accumulator goes into the exponential as it is.
 //
@@ -48,6 +48,8 @@
 // workspace an XCD works on a contiguous eighth of the query blocks of every head, in index
 // order.  With fewer query blocks than places for workgroups the lists themselves are split
 // (kSplit below).
+#include <type_traits>
+
 #include "heart_internal.h"
 
 namespace heart {
@@ -90,7 +92,13 @@ __device__ __forceinline__ u32x4_t head_rsrc_words(const uint16_t *base, uint32_
   return r;
 }
 
-constexpr int kStageRows = 64;    // key rows per K / V stage buffer (two 32-key slices)
+// Key rows per K / V stage buffer: two 32-key slices, or one at D = 128, block 64.  There a workgroup
+// has two wavefronts, and with stages of 64 rows (64 KB) the LDS of a CU holds two workgroups, one
+// wavefront per SIMD; with 32 KB it holds four.  The price is a barrier per slice and loads that are one
+// slice ahead instead of two; with two wavefronts per SIMD it is paid (N = 16384, 40 heads, 60 of 256
+// blocks kept: 1764 -> 1289 us, 731 -> 1000 TFLOP/s; 4 blocks: 257 -> 193 us).
+template <int D, int BLK>
+constexpr int kStageRows = D == 128 && BLK == 64 ? 32 : 64;
 // An XCD with no more heads than this walks their rows in turn: one after the other, the second
 // head's long rows would start late and their length decide when the launch ends (12 heads at
 // N = 32760: 1428 -> 1406 us for the whole step); with three heads the L2 sharing that this gives
@@ -109,7 +117,7 @@ constexpr int kHeadsInTurn = 2;
 #endif
 
 // Split rows.  A launch with fewer rows than the chip has places for workgroups (two per CU, four
-// of the small ones at D = 64, block 64) would leave the rest idle while each row walks its list
+// of the small ones at block 64) would leave the rest idle while each row walks its list
 // alone; there S workgroups take a part of each list and write their unnormalised outputs, and
 // attn_merge_kernel adds them up.  S is as many as there are places for, with at least kSplitMinBlocks
 // blocks a part where lists are full: a part costs about 10 us beside its blocks (launch, first
@@ -126,7 +134,8 @@ template <int D>
 constexpr int kPartFloats = 64 * (D / 2) + 128;
 
 int attn_split(long long BH, long long Nb, int D, int block) {
-  const int by_waves = HEART_ATTN_OCC * 4 / (block / 32), by_lds = kLdsPerCu / (4 * kStageRows * D * 2);
+  const int rows = D == 128 && block == 64 ? kStageRows<128, 64> : kStageRows<64, 64>;
+  const int by_waves = HEART_ATTN_OCC * 4 / (block / 32), by_lds = kLdsPerCu / (4 * rows * D * 2);
   const long long places = (long long)kSplitCus * (by_waves < by_lds ? by_waves : by_lds);
   long long s = places / (BH * Nb);
   if (s > Nb / kSplitMinBlocks) s = Nb / kSplitMinBlocks;
@@ -225,9 +234,11 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   constexpr int CPR = D / 8;             // 16-byte chunks per token row
   constexpr int ROWB = D * 2;            // bytes of a token row in LDS (no padding)
   constexpr int RPB = 16 / CPR;          // rows per 256 bytes (one pass over the 64 banks)
-  constexpr int TILE_B = kStageRows * ROWB;  // bytes of one K or V stage buffer
+  constexpr int SR = kStageRows<D, BLK>;
+  constexpr bool kOne = SR == 32;        // stages of one slice
+  constexpr int TILE_B = SR * ROWB;      // bytes of one K or V stage buffer
   constexpr int RPI = 64 / CPR;          // rows one LDS-direct load instruction covers
-  constexpr int IPW = kStageRows / RPI / NW;  // such instructions per wavefront and tile
+  constexpr int IPW = SR / RPI / NW;  // such instructions per wavefront and tile
   constexpr int NSL = BLK / 32;          // 32-key slices per key block
   constexpr int SO = D + 8;              // LDS row stride of the output staging (elements)
   // kExact: S^T comes out of the matrix cores in raw logit units and is multiplied by
@@ -303,7 +314,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   // tile `buf` of K (is_v = 0) or V (is_v = 1): instruction ii of this wavefront; the
   // first 32 rows of the tile come from key rows key_a.., the last 32 from key_b..
   auto dma = [&](int is_v, int ii, int buf, int key_a, int key_b) __attribute__((always_inline)) {
-    const int half = wave / (NW / 2), wi = wave % (NW / 2);
+    const int half = kOne ? 0 : wave / (NW / 2), wi = kOne ? wave : wave % (NW / 2);
     const int krow = (half ? key_b : key_a) + (wi * IPW + ii) * RPI;
     const uint32_t voffset =
         is_v ? vdma + (uint32_t)krow * v_row_bytes : kdma[ii] + (uint32_t)krow * k_row_bytes;
@@ -407,7 +418,9 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   constexpr int STEP = KS + NPV;
   constexpr int SEQ = 4 * STEP;
   constexpr int G_B0 = STEP, G_B1 = 3 * STEP;  // stream positions right after the barriers
+  // (stages of one slice: K and V stage i hold slice i, and a barrier follows every slice)
   constexpr int PF = HEART_ATTN_PF < KS ? HEART_ATTN_PF : KS;
+  static_assert(!kOne || NSL == 2, "stages of one slice: blocks of two");
   static_assert(16 % KS == 0 && SEQ % PF == 0 && PF <= KS && PF <= NPV, "stream layout");
 
   // A-operand fragment of stream position g.  Slice q (0..3) of the body: its V and the
@@ -415,7 +428,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   auto fetch = [&](int g) __attribute__((always_inline)) -> u32x4_t {
     g %= SEQ;
     const int n = g / STEP + 1, r = g % STEP;
-    const int buf = (n >> 1) & 1, row0 = (n & 1) * 32;
+    const int buf = kOne ? (r < KS ? n : n - 1) & 1 : (n >> 1) & 1, row0 = kOne ? 0 : (n & 1) * 32;
     if (r < KS)
       return *reinterpret_cast<const u32x4_t *>(smem + buf * TILE_B + row0 * ROWB + koff[r]);
     const int m = r - KS;
@@ -430,7 +443,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   Frag8 ring[PF];
   auto prefetch_after = [&](int g) __attribute__((always_inline)) {
     const int t2 = g + PF;
-    const bool crosses = (g < G_B0 && t2 >= G_B0) || (g < G_B1 && t2 >= G_B1);
+    const bool crosses = kOne ? t2 / STEP != g / STEP : (g < G_B0 && t2 >= G_B0) || (g < G_B1 && t2 >= G_B1);
     if (!crosses) ring[t2 % PF].u = fetch(t2);
   };
   auto refill = [&](int g0) __attribute__((always_inline)) {
@@ -672,12 +685,18 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
       for (int ii = 0; ii < IPW; ++ii) dma(0, ii, 0, k0, k1);
 #pragma unroll
       for (int ii = 0; ii < IPW; ++ii) dma(1, ii, 0, k0, k0);
+      if constexpr (kOne) {
 #pragma unroll
-      for (int ii = 0; ii < IPW; ++ii) dma(0, ii, 1, k2, k3);
+        for (int ii = 0; ii < IPW; ++ii) dma(0, ii, 1, k1, k1);
+        wait_loads_and_barrier();
+      } else {
 #pragma unroll
-      for (int ii = 0; ii < IPW; ++ii) dma(1, ii, 1, k1, k2);
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * IPW) : "memory");  // stage 0 has landed
-      __syncthreads();
+        for (int ii = 0; ii < IPW; ++ii) dma(0, ii, 1, k2, k3);
+#pragma unroll
+        for (int ii = 0; ii < IPW; ++ii) dma(1, ii, 1, k1, k2);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * IPW) : "memory");  // stage 0 has landed
+        __syncthreads();
+      }
       f32x16_t acc = cinit;  // zeros: no reference exponent yet
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
@@ -697,9 +716,56 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
 #pragma unroll
     for (int i = 0; i < 4; ++i) m_loc = max_part(sacc[0], i, m_loc);
     finish_max(m_loc, sacc[0]);
+    if constexpr (kOne) __syncthreads();  // K of slice 0 has been read
     refill(0);
 
-    const int T = cnt * NSL / 2;  // stages
+    const int T = cnt * NSL / 2;  // pairs of slices
+    if constexpr (kOne) {
+      // stages of one slice: while slice s is worked on, K of slice s+2 goes to the buffer that
+      // slice s left and V of slice s+1 to that of slice s-1
+      auto one_slice = [&](auto j_const) __attribute__((always_inline)) {
+        constexpr int j = decltype(j_const)::value;  // slice s0 + j of the body
+        const int kn = key_of(j + 2), vn = key_of(j + 1);
+        qk_step((j + 1) & 1, j * STEP, [&](int ks) {
+#pragma unroll
+          for (int ii = 0; ii < 2 * IPW; ++ii)
+            if (ii * KS / (2 * IPW) == ks) {
+              if (ii < IPW) dma(0, ii, j & 1, kn, kn);
+              else dma(1, ii - IPW, (j + 1) & 1, vn, vn);
+            }
+        });
+        const int nv = N - vn;
+        if (nv < 32) mask_slice(sacc[(j + 1) & 1], nv);
+        m_loc = pv_step(j & 1, j * STEP + KS);
+        finish_max(m_loc, sacc[(j + 1) & 1]);
+      };
+      for (int st = 0; st < T; st += 2) {
+        int jn[EPB];
+        one_slice(std::integral_constant<int, 0>{});
+#pragma unroll
+        for (int i = 0; i < EPB; ++i) jn[i] = kept(2 * st / NSL + NE + i);
+        wait_loads_and_barrier();
+#pragma unroll
+        for (int i = 0; i < EPB; ++i) asm volatile("" : "+s"(jn[i]));  // loaded before the barrier
+        if (ahead && t == 0 && st + 2 >= T) i_next = atomicAdd(&cursors[x0 * cursor_step], 1);
+        refill(STEP);
+        one_slice(std::integral_constant<int, 1>{});
+        if (st + 1 >= T) break;
+        wait_loads_and_barrier();
+        refill(2 * STEP);
+        one_slice(std::integral_constant<int, 2>{});
+        wait_loads_and_barrier();
+        refill(3 * STEP);
+        one_slice(std::integral_constant<int, 3>{});
+        wait_loads_and_barrier();
+        refill(0);
+        // advance the entry window
+#pragma unroll
+        for (int e = 0; e + EPB < NE; ++e) jb[e] = jb[e + EPB];
+#pragma unroll
+        for (int i = 0; i < EPB; ++i) jb[NE - EPB + i] = jn[i];
+      }
+    } else
     for (int st = 0; st < T; st += 2) {
       // (body: slices s0 = 2 st .. s0+3, list entry eb = s0 / NSL)
       int jn[EPB];
@@ -846,7 +912,7 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
   const int BH = s.B * s.H;
   const int n_split = order ? attn_split(BH, Nb, D, BLK) : 1;
   const bool split = n_split > 1 && order_bytes >= attn_split_bytes(BH, Nb, D, BLK);
-  const size_t lds = 4 * (size_t)kStageRows * D * 2;  // >= BLK * (D + 8) * 2 of the output staging
+  const size_t lds = 4 * (size_t)kStageRows<D, BLK> * D * 2;  // >= BLK * (D + 8) * 2 of the output staging
   auto kern = split ? attn_kernel<D, BLK, kExact, true> : attn_kernel<D, BLK, kExact, false>;
   const int dev = current_device();
   if (dev < 0) return fail(HEART_EHIP, "heart_block_sparse_attn: cannot identify the current device");
