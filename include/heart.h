@@ -295,8 +295,8 @@ size_t heart_attn_workspace_bytes(const heart_shape *shape);
  *   array of the four band weights (LL, LH, HL, HH); epsilon >= 0.  out6: DEVICE double[6]
  *   = {weighted error, E_LL, E_LH, E_HL, E_HH, spectral energy of dense}, in the units of an
  *   unnormalised DFT.  workspace: DEVICE, heart_ebc_workspace_bytes(C,T,Y,X), 16-byte
- *   aligned.  Computed without a transform (band projections are circular convolutions
- *   with Dirichlet kernels, in fp64); results are reproducible run to run.
+ *   aligned.  Computed in fp64 from the 2 floor(n/4) + 1 low Fourier coefficients of each
+ *   axis; results are reproducible run to run.
  * heart_ebc_select: the one-candidate-per-head selection of Eq. 5, solved exactly on the
  *   HOST.  error_host, sparsity_host: [n_heads, n_candidates] doubles; minimises the summed
  *   error subject to mean sparsity >= min_mean_sparsity; choice_host: int[n_heads];
