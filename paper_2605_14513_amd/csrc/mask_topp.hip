@@ -38,6 +38,7 @@ namespace heart {
 constexpr int kRows = 16;      // query-block rows per workgroup (one MFMA tile high)
 constexpr int kMaxF4 = 8;      // float4 per lane and tile at D = 128 (D/16)
 constexpr int kWaves = 8;      // wavefronts per workgroup: two rows each per selection pass
+constexpr int kDealRows = 256, kDealHeads = 256;  // more rows, no more heads: see the kernel
 typedef __attribute__((ext_vector_type(4))) double f64x4_t;
 typedef __attribute__((ext_vector_type(4))) int i32x4_t;
 
@@ -115,24 +116,33 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
 
   if (NF4T) D = 16 * NF4T;  // (a compile-time constant from here on)
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // Workgroup -> (refreshed head, row group): the work items of the refreshed heads (reused heads keep
-  // their masks and have none), in order, cut into eighths, one per XCD (workgroup ids are dealt to
-  // them round-robin).  Every row group reads all block means of its head; this way an XCD reads
-  // those of two or three heads, one or two at a time, instead of all heads' (13 of 24 heads refreshed,
-  // Nb = 931, slices: 114 -> 97 us, 0.48 MB of slices a head against 4 MB of L2; at Nb = 256, where
-  // all heads' means fit, no change).
+  // Workgroup -> (head, row group).  Every row group reads all block means of its head.  With long rows
+  // (kDealRows) the work items of the refreshed heads are taken in order and cut into eighths, one per
+  // XCD (workgroup ids are dealt to them round-robin): an XCD then reads the means of two or three
+  // heads, one or two at a time, instead of all heads' (13 of 24 heads refreshed, Nb = 931, slices:
+  // 114 -> 97 us, 0.48 MB of slices a head against 4 MB of L2).  Up to 256 key blocks the means of the
+  // heads in flight fit every L2 and this gained nothing (Nb = 256, 40 heads: 25.0 and 25.4 us), and with
+  // hundreds of heads the look at all flags costs (1024 heads of 32 rows: 34 -> 47 us): there the heads
+  // follow each other in index order.
   const int groups = (Nb + kRows - 1) / kRows;
   long long bh;
   int i0;
-  {
+  if (CMAX > kDealRows / 64 && BH <= kDealHeads) {
     int n_heads = BH;
     unsigned long long set = ~0ull;  // refreshed heads among the first 64
     if (refresh) {
       n_heads = 0;
-      for (int h0 = 0; h0 < BH; h0 += 64) {
-        const unsigned long long b = __ballot(h0 + lane < BH && refresh[min(h0 + lane, BH - 1)] != 0);
-        if (h0 == 0) set = b;
-        n_heads += __popcll(b);
+      constexpr int U = 4;  // looks whose loads are in flight together
+      for (int h0 = 0; h0 < BH; h0 += 64 * U) {
+        unsigned char f[U];
+#pragma unroll
+        for (int c = 0; c < U; ++c) f[c] = refresh[min(h0 + 64 * c + lane, BH - 1)];
+#pragma unroll
+        for (int c = 0; c < U; ++c) {
+          const unsigned long long b = __ballot(h0 + 64 * c + lane < BH && f[c] != 0);
+          if (h0 + c == 0) set = b;
+          n_heads += __popcll(b);
+        }
       }
     }
     const long long items = (long long)n_heads * groups;
@@ -153,6 +163,10 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
     } else {
       bh = rank;
     }
+  } else {
+    bh = blockIdx.x / groups;
+    i0 = (int)(blockIdx.x % groups) * kRows;
+    if (bh >= BH || (refresh && !refresh[bh])) return;  // reused head: cached mask persists
   }
   const int h = (int)(bh % H);
 
