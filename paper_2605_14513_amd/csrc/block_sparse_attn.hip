@@ -157,6 +157,7 @@ template <int D, int BLK>
 __global__ __launch_bounds__(D * 2) void attn_merge_kernel(const float *__restrict__ part, int n_split,
                                                            uint16_t *__restrict__ out, long long osb, long long osh,
                                                            long long osn, int H, int N, int Nb,
+                                                           const int *__restrict__ kept_count,
                                                            float *__restrict__ lse) {
   constexpr int NW = BLK / 32;
   const int lane = threadIdx.x & 63, dt = threadIdx.x >> 6, l32 = lane & 31, hf = lane >> 5;
@@ -164,6 +165,8 @@ __global__ __launch_bounds__(D * 2) void attn_merge_kernel(const float *__restri
   const size_t step = (size_t)NW * kPartFloats<D>;  // from part to part of a row
   const float *src = part + ((size_t)item * n_split * NW + wave) * kPartFloats<D>;
   const float ninf = -__builtin_inff();
+  // keys of a part: per * s .. of the cnt kept blocks, as attn_kernel deals them
+  const int cnt = min(max(kept_count[item], 0), Nb), per = (cnt + n_split - 1) / n_split;
   float ms[kSplitMax], ls[kSplitMax];
 #pragma unroll
   for (int s = 0; s < kSplitMax; ++s) {
@@ -173,10 +176,12 @@ __global__ __launch_bounds__(D * 2) void attn_merge_kernel(const float *__restri
   float m = ninf, l = 0.f;
 #pragma unroll
   for (int s = 0; s < kSplitMax; ++s) m = fmaxf(m, ms[s]);
+  // (a part whose logits are all NaN or -inf keeps the reference -inf, like one without keys: its weight
+  // is 0, but its sums count, because a NaN among them has to reach the result)
+  const float m_fin = m == ninf ? 0.f : m;
 #pragma unroll
   for (int s = 0; s < kSplitMax; ++s) {
-    // weight of a part; one without keys (reference exponent -inf, same for all lanes) has none
-    ms[s] = ms[s] == ninf ? 0.f : __builtin_amdgcn_exp2f(ms[s] - m);
+    ms[s] = __builtin_amdgcn_exp2f(ms[s] - m_fin);  // weight of a part
     l = fmaf(ls[s], ms[s], l);
   }
   f32x4_t o[4];
@@ -198,7 +203,7 @@ __global__ __launch_bounds__(D * 2) void attn_merge_kernel(const float *__restri
         for (int g = 0; g < 4; ++g)
 #pragma unroll
           for (int e = 0; e < 4; ++e)  // (accumulators of a part without keys are not written)
-            o[g][e] = ms[s0 + s] != 0.f ? fmaf(x[s][g][e], ms[s0 + s], o[g][e]) : o[g][e];
+            o[g][e] = (s0 + s) * per < cnt ? fmaf(x[s][g][e], ms[s0 + s], o[g][e]) : o[g][e];
     }
   }
   const int bh = item / Nb, qb = item % Nb, n = qb * BLK + wave * 32 + l32;
@@ -953,7 +958,7 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
   if (int rc = check_launch("attn_kernel")) return rc;
   if (!split) return HEART_OK;
   hipLaunchKernelGGL((attn_merge_kernel<D, BLK>), dim3((unsigned)(n_items * (BLK / 32))), dim3(D * 2), 0, st, part, n_split,
-                     (uint16_t *)out, s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, s.N, Nb, lse);
+                     (uint16_t *)out, s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, s.N, Nb, kept_count, lse);
   return check_launch("attn_merge_kernel");
 }
 

@@ -116,3 +116,56 @@ def test_split_rows(H, Nb, D, block, tail, parts):
             want = oracle.attn(u16(q.contiguous()), u16(k.contiguous()), u16(v.contiguous()), block, idx, cnt)
             want = np.nan_to_num(want)  # (the oracle has no value for a row without blocks, the kernel zeros)
         assert np.abs(out.float().cpu().numpy() - want).max() <= attn_atol(want)
+
+
+# D = 128: eight parts of eight blocks; the small workgroups of blocks of 64: sixteen parts of four
+@pytest.mark.parametrize("D,block", [(128, 128), (64, 64)])
+@pytest.mark.parametrize("flags", [0, 1])
+def test_split_rows_show_non_finite_inputs(D, block, flags):
+    """A NaN or an infinity that reaches a row of the unsplit launch reaches it in the split one, also
+    where it lies in one part alone or in one that has no weight; and no other row."""
+    import paper_2605_14513_amd as heart
+
+    Nb = 64
+    N = Nb * block
+    g = torch.Generator(device="cuda").manual_seed(D)
+    q, k, v = (torch.randn((1, 1, N, D), generator=g, device="cuda").bfloat16() for _ in range(3))
+    blk = lambda i: slice(i * block, (i + 1) * block)
+    nan_k, neg_k, inf_v, low = 20, 37, 51, 9  # key blocks that only some rows keep
+    k[0, 0, blk(nan_k).start + 3] = float("nan")
+    k[0, 0, blk(neg_k), 0] = float("-inf")
+    v[0, 0, blk(inf_v), 2] = float("inf")
+    k[0, 0, blk(low), 1], v[0, 0, blk(low), 2] = -400.0, float("nan")
+    rows = [[j for j in range(Nb) if j not in (nan_k, neg_k, inf_v, low)] for _ in range(Nb)]
+    q[0, 0, blk(0).start + 5] = float("nan")         # row 0: one query without a finite logit
+    rows[1] = sorted(rows[1] + [nan_k])              # row 1: one key of NaN
+    rows[2] = sorted(rows[2] + [neg_k])              # row 2: logits of -inf in one block
+    rows[3] = [neg_k]                                # row 3: no other logits
+    rows[4] = sorted(rows[4] + [neg_k])              # row 4: logits of +inf
+    rows[5] = sorted(rows[5] + [inf_v])              # row 5: an infinite value
+    rows[6] = sorted(rows[6] + [low])                # row 6: a value of NaN without weight
+    q[0, 0, blk(2), 0] = q[0, 0, blk(3), 0] = 1.0
+    q[0, 0, blk(4), 0] = -1.0
+    q[0, 0, blk(6), 1] = 8.0                         # (logits 400 to 600 in log2 units lower)
+    cnt = np.array([len(r) for r in rows], np.int32).reshape(1, 1, Nb)
+    idx = np.zeros((1, 1, Nb, Nb), np.int32)
+    for i, r in enumerate(rows):
+        idx[0, 0, i, :len(r)] = r
+    gi, gc = np_gpu(idx), np_gpu(cnt)
+    res = []
+    for n_bytes in (heart.heart_attn_workspace_bytes(q, block), heart.heart_workspace_bytes(1, 1, Nb, D)):
+        ws = torch.full((n_bytes,), 255, dtype=torch.uint8, device="cuda")
+        lse = torch.empty((1, 1, N), device="cuda")
+        out = heart.heart_block_sparse_attn(q, k, v, block, gi, gc, workspace=ws, flags=flags, lse=lse)
+        res.append((out.float().cpu().numpy()[0, 0], lse.cpu().numpy()[0, 0]))
+    torch.cuda.synchronize()
+    (out, lse), (one, lse1) = res
+    for i in range(Nb):
+        a, b = out[blk(i)], one[blk(i)]
+        assert np.array_equal(np.isnan(a), np.isnan(b)) and np.array_equal(np.isinf(a), np.isinf(b)), f"row {i}"
+        assert np.array_equal(np.isneginf(lse[blk(i)]), np.isneginf(lse1[blk(i)])), f"row {i}: lse"
+    # what the rows above must show, whichever launch
+    assert np.isnan(one[blk(0)][5]).all() and np.isfinite(np.delete(one[blk(0)], 5, 0)).all()
+    assert np.isnan(one[blk(1)]).all() and np.isfinite(one[blk(2)]).all() and (one[blk(3)] == 0).all()
+    assert np.isnan(one[blk(4)]).all() and not np.isfinite(one[blk(5)][:, 2]).any()
+    assert np.isnan(one[blk(6)][:, 2]).all() and np.isfinite(one[7 * block:]).all()
