@@ -137,6 +137,7 @@ int attn_split(long long BH, long long Nb, int D, int block) {
   const int rows = D == 128 && block == 64 ? kStageRows<128, 64> : kStageRows<64, 64>;
   const int by_waves = HEART_ATTN_OCC * 4 / (block / 32), by_lds = kLdsPerCu / (4 * rows * D * 2);
   const long long places = (long long)kSplitCus * (by_waves < by_lds ? by_waves : by_lds);
+  if (BH > places || Nb > places) return 1;  // (beyond that their product can leave 64 bits)
   long long s = places / (BH * Nb);
   if (s > Nb / kSplitMinBlocks) s = Nb / kSplitMinBlocks;
   if (s > kSplitMax) s = kSplitMax;

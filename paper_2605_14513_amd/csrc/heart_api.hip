@@ -27,6 +27,8 @@ int check_launch(const char *what) {
   return HEART_OK;
 }
 
+static long long n_blocks(const heart_shape *s) { return ((long long)s->N + s->block - 1) / s->block; }
+
 static int check_shape(const heart_shape *s, const char *fn) {
   if (!s) return fail(HEART_EINVAL, "%s: shape is NULL", fn);
   if (s->B <= 0 || s->H <= 0 || s->N <= 0)
@@ -36,8 +38,7 @@ static int check_shape(const heart_shape *s, const char *fn) {
     return fail(HEART_EUNSUPPORTED, "%s: D must be 64 or 128 (got %d)", fn, s->D);
   if (s->block != 64 && s->block != 128)
     return fail(HEART_EUNSUPPORTED, "%s: block must be 64 or 128 (got %d)", fn, s->block);
-  long long nb = ((long long)s->N + s->block - 1) / s->block;
-  if ((long long)s->B * s->H * nb > 0x7fffffffLL)
+  if ((long long)s->B * s->H > 0x7fffffffLL / n_blocks(s))  // (the product of the three can leave 64 bits)
     return fail(HEART_EUNSUPPORTED, "%s: B*H*Nb exceeds the 1-D grid limit", fn);
   return HEART_OK;
 }
@@ -148,7 +149,7 @@ static int mask_topp_checked(int B, int H, int Nb, int D, const float *qblk, con
     return fail(HEART_EINVAL, "heart_mask_topp: NULL pointer argument");
   if (n_always_kv_blocks < 0 || n_dense_q_blocks < 0 || min_keep < 0)
     return fail(HEART_EINVAL, "heart_mask_topp: negative block-count argument");
-  if ((long long)B * H * Nb > 0x7fffffffLL)
+  if ((long long)B * H > 0x7fffffffLL / Nb)
     return fail(HEART_EUNSUPPORTED, "heart_mask_topp: B*H*Nb exceeds the 1-D grid limit");
   if (workspace) {
     if (!aligned16(workspace))
@@ -209,8 +210,7 @@ static int attn_checked(const heart_shape *shape, const void *q, const void *k, 
   if (workspace) {
     if (!aligned16(workspace))
       return fail(HEART_EUNSUPPORTED, "heart_block_sparse_attn: workspace must be 16-byte aligned");
-    const int nb = (shape->N + shape->block - 1) / shape->block;
-    const size_t need = attn_plan_bytes((long long)shape->B * shape->H, nb);
+    const size_t need = attn_plan_bytes((long long)shape->B * shape->H, n_blocks(shape));
     if (workspace_bytes < need)
       return fail(HEART_EINVAL, "heart_block_sparse_attn: workspace of %zu bytes, need %zu",
                   workspace_bytes, need);
@@ -241,8 +241,7 @@ int heart_block_sparse_attn_static(const heart_shape *shape, const void *q, cons
                                    void *stream) {
   clear_error();
   if (int rc = check_shape(shape, "heart_block_sparse_attn_static")) return rc;
-  const int nb = (shape->N + shape->block - 1) / shape->block;
-  const size_t need = attn_plan_bytes((long long)shape->B * shape->H, nb);
+  const size_t need = attn_plan_bytes((long long)shape->B * shape->H, n_blocks(shape));
   if (need > HEART_ATTN_STATIC_PLAN_BYTES)
     return fail(HEART_EUNSUPPORTED,
                 "heart_block_sparse_attn_static: the launch plan of this shape takes %zu bytes, the "
@@ -263,9 +262,9 @@ size_t heart_workspace_bytes(int B, int H, int Nb, int D) {
 
 size_t heart_attn_workspace_bytes(const heart_shape *s) {
   if (!s || s->B <= 0 || s->H <= 0 || s->N <= 0 || s->block <= 0) return 0;
-  const long long nb = ((long long)s->N + s->block - 1) / s->block;
+  const long long nb = n_blocks(s);
   const long long BH = (long long)s->B * s->H;
-  const size_t plan = attn_plan_bytes(BH, nb) + attn_near_bytes(BH, nb) + (BH * nb > kCursorMinItems ? kCursorBytes : 0);
+  const size_t plan = attn_plan_bytes(BH, nb) + attn_near_bytes(BH, nb) + (BH > kCursorMinItems / nb ? kCursorBytes : 0);
   const size_t parts = (s->D == 64 || s->D == 128) && (s->block == 64 || s->block == 128) ? attn_split_bytes(BH, nb, s->D, s->block) : 0;
   return plan > parts ? plan : parts;
 }
@@ -275,7 +274,7 @@ static int check_antidiag(const heart_shape *s, int stride, const char *fn) {
   if (stride <= 0 || s->block != 8 * stride)
     return fail(HEART_EUNSUPPORTED, "%s: block must be 8 * stride (got block %d, stride %d)", fn,
                 s->block, stride);
-  const long long nb = ((long long)s->N + s->block - 1) / s->block;
+  const long long nb = n_blocks(s);
   if (nb > HEART_MAX_NB)
     return fail(HEART_EUNSUPPORTED, "%s: Nb = %lld exceeds HEART_MAX_NB = %d", fn, nb, HEART_MAX_NB);
   return HEART_OK;

@@ -214,11 +214,11 @@ int launch_attn(const heart_shape &s, const void *q, const void *k, const void *
 // for it, a second such sequence with the items in batches of similar kept lists.
 constexpr int kNumXcd = 8;
 constexpr int kPlanHdr = 24;
-inline size_t attn_plan_bytes(long long BH, long long Nb) { return (size_t)(kPlanHdr + BH * (Nb + 2)) * sizeof(int); }
+inline size_t attn_plan_bytes(long long BH, long long Nb) { return (kPlanHdr + (size_t)BH * ((size_t)Nb + 2)) * sizeof(int); }
 // rows per head for which the second sequence exists (0 bytes otherwise)
 constexpr int kNearMinRows = 64, kNearMaxRows = 1024;
 inline size_t attn_near_bytes(long long BH, long long Nb) {
-  return Nb >= kNearMinRows && Nb <= kNearMaxRows ? (size_t)(BH * Nb) * sizeof(int) : 0;
+  return Nb >= kNearMinRows && Nb <= kNearMaxRows ? (size_t)BH * (size_t)Nb * sizeof(int) : 0;
 }
 // In a workspace that has room for them the cursors in use are a second set behind all that, one per
 // 256 bytes (those of the header then say that every list is handed out).  Atomics on one cache line

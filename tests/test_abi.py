@@ -98,6 +98,34 @@ def test_host_validation_rejects_bad_calls_without_a_gpu(lib):
                                None, None, None) == -1
 
 
+def test_sizes_at_the_ends_of_their_types_without_a_gpu(lib):
+    """B*H*Nb that leaves 64 bits is refused, and the workspace sizes of such shapes (and of the largest
+    N) can be asked for; none of these calls reaches a GPU."""
+    from paper_2605_14513_amd.binding import HeartShape
+
+    s = HeartShape()
+    f = ctypes.c_void_p(0x10000)
+    for arr in (s.q_stride, s.k_stride, s.v_stride, s.o_stride):
+        arr[0], arr[1], arr[2] = 0, 64, 64
+    s.D = s.block = 64
+    attn = lambda n_bytes: lib.heart_block_sparse_attn(ctypes.byref(s), f, f, f, f, f, 0.0, f, None, f, n_bytes, None)
+    # 2^30 * 2^30 heads of 16 or 15 blocks: the number of rows is 2^64 (0 in 64 bits) or 15 * 2^60 (negative)
+    for s.N in (1024, 960):
+        s.B = s.H = 1 << 30
+        assert lib.heart_attn_workspace_bytes(ctypes.byref(s)) > 0
+        assert attn((1 << 64) - 1) == -2 and b"grid limit" in lib.heart_last_error()
+        assert lib.heart_pool_qk(ctypes.byref(s), f, f, f, f, f, f, None) == -2
+        assert lib.heart_mask_topp(s.B, s.H, s.N // 64, 64, f, f, None, f, None, 0, 0, 1, f, f, f, None, None) == -2
+    s.B, s.H, s.N = 1, 1, 2 ** 31 - 1
+    nb = 2 ** 25  # (N + block - 1 is past 32 bits)
+    need = lib.heart_workspace_bytes(1, 1, nb, 64)
+    assert need == (nb + 2 + 24) * 4 and lib.heart_attn_workspace_bytes(ctypes.byref(s)) == need + 2304
+    assert attn(need - 1) == -1 and str(need).encode() in lib.heart_last_error()
+    assert attn(need) == -2 and b"4 GiB" in lib.heart_last_error()
+    assert lib.heart_block_sparse_attn_static(ctypes.byref(s), f, f, f, f, f, 0.0, 0, f, None, None) == -2
+    assert b"static array" in lib.heart_last_error()
+
+
 def test_mask_topp_workspace_validation_without_a_gpu(lib):
     f = ctypes.c_void_p(0x10000)
     need = 1 * 40 * 256 * (2 * 4 * 128 + 2 * 4)  # slices of Q and K blocks and their exponents
