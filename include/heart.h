@@ -258,7 +258,9 @@ int heart_block_sparse_attn_flags(const heart_shape *shape, const void *q_bf16,
  * hipMalloc.  The launch plan lives in a static device array of the library
  * (HEART_ATTN_STATIC_PLAN_BYTES on every GPU the library runs on, held until the process
  * ends); the call allocates nothing and otherwise does what heart_block_sparse_attn_flags does
- * with a workspace of that size, with the same results.  It needs heart_workspace_bytes(B, H, Nb, D) <=
+ * with a workspace of heart_workspace_bytes(B, H, Nb, D) bytes or without one, with the same results,
+ * bit for bit.  (Kept lists are never split here: with few query blocks a workspace of
+ * heart_attn_workspace_bytes is faster.)  It needs heart_workspace_bytes(B, H, Nb, D) <=
  * HEART_ATTN_STATIC_PLAN_BYTES, i.e. B*H*(Nb+2) + 24 <= 262144, and returns HEART_EUNSUPPORTED
  * beyond that.  Every call on a GPU shares that GPU's array (each call rebuilds the plan, so
  * nothing carries over from the previous one): calls that overlap on one GPU -- different

@@ -249,8 +249,10 @@ int heart_block_sparse_attn_static(const heart_shape *shape, const void *q, cons
                 need, HEART_ATTN_STATIC_PLAN_BYTES, HEART_ATTN_STATIC_PLAN_BYTES / 4u);
   int *plan = nullptr;
   if (int rc = attn_static_plan(&plan)) return rc;
+  // the array is offered as far as a plan can use it: rows are not split, whatever the shape
+  const size_t full = attn_full_plan_bytes((long long)shape->B * shape->H, n_blocks(shape));
   return attn_checked(shape, q, k, v, kept_idx, kept_count, scale, flags, out, lse, plan,
-                      HEART_ATTN_STATIC_PLAN_BYTES, stream);
+                      full < HEART_ATTN_STATIC_PLAN_BYTES ? full : HEART_ATTN_STATIC_PLAN_BYTES, stream);
 }
 
 size_t heart_workspace_bytes(int B, int H, int Nb, int D) {
@@ -264,7 +266,7 @@ size_t heart_attn_workspace_bytes(const heart_shape *s) {
   if (!s || s->B <= 0 || s->H <= 0 || s->N <= 0 || s->block <= 0) return 0;
   const long long nb = n_blocks(s);
   const long long BH = (long long)s->B * s->H;
-  const size_t plan = attn_plan_bytes(BH, nb) + attn_near_bytes(BH, nb) + (BH > kCursorMinItems / nb ? kCursorBytes : 0);
+  const size_t plan = attn_full_plan_bytes(BH, nb);
   const size_t parts = (s->D == 64 || s->D == 128) && (s->block == 64 || s->block == 128) ? attn_split_bytes(BH, nb, s->D, s->block) : 0;
   return plan > parts ? plan : parts;
 }

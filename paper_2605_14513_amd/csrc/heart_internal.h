@@ -231,6 +231,11 @@ constexpr size_t kCursorLine = 256;
 constexpr int kCursorSpread = (int)(kCursorLine / sizeof(int));
 constexpr size_t kCursorBytes = (kNumXcd + 1) * kCursorLine;  // (the workspace is aligned to 16 bytes only)
 constexpr long long kCursorMinItems = 512;
+// A plan with everything that can go with it.  Never as much as the parts of split rows take (below), so a
+// workspace of this size always holds a plan.
+inline size_t attn_full_plan_bytes(long long BH, long long Nb) {
+  return attn_plan_bytes(BH, Nb) + attn_near_bytes(BH, Nb) + (BH > kCursorMinItems / Nb ? kCursorBytes : 0);
+}
 // Enqueues the plan for a launch of n_wg attention workgroups over n_items items; *seq = the
 // sequence that launch follows; *cursors = the spread cursors or null.
 int launch_attn_plan(int BH, int Nb, int n_wg, int n_items, const int *kept_idx, const int *kept_count, int *plan,

@@ -67,3 +67,34 @@ def test_static_plan_entry_point_rejects_shapes_beyond_its_array():
     fake = ctypes.c_void_p(0x10000)  # never dereferenced: the size check comes first
     rc = lib.heart_block_sparse_attn_static(ctypes.byref(s), fake, fake, fake, fake, fake, 0.0, 0, fake, None, None)
     assert rc == -2 and b"static array" in lib.heart_last_error()
+
+
+# shapes of few rows, whose kept lists are split over workgroups in the workspace that
+# heart_attn_workspace_bytes asks for: the parts would fit the static array (278 KB, 1 MB), or would not
+@pytest.mark.parametrize("H,Nb,D,block,tail", [(1, 8, 64, 64, 0), (2, 8, 128, 64, 5), (1, 64, 128, 128, 77)])
+def test_static_plan_entry_point_with_few_rows(H, Nb, D, block, tail):
+    import paper_2605_14513_amd as heart
+
+    N = Nb * block - tail
+    rng = np.random.default_rng(Nb + D)
+    cnt = rng.integers(0, Nb + 1, size=(1, H, Nb)).astype(np.int32)
+    cnt[0, 0, :2] = (0, Nb)
+    idx = np.zeros((1, H, Nb, Nb), np.int32)
+    for h in range(H):
+        for i in range(Nb):
+            idx[0, h, i, :cnt[0, h, i]] = np.sort(rng.permutation(Nb)[:cnt[0, h, i]])
+    g = torch.Generator(device="cuda").manual_seed(D)
+    q, k, v = (torch.randn((1, H, N, D), generator=g, device="cuda").bfloat16() for _ in range(3))
+    gi, gc = np_gpu(idx), np_gpu(cnt)
+    print(f"static plan: H={H} Nb={Nb} D={D} block={block}", flush=True)
+    assert heart.heart_attn_workspace_bytes(q, block) > heart.heart_workspace_bytes(1, H, Nb, D) + 4096  # (parts)
+    for flags in (0, 1):
+        out, lse = torch.full_like(q, float("nan")), torch.full((1, H, N), float("nan"), device="cuda")
+        heart.heart_block_sparse_attn_static(q, k, v, block, gi, gc, out, flags=flags, lse=lse)
+        for ws in (torch.empty(heart.heart_workspace_bytes(1, H, Nb, D), dtype=torch.uint8, device="cuda"), None):
+            lse_ref = torch.empty_like(lse)
+            ref = heart.heart_block_sparse_attn(q, k, v, block, gi, gc, workspace=ws, flags=flags, lse=lse_ref)
+            torch.cuda.synchronize()
+            assert torch.equal(out, ref) and torch.equal(lse, lse_ref)
+        want = np.nan_to_num(oracle.attn(u16(q), u16(k), u16(v), block, idx, cnt))  # (rows without blocks: zeros)
+        assert np.abs(out.float().cpu().numpy() - want).max() <= ATTN_ATOL
