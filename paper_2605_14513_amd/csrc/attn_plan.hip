@@ -6,7 +6,7 @@
 //                kept lists, the sequence the attention then follows
 //   plan_heads   (one workgroup) total kept count per head, heads ranked by it and assigned
 //                greedily to the XCDs, head table, cursors
-//   class_order  (one workgroup per head) rows by count class, longest first, the sequence for a
+//   class_order  (one workgroup per head, up to 2^20) rows by count class, longest first, the sequence for a
 //                workspace without room for the other
 // It is bound by latency: about 5 us at 40 heads of 256 rows without near_order.
 #include "heart_internal.h"
@@ -19,6 +19,7 @@ constexpr int kOrderClasses = 32;   // count classes of the per-head sort
 constexpr int kPlanMaxHeads = 1024; // beyond this heads are dealt to the XCDs round-robin
 constexpr int kPlanThreads = 1024;
 constexpr int kOrderCols = 256;     // columns of the class histogram
+constexpr int kPlanMaxGroups = 1 << 20;  // workgroups per part of the launch (a launch has less than 2^32 threads)
 static_assert(kCursorSpread * kNumXcd * sizeof(int) + kCursorLine <= kCursorBytes, "room of the spread cursors");
 
 // kept count of a row as the attention kernel reads it
@@ -305,10 +306,14 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(const int *__re
     }
     id -= BH;
   }
-  if (id == 0)
+  if (id == 0) {
     plan_heads(kept_count, BH, Nb, n_wg, plan, spread, lds);
-  else
-    class_order<kStaged>(kept_count, id - 1, Nb, mult, plan + kPlanHdr + 2 * BH, lds);
+    return;
+  }
+  for (long long head = id - 1; head < BH; head += kPlanMaxGroups) {
+    class_order<kStaged>(kept_count, (int)head, Nb, mult, plan + kPlanHdr + 2 * BH, lds);
+    __syncthreads();  // the LDS is free for the next head
+  }
 }
 
 }  // namespace
@@ -319,7 +324,8 @@ int launch_attn_plan(int BH, int Nb, int n_wg, int n_items, const int *kept_idx,
   int *near_seq = nullptr;
   // (with one row per workgroup there is nothing to order)
   const size_t near_bytes = attn_near_bytes(BH, Nb);
-  if (near_bytes && n_items > n_wg && plan_bytes >= attn_plan_bytes(BH, Nb) + near_bytes) near_seq = class_seq + (size_t)BH * Nb;
+  if (near_bytes && BH <= kPlanMaxGroups && n_items > n_wg && plan_bytes >= attn_plan_bytes(BH, Nb) + near_bytes)
+    near_seq = class_seq + (size_t)BH * Nb;
   *seq = near_seq ? near_seq : class_seq;
   int *spread = nullptr;
   const size_t used = attn_plan_bytes(BH, Nb) + near_bytes;
@@ -347,7 +353,7 @@ int launch_attn_plan(int BH, int Nb, int n_wg, int n_items, const int *kept_idx,
       return fail(HEART_EHIP, "hipFuncSetAttribute(plan kernel LDS): %s", hipGetErrorString(e));
   }
   const uint32_t mult = (uint32_t)(((kOrderClasses - 1) << 16) / Nb);
-  const unsigned grid = (unsigned)(1 + BH + (near_seq ? BH : 0));
+  const unsigned grid = (unsigned)(1 + (BH < kPlanMaxGroups ? BH : kPlanMaxGroups) + (near_seq ? BH : 0));
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kPlanThreads), lds, st, kept_idx, kept_count, BH, Nb, n_wg, mult, batch,
                      plan, spread, near_seq);
   return check_launch("attn_plan_kernel");

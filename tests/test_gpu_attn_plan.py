@@ -169,3 +169,24 @@ def test_split_rows_show_non_finite_inputs(D, block, flags):
     assert np.isnan(one[blk(1)]).all() and np.isfinite(one[blk(2)]).all() and (one[blk(3)] == 0).all()
     assert np.isnan(one[blk(4)]).all() and not np.isfinite(one[blk(5)][:, 2]).any()
     assert np.isnan(one[blk(6)][:, 2]).all() and np.isfinite(one[7 * block:]).all()
+
+
+def test_more_heads_than_plan_workgroups():
+    """More heads than a launch of one 1024-thread workgroup per head can have (2^32 threads); every
+    head has one row of one key, so its output is that key's value."""
+    import paper_2605_14513_amd as heart
+
+    H = (1 << 22) + 5
+    v = torch.randn((1, H, 1, 64), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda",
+                    dtype=torch.bfloat16)
+    cnt = torch.ones((1, H, 1), dtype=torch.int32, device="cuda")
+    cnt[0, 7::1001] = 0
+    idx = torch.zeros((1, H, 1, 1), dtype=torch.int32, device="cuda")
+    ws = torch.full((heart.heart_workspace_bytes(1, H, 1, 64) // 4,), -7, dtype=torch.int32, device="cuda")
+    print(f"H={H}", flush=True)
+    out = heart.heart_block_sparse_attn(v, v, v, 64, idx, cnt, workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(out, v * cnt[..., None])
+    # totals per head, then the only row of every head
+    assert torch.equal(ws[24 + H:24 + 2 * H], cnt.view(-1))
+    assert torch.equal(ws[24 + 2 * H:], torch.arange(H, dtype=torch.int32, device="cuda"))
