@@ -5,7 +5,10 @@
 //   near_order   (one workgroup per head, if the workspace has room) rows in batches of similar
 //                kept lists, the sequence the attention then follows
 //   plan_heads   (one workgroup) total kept count per head, heads ranked by it and assigned
-//                greedily to the XCDs, head table, cursors
+//                greedily to the XCDs, head table, cursors; beyond 1024 heads they are dealt to the XCDs
+//                without a look at the totals, which class_order then writes (one workgroup
+//                that sums them all up takes longer than the others together: 131072 heads of
+//                one row, whole call 3069 -> 2805 us)
 //   class_order  (one workgroup per head, up to 2^20) rows by count class, longest first, the sequence for a
 //                workspace without room for the other
 // It is bound by latency: about 5 us at 40 heads of 256 rows without near_order.
@@ -30,26 +33,27 @@ __device__ __forceinline__ int row_count(const int *kept_count, int i, int Nb) {
 // Heads ranked by total kept count, greedy assignment of heads (heaviest first) to the least
 // loaded XCD, head table, cursors (`spread` if given, else the header's) reset to the number of
 // attention workgroups of their XCD (n_wg in all; those take the first items of its list).
+template <int kThreads>
 __device__ __forceinline__ void plan_heads(const int *__restrict__ kept_count, int BH, int Nb, int n_wg,
                                            int *__restrict__ plan, int *__restrict__ spread, unsigned char *lds) {
   int *w_head = reinterpret_cast<int *>(lds);
   int *sorted = w_head + kPlanMaxHeads, *xcd_of = sorted + kPlanMaxHeads, *rank_of = xcd_of + kPlanMaxHeads;
   __shared__ int n_heads[kNumXcd], off[kNumXcd];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  for (int bh = wave; bh < BH; bh += kPlanThreads / 64) {
-    int w = 0;
-#pragma unroll 8
-    for (int i = lane; i < Nb; i += 64) w += row_count(kept_count + (size_t)bh * Nb, i, Nb);
-    w = wave_sum_i32(w);
-    if (lane == 0) {
-      plan[kPlanHdr + BH + bh] = w;
-      if (BH <= kPlanMaxHeads) w_head[bh] = w;
-    }
-  }
-  __syncthreads();
   if (BH <= kPlanMaxHeads) {
+    for (int bh = wave; bh < BH; bh += kThreads / 64) {
+      int w = 0;
+#pragma unroll 8
+      for (int i = lane; i < Nb; i += 64) w += row_count(kept_count + (size_t)bh * Nb, i, Nb);
+      w = wave_sum_i32(w);
+      if (lane == 0) {
+        plan[kPlanHdr + BH + bh] = w;
+        w_head[bh] = w;
+      }
+    }
+    __syncthreads();
     // rank by (work descending, index ascending)
-    for (int bh = t; bh < BH; bh += kPlanThreads) {
+    for (int bh = t; bh < BH; bh += kThreads) {
       const int w = w_head[bh];
       int r = 0;
       for (int j = 0; j < BH; ++j) {
@@ -99,22 +103,22 @@ __device__ __forceinline__ void plan_heads(const int *__restrict__ kept_count, i
     plan[kNumXcd + t] = n_heads[t] * Nb;
     plan[2 * kNumXcd + t] = off[t];
   }
-  for (int bh = t; bh < BH; bh += kPlanThreads) {
+  for (int bh = t; bh < BH; bh += kThreads) {
     const int x = BH <= kPlanMaxHeads ? xcd_of[bh] : bh % kNumXcd;
     const int r = BH <= kPlanMaxHeads ? rank_of[bh] : bh / kNumXcd;
     plan[kPlanHdr + off[x] + r] = bh;
   }
 }
 
-// The Nb items of a head, longest kept list first: stable counting sort by count class (class 0 =
-// the longest rows).  Thread t < 256 owns a contiguous segment of the items and one column of the
+// The Nb items of a head, longest kept list first, and, if `total` is given, the head's total kept
+// count.  Stable counting sort by count class (class 0 = the longest rows).  Thread t < 256 owns a contiguous segment of the items and one column of the
 // class histogram, so that items of a class keep their natural order.  The counts are first read
 // once, coalesced and all in flight, and kept as class bytes in LDS when they fit (kStaged);
 // otherwise the segments are read from global memory.
 constexpr int kOrderStagedMax = 96 * 1024;  // items whose classes fit next to the histogram
-template <bool kStaged>
+template <bool kStaged, int kThreads>
 __device__ __forceinline__ void class_order(const int *__restrict__ kept_count, int head, int Nb, uint32_t mult,
-                                            int *__restrict__ seq, unsigned char *lds) {
+                                            int *__restrict__ seq, int *__restrict__ total, unsigned char *lds) {
   const int n = Nb;
   const int item0 = head * Nb;
   kept_count += item0;
@@ -134,14 +138,23 @@ __device__ __forceinline__ void class_order(const int *__restrict__ kept_count, 
   auto cls_of = [&](int i) -> int { return kStaged ? (int)cls_lds[i] : cls(i); };
   if (kStaged) {
 #pragma unroll 4
-    for (int i = t; i < n; i += kPlanThreads) cls_lds[i] = (unsigned char)cls(i);
+    for (int i = t; i < n; i += kThreads) cls_lds[i] = (unsigned char)cls(i);
   }
   int *flat = &hist[0][0];
-#pragma unroll
-  for (int j = t; j < kOrderClasses * kOrderCols; j += kPlanThreads) flat[j] = 0;
+#pragma unroll 8
+  for (int j = t; j < kOrderClasses * kOrderCols; j += kThreads) flat[j] = 0;
+  __shared__ int sum_lds;
+  if (t == 0) sum_lds = 0;
   __syncthreads();
   for (int i = i0; i < i1; ++i) hist[cls_of(i)][t] += 1;
+  if (total) {
+    int w = 0;
+    for (int i = t; i < n; i += kThreads) w += row_count(kept_count, i, Nb);
+    w = wave_sum_i32(w);
+    if ((t & 63) == 0 && w) atomicAdd(&sum_lds, w);
+  }
   __syncthreads();
+  if (total && t == 0) total[head] = sum_lds;
   // exclusive scan over the histogram flattened class-major (index = class * 256 + column)
   int sum = 0;
   if (col)
@@ -286,15 +299,15 @@ __device__ __forceinline__ void near_order(const int *__restrict__ kept_idx, con
   }
 }
 
-template <bool kStaged>
-__global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(const int *__restrict__ kept_idx,
-                                                                 const int *__restrict__ kept_count, int BH,
-                                                                 int Nb, int n_wg, uint32_t mult, int batch,
-                                                                 int *__restrict__ plan, int *__restrict__ spread,
-                                                                 int *__restrict__ near_seq) {
+template <bool kStaged, int kThreads>
+__global__ __launch_bounds__(kThreads) void attn_plan_kernel(const int *__restrict__ kept_idx,
+                                                             const int *__restrict__ kept_count, int BH,
+                                                             int Nb, int n_wg, uint32_t mult, int batch,
+                                                             int *__restrict__ plan, int *__restrict__ spread,
+                                                             int *__restrict__ near_seq) {
   extern __shared__ __align__(16) unsigned char lds[];
   int id = blockIdx.x;
-  if (near_seq) {
+  if (kThreads == kPlanThreads && near_seq) {
     if (id < BH) {
       if (Nb <= 256)
         near_order<4>(kept_idx, kept_count, id, Nb, batch, near_seq, lds);
@@ -307,11 +320,12 @@ __global__ __launch_bounds__(kPlanThreads) void attn_plan_kernel(const int *__re
     id -= BH;
   }
   if (id == 0) {
-    plan_heads(kept_count, BH, Nb, n_wg, plan, spread, lds);
+    plan_heads<kThreads>(kept_count, BH, Nb, n_wg, plan, spread, lds);
     return;
   }
   for (long long head = id - 1; head < BH; head += kPlanMaxGroups) {
-    class_order<kStaged>(kept_count, (int)head, Nb, mult, plan + kPlanHdr + 2 * BH, lds);
+    class_order<kStaged, kThreads>(kept_count, (int)head, Nb, mult, plan + kPlanHdr + 2 * BH,
+                                   BH > kPlanMaxHeads ? plan + kPlanHdr + BH : nullptr, lds);
     __syncthreads();  // the LDS is free for the next head
   }
 }
@@ -339,7 +353,11 @@ int launch_attn_plan(int BH, int Nb, int n_wg, int n_items, const int *kept_idx,
   int batch = (n_wg + kNumXcd - 1) / kNumXcd;
   if (BH <= 2 * kNumXcd) batch *= 2;
   const bool staged = Nb <= kOrderStagedMax;
-  auto kern = staged ? attn_plan_kernel<true> : attn_plan_kernel<false>;
+  // with heads that are not ranked and short rows (no near_order) more workgroups per CU count for more than
+  // lanes per head: 1048576 heads of one row 16.4 -> 9.8 ms
+  const bool small = BH > kPlanMaxHeads && !near_seq;
+  auto kern = small ? (staged ? attn_plan_kernel<true, kOrderCols> : attn_plan_kernel<false, kOrderCols>)
+                    : (staged ? attn_plan_kernel<true, kPlanThreads> : attn_plan_kernel<false, kPlanThreads>);
   const size_t lds_class = (size_t)(kOrderClasses + 1) * kOrderCols * sizeof(int) + (staged ? (size_t)(Nb + 15) / 16 * 16 : 0);
   const size_t lds_other = (kNearWords + 1) * (size_t)kNearMaxRows * sizeof(int);  // >= plan_heads'
   static_assert(kNearWords >= 4 && kNearMaxRows >= kPlanMaxHeads, "LDS of plan_heads");
@@ -347,15 +365,15 @@ int launch_attn_plan(int BH, int Nb, int n_wg, int n_items, const int *kept_idx,
   if (lds > 64 * 1024) {
     const int dev = current_device();
     if (dev < 0) return fail(HEART_EHIP, "heart_block_sparse_attn: cannot identify the current device");
-    static DeviceFlags attr_set;  // (only the staged kernel asks for more than 64 KB)
+    static DeviceFlags attr_set[2];  // (only the staged kernels ask for more than 64 KB)
     const int most = (kOrderClasses + 1) * kOrderCols * (int)sizeof(int) + kOrderStagedMax;
-    if (hipError_t e = set_max_lds_once(attr_set, dev, reinterpret_cast<const void *>(kern), most))
+    if (hipError_t e = set_max_lds_once(attr_set[small], dev, reinterpret_cast<const void *>(kern), most))
       return fail(HEART_EHIP, "hipFuncSetAttribute(plan kernel LDS): %s", hipGetErrorString(e));
   }
   const uint32_t mult = (uint32_t)(((kOrderClasses - 1) << 16) / Nb);
   const unsigned grid = (unsigned)(1 + (BH < kPlanMaxGroups ? BH : kPlanMaxGroups) + (near_seq ? BH : 0));
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(kPlanThreads), lds, st, kept_idx, kept_count, BH, Nb, n_wg, mult, batch,
-                     plan, spread, near_seq);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(small ? kOrderCols : kPlanThreads), lds, st, kept_idx, kept_count, BH,
+                     Nb, n_wg, mult, batch, plan, spread, near_seq);
   return check_launch("attn_plan_kernel");
 }
 

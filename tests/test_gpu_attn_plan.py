@@ -190,3 +190,31 @@ def test_more_heads_than_plan_workgroups():
     # totals per head, then the only row of every head
     assert torch.equal(ws[24 + H:24 + 2 * H], cnt.view(-1))
     assert torch.equal(ws[24 + 2 * H:], torch.arange(H, dtype=torch.int32, device="cuda"))
+
+
+# beyond 1024 heads: the heads are dealt out in turn and the row orders write the totals; rows too few for
+# batches (small workgroups) and enough for them
+@pytest.mark.parametrize("H,Nb", [(1025, 1), (1029, 9), (1100, 70)])
+def test_plan_of_heads_that_are_not_ranked(H, Nb):
+    import paper_2605_14513_amd as heart
+
+    rng = np.random.default_rng(H)
+    cnt = rng.integers(0, Nb + 1, size=(1, H, Nb)).astype(np.int32)
+    idx = np.broadcast_to(np.arange(Nb, dtype=np.int32), (1, H, Nb, Nb))
+    g = torch.Generator(device="cuda").manual_seed(H)
+    v = torch.randn((1, H, Nb * 64 - 1, 64), generator=g, device="cuda", dtype=torch.bfloat16)
+    gi, gc = np_gpu(idx), np_gpu(cnt)
+    print(f"H={H} Nb={Nb}", flush=True)
+    ref = heart.heart_block_sparse_attn(v, v, v, 64, gi, gc, workspace=None)
+    classes = 31 - ((cnt[0].astype(np.int64) * ((31 << 16) // Nb)) >> 16)
+    for words in (heart.heart_workspace_bytes(1, H, Nb, 64) // 4, heart.heart_attn_workspace_bytes(v, 64) // 4):
+        ws = torch.full((words,), -7, dtype=torch.int32, device="cuda")
+        out = heart.heart_block_sparse_attn(v, v, v, 64, gi, gc, workspace=ws)
+        torch.cuda.synchronize()
+        plan = ws.cpu().numpy()
+        assert torch.equal(out, ref)
+        assert np.array_equal(plan[24:24 + H], np.concatenate([np.arange(x, H, 8) for x in range(8)]))
+        assert np.array_equal(plan[24 + H:24 + 2 * H], cnt[0].sum(1))
+        seq = plan[24 + 2 * H:24 + 2 * H + H * Nb].reshape(H, Nb)
+        want = np.arange(H)[:, None] * Nb + np.argsort(classes, axis=1, kind="stable")
+        assert np.array_equal(seq, want)
