@@ -86,6 +86,7 @@ struct EbcLines {
   long long inner, lines;
   long long wdiv;  // 0: all weights are 1
   int wmod;
+  int share;  // wavefronts that the coefficients of 32 lines are dealt over, in pairs of 16
 };
 
 __device__ __forceinline__ long long ebc_div(long long a, long long b) {
@@ -204,26 +205,33 @@ __device__ __forceinline__ void ebc_tile(EbcBatch<TIn> &cur, const EbcTile<TIn> 
 // squares, e_in += sum of the squares of the elements (kSumIn).  The loads of the next 16 elements,
 // or of the next tile, are always in flight, those of the first while the table is made: a line is
 // short, and a wavefront that waited for every load would do nothing else.
-template <typename TIn, bool kUnit, bool kStore, bool kSumIn>
+// A unit of work is a tile of lines, or (kShared) every share-th pair of its coefficient tiles.
+template <bool kShared, typename TIn, bool kUnit, bool kStore, bool kSumIn>
 __device__ __forceinline__ void ebc_contract(const TIn *__restrict__ in, double *__restrict__ out,
                                              const EbcLines &L, int blk, int n_blk, double *tab,
                                              double &e_out, double &e_in) {
   const int wave = threadIdx.x >> 6;
-  const int K = ebc_coefs(L.n), KT = (K + 15) / 16;
-  const long long tiles = (L.lines + kEbcTileCols - 1) / kEbcTileCols;
+  const int K = ebc_coefs(L.n), KT = (K + 15) / 16, share = kShared ? L.share : 1;
+  const long long units = (L.lines + kEbcTileCols - 1) / kEbcTileCols * share;
   const long long first = (long long)blk * kEbcWaves + wave, stride = (long long)n_blk * kEbcWaves;
-  EbcTile<TIn> t = ebc_tile_at<TIn, kUnit>(in, L, first);
+  auto tile_of = [&](long long u) -> long long { return kShared ? ebc_div(u, share) : u; };
+  EbcTile<TIn> t = ebc_tile_at<TIn, kUnit>(in, L, tile_of(first));
   EbcBatch<TIn> cur;
   ebc_load<TIn, kUnit>(cur, t, L, 0);
   ebc_table(L.n, tab);
-  for (long long tile = first; tile < tiles; tile += stride) {
-    const EbcTile<TIn> next = ebc_tile_at<TIn, kUnit>(in, L, tile + stride);  // (past the end: no line exists)
+  for (long long u = first; u < units; u += stride) {
+    const EbcTile<TIn> next = ebc_tile_at<TIn, kUnit>(in, L, tile_of(u + stride));  // (past the end: no line exists)
+    int kt = kShared ? 2 * (int)(u - tile_of(u) * share) : 0;
+    auto after = [&](int k) -> const EbcTile<TIn> & { return k < KT ? t : next; };
     if (KT == 1) {
       ebc_tile<1, TIn, kUnit, kStore, kSumIn>(cur, t, next, out, L, tab, 0, K, e_out, e_in);
     } else {
-      ebc_tile<2, TIn, kUnit, kStore, kSumIn>(cur, t, KT > 2 ? t : next, out, L, tab, 0, K, e_out, e_in);
-      for (int kt = 2; kt < KT; kt += 2)  // (rows of the last pair past K are dropped)
-        ebc_tile<2, TIn, kUnit, kStore, false>(cur, t, kt + 2 < KT ? t : next, out, L, tab, kt, K, e_out, e_in);
+      if (kt == 0) {
+        ebc_tile<2, TIn, kUnit, kStore, kSumIn>(cur, t, after(2 * share), out, L, tab, 0, K, e_out, e_in);
+        kt = 2 * share;
+      }
+      for (; kt < KT; kt += 2 * share)  // (rows of the last pair past K are dropped)
+        ebc_tile<2, TIn, kUnit, kStore, false>(cur, t, after(kt + 2 * share), out, L, tab, kt, K, e_out, e_in);
     }
     t = next;
   }
@@ -231,6 +239,7 @@ __device__ __forceinline__ void ebc_contract(const TIn *__restrict__ in, double 
 
 // Workgroups [0, gx): x coefficients of err -> cx, |err|^2.  [gx, gx + gt): S_T of err.  The rest:
 // |dense|^2.  ticket: zeroed for ebc_third.
+template <bool kShared>
 __global__ __launch_bounds__(kEbcThreads, 4) void ebc_first_kernel(
     const float *__restrict__ err, const float *__restrict__ dense, long long total, EbcLines lx, EbcLines lt,
     int gx, int gt, double *__restrict__ cx, double *__restrict__ partials, unsigned *__restrict__ ticket) {
@@ -239,7 +248,7 @@ __global__ __launch_bounds__(kEbcThreads, 4) void ebc_first_kernel(
   int blk = blockIdx.x;
   double e_out = 0.0, e_in = 0.0;
   if (blk < gx) {
-    ebc_contract<float, true, true, true>(err, cx, lx, blk, gx, tab, e_out, e_in);
+    ebc_contract<kShared, float, true, true, true>(err, cx, lx, blk, gx, tab, e_out, e_in);
     // (e_in of a line is spread over the four lane groups, each element once)
     const double s = ebc_block_sum(e_in, red);
     if (threadIdx.x == 0) {
@@ -248,7 +257,7 @@ __global__ __launch_bounds__(kEbcThreads, 4) void ebc_first_kernel(
     }
   } else if (blk < gx + gt) {
     blk -= gx;
-    ebc_contract<float, false, false, false>(err, nullptr, lt, blk, gt, tab, e_out, e_in);
+    ebc_contract<kShared, float, false, false, false>(err, nullptr, lt, blk, gt, tab, e_out, e_in);
     const double s = ebc_block_sum(e_out, red);
     if (threadIdx.x == 0) partials[1 * kEbcPartials + blk] = s;
   } else {
@@ -274,13 +283,14 @@ __global__ __launch_bounds__(kEbcThreads, 4) void ebc_first_kernel(
 }
 
 // y coefficients of the x coefficients -> cyx, S_XY
+template <bool kShared>
 __global__ __launch_bounds__(kEbcThreads, 3) void ebc_second_kernel(const double *__restrict__ cx, EbcLines ly,
                                                                  double *__restrict__ cyx,
                                                                  double *__restrict__ partials) {
   __shared__ double tab[2 * kEbcMaxAxis];
   __shared__ double red[kEbcWaves];
   double e_out = 0.0, e_in = 0.0;
-  ebc_contract<double, true, true, false>(cx, cyx, ly, blockIdx.x, gridDim.x, tab, e_out, e_in);
+  ebc_contract<kShared, double, true, true, false>(cx, cyx, ly, blockIdx.x, gridDim.x, tab, e_out, e_in);
   const double s = ebc_block_sum(e_out, red);
   if (threadIdx.x == 0) partials[2 * kEbcPartials + blockIdx.x] = s;
 }
@@ -293,6 +303,7 @@ struct EbcFinish {
 // S_XYT; the workgroup that draws the last ticket adds up the partial sums and writes the result.
 // The partial sums of this launch cross workgroups of different XCDs and therefore move with
 // device-scope stores and loads; a workgroup takes its ticket after its store is acknowledged.
+template <bool kShared>
 __global__ __launch_bounds__(kEbcThreads, 3) void ebc_third_kernel(const double *__restrict__ cyx, EbcLines lt,
                                                                 double *__restrict__ partials,
                                                                 unsigned *__restrict__ ticket, EbcFinish f,
@@ -301,7 +312,7 @@ __global__ __launch_bounds__(kEbcThreads, 3) void ebc_third_kernel(const double 
   __shared__ double red[kEbcWaves];
   __shared__ int s_last;
   double e_out = 0.0, e_in = 0.0;
-  ebc_contract<double, true, false, false>(cyx, nullptr, lt, blockIdx.x, gridDim.x, tab, e_out, e_in);
+  ebc_contract<kShared, double, true, false, false>(cyx, nullptr, lt, blockIdx.x, gridDim.x, tab, e_out, e_in);
   const double s = ebc_block_sum(e_out, red);
   if (threadIdx.x == 0) {
     __hip_atomic_store(&partials[3 * kEbcPartials + blockIdx.x], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -359,26 +370,35 @@ int launch_ebc_band_error(long long C, int T, int Y, int X, const float *err, co
   const int KX = ebc_coefs(X), KY = ebc_coefs(Y);
   double *cx = ws, *cyx = cx + total, *partials = cyx + total;
   unsigned *ticket = reinterpret_cast<unsigned *>(partials + kEbcSums * (size_t)kEbcPartials);
-  const EbcLines lx{X, 1, C * T * Y, 0, 1};
-  const EbcLines lt{T, (long long)Y * X, C * Y * X, 0, 1};
-  const EbcLines ly{Y, 1, (long long)KX * C * T, C * T, KX};
-  const EbcLines lyx{T, 1, (long long)KY * KX * C, C, KX};
+  EbcLines lx{X, 1, C * T * Y, 0, 1, 1};
+  EbcLines lt{T, (long long)Y * X, C * Y * X, 0, 1, 1};
+  EbcLines ly{Y, 1, (long long)KX * C * T, C * T, KX, 1};
+  EbcLines lyx{T, 1, (long long)KY * KX * C, C, KX, 1};
   // workgroups of a contraction: one tile per wavefront, or the fewest equal rounds that leave no
   // more than `most`: the workgroups of a launch are resident at once (four wavefronts per SIMD in
-  // the first, where the three parts share them by their matrix work and bytes; three in the others)
-  auto groups = [](const EbcLines &l, long long most) -> int {
-    const long long g = (l.lines + kEbcTileCols * kEbcWaves - 1) / (kEbcTileCols * kEbcWaves);
+  // the first, where the three parts share them by their matrix work and bytes at 21 x 30 x 52; three
+  // in the others).  With at most a quarter as many tiles as wavefronts the coefficients of a tile are dealt over
+  // as many as there are for it: a long axis and few lines would else leave one wavefront hundreds of
+  // coefficients of hundreds of elements (1 x 5 x 9 x 1000: 912 -> 83 us, 16 x 1024 x 8 x 8: 2003 -> 169 us;
+  // with half as many tiles, 16 x 33 x 45 x 80: 37.5 -> 38.7 us).
+  auto groups = [](EbcLines &l, long long most) -> int {
+    const long long tiles = (l.lines + kEbcTileCols - 1) / kEbcTileCols, places = most * kEbcWaves / tiles;
+    const int pairs = ((ebc_coefs(l.n) + 15) / 16 + 1) / 2;
+    if (places >= 4) l.share = places < pairs ? (int)places : pairs;
+    const long long g = (tiles * l.share + kEbcWaves - 1) / kEbcWaves;
     const long long rounds = (g + most - 1) / most;
     return (int)((g + rounds - 1) / rounds);
   };
   const int gx = groups(lx, 384), gt = groups(lt, 400), gy = groups(ly, 768), gyx = groups(lyx, 768);
   const int gd = (int)std::min<long long>((total + 8 * kEbcThreads - 1) / (8 * kEbcThreads), 240);
   const EbcFinish f{{gx, gt, gy, gyx, gd}, (double)T, (double)Y * X, {w[0], w[1], w[2], w[3]}, epsilon};
-  hipLaunchKernelGGL(ebc_first_kernel, dim3((unsigned)(gx + gt + gd)), dim3(kEbcThreads), 0, st, err, dense, total, lx,
-                     lt, gx, gt, cx, partials, ticket);
-  hipLaunchKernelGGL(ebc_second_kernel, dim3((unsigned)gy), dim3(kEbcThreads), 0, st, cx, ly, cyx, partials);
-  hipLaunchKernelGGL(ebc_third_kernel, dim3((unsigned)gyx), dim3(kEbcThreads), 0, st, cyx, lyx, partials, ticket, f,
-                     out);
+  auto first = lx.share > 1 || lt.share > 1 ? ebc_first_kernel<true> : ebc_first_kernel<false>;
+  auto second = ly.share > 1 ? ebc_second_kernel<true> : ebc_second_kernel<false>;
+  auto third = lyx.share > 1 ? ebc_third_kernel<true> : ebc_third_kernel<false>;
+  hipLaunchKernelGGL(first, dim3((unsigned)(gx + gt + gd)), dim3(kEbcThreads), 0, st, err, dense, total, lx, lt, gx, gt, cx,
+                     partials, ticket);
+  hipLaunchKernelGGL(second, dim3((unsigned)gy), dim3(kEbcThreads), 0, st, cx, ly, cyx, partials);
+  hipLaunchKernelGGL(third, dim3((unsigned)gyx), dim3(kEbcThreads), 0, st, cyx, lyx, partials, ticket, f, out);
   return check_launch("ebc kernels");
 }
 

@@ -41,9 +41,11 @@ def test_band_error_matches_fft_definition(shape):
 
 
 # axes around the edges of the coefficient tiles (16 coefficients a tile, in pairs: 31 / 33 coefficients at
-# 63 / 64 elements, 49 at 96..99), the longest axis in each place, lines that do not fill a tile of 32
+# 63 / 64 elements, 49 at 96..99), the longest axis in each place, lines that do not fill a tile of 32; long axes
+# of few lines, whose coefficients several wavefronts share: one pair of tiles each, or not the same number
 @pytest.mark.parametrize("shape", [(1, 1, 1, 1), (3, 63, 2, 64), (1, 64, 65, 3), (2, 99, 5, 96), (1, 1024, 3, 5),
-                                   (2, 3, 1024, 1), (1, 2, 5, 1023), (33, 4, 4, 1), (700, 5, 6, 33)])
+                                   (2, 3, 1024, 1), (1, 2, 5, 1023), (33, 4, 4, 1), (700, 5, 6, 33),
+                                   (1, 5, 9, 1000), (4, 9, 113, 1000)])
 def test_band_error_at_tile_edges(shape):
     import paper_2605_14513_amd as heart
 
