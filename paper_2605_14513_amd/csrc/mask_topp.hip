@@ -120,10 +120,11 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
   // (kDealRows) the work items of the refreshed heads are taken in order and cut into eighths, one per
   // XCD (workgroup ids are dealt to them round-robin): an XCD then reads the means of two or three
   // heads, one or two at a time, instead of all heads' (13 of 24 heads refreshed, Nb = 931, slices:
-  // 114 -> 97 us, 0.48 MB of slices a head against 4 MB of L2).  Up to 256 key blocks the means of the
-  // heads in flight fit every L2 and this gained nothing (Nb = 256, 40 heads: 25.0 and 25.4 us), and with
-  // hundreds of heads the look at all flags costs (1024 heads of 32 rows: 34 -> 47 us): there the heads
-  // follow each other in index order.
+  // 114 -> 97 us, 0.48 MB of slices a head against 4 MB of L2; no head refreshed: 23 -> 11 us), at 0.1 to 0.5 us
+  // for the look at the flags where neither counts (12 heads of 400 rows, fp64 scores: 25.6 -> 26.1 us).
+  // Up to 256 key blocks the means of the heads in flight fit every L2 and this gained nothing (Nb = 256, 40
+  // heads: 25.0 and 25.4 us), and with hundreds of heads the look at all flags costs (1024 heads of 32 rows:
+  // 34 -> 47 us): there the heads follow each other in index order.
   const int groups = (Nb + kRows - 1) / kRows;
   long long bh;
   int i0;
@@ -145,12 +146,12 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
         }
       }
     }
-    const long long items = (long long)n_heads * groups;
-    const int x = (int)(blockIdx.x % kNumXcd);
-    const long long w = items * x / kNumXcd + blockIdx.x / kNumXcd;
+    // (32 bits hold it: at most 256 heads of 64 row groups; in 64 bits the divisions cost 0.2 to 0.4 us)
+    const unsigned items = (unsigned)(n_heads * groups), x = blockIdx.x % kNumXcd;
+    const unsigned w = items * x / kNumXcd + blockIdx.x / kNumXcd;
     if (w >= items * (x + 1) / kNumXcd) return;
-    int rank = (int)(w / groups);
-    i0 = (int)(w - (long long)rank * groups) * kRows;
+    int rank = (int)(w / (unsigned)groups);
+    i0 = (int)(w - (unsigned)(rank * groups)) * kRows;
     if (refresh) {
       int h0 = 0;
       while (rank >= __popcll(set)) {  // (ends: rank < n_heads)
