@@ -167,7 +167,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
   } else {
     bh = blockIdx.x / groups;
     i0 = (int)(blockIdx.x % groups) * kRows;
-    if (bh >= BH || (refresh && !refresh[bh])) return;  // reused head: cached mask persists
+    if (refresh && !refresh[bh]) return;  // reused head: cached mask persists
   }
   const int h = (int)(bh % H);
 
@@ -667,8 +667,10 @@ static int launch_cmax_d(int B, int H, int Nb, int D, const float *qblk, const f
   int groups = (Nb + kRows - 1) / kRows;
   // logits of the row group; the fp64 score stage also keeps its query rows there
   size_t lds = scores_in ? 0 : (size_t)kRows * 64 * CMAX * 4 + (kInt8 ? 0 : (size_t)kRows * (D + 2) * 8);
-  // (eight XCDs with a place for an eighth of all items, rounded up)
-  long long nwg = ((long long)B * H * groups + kNumXcd - 1) / kNumXcd * kNumXcd;
+  long long nwg = (long long)B * H * groups;
+  // dealt over the XCDs: a place for an eighth of all items on each, rounded up.  (Not otherwise: a launch holds
+  // 2^23 - 1 workgroups of 512 threads)
+  if (CMAX > kDealRows / 64 && (long long)B * H <= kDealHeads) nwg = (nwg + kNumXcd - 1) / kNumXcd * kNumXcd;
   auto kern = mask_topp_kernel<CMAX, NF4T, kInt8>;
   if (lds > 64 * 1024) {
     const int dev = current_device();

@@ -55,3 +55,18 @@ def test_refreshed_heads_only(B, H, Nb, which, slices):
     for got, want, untouched in ((mask, full[0], 9), (idx, full[1], -1), (cnt, full[2], -5)):
         assert torch.equal(got[on], want[on])
         assert (got[~on] == untouched).all()
+
+
+def test_as_many_workgroups_as_a_launch_holds():
+    """2^23 - 1 heads of one block: the last grid of 512-thread workgroups whose threads fit 32 bits."""
+    import paper_2605_14513_amd as heart
+
+    H = (1 << 23) - 1
+    x = torch.ones((1, H, 1, 16), device="cuda")
+    tau = torch.full((H,), 0.9, device="cuda")
+    mask = torch.zeros((1, H, 1, 1), dtype=torch.uint8, device="cuda")
+    idx, cnt = torch.full((1, H, 1, 1), -1, dtype=torch.int32, device="cuda"), mask[..., 0].int()
+    print(f"H={H}", flush=True)
+    heart.heart_mask_topp(x, x, tau, mask=mask, kept_idx=idx, kept_count=cnt)
+    torch.cuda.synchronize()
+    assert (mask == 1).all() and (idx == 0).all() and (cnt == 1).all()
