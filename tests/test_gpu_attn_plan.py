@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import oracle
-from heart_testlib import attn_atol, check_attn_plan, np_gpu, u16
+from heart_testlib import check_attn_plan, np_gpu, u16
 
 pytestmark = pytest.mark.gpu
 
@@ -73,30 +73,47 @@ def test_batches_of_similar_rows(H, Nb, block):
 
 
 # parts per row with two workgroups per CU (block 128) or four; one head's places not divisible by the
-# rows; both block sizes; token-major tensors; short last blocks
-@pytest.mark.parametrize("H,Nb,D,block,tail,parts", [(1, 8, 128, 128, 0, 2), (1, 64, 128, 128, 5, 8), (1, 67, 128, 64, 63, 15),
-                                                     (3, 50, 128, 128, 127, 3), (1, 64, 64, 64, 1, 16), (3, 50, 64, 64, 0, 6),
-                                                     (4, 9, 64, 128, 100, 2)])
-def test_split_rows(H, Nb, D, block, tail, parts):
+# rows; both block sizes; token-major tensors; short last blocks; with `ramp` the logits of a block lie that many
+# log2 units above (or below) those of the block before it, so that the parts' reference exponents lie
+# 160 to 200 apart and all parts but the last, or the first, have no weight
+@pytest.mark.parametrize("H,Nb,D,block,tail,parts,ramp", [
+    (1, 8, 128, 128, 0, 2, 0), (1, 64, 128, 128, 5, 8, 0), (1, 67, 128, 64, 63, 15, 0), (3, 50, 128, 128, 127, 3, 0),
+    (1, 64, 64, 64, 1, 16, 0), (3, 50, 64, 64, 0, 6, 0), (4, 9, 64, 128, 100, 2, 0), (1, 64, 128, 128, 5, 8, 25),
+    (1, 64, 64, 64, 1, 16, 40), (1, 66, 128, 64, 17, 15, 40)])
+def test_split_rows(H, Nb, D, block, tail, parts, ramp):
     import paper_2605_14513_amd as heart
 
     N = Nb * block - tail
     rng = np.random.default_rng(Nb * 131 + D)
     cnt = rng.integers(0, Nb + 1, size=(1, H, Nb)).astype(np.int32)
     cnt[0, 0, :4] = (0, 1, parts - 1, Nb)  # no, one, almost one key block a part, all
+    if ramp:
+        cnt[0, 0, 4:12] = Nb
     idx = np.zeros((1, H, Nb, Nb), np.int32)
     for h in range(H):
         for i in range(Nb):
             idx[0, h, i, :cnt[0, h, i]] = np.sort(rng.permutation(Nb)[:cnt[0, h, i]])
     idx[0, 0, 1, 0] = Nb - 1  # the short last block alone
     g = torch.Generator(device="cuda").manual_seed(Nb)
-    q, k, v = (torch.randn((1, N, H, D), generator=g, device="cuda").bfloat16().transpose(1, 2) for _ in range(3))
+    q, k, v = (torch.randn((1, N, H, D), generator=g, device="cuda") for _ in range(3))
+    if ramp:
+        # rising, falling, and nearly level (parts that all have some weight)
+        blk = torch.arange(N, device="cuda") // block
+        q[..., 0] = torch.tensor([8.0, -8.0, 0.05], device="cuda")[blk % 3][None, :, None]
+        k[..., 0] = (blk * (ramp * D ** 0.5 / (8 * 1.442695)))[None, :, None]
+    q, k, v = (x.bfloat16().transpose(1, 2) for x in (q, k, v))
     gi, gc = np_gpu(idx), np_gpu(cnt)
     n_bytes = heart.heart_attn_workspace_bytes(q, block)
     # per part and 32 query rows: 32 x D accumulators and 64 lanes' softmax states, 4 bytes each
     assert n_bytes == 4 * parts * H * Nb * (block // 32) * (32 * D + 128)
-    print(f"H={H} Nb={Nb} D={D} block={block} parts={parts}", flush=True)
-    want = None
+    print(f"H={H} Nb={Nb} D={D} block={block} parts={parts} ramp={ramp}", flush=True)
+    # (the oracle has no value for a row without blocks, the kernel zeros)
+    want, mass = (np.nan_to_num(oracle.attn(u16(q.contiguous()), u16(k.contiguous()), u16(x.contiguous()), block, idx, cnt))
+                  for x in (v, v.abs()))
+    # The kernel rounds every weight to bf16 (by at most 2^-8 of it, so at most 2^-8 sum p|v| of an output) and the
+    # output (2^-8 of it); a tenth more for fp32.  With a ramp the logits reach 1.4e4 before the scaling, where fp32
+    # has steps of 2^-10: four of them in a sum move a weight by up to 4 * 2^-10 / sqrt(64).
+    each = 1.1 * 2.0 ** -8 * (mass + np.abs(want)) + (5e-4 * mass if ramp else 0.0)
     for flags in (0, heart.HEART_ATTN_FOLD_SCALE):
         ws = torch.full((n_bytes + 64,), 255, dtype=torch.uint8, device="cuda")  # (NaN where nothing is written)
         lse, lse0 = (torch.full((1, H, N), float("nan"), device="cuda") for _ in range(2))
@@ -106,16 +123,21 @@ def test_split_rows(H, Nb, D, block, tail, parts):
         torch.cuda.synchronize()
         assert (ws[n_bytes:] == 255).all()
         assert torch.equal(small, one)  # no room for the parts: the unsplit launch
-        # either side rounds every weight to bf16, relative to its own reference exponent: 2^-9 of each
-        # weight, at most 2^-9 max|v| of the output; and its output: 2^-9 of the value
-        a, b = out.float(), one.float()
-        assert ((a - b).abs() <= 2.0 ** -8 * (v.float().abs().max() + b.abs())).all(), (a - b).abs().max().item()
         empty = torch.isinf(lse0)
         assert torch.equal(torch.isinf(lse), empty) and (lse - lse0)[~empty].abs().max() <= 2e-5 * lse0[~empty].abs().max()
-        if want is None:
-            want = oracle.attn(u16(q.contiguous()), u16(k.contiguous()), u16(v.contiguous()), block, idx, cnt)
-            want = np.nan_to_num(want)  # (the oracle has no value for a row without blocks, the kernel zeros)
-        assert np.abs(out.float().cpu().numpy() - want).max() <= attn_atol(want)
+        a, b = out.float().cpu().numpy(), one.float().cpu().numpy()
+        assert (np.abs(a - b) <= 2.0 * each).all(), (np.abs(a - b) / np.maximum(each, 1e-30)).max()
+        if flags and ramp:
+            continue  # (the folded scale rounds the query's 8 and with it logits of 2^11: only the launches are compared)
+        # each output; the folded scale rounds q as well, 2^-8 of every product of a logit (their absolute values
+        # add up to about 0.64 sqrt(D), at most 8)
+        bound = each + (8 * 2.0 ** -8 * mass if flags else 0.0)
+        assert (np.abs(a - want) <= bound).all(), (np.abs(a - want) / np.maximum(bound, 1e-30)).max()
+        # each row: the roundings are independent and a bf16 rounding is 1.6e-3 in the root mean square (2^-8 / sqrt(3),
+        # over the values between two powers of two), so its relative error is about sqrt(2) of that, with the folded
+        # scale sqrt(3); three times as much
+        err, size = np.linalg.norm(a - want, axis=-1), np.linalg.norm(want, axis=-1)
+        assert (err <= 3 * 1.63e-3 * (3 if flags else 2) ** 0.5 * size).all(), (err / np.maximum(size, 1e-30)).max()
 
 
 # D = 128: eight parts of eight blocks; the small workgroups of blocks of 64: sixteen parts of four
