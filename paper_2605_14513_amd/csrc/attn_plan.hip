@@ -31,8 +31,8 @@ __device__ __forceinline__ int row_count(const int *kept_count, int i, int Nb) {
 }
 
 // Heads ranked by total kept count, greedy assignment of heads (heaviest first) to the least
-// loaded XCD, head table, cursors (`spread` if given, else the header's) reset to the number of
-// attention workgroups of their XCD (n_wg in all; those take the first items of its list).
+// loaded XCD, head table, cursors (`spread` if given, else the header's) reset behind the items that the
+// n_wg attention workgroups start with.
 template <int kThreads>
 __device__ __forceinline__ void plan_heads(const int *__restrict__ kept_count, int BH, int Nb, int n_wg,
                                            int *__restrict__ plan, int *__restrict__ spread, unsigned char *lds) {
@@ -97,7 +97,7 @@ __device__ __forceinline__ void plan_heads(const int *__restrict__ kept_count, i
   }
   __syncthreads();
   if (t < kNumXcd) {
-    const int first = n_wg / kNumXcd + (t < n_wg % kNumXcd ? 1 : 0);
+    const int first = list_first(n_wg, t, BH);
     if (spread) spread[t * kCursorSpread] = first;
     plan[t] = spread ? n_heads[t] * Nb : first;
     plan[kNumXcd + t] = n_heads[t] * Nb;

@@ -588,15 +588,16 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
 
   // ---- work loop --------------------------------------------------------------------------
   // With a plan the workgroups are persistent (two per CU): each takes items from the list
-  // of its XCD (workgroup ids are dealt round-robin to the XCDs) and, once that list is
-  // empty, from the other XCDs' lists.  The first item of a workgroup is the one its number
-  // among the workgroups of its XCD names; the plan starts the cursors behind those, so the
+  // of its XCD (workgroup ids are dealt round-robin to the XCDs; one head: all from list 0) and,
+  // once that list is empty, from the other XCDs' lists.  The first item of a workgroup is the
+  // one its number among the workgroups of its list names; the plan starts the cursors behind those, so the
   // launch does not begin with hundreds of atomics on one cache line.  Without a plan a
   // workgroup processes the one item its id maps to.
   __shared__ int s_item;
   const int x0 = (int)(blockIdx.x % kNumXcd);
-  const int len0 = plan ? plan[kNumXcd + x0] : 0;
-  const int off0 = plan ? plan[2 * kNumXcd + x0] : 0;
+  const int own = BH == 1 ? 0 : x0;  // own list
+  const int len0 = plan ? plan[kNumXcd + own] : 0;
+  const int off0 = plan ? plan[2 * kNumXcd + own] : 0;
   // entry i of a list of `len` items whose heads start at off_x in the head table: the heads one
   // after the other, or, where a list has few of them, their rows in turn
   const int *head_tbl = plan + kPlanHdr;
@@ -606,8 +607,8 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     const int r = in_turn ? i % nh : i / Nb, p = in_turn ? i / nh : i - r * Nb;
     return seq[head_tbl[off_x + r] * Nb + p];
   };
-  const int n_own = ((int)gridDim.x - x0 + kNumXcd - 1) / kNumXcd;  // workgroups of this XCD
-  int i_own = (int)(blockIdx.x / kNumXcd);  // (wavefront 0) last entry taken from the own list
+  const int n_own = list_first((int)gridDim.x, own, BH);  // workgroups of this list
+  int i_own = (int)(BH == 1 ? blockIdx.x : blockIdx.x / kNumXcd);  // (wavefront 0) last entry taken from the own list
   // (wavefront 0) an item of the own list, else of the list whose next item is the longest, else
   // -1.  Lanes 0..7 look at the eight cursors at once and an atomic goes only to a list that still
   // has items: same-address atomics of all XCDs are served one after another (about 40 ns each),
@@ -615,7 +616,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   // queue of 8 atomics per workgroup -- 300 us at 1024 workgroups (D = 64, block 64, N = 6417,
   // 20 heads: 406 -> 90 us), 150 us at 512.
   auto take = [&]() -> int {
-    const int x = (x0 + lane) % kNumXcd;
+    const int x = (own + lane) % kNumXcd;
     const int len = lane < kNumXcd ? plan[kNumXcd + x] : 0;
     const int off = lane < kNumXcd ? plan[2 * kNumXcd + x] : 0;
     unsigned long long asked = 0;
@@ -632,7 +633,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
       if (key == 0) return -1;
       const int l = kNumXcd - 1 - (int)(key % kNumXcd);
       asked |= 1ull << l;  // (a list that turns out to be empty is not asked again)
-      const int xs = (x0 + l) % kNumXcd;
+      const int xs = (own + l) % kNumXcd;
       int i = 0;
       if (lane == 0) i = atomicAdd(&cursors[xs * cursor_step], 1);
       i = __builtin_amdgcn_readfirstlane(i);
@@ -677,7 +678,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   // microsecond, and neighbouring rows of a head, whose kept lists overlap, walk through
   // K/V together (reserving the next item a whole row ahead costs a third of the L2 hits).
   int i_next = -1, item_next = -1;
-  // (only while every workgroup of the XCD can expect another item of the own list: the last
+  // (only while every workgroup of the list can expect another item of the own list: the last
   // round looks at the cursors first, so that it ends without a queue of failing atomics)
   const bool ahead = !kSplit && plan && i_own + n_own < len0;
 
@@ -753,7 +754,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
         wait_loads_and_barrier();
 #pragma unroll
         for (int i = 0; i < EPB; ++i) asm volatile("" : "+s"(jn[i]));  // loaded before the barrier
-        if (ahead && t == 0 && st + 2 >= T) i_next = atomicAdd(&cursors[x0 * cursor_step], 1);
+        if (ahead && t == 0 && st + 2 >= T) i_next = atomicAdd(&cursors[own * cursor_step], 1);
         refill(STEP);
         one_slice(std::integral_constant<int, 1>{});
         if (st + 1 >= T) break;
@@ -788,7 +789,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
       wait_loads_and_barrier();
 #pragma unroll
       for (int i = 0; i < EPB; ++i) asm volatile("" : "+s"(jn[i]));  // loaded before the barrier
-      if (ahead && t == 0 && st + 2 >= T) i_next = atomicAdd(&cursors[x0 * cursor_step], 1);
+      if (ahead && t == 0 && st + 2 >= T) i_next = atomicAdd(&cursors[own * cursor_step], 1);
       refill(G_B0);
       // ---- slice s0+1; stage st+2 -> buffers 0 ----
       {
@@ -847,7 +848,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     wait_loads_and_barrier();
   }
   if (ahead && wave == 0) {
-    if (lane == 0 && i_next < 0) i_next = atomicAdd(&cursors[x0 * cursor_step], 1);  // (row without kept blocks)
+    if (lane == 0 && i_next < 0) i_next = atomicAdd(&cursors[own * cursor_step], 1);  // (row without kept blocks)
     i_next = __builtin_amdgcn_readfirstlane(i_next);
     if (i_next < len0) {
       i_own = i_next;
