@@ -141,6 +141,7 @@ constexpr int kSplitMax = 16;
 // floats of one wavefront's part: accumulators, reference exponent and row sum of every lane
 template <int D>
 constexpr int kPartFloats = 64 * (D / 2) + 128;
+constexpr float kNoKeys = -1.f;  // in the place of the row sum: a part without keys (a sum is not negative, but may be NaN)
 
 int attn_split(long long BH, long long Nb, int D, int block) {
   const int rows = D == 128 && block == 64 ? kStageRows<128, 64> : kStageRows<64, 64>;
@@ -167,7 +168,6 @@ template <int D, int BLK>
 __global__ __launch_bounds__(D * 2) void attn_merge_kernel(const float *__restrict__ part, int n_split,
                                                            uint16_t *__restrict__ out, long long osb, long long osh,
                                                            long long osn, int H, int N, int Nb,
-                                                           const int *__restrict__ kept_count,
                                                            float *__restrict__ lse) {
   constexpr int NW = BLK / 32;
   const int lane = threadIdx.x & 63, dt = threadIdx.x >> 6, l32 = lane & 31, hf = lane >> 5;
@@ -175,13 +175,11 @@ __global__ __launch_bounds__(D * 2) void attn_merge_kernel(const float *__restri
   const size_t step = (size_t)NW * kPartFloats<D>;  // from part to part of a row
   const float *src = part + ((size_t)item * n_split * NW + wave) * kPartFloats<D>;
   const float ninf = -__builtin_inff();
-  // keys of a part: per * s .. of the cnt kept blocks, as attn_kernel deals them
-  const int cnt = min(max(kept_count[item], 0), Nb), per = (cnt + n_split - 1) / n_split;
   float ms[kSplitMax], ls[kSplitMax];
 #pragma unroll
   for (int s = 0; s < kSplitMax; ++s) {
     ms[s] = s < n_split ? src[s * step + 64 * (D / 2) + lane] : ninf;
-    ls[s] = s < n_split ? src[s * step + 64 * (D / 2) + 64 + lane] : 0.f;
+    ls[s] = s < n_split ? src[s * step + 64 * (D / 2) + 64 + lane] : kNoKeys;
   }
   float m = ninf, l = 0.f;
 #pragma unroll
@@ -191,7 +189,7 @@ __global__ __launch_bounds__(D * 2) void attn_merge_kernel(const float *__restri
   const float m_fin = m == ninf ? 0.f : m;
 #pragma unroll
   for (int s = 0; s < kSplitMax; ++s) {
-    ms[s] = __builtin_amdgcn_exp2f(ms[s] - m_fin);  // weight of a part
+    ms[s] = __builtin_amdgcn_exp2f(ms[s] - m_fin);  // weight of a part (one without keys: 0)
     l = fmaf(ls[s], ms[s], l);
   }
   f32x4_t o[4];
@@ -213,7 +211,7 @@ __global__ __launch_bounds__(D * 2) void attn_merge_kernel(const float *__restri
         for (int g = 0; g < 4; ++g)
 #pragma unroll
           for (int e = 0; e < 4; ++e)  // (accumulators of a part without keys are not written)
-            o[g][e] = (s0 + s) * per < cnt ? fmaf(x[s][g][e], ms[s0 + s], o[g][e]) : o[g][e];
+            o[g][e] = ls[s0 + s] != kNoKeys ? fmaf(x[s][g][e], ms[s0 + s], o[g][e]) : o[g][e];
     }
   }
   const int bh = item / Nb, qb = item % Nb, n = qb * BLK + wave * 32 + l32;
@@ -868,7 +866,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     // ---- part of a row: unnormalised output and its softmax state, as the lanes hold them ----
     float *dst = part + ((size_t)(item * n_split + split) * NW + wave) * kPartFloats<D>;
     dst[64 * 16 * DT + lane] = m_ref;
-    dst[64 * 16 * DT + 64 + lane] = l_run;
+    dst[64 * 16 * DT + 64 + lane] = cnt > 0 ? l_run : kNoKeys;
     if (cnt > 0) {
       f32x4_t *o4 = reinterpret_cast<f32x4_t *>(dst);
 #pragma unroll
@@ -976,7 +974,7 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
   if (int rc = check_launch("attn_kernel")) return rc;
   if (!split) return HEART_OK;
   hipLaunchKernelGGL((attn_merge_kernel<D, BLK>), dim3((unsigned)(n_items * (BLK / 32))), dim3(D * 2), 0, st, part, n_split,
-                     (uint16_t *)out, s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, s.N, Nb, kept_count, lse);
+                     (uint16_t *)out, s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, s.N, Nb, lse);
   return check_launch("attn_merge_kernel");
 }
 
