@@ -214,8 +214,8 @@ int heart_scores_antidiag(const heart_shape *shape, const void *q, const void *k
  *   bf16.  The error against exact attention on the given bf16 inputs is that of the bf16
  *   rounding of weights and output: within 2e-2 * max(1, max|out| / 2) for any input scale.
  *   With HEART_ATTN_FOLD_SCALE (heart_block_sparse_attn_flags) q is instead multiplied by
- *   scale * log2(e) and rounded to bf16 once, which removes one multiply per logit (about
- *   3 % faster) at the price of one more bf16 rounding of the query: the same bound holds
+ *   scale * log2(e) and rounded to bf16 once, which removes one multiply per logit (1 to
+ *   2 % faster) at the price of one more bf16 rounding of the query: the same bound holds
  *   for q, k of unit scale (logits of a few units; normalised activations), but that error
  *   grows with the cube of the input scale.
  * q, k, v: bf16 with the strides of `shape`; out: bf16 with o_stride; kept_idx /

@@ -320,8 +320,9 @@ def heart_block_sparse_attn(q, k, v, block: int, kept_idx, kept_count, scale: fl
                             out=None, lse=None, workspace="auto", flags: int = 0):
     """Block-sparse attention over the kept key blocks; returns bf16 out like q.
 
-    workspace: a uint8/int32 GPU tensor of heart_attn_workspace_bytes (at least
-    heart_workspace_bytes; with few query blocks the full size splits their lists), None (natural launch order), or "auto" (a fresh tensor from torch's allocator).
+    workspace: a uint8/int32 GPU tensor of heart_attn_workspace_bytes (at least heart_workspace_bytes;
+    with few query blocks the full size splits their lists), None (natural launch order), or "auto" (a
+    fresh tensor from torch's allocator).
     flags: 0 (heart_block_sparse_attn) or HEART_ATTN_FOLD_SCALE (heart_block_sparse_attn_flags)."""
     lib = load_library()
     if q.shape != k.shape or q.shape != v.shape:

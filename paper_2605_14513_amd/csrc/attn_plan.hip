@@ -9,9 +9,10 @@
 //                without a look at the totals, which class_order then writes (one workgroup
 //                that sums them all up takes longer than the others together: 131072 heads of
 //                one row, whole call 3069 -> 2805 us)
-//   class_order  (one workgroup per head, up to 2^20) rows by count class, longest first, the sequence for a
-//                workspace without room for the other
-// It is bound by latency: about 5 us at 40 heads of 256 rows without near_order.
+//   class_order  (one workgroup per head, up to 2^20) rows by count class, longest first: the sequence of a
+//                workspace without room for the other (it is there in every plan)
+// Bound by latency.  At 40 heads of 256 rows 14 us without near_order and 15 to 22 with it (longer between long
+// attention launches, at the clock these leave), at 24 heads of 931 rows 13 and 87 to 124.
 #include "heart_internal.h"
 
 namespace heart {
@@ -111,10 +112,10 @@ __device__ __forceinline__ void plan_heads(const int *__restrict__ kept_count, i
 }
 
 // The Nb items of a head, longest kept list first, and, if `total` is given, the head's total kept
-// count.  Stable counting sort by count class (class 0 = the longest rows).  Thread t < 256 owns a contiguous segment of the items and one column of the
-// class histogram, so that items of a class keep their natural order.  The counts are first read
-// once, coalesced and all in flight, and kept as class bytes in LDS when they fit (kStaged);
-// otherwise the segments are read from global memory.
+// count.  Stable counting sort by count class (class 0 = the longest rows).  Thread t < 256 owns a
+// contiguous segment of the items and one column of the class histogram, so that items of a class
+// keep their natural order.  The counts are first read once, coalesced and all in flight, and kept as
+// class bytes in LDS when they fit (kStaged); otherwise the segments are read from global memory.
 constexpr int kOrderStagedMax = 96 * 1024;  // items whose classes fit next to the histogram
 template <bool kStaged, int kThreads>
 __device__ __forceinline__ void class_order(const int *__restrict__ kept_count, int head, int Nb, uint32_t mult,
@@ -189,11 +190,10 @@ __device__ __forceinline__ void class_order(const int *__restrict__ kept_count, 
 // if other rows read it at about the same moment.  A batch is the longest row left and the rows
 // whose lists are most like its list; inside a batch the longest row starts first.  Likeness: the
 // list at eight evenly spaced ranks and its length, sum of absolute differences (as good as the
-// overlap of the whole lists, which costs a pass over them).  Misses of the L2 in a simulation
-// of 64 rows per XCD, class order -> this: 40 -> 33 % at N = 32760, 75 -> 42 % at N = 119056.
-// Measured, this launch included: 4780 -> 4720 us (whole step, 40 heads, N = 32760), 16.8 -> 16.1 ms
-// (attention, 40 heads, N = 75600), 34.0 -> 32.5 ms (whole step, 24 heads, N = 119056); no change at
-// 12 heads or for dense lists.  This launch itself: 10 -> 17 us at N = 32760, 94 us at N = 119056.
+// overlap of the whole lists, which costs a pass over them).  Measured side by side with the other
+// sequence, lists of the timed fields: L2 hits 57 -> 68 % at 40 heads, N = 32760, and 23 -> 45 % at 24 heads,
+// N = 119056; attention with its plan 4617 -> 4510 us and 30.4 -> 29.3 ms, 16.2 -> 15.6 ms at 40 heads, N = 75600, 1376 ->
+// 1365 us at 12 heads; no change for dense lists.
 // One lane per row sorts the rows by length and gathers the samples; then one wavefront holds all
 // rows in registers, sorted (RPL per lane, row 64 c + lane of the sorted order), and picks one
 // batch after the other.
@@ -348,8 +348,8 @@ int launch_attn_plan(int BH, int Nb, int n_wg, int n_items, bool batches, const 
     spread = reinterpret_cast<int *>((a + kCursorLine - 1) / kCursorLine * kCursorLine);
   }
   *cursors = spread;
-  // rows an XCD works on at a time; twice as many where it walks two heads in turn, so that their
-  // long rows start early (12 heads, N = 32760: 1407 -> 1359 us)
+  // rows an XCD works on at a time; twice as many with up to two heads per XCD on average, whose lists mostly
+  // are walked in turn (kHeadsInTurn), so that their long rows start early (12 heads, N = 32760: 1407 -> 1359 us)
   int batch = (n_wg + kNumXcd - 1) / kNumXcd;
   if (BH <= 2 * kNumXcd) batch *= 2;
   const bool staged = Nb <= kOrderStagedMax;

@@ -29,8 +29,9 @@
 //
 // The kept key blocks are consumed as one stream of 32-key slices.  K and V arrive in
 // double-buffered stages of 64 rows, loaded two slices ahead; V stages are skewed by one
-// slice against K stages so that one workgroup barrier per 64 keys retires both (see
-// the comment at the loop; D = 128 with blocks of 64 has stages of one slice, kStageRows).  The softmax scale and log2(e) are folded into Q once, and
+// slice against K stages so that one workgroup barrier per 64 keys retires both (see the
+// comment at the loop; D = 128 with blocks of 64 mostly has stages of one slice, kStageRows).
+// The softmax scale and log2(e) are folded into Q once (or applied to the logits, kExact), and
 // the S^T accumulators start from minus the running reference exponent, so an
 // accumulator goes into the exponential as it is.
 //
@@ -556,9 +557,10 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
       for (int r = 0; r < 16; ++r) cinit[r] = c0;
     }
   };
-  // C: O^T += V^T P^T of the slice in sacc[cur], stream positions g0 .. g0+NPV-1.  The first DT slots finish the weights of the slice (consumed by the
-  // second half of the MFMAs); the second half of the slots folds the maximum of
-  // sacc[cur ^ 1], whose MFMAs were issued before this phase and have drained by then.
+  // C: O^T += V^T P^T of the slice in sacc[cur], stream positions g0 .. g0+NPV-1.  The first DT slots
+  // finish the weights of the slice (consumed by the second half of the MFMAs); the second half of the
+  // slots folds the maximum of sacc[cur ^ 1], whose MFMAs were issued before this phase and have drained
+  // by then.
   auto pv_step = [&](int cur, int g0) __attribute__((always_inline)) -> float {
     float m_loc = -__builtin_inff();
     f32x16_t &nx = sacc[cur ^ 1];
@@ -970,11 +972,12 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
                      (uint16_t *)out, s.q_stride[0], s.q_stride[1], s.q_stride[2], s.k_stride[0],
                      s.k_stride[1], s.k_stride[2], s.v_stride[0], s.v_stride[1], s.v_stride[2],
                      s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, BH, s.N, Nb, kept_idx,
-                     kept_count, scale_log2e, lse, order, seq, spread ? spread : order, spread ? kCursorSpread : 1, part, n_split);
+                     kept_count, scale_log2e, lse, order, seq, spread ? spread : order,
+                     spread ? kCursorSpread : 1, part, n_split);
   if (int rc = check_launch("attn_kernel")) return rc;
   if (!split) return HEART_OK;
-  hipLaunchKernelGGL((attn_merge_kernel<D, BLK>), dim3((unsigned)(n_items * (BLK / 32))), dim3(D * 2), 0, st, part, n_split,
-                     (uint16_t *)out, s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, s.N, Nb, lse);
+  hipLaunchKernelGGL((attn_merge_kernel<D, BLK>), dim3((unsigned)(n_items * (BLK / 32))), dim3(D * 2), 0, st, part,
+                     n_split, (uint16_t *)out, s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, s.N, Nb, lse);
   return check_launch("attn_merge_kernel");
 }
 

@@ -267,7 +267,8 @@ size_t heart_attn_workspace_bytes(const heart_shape *s) {
   const long long nb = n_blocks(s);
   const long long BH = (long long)s->B * s->H;
   const size_t plan = attn_full_plan_bytes(BH, nb);
-  const size_t parts = (s->D == 64 || s->D == 128) && (s->block == 64 || s->block == 128) ? attn_split_bytes(BH, nb, s->D, s->block) : 0;
+  const bool valid = (s->D == 64 || s->D == 128) && (s->block == 64 || s->block == 128);
+  const size_t parts = valid ? attn_split_bytes(BH, nb, s->D, s->block) : 0;
   return plan > parts ? plan : parts;
 }
 
