@@ -332,13 +332,13 @@ __global__ __launch_bounds__(kThreads) void attn_plan_kernel(const int *__restri
 
 }  // namespace
 
-int launch_attn_plan(int BH, int Nb, int n_wg, int n_items, bool batches, const int *kept_idx, const int *kept_count, int *plan,
+int launch_attn_plan(int BH, int Nb, int n_wg, int n_items, const int *kept_idx, const int *kept_count, int *plan,
                      size_t plan_bytes, const int **seq, int **cursors, hipStream_t st) {
   int *class_seq = plan + kPlanHdr + 2 * BH;
   int *near_seq = nullptr;
   // (with one row per workgroup there is nothing to order)
   const size_t near_bytes = attn_near_bytes(BH, Nb);
-  if (near_bytes && batches && BH <= kPlanMaxGroups && n_items > n_wg && plan_bytes >= attn_plan_bytes(BH, Nb) + near_bytes)
+  if (near_bytes && BH <= kPlanMaxGroups && n_items > n_wg && plan_bytes >= attn_plan_bytes(BH, Nb) + near_bytes)
     near_seq = class_seq + (size_t)BH * Nb;
   *seq = near_seq ? near_seq : class_seq;
   int *spread = nullptr;

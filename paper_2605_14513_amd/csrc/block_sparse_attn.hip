@@ -93,24 +93,13 @@ __device__ __forceinline__ u32x4_t head_rsrc_words(const uint16_t *base, uint32_
   return r;
 }
 
-// Key rows per K / V stage buffer: two 32-key slices, or one (kOne) at D = 128, block 64.  There a workgroup
+// Key rows per K / V stage buffer: two 32-key slices, or one at D = 128, block 64.  There a workgroup
 // has two wavefronts, and with stages of 64 rows (64 KB) the LDS of a CU holds two workgroups, one
 // wavefront per SIMD; with 32 KB it holds four.  The price is a barrier per slice and loads that are one
 // slice ahead instead of two; with two wavefronts per SIMD it is paid (N = 16384, 40 heads, 60 of 256
-// blocks kept: 1764 -> 1289 us, 731 -> 1000 TFLOP/s; 4 blocks: 257 -> 193 us).  Not with few rows of few heads
-// (kFewRows, kFewHeads): several XCDs share a head there, find less of its K/V in their L2s and wait longer for
-// it, and the longest rows, which are slower four to a CU, decide when the launch ends.  There the stages have 64
-// rows, and with a plan the rows start in order of their length (lists of the timed fields, one slice -> 64
-// rows: one head of 844 rows 1066 -> 923 us, two 1077 -> 831, three 1266 -> 1164, four of 563 rows 825 -> 811, five
-// 926 -> 1040, eight of 282 rows 364 -> 415; four of 844: 1640 -> 1805; two of 254, at most two rows a CU: 245 -> 252).
-// Without a plan the rows of a head are spread over all XCDs: two to four heads have the long stages at any size (two
-// of 675 rows 1012 -> 964 us, one of 844 1033 -> 1093), more heads beyond kNaturalRows (40 of 254 rows 1840 -> 1718,
-// twelve of 282 585 -> 658).
-constexpr int kLdsPerCu = 160 * 1024;
-constexpr int kSplitCus = 256;  // CUs the places for workgroups are counted for
+// blocks kept: 1764 -> 1289 us, 731 -> 1000 TFLOP/s; 4 blocks: 257 -> 193 us).
 template <int D, int BLK>
 constexpr int kStageRows = D == 128 && BLK == 64 ? 32 : 64;
-constexpr int kFewRows = 3 * 4 * kSplitCus, kFewHeads = 4, kNaturalRows = 4 * 4 * kSplitCus;
 // An XCD with no more heads than this walks their rows in turn: one after the other, the second
 // head's long rows would start late and their length decide when the launch ends (12 heads at
 // N = 32760: 1428 -> 1406 us for the whole step); with three heads the L2 sharing that this gives
@@ -137,8 +126,10 @@ constexpr int kHeadsInTurn = 2;
 // D = 128).  All parts start at once, so such a launch needs no plan.  A function of the sizes only.
 // Measured, whole call: dense 38 -> 19 us, a step at two heads of 16 rows 36 -> 31.5 us (which the
 // host now bounds), steps of 100 to 250 rows 67 -> 33, 88 -> 38, 88 -> 43 us.
+constexpr int kSplitCus = 256;        // CUs the places are counted for
 constexpr int kSplitMinBlocks = 4;
 constexpr int kSplitMax = 16;
+constexpr int kLdsPerCu = 160 * 1024;
 // floats of one wavefront's part: accumulators, reference exponent and row sum of every lane
 template <int D>
 constexpr int kPartFloats = 64 * (D / 2) + 128;
@@ -231,8 +222,8 @@ __global__ __launch_bounds__(D * 2) void attn_merge_kernel(const float *__restri
   }
 }
 
-// kSplit: a workgroup takes part of a row's list and leaves it in `part` (no plan).  SR: rows per stage
-template <int D, int BLK, bool kExact, bool kSplit, int SR>
+// kSplit: a workgroup takes part of a row's list and leaves it in `part` (no plan)
+template <int D, int BLK, bool kExact, bool kSplit>
 __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k,
     const uint16_t *__restrict__ v, uint16_t *__restrict__ out, long long qsb, long long qsh,
@@ -248,6 +239,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   constexpr int CPR = D / 8;             // 16-byte chunks per token row
   constexpr int ROWB = D * 2;            // bytes of a token row in LDS (no padding)
   constexpr int RPB = 16 / CPR;          // rows per 256 bytes (one pass over the 64 banks)
+  constexpr int SR = kStageRows<D, BLK>;
   constexpr bool kOne = SR == 32;        // stages of one slice
   constexpr int TILE_B = SR * ROWB;      // bytes of one K or V stage buffer
   constexpr int RPI = 64 / CPR;          // rows one LDS-direct load instruction covers
@@ -927,22 +919,16 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
   const int BH = s.B * s.H;
   const int n_split = order ? attn_split(BH, Nb, D, BLK) : 1;
   const bool split = n_split > 1 && order_bytes >= attn_split_bytes(BH, Nb, D, BLK);
-  const long long n_items = (long long)BH * Nb;
-  constexpr int SR = kStageRows<D, BLK>;
-  // stages of 64 rows where those of one slice do not pay
-  const bool few = BH <= kFewHeads;
-  const bool wide = SR < 64 && !split && (order ? few && n_items > 2 * kSplitCus && n_items <= kFewRows
-                                                : (few && BH > 1) || n_items > kNaturalRows);
-  const size_t lds = 4 * (size_t)(wide ? 64 : SR) * D * 2;  // >= BLK * (D + 8) * 2 of the output staging
-  auto kern = split ? attn_kernel<D, BLK, kExact, true, SR>
-                    : wide ? attn_kernel<D, BLK, kExact, false, 64> : attn_kernel<D, BLK, kExact, false, SR>;
+  const size_t lds = 4 * (size_t)kStageRows<D, BLK> * D * 2;  // >= BLK * (D + 8) * 2 of the output staging
+  auto kern = split ? attn_kernel<D, BLK, kExact, true> : attn_kernel<D, BLK, kExact, false>;
   const int dev = current_device();
   if (dev < 0) return fail(HEART_EHIP, "heart_block_sparse_attn: cannot identify the current device");
-  static DeviceFlags attr_set[3];  // per instantiation: the attribute is per function and device
-  if (hipError_t e = set_max_lds_once(attr_set[wide ? 2 : split], dev, reinterpret_cast<const void *>(kern), (int)lds))
+  static DeviceFlags attr_set[2];  // per instantiation: the attribute is per function and device
+  if (hipError_t e = set_max_lds_once(attr_set[split], dev, reinterpret_cast<const void *>(kern), (int)lds))
     return fail(HEART_EHIP, "hipFuncSetAttribute(max dynamic LDS %zu): %s", lds, hipGetErrorString(e));
   const float sc = scale > 0.f ? scale : 1.0f / sqrtf((float)D);
   const float scale_log2e = sc * 1.4426950408889634f;
+  const long long n_items = (long long)BH * Nb;
   long long grid = (long long)BH * ((Nb + kNumXcd - 1) / kNumXcd) * kNumXcd;
   float *part = nullptr;
   if (split) {
@@ -952,19 +938,17 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
   }
   if (order) {
     // persistent workgroups: as many as are resident at once (HEART_ATTN_OCC per SIMD, i.e.
-    // two workgroups of four wavefronts per CU, as far as their LDS fits)
+    // two workgroups of four wavefronts per CU)
     const int n_cu = cu_count(dev);
     if (n_cu <= 0) return fail(HEART_EHIP, "heart_block_sparse_attn: cannot query the number of CUs");
-    const int by_waves = HEART_ATTN_OCC * 4 / (BLK / 32), by_lds = kLdsPerCu / (int)lds;
-    const long long resident = (long long)n_cu * (by_waves < by_lds ? by_waves : by_lds);
+    const long long resident = (long long)n_cu * HEART_ATTN_OCC * 4 / (BLK / 32);
     grid = n_items < resident ? n_items : resident;
   }
   if (grid > 0x7fffffffLL) return fail(HEART_EUNSUPPORTED, "heart_block_sparse_attn: grid too large");
   const int *seq = nullptr;
   int *spread = nullptr;
   if (order) {
-    if (int rc = launch_attn_plan(BH, Nb, (int)grid, (int)n_items, !wide, kept_idx, kept_count, order, order_bytes,
-                                  &seq, &spread, st))
+    if (int rc = launch_attn_plan(BH, Nb, (int)grid, (int)n_items, kept_idx, kept_count, order, order_bytes, &seq, &spread, st))
       return rc;
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(BLK * 2), lds, st,

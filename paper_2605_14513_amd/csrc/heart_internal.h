@@ -243,9 +243,9 @@ inline size_t attn_full_plan_bytes(long long BH, long long Nb) {
 __host__ __device__ constexpr int list_first(int n_wg, int list, int BH) {
   return BH == 1 ? (list == 0 ? n_wg : 0) : n_wg / kNumXcd + (list < n_wg % kNumXcd ? 1 : 0);
 }
-// Enqueues the plan for a launch of n_wg attention workgroups over n_items items, with the second sequence
-// if `batches` and there is room; *seq = the sequence that launch follows; *cursors = the spread cursors or null.
-int launch_attn_plan(int BH, int Nb, int n_wg, int n_items, bool batches, const int *kept_idx, const int *kept_count, int *plan,
+// Enqueues the plan for a launch of n_wg attention workgroups over n_items items; *seq = the
+// sequence that launch follows; *cursors = the spread cursors or null.
+int launch_attn_plan(int BH, int Nb, int n_wg, int n_items, const int *kept_idx, const int *kept_count, int *plan,
                      size_t plan_bytes, const int **seq, int **cursors, hipStream_t st);
 
 // Parts that the kept list of every row is split into, 1 = not (a function of the sizes alone), and the
