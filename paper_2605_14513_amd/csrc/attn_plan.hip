@@ -35,7 +35,7 @@ __device__ __forceinline__ int row_count(const int *kept_count, int i, int Nb) {
 // loaded XCD, head table, cursors (`spread` if given, else the header's) reset behind the items that the
 // n_wg attention workgroups start with.
 template <int kThreads>
-__device__ __forceinline__ void plan_heads(const int *__restrict__ kept_count, int BH, int Nb, int n_wg,
+__device__ __forceinline__ void plan_heads(const int *__restrict__ kept_count, int BH, int Nb, int n_wg, int n_few,
                                            int *__restrict__ plan, int *__restrict__ spread, unsigned char *lds) {
   int *w_head = reinterpret_cast<int *>(lds);
   int *sorted = w_head + kPlanMaxHeads, *xcd_of = sorted + kPlanMaxHeads, *rank_of = xcd_of + kPlanMaxHeads;
@@ -98,7 +98,10 @@ __device__ __forceinline__ void plan_heads(const int *__restrict__ kept_count, i
   }
   __syncthreads();
   if (t < kNumXcd) {
-    const int first = list_first(n_wg, t, BH);
+    long long kept = 0;
+    if (n_few < n_wg)  // (at most kFewHeads heads)
+      for (int bh = 0; bh < BH; ++bh) kept += w_head[bh];
+    const int first = list_first(working_groups(n_wg, n_few, kept, BH, Nb), t, BH);
     if (spread) spread[t * kCursorSpread] = first;
     plan[t] = spread ? n_heads[t] * Nb : first;
     plan[kNumXcd + t] = n_heads[t] * Nb;
@@ -302,7 +305,7 @@ __device__ __forceinline__ void near_order(const int *__restrict__ kept_idx, con
 template <bool kStaged, int kThreads>
 __global__ __launch_bounds__(kThreads) void attn_plan_kernel(const int *__restrict__ kept_idx,
                                                              const int *__restrict__ kept_count, int BH,
-                                                             int Nb, int n_wg, uint32_t mult, int batch,
+                                                             int Nb, int n_wg, int n_few, uint32_t mult, int batch,
                                                              int *__restrict__ plan, int *__restrict__ spread,
                                                              int *__restrict__ near_seq) {
   extern __shared__ __align__(16) unsigned char lds[];
@@ -320,7 +323,7 @@ __global__ __launch_bounds__(kThreads) void attn_plan_kernel(const int *__restri
     id -= BH;
   }
   if (id == 0) {
-    plan_heads<kThreads>(kept_count, BH, Nb, n_wg, plan, spread, lds);
+    plan_heads<kThreads>(kept_count, BH, Nb, n_wg, n_few, plan, spread, lds);
     return;
   }
   for (long long head = id - 1; head < BH; head += kPlanMaxGroups) {
@@ -332,18 +335,18 @@ __global__ __launch_bounds__(kThreads) void attn_plan_kernel(const int *__restri
 
 }  // namespace
 
-int launch_attn_plan(int BH, int Nb, int n_wg, int n_items, const int *kept_idx, const int *kept_count, int *plan,
-                     size_t plan_bytes, const int **seq, int **cursors, hipStream_t st) {
+int launch_attn_plan(int BH, int Nb, int n_wg, int n_few, int n_items, const int *kept_idx, const int *kept_count,
+                     int *plan, size_t plan_bytes, const int **seq, int **cursors, hipStream_t st) {
   int *class_seq = plan + kPlanHdr + 2 * BH;
   int *near_seq = nullptr;
   // (with one row per workgroup there is nothing to order)
   const size_t near_bytes = attn_near_bytes(BH, Nb);
-  if (near_bytes && BH <= kPlanMaxGroups && n_items > n_wg && plan_bytes >= attn_plan_bytes(BH, Nb) + near_bytes)
+  if (near_bytes && BH <= kPlanMaxGroups && n_few == n_wg && n_items > n_wg && plan_bytes >= attn_plan_bytes(BH, Nb) + near_bytes)
     near_seq = class_seq + (size_t)BH * Nb;
   *seq = near_seq ? near_seq : class_seq;
   int *spread = nullptr;
   const size_t used = attn_plan_bytes(BH, Nb) + near_bytes;
-  if (n_items > n_wg && plan_bytes >= used + kCursorBytes) {
+  if (n_items > n_few && plan_bytes >= used + kCursorBytes) {
     const uintptr_t a = reinterpret_cast<uintptr_t>(plan) + used;
     spread = reinterpret_cast<int *>((a + kCursorLine - 1) / kCursorLine * kCursorLine);
   }
@@ -373,7 +376,7 @@ int launch_attn_plan(int BH, int Nb, int n_wg, int n_items, const int *kept_idx,
   const uint32_t mult = (uint32_t)(((kOrderClasses - 1) << 16) / Nb);
   const unsigned grid = (unsigned)(1 + (BH < kPlanMaxGroups ? BH : kPlanMaxGroups) + (near_seq ? BH : 0));
   hipLaunchKernelGGL(kern, dim3(grid), dim3(small ? kOrderCols : kPlanThreads), lds, st, kept_idx, kept_count, BH,
-                     Nb, n_wg, mult, batch, plan, spread, near_seq);
+                     Nb, n_wg, n_few, mult, batch, plan, spread, near_seq);
   return check_launch("attn_plan_kernel");
 }
 

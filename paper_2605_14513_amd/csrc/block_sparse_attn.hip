@@ -231,7 +231,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     long long vsn, long long osb, long long osh, long long osn, int H, int BH, int N, int Nb,
     const int *__restrict__ kept_idx, const int *__restrict__ kept_count, float scale_log2e,
     float *__restrict__ lse, int *__restrict__ plan, const int *__restrict__ seq, int *__restrict__ cursors,
-    int cursor_step, float *__restrict__ part, int n_split) {
+    int cursor_step, float *__restrict__ part, int n_split, int n_few) {
   constexpr int NT = BLK * 2;            // threads
   constexpr int NW = NT / 64;            // wavefronts
   constexpr int DT = D / 32;             // 32-wide d tiles of the output
@@ -595,6 +595,14 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   // workgroup processes the one item its id maps to.
   __shared__ int s_item;
   const int x0 = (int)(blockIdx.x % kNumXcd);
+  int n_wg = (int)gridDim.x;  // workgroups that take items
+  if constexpr (kOne && !kSplit)
+    if (plan && n_few < n_wg) {
+      long long kept = 0;
+      for (int i = 0; i < BH; ++i) kept += plan[kPlanHdr + BH + i];
+      n_wg = working_groups(n_wg, n_few, kept, BH, Nb);
+      if ((int)blockIdx.x >= n_wg) return;
+    }
   const int own = BH == 1 ? 0 : x0;  // own list
   const int len0 = plan ? plan[kNumXcd + own] : 0;
   const int off0 = plan ? plan[2 * kNumXcd + own] : 0;
@@ -607,7 +615,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     const int r = in_turn ? i % nh : i / Nb, p = in_turn ? i / nh : i - r * Nb;
     return seq[head_tbl[off_x + r] * Nb + p];
   };
-  const int n_own = list_first((int)gridDim.x, own, BH);  // workgroups of this list
+  const int n_own = list_first(n_wg, own, BH);  // workgroups of this list
   int i_own = (int)(BH == 1 ? blockIdx.x : blockIdx.x / kNumXcd);  // (wavefront 0) last entry taken from the own list
   // (wavefront 0) an item of the own list, else of the list whose next item is the longest, else
   // -1.  Lanes 0..7 look at the eight cursors at once and an atomic goes only to a list that still
@@ -930,6 +938,7 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
   const float scale_log2e = sc * 1.4426950408889634f;
   const long long n_items = (long long)BH * Nb;
   long long grid = (long long)BH * ((Nb + kNumXcd - 1) / kNumXcd) * kNumXcd;
+  int n_few = 0;  // (a plan: see working_groups)
   float *part = nullptr;
   if (split) {
     part = reinterpret_cast<float *>(order);
@@ -943,12 +952,15 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
     if (n_cu <= 0) return fail(HEART_EHIP, "heart_block_sparse_attn: cannot query the number of CUs");
     const long long resident = (long long)n_cu * HEART_ATTN_OCC * 4 / (BLK / 32);
     grid = n_items < resident ? n_items : resident;
+    const bool few = kStageRows<D, BLK> < 64 && BH <= kFewHeads && n_items <= kFewRows && grid > 2 * n_cu;
+    n_few = few ? 2 * n_cu : (int)grid;
   }
   if (grid > 0x7fffffffLL) return fail(HEART_EUNSUPPORTED, "heart_block_sparse_attn: grid too large");
   const int *seq = nullptr;
   int *spread = nullptr;
   if (order) {
-    if (int rc = launch_attn_plan(BH, Nb, (int)grid, (int)n_items, kept_idx, kept_count, order, order_bytes, &seq, &spread, st))
+    if (int rc = launch_attn_plan(BH, Nb, (int)grid, n_few, (int)n_items, kept_idx, kept_count, order, order_bytes,
+                                  &seq, &spread, st))
       return rc;
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(BLK * 2), lds, st,
@@ -957,7 +969,7 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
                      s.k_stride[1], s.k_stride[2], s.v_stride[0], s.v_stride[1], s.v_stride[2],
                      s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, BH, s.N, Nb, kept_idx,
                      kept_count, scale_log2e, lse, order, seq, spread ? spread : order,
-                     spread ? kCursorSpread : 1, part, n_split);
+                     spread ? kCursorSpread : 1, part, n_split, n_few);
   if (int rc = check_launch("attn_kernel")) return rc;
   if (!split) return HEART_OK;
   hipLaunchKernelGGL((attn_merge_kernel<D, BLK>), dim3((unsigned)(n_items * (BLK / 32))), dim3(D * 2), 0, st, part,

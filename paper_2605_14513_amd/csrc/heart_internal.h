@@ -236,6 +236,19 @@ constexpr long long kCursorMinItems = 512;
 inline size_t attn_full_plan_bytes(long long BH, long long Nb) {
   return attn_plan_bytes(BH, Nb) + attn_near_bytes(BH, Nb) + (BH > kCursorMinItems / Nb ? kCursorBytes : 0);
 }
+// Workgroups, of n_wg, that work.  Four workgroups to a CU (D = 128, block 64) are faster than two where rows are many or
+// keep most blocks.  Of few heads with few, uneven lists they are slower: several XCDs then share a head, more rows
+// in flight find less of its K/V in the L2s, and the longest rows, slower four to a CU, decide when the launch
+// ends.  So with at most kFewHeads heads and kFewRows rows, and less than kFewKept / 8 of the blocks kept, only the
+// first n_few work, two to a CU (n_few = n_wg where that is no question; kept: all kept blocks).  Four -> two a CU, lists
+// of the timed fields (13 to 35 % kept): one head of 844 rows 1052 -> 934 us, two 1053 -> 843, three 1218 -> 1131,
+// four of 563 rows 748 -> 681 (at 3376 rows 1608 -> 1800 with stages of 64 rows, which are as fast two to a CU); random
+// lists of half the blocks, one head of 520 rows 672 -> 573, two of 741 1561 -> 1569; dense lists, which keep four: one
+// head of 520 rows 791 -> 1168, two of 300 460 -> 669.
+constexpr int kFewHeads = 4, kFewRows = 3072, kFewKept = 5;
+__host__ __device__ constexpr int working_groups(int n_wg, int n_few, long long kept, int BH, int Nb) {
+  return n_few < n_wg && 8 * kept < (long long)kFewKept * BH * Nb * Nb ? n_few : n_wg;
+}
 // Workgroups, of n_wg, that start with an item of `list`: those of its XCD (they are dealt to the XCDs in turn); of
 // one head only list 0 has items, and all of them do, in order.  The rows with the longest lists come first, and
 // with the others coming for items later they would all start on XCD 0 (D = 128, block 128, lists of the timed
@@ -243,10 +256,11 @@ inline size_t attn_full_plan_bytes(long long BH, long long Nb) {
 __host__ __device__ constexpr int list_first(int n_wg, int list, int BH) {
   return BH == 1 ? (list == 0 ? n_wg : 0) : n_wg / kNumXcd + (list < n_wg % kNumXcd ? 1 : 0);
 }
-// Enqueues the plan for a launch of n_wg attention workgroups over n_items items; *seq = the
-// sequence that launch follows; *cursors = the spread cursors or null.
-int launch_attn_plan(int BH, int Nb, int n_wg, int n_items, const int *kept_idx, const int *kept_count, int *plan,
-                     size_t plan_bytes, const int **seq, int **cursors, hipStream_t st);
+// Enqueues the plan for a launch of n_wg attention workgroups, of which working_groups(n_wg, n_few, ..)
+// work (with n_few < n_wg in order of length alone), over n_items items; *seq = the sequence that launch
+// follows; *cursors = the spread cursors or null.
+int launch_attn_plan(int BH, int Nb, int n_wg, int n_few, int n_items, const int *kept_idx, const int *kept_count,
+                     int *plan, size_t plan_bytes, const int **seq, int **cursors, hipStream_t st);
 
 // Parts that the kept list of every row is split into, 1 = not (a function of the sizes alone), and the
 // workspace bytes the parts take (instead of a plan; 0 if rows are not split).

@@ -240,3 +240,36 @@ def test_plan_of_heads_that_are_not_ranked(H, Nb):
         seq = plan[24 + 2 * H:24 + 2 * H + H * Nb].reshape(H, Nb)
         want = np.arange(H)[:, None] * Nb + np.argsort(classes, axis=1, kind="stable")
         assert np.array_equal(seq, want)
+
+
+# D = 128, blocks of 64: few rows of few heads use two workgroups a CU while less than 5/8 of the blocks are kept: on
+# either side of that share, at the ends of the range of rows (the last size is beyond it) and of heads
+@pytest.mark.parametrize("H,Nb,tail", [(1, 515, 63), (4, 150, 33), (2, 301, 0), (4, 768, 0), (5, 150, 1), (4, 769, 9)])
+@pytest.mark.parametrize("share", ["few", "just below", "just above", "all"])
+def test_workgroups_of_few_heads(H, Nb, tail, share):
+    import paper_2605_14513_amd as heart
+
+    D, block = 128, 64
+    N = Nb * block - tail
+    rng = np.random.default_rng(Nb)
+    if share == "few":
+        cnt = rng.integers(0, 10, size=(1, H, Nb)).astype(np.int32)
+    else:
+        cnt = np.full((1, H, Nb), Nb if share == "all" else Nb * 5 // 8, np.int32)
+        if share != "all":
+            more = (5 * H * Nb * Nb + 7) // 8 - cnt.sum() - (share == "just below")  # (8 kept >= 5 H Nb^2, or one less)
+            cnt.reshape(-1)[:max(more, 0)] += 1
+            cnt[0, 0, 0] += min(more, 0)
+            assert (8 * int(cnt.sum()) >= 5 * H * Nb * Nb) == (share == "just above")
+    idx = torch.arange(Nb, dtype=torch.int32, device="cuda").expand(1, H, Nb, Nb).contiguous()
+    gc = np_gpu(cnt)
+    g = torch.Generator(device="cuda").manual_seed(Nb)
+    q, k, v = (torch.randn((1, H, N, D), generator=g, device="cuda").bfloat16() for _ in range(3))
+    print(f"H={H} Nb={Nb} {share}", flush=True)
+    want = heart.heart_block_sparse_attn(q, k, v, block, idx, gc, workspace=None)
+    for n_bytes in (heart.heart_attn_workspace_bytes(q, block), heart.heart_workspace_bytes(1, H, Nb, D)):
+        ws = torch.full((n_bytes // 4,), -7, dtype=torch.int32, device="cuda")
+        out = heart.heart_block_sparse_attn(q, k, v, block, idx, gc, workspace=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        check_attn_plan(ws.cpu().numpy(), cnt, Nb)
