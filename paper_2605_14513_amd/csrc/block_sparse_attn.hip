@@ -30,7 +30,7 @@
 // The kept key blocks are consumed as one stream of 32-key slices.  K and V arrive in
 // double-buffered stages of 64 rows, loaded two slices ahead; V stages are skewed by one
 // slice against K stages so that one workgroup barrier per 64 keys retires both (see the
-// comment at the loop; D = 128 with blocks of 64 mostly has stages of one slice, kStageRows).
+// comment at the loop; D = 128 with blocks of 64 has stages of one slice, kStageRows).
 // The softmax scale and log2(e) are folded into Q once (or applied to the logits, kExact), and
 // the S^T accumulators start from minus the running reference exponent, so an
 // accumulator goes into the exponential as it is.
