@@ -6,6 +6,7 @@ from .binding import (  # noqa: F401
     HEART_ATTN_FOLD_SCALE,
     HeartError,
     HeartShape,
+    heart_attn_balanced_workspace_bytes,
     heart_attn_workspace_bytes,
     heart_block_sparse_attn,
     heart_block_sparse_attn_flags,

@@ -75,6 +75,8 @@ def load_library() -> ctypes.CDLL:
     lib.heart_block_sparse_attn_static.restype = ci
     lib.heart_attn_workspace_bytes.argtypes = [sp]
     lib.heart_attn_workspace_bytes.restype = ctypes.c_size_t
+    lib.heart_attn_balanced_workspace_bytes.argtypes = [sp, ci]
+    lib.heart_attn_balanced_workspace_bytes.restype = ctypes.c_size_t
     lib.heart_workspace_bytes.argtypes = [ci, ci, ci, ci]
     lib.heart_workspace_bytes.restype = ctypes.c_size_t
     for f in (lib.heart_pool_qk, lib.heart_drift, lib.heart_mask_topp,
@@ -316,12 +318,18 @@ def heart_attn_workspace_bytes(q, block: int) -> int:
     return int(load_library().heart_attn_workspace_bytes(ctypes.byref(make_shape(q, q, block))))
 
 
+def heart_attn_balanced_workspace_bytes(q, block: int, dense: bool = False) -> int:
+    """Bytes with which heart_block_sparse_attn also divides the lists of few rows evenly (dense: of full lists)."""
+    return int(load_library().heart_attn_balanced_workspace_bytes(ctypes.byref(make_shape(q, q, block)), int(dense)))
+
+
 def heart_block_sparse_attn(q, k, v, block: int, kept_idx, kept_count, scale: float = 0.0,
                             out=None, lse=None, workspace="auto", flags: int = 0):
     """Block-sparse attention over the kept key blocks; returns bf16 out like q.
 
     workspace: a uint8/int32 GPU tensor of heart_attn_workspace_bytes (at least heart_workspace_bytes;
-    with few query blocks the full size splits their lists), None (natural launch order), or "auto" (a
+    with few query blocks the full size splits their lists, heart_attn_balanced_workspace_bytes divides
+    those of a few rows a workgroup evenly), None (natural launch order), or "auto" (a
     fresh tensor from torch's allocator).
     flags: 0 (heart_block_sparse_attn) or HEART_ATTN_FOLD_SCALE (heart_block_sparse_attn_flags)."""
     lib = load_library()

@@ -135,10 +135,15 @@ template <int D>
 constexpr int kPartFloats = 64 * (D / 2) + 128;
 constexpr float kNoKeys = -1.f;  // in the place of the row sum: a part without keys (a sum is not negative, but may be NaN)
 
-int attn_split(long long BH, long long Nb, int D, int block) {
+// places for workgroups on the chip
+static long long attn_places(int D, int block) {
   const int rows = D == 128 && block == 64 ? kStageRows<128, 64> : kStageRows<64, 64>;
   const int by_waves = HEART_ATTN_OCC * 4 / (block / 32), by_lds = kLdsPerCu / (4 * rows * D * 2);
-  const long long places = (long long)kSplitCus * (by_waves < by_lds ? by_waves : by_lds);
+  return (long long)kSplitCus * (by_waves < by_lds ? by_waves : by_lds);
+}
+
+int attn_split(long long BH, long long Nb, int D, int block) {
+  const long long places = attn_places(D, block);
   if (BH > places || Nb > places) return 1;  // (beyond that their product can leave 64 bits)
   long long s = places / (BH * Nb);
   if (s > Nb / kSplitMinBlocks) s = Nb / kSplitMinBlocks;
@@ -153,57 +158,127 @@ size_t attn_split_bytes(long long BH, long long Nb, int D, int block) {
   return (size_t)(BH * Nb) * s * (block / 32) * part * sizeof(float);
 }
 
-// Adds up the parts of every row: one wavefront per (32 query rows, 32 columns of the output), lanes
-// as in attn_kernel.  Bound by latency (the parts come from the L2s and the memory-side cache):
-// all softmax states are loaded at once, the accumulators of four parts at a time.
+// Shared rows.  Where a place works on at most a few rows, their uneven lengths decide when a launch ends: the
+// longest row alone takes as long as several of the mean.  With room for the parts
+// (heart_attn_balanced_workspace_bytes) lists are divided there, by one of three rules, and attn_merge_kernel adds up
+// the rows that were:
+//   shares  the kept blocks of all rows, row after row, are one sequence (lengths in half blocks) that is cut into equal
+//           shares, one per place
+//   parts   every row is split into parts of at most L blocks, L as small as the places allow; each workgroup has one
+//           part, all start at once
+//   whole   a workgroup per row, as far as that is no slower: few rows of nearly the same length
+// Every workgroup finds the rule and its part or share from the kept counts by itself (read once, 16 KB at most), so there
+// is no plan, no queue and no atomic, and what is divided where, and with it the bits, is a function of the counts alone.
+// XCD x takes the x-th eighth of the parts or shares, so it sees an eighth of the heads.
+// What it costs: 1.5 to 3 us until a workgroup knows its share, and the merge (4 to 10 us).  Attention with its plan ->
+// with shares, lists of the timed fields: 20 heads of 101 rows (D = 64, block 64) 122 -> 92 us; D = 128, block 128: six
+// heads of 88 rows 153 -> 93, two of 248 436 -> 236, 21 of 74 164 -> 148; dense lists, four heads of 147 rows 760 -> 659.
+constexpr int kShareGroup = 256, kShareMaxRows = 16 * kShareGroup;  // rows; counts are summed up in groups, four rows a lane
+constexpr int kShareMin = 8;       // shortest share
+constexpr int kSharePart = 2;      // fewest blocks of a part: a cut closer to an end of its row goes there
+constexpr int kShareRowCost = 6;   // what a row costs beside its blocks (10 instead: 2 % slower over 30 shapes)
+// The first workgroup of a CU is older than the others and its wavefronts go first: with equal shares it ends when the
+// others have a fifth of theirs left (D = 64, block 64: 65 against 80 us), so its share is 1 + 1 / kShareOlder times as long.
+constexpr int kShareOlder = 4;
+// blocks of a row of `cnt` that lie before a cut `d` behind the start of the row
+__device__ __forceinline__ int share_blocks(int d, int cnt) {
+  const int e = min(max((d - kShareRowCost + 1) >> 1, 0), cnt);
+  return e < kSharePart ? 0 : cnt - e < kSharePart ? cnt : e;
+}
+
+// Shares of a launch (workgroups; those that find no share for them end at once), 0 = rows are not shared.  A function
+// of the sizes.  Measured against the plan on lists of the timed fields, and on dense ones, at 0.5 to 3 rows a place and 1
+// to 30 heads: with more rows the workgroups of an XCD are at places of K/V that are too far apart for its L2 and the
+// rows level out by themselves (D = 128, block 128: 1.04 to 1.85 times as fast up to 2 rows a place, 0.95 to 1.04 at 3; D =
+// 64: 1.0 to 2.6 times up to 2.5).  Four workgroups a CU with long lists at D = 128, block 64 feel that most (two heads of 585
+// rows 0.90, four of 293 1.19 times as fast).  Rows of at most 15 blocks a part of kSplitRows are left to that.
+// Dense lists need no levelling: only where a last round of whole rows would leave many places empty.
+int attn_shares(long long BH, long long Nb, int D, int block, bool dense) {
+  const long long places = attn_places(D, block);
+  if (BH > kShareMaxRows || Nb > kShareMaxRows || BH * Nb > kShareMaxRows) return 0;
+  const long long rows = BH * Nb;
+  if (2 * rows > (D == 64 ? 5 : 4) * places) return 0;
+  const bool near = D == 64 || block == 128 || rows * Nb <= 300 * places;
+  if (rows > places && !near) return 0;
+  const int s = attn_split(BH, Nb, D, block);
+  if (s > 1 && (dense || Nb <= 15 * s)) return 0;
+  if (dense && (!near || (rows > places && 8 * rows > (D == 64 ? 13 : 10) * places))) return 0;
+  const long long most = rows * (Nb / kSharePart + 1);
+  return (int)((most < places ? most : places) + kNumXcd - 1) / kNumXcd * kNumXcd;
+}
+
+// owners of split rows (row, further parts, share), then two parts per share: the one a share starts with and the one it ends with
+size_t attn_share_bytes(long long BH, long long Nb, int D, int block, bool dense) {
+  const int n = attn_shares(BH, Nb, D, block, dense);
+  if (n == 0) return 0;
+  const size_t part = D == 128 ? kPartFloats<128> : kPartFloats<64>;
+  return (size_t)n * (sizeof(int4) + 2 * (size_t)(block / 32) * part * sizeof(float));
+}
+
+// Adds up the parts of a row: one wavefront per (32 query rows, 32 columns of the output), lanes
+// as in attn_kernel.  Parts of item i are i * n_split .. ; of shared rows (`owner` given) the last part of share k
+// and the first ones of the shares after it.  Bound by latency (the parts come from the L2s and the memory-side
+// cache): four parts at a time.
 template <int D, int BLK>
-__global__ __launch_bounds__(D * 2) void attn_merge_kernel(const float *__restrict__ part, int n_split,
-                                                           uint16_t *__restrict__ out, long long osb, long long osh,
-                                                           long long osn, int H, int N, int Nb,
+__global__ __launch_bounds__(D * 2) void attn_merge_kernel(const float *__restrict__ part, const int4 *__restrict__ owner,
+                                                           int n_split, uint16_t *__restrict__ out, long long osb,
+                                                           long long osh, long long osn, int H, int N, int Nb,
                                                            float *__restrict__ lse) {
   constexpr int NW = BLK / 32;
   const int lane = threadIdx.x & 63, dt = threadIdx.x >> 6, l32 = lane & 31, hf = lane >> 5;
-  const int item = (int)(blockIdx.x / NW), wave = (int)(blockIdx.x % NW);
-  const size_t step = (size_t)NW * kPartFloats<D>;  // from part to part of a row
-  const float *src = part + ((size_t)item * n_split * NW + wave) * kPartFloats<D>;
+  int item = (int)(blockIdx.x / NW);
+  const int wave = (int)(blockIdx.x % NW);
+  size_t first = (size_t)item * n_split, second = first + 1, step = 1;  // parts of the row
+  if (owner) {
+    const int4 own = owner[item];
+    if (own.x < 0) return;
+    first = 2 * (size_t)own.z + 1;
+    second = first + 1;
+    step = 2;
+    item = own.x;
+    n_split = own.y + 1;
+  }
+  auto part_of = [&](int s) -> const float * {
+    s = min(s, n_split - 1);
+    return part + ((s == 0 ? first : second + (size_t)(s - 1) * step) * NW + wave) * kPartFloats<D>;
+  };
   const float ninf = -__builtin_inff();
-  float ms[kSplitMax], ls[kSplitMax];
-#pragma unroll
-  for (int s = 0; s < kSplitMax; ++s) {
-    ms[s] = s < n_split ? src[s * step + 64 * (D / 2) + lane] : ninf;
-    ls[s] = s < n_split ? src[s * step + 64 * (D / 2) + 64 + lane] : kNoKeys;
-  }
   float m = ninf, l = 0.f;
-#pragma unroll
-  for (int s = 0; s < kSplitMax; ++s) m = fmaxf(m, ms[s]);
-  // (a part whose logits are all NaN or -inf keeps the reference -inf, like one without keys: its weight
-  // is 0, but its sums count, because a NaN among them has to reach the result)
-  const float m_fin = m == ninf ? 0.f : m;
-#pragma unroll
-  for (int s = 0; s < kSplitMax; ++s) {
-    ms[s] = __builtin_amdgcn_exp2f(ms[s] - m_fin);  // weight of a part (one without keys: 0)
-    l = fmaf(ls[s], ms[s], l);
-  }
   f32x4_t o[4];
 #pragma unroll
   for (int g = 0; g < 4; ++g) o[g] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < n_split; s0 += 4) {
+    float ms[4], ls[4];
+    f32x4_t x[4][4];
 #pragma unroll
-  for (int s0 = 0; s0 < kSplitMax; s0 += 4) {
-    if (s0 < n_split) {
-      f32x4_t x[4][4];
+    for (int s = 0; s < 4; ++s) {
+      const float *src = part_of(s0 + s);
+      ms[s] = src[64 * (D / 2) + lane];
+      ls[s] = src[64 * (D / 2) + 64 + lane];
+      const f32x4_t *o4 = reinterpret_cast<const f32x4_t *>(src) + 4 * 64 * dt + lane;
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const f32x4_t *o4 = reinterpret_cast<const f32x4_t *>(src + min(s0 + s, n_split - 1) * step) + 4 * 64 * dt + lane;
+      for (int g = 0; g < 4; ++g) x[s][g] = o4[64 * g];
+      if (s0 + s >= n_split) ms[s] = ninf, ls[s] = kNoKeys;
+    }
+    const float m_old = m;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) x[s][g] = o4[64 * g];
-      }
+    for (int s = 0; s < 4; ++s) m = fmaxf(m, ms[s]);
+    // (a part whose logits are all NaN or -inf keeps the reference -inf, like one without keys: its weight
+    // is 0, but its sums count, because a NaN among them has to reach the result)
+    const float m_fin = m == ninf ? 0.f : m;
+    const float alpha = __builtin_amdgcn_exp2f(m_old - m_fin);
+    l *= alpha;
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
+    for (int g = 0; g < 4; ++g) o[g] *= alpha;
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
+    for (int s = 0; s < 4; ++s) {
+      if (ls[s] == kNoKeys) continue;  // (accumulators of a part without keys are not written)
+      const float w = __builtin_amdgcn_exp2f(ms[s] - m_fin);
+      l = fmaf(ls[s], w, l);
 #pragma unroll
-          for (int e = 0; e < 4; ++e)  // (accumulators of a part without keys are not written)
-            o[g][e] = ls[s0 + s] != kNoKeys ? fmaf(x[s][g][e], ms[s0 + s], o[g][e]) : o[g][e];
+      for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[g][e] = fmaf(x[s][g][e], w, o[g][e]);
     }
   }
   const int bh = item / Nb, qb = item % Nb, n = qb * BLK + wave * 32 + l32;
@@ -222,8 +297,10 @@ __global__ __launch_bounds__(D * 2) void attn_merge_kernel(const float *__restri
   }
 }
 
-// kSplit: a workgroup takes part of a row's list and leaves it in `part` (no plan)
-template <int D, int BLK, bool kExact, bool kSplit>
+// kMode: kPlanned, rows as a plan (or, without one, the workgroup's number) says; kSplitRows: a workgroup takes part of
+// one row's list and leaves it in `part`; kSharedRows: a share of all rows
+enum AttnMode { kPlanned, kSplitRows, kSharedRows };
+template <int D, int BLK, bool kExact, AttnMode kMode>
 __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k,
     const uint16_t *__restrict__ v, uint16_t *__restrict__ out, long long qsb, long long qsh,
@@ -231,7 +308,8 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     long long vsn, long long osb, long long osh, long long osn, int H, int BH, int N, int Nb,
     const int *__restrict__ kept_idx, const int *__restrict__ kept_count, float scale_log2e,
     float *__restrict__ lse, int *__restrict__ plan, const int *__restrict__ seq, int *__restrict__ cursors,
-    int cursor_step, float *__restrict__ part, int n_split, int n_few) {
+    int cursor_step, float *__restrict__ part, int4 *__restrict__ owner, int n_split, int n_few) {
+  constexpr bool kSplit = kMode == kSplitRows, kShare = kMode == kSharedRows;
   constexpr int NT = BLK * 2;            // threads
   constexpr int NW = NT / 64;            // wavefronts
   constexpr int DT = D / 32;             // 32-wide d tiles of the output
@@ -347,6 +425,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   f32x16_t cinit;
   float l_run = 0.f;  // running sum over this lane's keys, relative to m_ref
   int split = 0;  // (split rows) which part of the kept list
+  int e_begin = 0, e_end = 0, row_cnt = 0;  // (shared rows) part of the kept list, its length
   auto begin_item = [&](int item) __attribute__((always_inline)) {
     bh = item / Nb;
     qb = item % Nb;
@@ -378,8 +457,13 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     for (int r = 0; r < 16; ++r) cinit[r] = 0.f;
     l_run = 0.f;
     const size_t row = (size_t)bh * Nb + qb;
-    cnt = min(kept_count[row], Nb);
     idx = kept_idx + row * Nb;
+    if constexpr (kShare) {
+      cnt = e_end - e_begin;
+      idx += e_begin;
+    } else {
+      cnt = min(kept_count[row], Nb);
+    }
     if constexpr (kSplit) {
       cnt = max(cnt, 0);
       const int per = (cnt + n_split - 1) / n_split, e0 = min(cnt, split * per);
@@ -596,7 +680,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   __shared__ int s_item;
   const int x0 = (int)(blockIdx.x % kNumXcd);
   int n_wg = (int)gridDim.x;  // workgroups that take items
-  if constexpr (kOne && !kSplit)
+  if constexpr (kOne && kMode == kPlanned)
     if (plan && n_few < n_wg) {
       long long kept = 0;
       for (int i = 0; i < BH; ++i) kept += plan[kPlanHdr + BH + i];
@@ -652,7 +736,176 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     }
   };
   int item = -1;
-  if (!kSplit && plan) {
+  // (shared rows) which share (or part), start of the row in the sequence, end of the share, parts of the row (0 = shares)
+  int share = 0, row0 = 0, cut1 = 0, parts = 0;
+  // boundary k of n shares: evenly, or, where every place has one, by XCD and with older shares 1 + 1 / kOlder times as
+  // long as the others (in steps of 1 / 256; the last of an XCD takes what the division leaves)
+  constexpr int kPlacesXcd = kSplitCus / kNumXcd * 8 / NW, kOldXcd = kSplitCus / kNumXcd, kOlder = kShareOlder;
+  int cut_step = 0, cut_rest = 0;
+  bool tiers = false;
+  auto share_cut = [&](int k) __attribute__((always_inline)) -> int {
+    if (!tiers) return k * cut_step + min(k, cut_rest);
+    const int x = k / kPlacesXcd, s = k % kPlacesXcd;  // (cut_rest: length of the sequence)
+    return x * (cut_rest / kNumXcd) + min(x, cut_rest % kNumXcd) + ((s * cut_step + min(s, kOldXcd) * (cut_step / kOlder)) >> 8);
+  };
+  auto next_row = [&]() __attribute__((always_inline)) {
+    row0 += 2 * row_cnt + kShareRowCost;
+    ++item;
+    e_begin = 0;
+    row_cnt = min(max(kept_count[min(item, BH * Nb - 1)], 0), Nb);
+  };
+  // the part of the row that belongs to this share; false if the share ends before it (a cut at the start of a
+  // row leaves it to the next share, also one without blocks)
+  auto in_share = [&]() __attribute__((always_inline)) -> bool {
+    if (parts) return true;
+    const int end = row0 + 2 * row_cnt + kShareRowCost;
+    e_end = cut1 < end ? share_blocks(cut1 - row0, row_cnt) : row_cnt;
+    return cut1 > row0 && (cut1 >= end || e_end > e_begin);
+  };
+  if constexpr (kShare) {
+    constexpr int kGroups = kShareMaxRows / kShareGroup, GPW = kGroups / NW;
+    constexpr int PG = (kNumXcd * kPlacesXcd + kShareGroup * NW - 1) / (kShareGroup * NW);  // groups a wavefront has of as many rows as places
+    __shared__ int group_sum[2][kGroups];
+    __shared__ int wave_longest[NW];
+    __shared__ int found[4];
+    const int rows = BH * Nb;
+    // counts of four rows a lane, group i * NW + wave, zero past the end (out of range for the descriptor).  No
+    // branches: a branch to code that is not in the instruction cache yet costs as much as the work it saves.
+    int c[GPW][4];
+    {
+      const __amdgpu_buffer_rsrc_t rs = head_rsrc(reinterpret_cast<const uint16_t *>(kept_count), (uint32_t)rows * 4u);
+#pragma unroll
+      for (int i = 0; i < GPW; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          c[i][j] = (int)__builtin_amdgcn_raw_buffer_load_b32(rs, ((i * NW + wave) * kShareGroup + 4 * lane + j) * 4, 0, 0);
+      int sum[GPW];
+#pragma unroll
+      for (int i = 0; i < GPW; ++i) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) c[i][j] = min(max(c[i][j], 0), Nb);
+        sum[i] = c[i][0] + c[i][1] + c[i][2] + c[i][3];
+      }
+#pragma unroll
+      for (int i = 0; i < GPW; ++i) sum[i] = wave_sum_i32(sum[i]);
+      // (the longest row is asked for where there are no more rows than places: the first PG groups)
+      int longest = 0;
+#pragma unroll
+      for (int i = 0; i < PG; ++i) longest = max(longest, max(max(c[i][0], c[i][1]), max(c[i][2], c[i][3])));
+      longest = (int)wave_max_u32((uint32_t)longest);
+      if (lane == 0) {
+#pragma unroll
+        for (int i = 0; i < GPW; ++i) group_sum[0][i * NW + wave] = sum[i];
+        wave_longest[wave] = longest;
+      }
+    }
+    __syncthreads();
+    int gl = lane < kGroups ? group_sum[0][lane] : 0;  // blocks of group `lane`, then its length
+    const int blocks = __builtin_amdgcn_readfirstlane(wave_sum_i32(gl)), total = 2 * blocks + kShareRowCost * rows, n_wg = (int)gridDim.x;
+    // blocks of a part, 0 = shares.  Any number from blocks / (n_wg - rows) up gives no more parts than workgroups
+    // (n / most + 1 a row).  The rule is the one with the shortest way, in half blocks: the longest row; a part and
+    // the merge of all; a share with a row more than the mean and the merge (which takes one for 64 parts).
+    int most = 0;
+    if (rows <= n_wg) {
+      int longest = 0;
+#pragma unroll
+      for (int i = 0; i < NW; ++i) longest = max(longest, wave_longest[i]);
+      const float per_wg = __builtin_amdgcn_rcpf((float)n_wg);
+      const int t_shares = (int)((float)total * per_wg) + kShareRowCost + 2 + n_wg / 64;
+      int t_parts = 0x7fffffff;
+      if (rows < n_wg) {
+        most = max((int)((float)blocks * __builtin_amdgcn_rcpf((float)(n_wg - rows)) * 1.00001f) + 1, kSharePart);
+        t_parts = 2 * most + 2 + (int)(((float)blocks * __builtin_amdgcn_rcpf((float)most) + (float)rows) * (1.f / 64.f));
+      }
+      // (rows that walk through long lists together find each other's K/V in the L2; four workgroups a CU feel it most)
+      const int t_whole = 2 * longest - longest / (kOne ? 4 : 8);
+      if (t_shares < t_parts) most = 0;
+      if (t_whole <= min(t_shares, t_parts)) most = max(longest, 1);
+      most = __builtin_amdgcn_readfirstlane(most);
+    }
+    // length of a row of n blocks in the sequence: its parts, or half blocks
+    const float len_a = most ? __builtin_amdgcn_rcpf((float)most) : 2.f;
+    const float len_b = most ? (float)(most - 1) * len_a : (float)kShareRowCost;
+    const int len_cap = most ? 1 : 0x7fffffff;
+    auto row_len = [&](int n, bool is_row) __attribute__((always_inline)) -> int {
+      const int len = min(max((int)fmaf((float)n, len_a, len_b), 1), max(n, len_cap));
+      return is_row ? len : 0;
+    };
+    if (most) {
+#pragma unroll
+      for (int i = 0; i < PG; ++i) {
+        int sum = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) sum += row_len(c[i][j], (i * NW + wave) * kShareGroup + 4 * lane + j < rows);
+        sum = wave_sum_i32(sum);
+        if (lane == 0) group_sum[1][i * NW + wave] = sum;
+      }
+      __syncthreads();
+      gl = lane < PG * NW ? group_sum[1][lane] : 0;
+    } else {
+      gl = 2 * gl + kShareRowCost * min(max(rows - lane * kShareGroup, 0), kShareGroup);
+    }
+    const int gs = wave_scan_i32(gl);
+    const int n_share = most ? __builtin_amdgcn_readlane(gs, 63) : min(n_wg, max(total / kShareMin, 1));
+    tiers = !most && n_share == kNumXcd * kPlacesXcd;
+    if (tiers) {
+      cut_step = (int)((uint32_t)(total / kNumXcd * 256) / (uint32_t)(kPlacesXcd + kOldXcd / kOlder));
+      cut_rest = total;
+    } else {
+      cut_step = most ? 1 : (int)((uint32_t)total / (uint32_t)n_share);
+      cut_rest = most ? 0 : total - cut_step * n_share;
+    }
+    const int s0 = x0 * n_share / kNumXcd, s1 = (x0 + 1) * n_share / kNumXcd;
+    share = s0 + (int)(blockIdx.x / kNumXcd);
+    const int cut0 = share_cut(share);
+    cut1 = share_cut(share + 1);
+    // the row that the share starts in: found by the wavefront that holds its group
+    const int g = __popcll(__ballot(gs <= cut0));
+    const int g0 = g ? __builtin_amdgcn_readlane(gs, g - 1) : 0;
+    if (share < s1 && g % NW == wave) {
+      const int r0 = g * kShareGroup + 4 * lane;
+      int l[4], n[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        n[j] = c[0][j];
+#pragma unroll
+        for (int i = 1; i < GPW; ++i)
+          if (i == g / NW) n[j] = c[i][j];
+        l[j] = row_len(n[j], r0 + j < rows);
+      }
+      const int sum = l[0] + l[1] + l[2] + l[3];
+      int end = g0 + wave_scan_i32(sum), at = end - sum;  // rows of this lane: at .. end
+      if (at <= cut0 && cut0 < end) {
+        int j = 0, len = l[0], cnt_j = n[0];
+#pragma unroll
+        for (int i = 1; i < 4; ++i) {
+          const bool later = j == i - 1 && cut0 >= at + len;
+          at = later ? at + len : at;
+          len = later ? l[i] : len;
+          cnt_j = later ? n[i] : cnt_j;
+          j = later ? i : j;
+        }
+        found[0] = r0 + j;
+        found[1] = at;
+        found[2] = cnt_j;
+        found[3] = len;
+      }
+    }
+    __syncthreads();
+    item = __builtin_amdgcn_readfirstlane(found[0]);
+    row0 = __builtin_amdgcn_readfirstlane(found[1]);
+    row_cnt = __builtin_amdgcn_readfirstlane(found[2]);
+    if (most) {
+      parts = __builtin_amdgcn_readfirstlane(found[3]);
+      e_begin = (share - row0) * row_cnt / parts;
+      e_end = (share - row0 + 1) * row_cnt / parts;
+    } else {
+      e_begin = share_blocks(cut0 - row0, row_cnt);
+    }
+    if (t == 0) owner[blockIdx.x] = int4{-1, 0, 0, 0};
+    if (share >= s1) return;
+    if (!parts && e_begin > 0 && e_begin == row_cnt) next_row();
+  } else if (kMode == kPlanned && plan) {
     if (i_own < len0) {
       item = __builtin_amdgcn_readfirstlane(entry(off0, len0, i_own));
     } else {
@@ -679,7 +932,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     const int qb0 = x0 * per + (int)(slot % per);
     if (qb0 < Nb) item = (int)(slot / per) * Nb + qb0;  // else: padding of the last eighth
   }
-  while (item >= 0 && item < BH * Nb) {
+  while (kShare ? in_share() : item >= 0 && item < BH * Nb) {
   begin_item(item);
   // (thread 0) cursor value and item id of the NEXT item.  The cursor is advanced only in
   // the last loop body, not earlier: items are then started in list order up to about a
@@ -688,7 +941,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   int i_next = -1, item_next = -1;
   // (only while every workgroup of the list can expect another item of the own list: the last
   // round looks at the cursors first, so that it ends without a queue of failing atomics)
-  const bool ahead = !kSplit && plan && i_own + n_own < len0;
+  const bool ahead = kMode == kPlanned && plan && i_own + n_own < len0;
 
   if (cnt > 0) {
     // ---- prologue: stages 0 and 1 in flight, S^T and maximum of slice 0 --------------------
@@ -864,9 +1117,11 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     }
   }
 
-  if constexpr (kSplit) {
+  const bool partial = kSplit || (kShare && e_end - e_begin < row_cnt);
+  if (partial) {
     // ---- part of a row: unnormalised output and its softmax state, as the lanes hold them ----
-    float *dst = part + ((size_t)(item * n_split + split) * NW + wave) * kPartFloats<D>;
+    const int slot = kShare ? 2 * share + (e_begin == 0) : item * n_split + split;
+    float *dst = part + ((size_t)slot * NW + wave) * kPartFloats<D>;
     dst[64 * 16 * DT + lane] = m_ref;
     dst[64 * 16 * DT + 64 + lane] = cnt > 0 ? l_run : kNoKeys;
     if (cnt > 0) {
@@ -877,7 +1132,18 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
         for (int g = 0; g < 4; ++g)
           o4[(4 * dt + g) * 64 + lane] = f32x4_t{o[dt][4 * g], o[dt][4 * g + 1], o[dt][4 * g + 2], o[dt][4 * g + 3]};
     }
-    break;
+    if (kShare && e_begin == 0 && t == 0) {
+      int more = max(parts - 1, 1);
+      for (int k = share + 2; !parts; ++k) {
+        const int d = share_cut(k) - row0;
+        if (d >= 2 * row_cnt + kShareRowCost || share_blocks(d, row_cnt) == row_cnt) break;
+        ++more;
+      }
+      owner[blockIdx.x] = int4{item, more, share, 0};
+    }
+    if (kSplit || parts || e_end < row_cnt) break;
+    next_row();
+    continue;
   }
 
   // ---- epilogue: normalise, stage through LDS, coalesced bf16 store -----------------------
@@ -909,6 +1175,12 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
       *reinterpret_cast<u32x4_t *>(obase + (long long)n * osn + o_c) =
           *reinterpret_cast<const u32x4_t *>(sO + r * SO + o_c);
   }
+  if constexpr (kShare) {
+    if (parts) break;
+    next_row();
+    __syncthreads();  // everyone has read the output staging before the next row's loads
+    continue;
+  }
   if (!plan) break;
   if (wave == 0) {
     if (item_next < 0) item_next = take();
@@ -926,13 +1198,17 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
   const int Nb = (s.N + BLK - 1) / BLK;
   const int BH = s.B * s.H;
   const int n_split = order ? attn_split(BH, Nb, D, BLK) : 1;
-  const bool split = n_split > 1 && order_bytes >= attn_split_bytes(BH, Nb, D, BLK);
+  const int n_share = order ? attn_shares(BH, Nb, D, BLK, false) : 0;
+  const bool share = n_share > 0 && order_bytes >= attn_balanced_bytes(BH, Nb, D, BLK, false);
+  const bool split = !share && n_split > 1 && order_bytes >= attn_split_bytes(BH, Nb, D, BLK);
   const size_t lds = 4 * (size_t)kStageRows<D, BLK> * D * 2;  // >= BLK * (D + 8) * 2 of the output staging
-  auto kern = split ? attn_kernel<D, BLK, kExact, true> : attn_kernel<D, BLK, kExact, false>;
+  const AttnMode mode = share ? kSharedRows : split ? kSplitRows : kPlanned;
+  auto kern = share ? attn_kernel<D, BLK, kExact, kSharedRows>
+              : split ? attn_kernel<D, BLK, kExact, kSplitRows> : attn_kernel<D, BLK, kExact, kPlanned>;
   const int dev = current_device();
   if (dev < 0) return fail(HEART_EHIP, "heart_block_sparse_attn: cannot identify the current device");
-  static DeviceFlags attr_set[2];  // per instantiation: the attribute is per function and device
-  if (hipError_t e = set_max_lds_once(attr_set[split], dev, reinterpret_cast<const void *>(kern), (int)lds))
+  static DeviceFlags attr_set[3];  // per instantiation: the attribute is per function and device
+  if (hipError_t e = set_max_lds_once(attr_set[mode], dev, reinterpret_cast<const void *>(kern), (int)lds))
     return fail(HEART_EHIP, "hipFuncSetAttribute(max dynamic LDS %zu): %s", lds, hipGetErrorString(e));
   const float sc = scale > 0.f ? scale : 1.0f / sqrtf((float)D);
   const float scale_log2e = sc * 1.4426950408889634f;
@@ -940,6 +1216,13 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
   long long grid = (long long)BH * ((Nb + kNumXcd - 1) / kNumXcd) * kNumXcd;
   int n_few = 0;  // (a plan: see working_groups)
   float *part = nullptr;
+  int4 *owner = nullptr;
+  if (share) {
+    owner = reinterpret_cast<int4 *>(order);
+    part = reinterpret_cast<float *>(owner + n_share);
+    order = nullptr;
+    grid = n_share;
+  }
   if (split) {
     part = reinterpret_cast<float *>(order);
     order = nullptr;
@@ -969,11 +1252,11 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
                      s.k_stride[1], s.k_stride[2], s.v_stride[0], s.v_stride[1], s.v_stride[2],
                      s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, BH, s.N, Nb, kept_idx,
                      kept_count, scale_log2e, lse, order, seq, spread ? spread : order,
-                     spread ? kCursorSpread : 1, part, n_split, n_few);
+                     spread ? kCursorSpread : 1, part, owner, n_split, n_few);
   if (int rc = check_launch("attn_kernel")) return rc;
-  if (!split) return HEART_OK;
-  hipLaunchKernelGGL((attn_merge_kernel<D, BLK>), dim3((unsigned)(n_items * (BLK / 32))), dim3(D * 2), 0, st, part,
-                     n_split, (uint16_t *)out, s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, s.N, Nb, lse);
+  if (!split && !share) return HEART_OK;
+  hipLaunchKernelGGL((attn_merge_kernel<D, BLK>), dim3((unsigned)((share ? n_share : n_items) * (BLK / 32))), dim3(D * 2), 0, st, part,
+                     owner, n_split, (uint16_t *)out, s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, s.N, Nb, lse);
   return check_launch("attn_merge_kernel");
 }
 

@@ -264,12 +264,15 @@ size_t heart_workspace_bytes(int B, int H, int Nb, int D) {
 
 size_t heart_attn_workspace_bytes(const heart_shape *s) {
   if (!s || s->B <= 0 || s->H <= 0 || s->N <= 0 || s->block <= 0) return 0;
-  const long long nb = n_blocks(s);
-  const long long BH = (long long)s->B * s->H;
-  const size_t plan = attn_full_plan_bytes(BH, nb);
+  const long long nb = n_blocks(s), BH = (long long)s->B * s->H;
   const bool valid = (s->D == 64 || s->D == 128) && (s->block == 64 || s->block == 128);
-  const size_t parts = valid ? attn_split_bytes(BH, nb, s->D, s->block) : 0;
-  return plan > parts ? plan : parts;
+  return valid ? attn_any_bytes(BH, nb, s->D, s->block) : attn_full_plan_bytes(BH, nb);
+}
+
+size_t heart_attn_balanced_workspace_bytes(const heart_shape *s, int dense) {
+  const size_t any = heart_attn_workspace_bytes(s);
+  const bool valid = any && (s->D == 64 || s->D == 128) && (s->block == 64 || s->block == 128);
+  return valid ? attn_balanced_bytes((long long)s->B * s->H, n_blocks(s), s->D, s->block, dense != 0) : any;
 }
 
 static int check_antidiag(const heart_shape *s, int stride, const char *fn) {

@@ -123,8 +123,23 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
   HEART_WAVE_REDUCE(uint32_t, hi, HEART_OP_ADD);
   return ((unsigned long long)hi << 20) + lo;
 }
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  HEART_WAVE_REDUCE(uint32_t, v, HEART_OP_UMAX);
+  return v;
+}
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
   HEART_WAVE_REDUCE(uint32_t, v, HEART_OP_UMIN);
+  return v;
+}
+// Inclusive prefix sum over the wavefront: shifts by 1, 2, 4, 8 inside rows of 16 lanes, then the last lane
+// of rows 0 and 2, then of the lower half, added to the lanes behind it.
+__device__ __forceinline__ int wave_scan_i32(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
   return v;
 }
 __device__ __forceinline__ int wave_sum_i32(int v) { return (int)wave_sum_u32((uint32_t)v); }
@@ -266,6 +281,18 @@ int launch_attn_plan(int BH, int Nb, int n_wg, int n_few, int n_items, const int
 // workspace bytes the parts take (instead of a plan; 0 if rows are not split).
 int attn_split(long long BH, long long Nb, int D, int block);
 size_t attn_split_bytes(long long BH, long long Nb, int D, int block);
+// Shares that the kept blocks of all rows are dealt out in (0 = not), and the bytes their parts take.
+int attn_shares(long long BH, long long Nb, int D, int block, bool dense);
+size_t attn_share_bytes(long long BH, long long Nb, int D, int block, bool dense);
+// What a call can use without shares, and with them (always more, so the size says which launch is meant).
+inline size_t attn_any_bytes(long long BH, long long Nb, int D, int block) {
+  const size_t plan = attn_full_plan_bytes(BH, Nb), parts = attn_split_bytes(BH, Nb, D, block);
+  return plan > parts ? plan : parts;
+}
+inline size_t attn_balanced_bytes(long long BH, long long Nb, int D, int block, bool dense) {
+  const size_t any = attn_any_bytes(BH, Nb, D, block), shares = attn_share_bytes(BH, Nb, D, block, dense);
+  return shares == 0 ? any : shares > any ? shares : any + 16;
+}
 
 // Device address, on the current device, of the library's static launch-plan array
 // (HEART_ATTN_STATIC_PLAN_BYTES bytes).

@@ -103,6 +103,7 @@ class TmrDriver:
         self.qmean = torch.empty((B, H, D), **f32)
         self.kmean = torch.empty((B, H, D), **f32)
         self.workspace: Optional[torch.Tensor] = None
+        self.dense_workspace: Optional[torch.Tensor] = None
         # completion tickets of the fused pooling + drift launch (zero now, zero after every call)
         self.tickets = torch.zeros(_b.heart_pool_drift_workspace_bytes(B, H), dtype=torch.uint8,
                                    device=self.device)
@@ -167,8 +168,10 @@ class TmrDriver:
         if out is None:
             out = torch.empty_like(q)
         if self.workspace is None:
-            self.workspace = torch.empty(_b.heart_attn_workspace_bytes(q, cfg.block),
+            self.workspace = torch.empty(_b.heart_attn_balanced_workspace_bytes(q, cfg.block),
                                          dtype=torch.uint8, device=self.device)
+            # (the size says how lists are divided; full ones ask for the same or less)
+            self.dense_workspace = self.workspace[:_b.heart_attn_balanced_workspace_bytes(q, cfg.block, True)]
         if self.scores is not None and self.estimator_ws is None:
             self.estimator_ws = torch.empty(
                 _b.heart_scores_antidiag_workspace_bytes(q, cfg.block, cfg.block // 8),
@@ -203,7 +206,7 @@ class TmrDriver:
             kind = "dense"
             mark(); mark(); mark()
             _b.heart_block_sparse_attn(q, k, v, cfg.block, self.dense_idx, self.dense_cnt, out=out,
-                                       workspace=self.workspace)
+                                       workspace=self.dense_workspace)
         else:
             if self.policy == "heart":
                 kind = "heart"
