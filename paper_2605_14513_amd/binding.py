@@ -1,4 +1,5 @@
-"""ctypes binding of libheart.so.  Argument marshalling only.
+"""Binding of libheart.so.  Argument marshalling only: ctypes, and for the calls of a serving loop the extension
+module _native (csrc/native_calls.cpp), which checks and passes on its arguments without ctypes.
 
 Functions take torch tensors that live on the GPU, pass their device pointers,
 shapes and strides to the C ABI declared in include/heart.h, and enqueue on
@@ -16,6 +17,7 @@ import torch
 _PKG = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_PKG, "libheart.so")
 _lib: Optional[ctypes.CDLL] = None
+_calls = None  # the extension module
 
 
 class HeartError(RuntimeError):
@@ -102,6 +104,19 @@ def load_library() -> ctypes.CDLL:
     lib.heart_last_error.restype = ctypes.c_char_p
     _lib = lib
     return lib
+
+
+def _native():
+    """The extension module; raise if it is not built."""
+    global _calls
+    if _calls is None:
+        load_library()
+        if not os.path.exists(os.path.join(_PKG, "_native.so")):
+            raise FileNotFoundError(f"{_PKG}/_native.so is not built; run `python -m paper_2605_14513_amd.build`")
+        from . import _native as calls
+
+        _calls = calls
+    return _calls
 
 
 def heart_last_error() -> str:
@@ -209,38 +224,21 @@ def heart_pool_drift(q, k, block: int, qanchor, kanchor, has_anchor, delta, work
     """heart_pool_qk and heart_drift with one launch fewer (token means and drift share a launch).  workspace: a GPU tensor of at least
     heart_pool_drift_workspace_bytes(B, H) bytes that was zero before its first use (the call
     leaves it zero).  Returns (qblk, kblk, qmean, kmean, drift, refresh)."""
-    lib = load_library()
-    if q.shape != k.shape:
-        raise ValueError("q and k must have the same shape")
-    B, H, N, D = q.shape
-    Nb = (N + block - 1) // block
-    f32 = dict(dtype=torch.float32, device=q.device)
-    qblk = torch.empty((B, H, Nb, D), **f32) if qblk is None else qblk
-    kblk = torch.empty((B, H, Nb, D), **f32) if kblk is None else kblk
-    qmean = torch.empty((B, H, D), **f32) if qmean is None else qmean
-    kmean = torch.empty((B, H, D), **f32) if kmean is None else kmean
-    drift = torch.empty((B, H), **f32) if drift is None else drift
-    refresh = torch.empty((B, H), dtype=torch.uint8, device=q.device) if refresh is None else refresh
-    if delta.numel() != H:
-        raise ValueError("delta must have H entries")
-    for t, n in ((qanchor, "qanchor"), (kanchor, "kanchor"), (qmean, "qmean"), (kmean, "kmean")):
-        if t.shape != (B, H, D):
-            raise ValueError(f"{n} must be [B,H,D]")
-    if has_anchor.shape != (B, H) or drift.shape != (B, H) or refresh.shape != (B, H):
-        raise ValueError("has_anchor, drift, refresh must be [B,H]")
-    if not workspace.is_cuda or not workspace.is_contiguous():
-        raise ValueError("workspace must be a contiguous GPU tensor")
-    shape = make_shape(q, k, block)
-    rc = lib.heart_pool_drift(
-        ctypes.byref(shape), _dev(q, torch.bfloat16, "q", False), _dev(k, torch.bfloat16, "k", False),
-        _dev(qblk, torch.float32, "qblk"), _dev(kblk, torch.float32, "kblk"),
-        _dev(qmean, torch.float32, "qmean"), _dev(kmean, torch.float32, "kmean"),
-        _dev(qanchor, torch.float32, "qanchor"), _dev(kanchor, torch.float32, "kanchor"),
-        _dev(has_anchor, torch.uint8, "has_anchor"), _dev(delta, torch.float32, "delta"),
-        float(gate_lo), float(gate_hi), 1 if commit else 0, _dev(drift, torch.float32, "drift"),
-        _dev(refresh, torch.uint8, "refresh"), workspace.data_ptr(),
-        workspace.nbytes, _stream())
-    _check("heart_pool_drift", rc)
+    native = _native()
+    if qblk is None or kblk is None or qmean is None or kmean is None or drift is None or refresh is None:
+        B, H, N, D = q.shape
+        Nb = (N + block - 1) // block
+        f32 = dict(dtype=torch.float32, device=q.device)
+        qblk = torch.empty((B, H, Nb, D), **f32) if qblk is None else qblk
+        kblk = torch.empty((B, H, Nb, D), **f32) if kblk is None else kblk
+        qmean = torch.empty((B, H, D), **f32) if qmean is None else qmean
+        kmean = torch.empty((B, H, D), **f32) if kmean is None else kmean
+        drift = torch.empty((B, H), **f32) if drift is None else drift
+        refresh = torch.empty((B, H), dtype=torch.uint8, device=q.device) if refresh is None else refresh
+    rc = native.pool_drift(q, k, block, qanchor, kanchor, has_anchor, delta, workspace, gate_lo, gate_hi, commit,
+                           qblk, kblk, qmean, kmean, drift, refresh, _stream())
+    if rc:
+        _check("heart_pool_drift", rc)
     return qblk, kblk, qmean, kmean, drift, refresh
 
 
@@ -250,46 +248,20 @@ def heart_mask_topp(qblk, kblk, tau, refresh=None, scores_in=None, n_always_kv_b
     """Top-p block mask; writes mask/kept_idx/kept_count in place for refreshed heads.
     workspace: a contiguous GPU tensor of at least heart_mask_topp_workspace_bytes(B, H, Nb, D)
     bytes (heart_mask_topp_ws: score stage on the int8 matrix cores), or None."""
-    lib = load_library()
-    if scores_in is not None:
-        B, H, Nb, _ = scores_in.shape
-        D = 0 if qblk is None else qblk.shape[-1]
-        dev = scores_in.device
-    else:
-        B, H, Nb, D = qblk.shape
-        dev = qblk.device
-    if mask is None:
-        mask = torch.zeros((B, H, Nb, Nb), dtype=torch.uint8, device=dev)
-    if kept_idx is None:
-        kept_idx = torch.full((B, H, Nb, Nb), -1, dtype=torch.int32, device=dev)
-    if kept_count is None:
-        kept_count = torch.zeros((B, H, Nb), dtype=torch.int32, device=dev)
-    if tau.numel() != H:
-        raise ValueError("tau must have H entries")
-    for t, shp, n in ((mask, (B, H, Nb, Nb), "mask"), (kept_idx, (B, H, Nb, Nb), "kept_idx"),
-                      (kept_count, (B, H, Nb), "kept_count")):
-        if t.shape != shp:
-            raise ValueError(f"{n} must have shape {shp}")
-    if scores_out is not None and scores_out.shape != (B, H, Nb, Nb):
-        raise ValueError("scores_out must be [B,H,Nb,Nb]")
-    if refresh is not None and refresh.shape != (B, H):
-        raise ValueError("refresh must be [B,H]")
-    if scores_in is None and kblk.shape != (B, H, Nb, D):
-        raise ValueError("kblk must match qblk")
-    args = (B, H, Nb, D, _dev(qblk, torch.float32, "qblk"), _dev(kblk, torch.float32, "kblk"),
-            _dev(scores_in, torch.float32, "scores_in"), _dev(tau, torch.float32, "tau"),
-            _dev(refresh, torch.uint8, "refresh"), int(n_always_kv_blocks), int(n_dense_q_blocks),
-            int(min_keep), _dev(mask, torch.uint8, "mask"), _dev(kept_idx, torch.int32, "kept_idx"),
-            _dev(kept_count, torch.int32, "kept_count"), _dev(scores_out, torch.float32, "scores_out"))
-    if workspace is None:
-        rc = lib.heart_mask_topp(*args, _stream())
-        _check("heart_mask_topp", rc)
-    else:
-        if not workspace.is_contiguous():
-            raise ValueError("workspace must be contiguous")
-        rc = lib.heart_mask_topp_ws(*args, workspace.data_ptr(),
-                                    workspace.nbytes, _stream())
-        _check("heart_mask_topp_ws", rc)
+    native = _native()
+    if mask is None or kept_idx is None or kept_count is None:
+        B, H, Nb, _ = (qblk if scores_in is None else scores_in).shape
+        dev = (qblk if scores_in is None else scores_in).device
+        if mask is None:
+            mask = torch.zeros((B, H, Nb, Nb), dtype=torch.uint8, device=dev)
+        if kept_idx is None:
+            kept_idx = torch.full((B, H, Nb, Nb), -1, dtype=torch.int32, device=dev)
+        if kept_count is None:
+            kept_count = torch.zeros((B, H, Nb), dtype=torch.int32, device=dev)
+    rc = native.mask_topp(qblk, kblk, tau, refresh, scores_in, n_always_kv_blocks, n_dense_q_blocks, min_keep, mask,
+                          kept_idx, kept_count, scores_out, workspace, _stream())
+    if rc:
+        _check("heart_mask_topp" if workspace is None else "heart_mask_topp_ws", rc)
     return mask, kept_idx, kept_count
 
 
@@ -332,39 +304,18 @@ def heart_block_sparse_attn(q, k, v, block: int, kept_idx, kept_count, scale: fl
     those of a few rows a workgroup evenly), None (natural launch order), or "auto" (a
     fresh tensor from torch's allocator).
     flags: 0 (heart_block_sparse_attn) or HEART_ATTN_FOLD_SCALE (heart_block_sparse_attn_flags)."""
-    lib = load_library()
-    if q.shape != k.shape or q.shape != v.shape:
-        raise ValueError("q, k, v must have the same shape")
-    B, H, N, D = q.shape
-    Nb = (N + block - 1) // block
+    native = _native()
     if out is None:
         out = torch.empty_like(q)
-    if kept_idx.shape != (B, H, Nb, Nb) or kept_count.shape != (B, H, Nb):
-        raise ValueError("kept_idx must be [B,H,Nb,Nb] and kept_count [B,H,Nb]")
-    if lse is not None and lse.shape != (B, H, N):
-        raise ValueError("lse must be [B,H,N]")
-    shape = make_shape(q, k, block, v, out)
     if isinstance(workspace, str):
         if workspace != "auto":
             raise ValueError("workspace must be a tensor, None or 'auto'")
-        workspace = torch.empty(int(lib.heart_attn_workspace_bytes(ctypes.byref(shape))),
-                                dtype=torch.uint8, device=q.device)
-    ws_ptr, ws_bytes = None, 0
-    if workspace is not None:
-        if not workspace.is_cuda or not workspace.is_contiguous():
-            raise ValueError("workspace must be a contiguous GPU tensor")
-        ws_ptr, ws_bytes = workspace.data_ptr(), workspace.nbytes
-    args = [ctypes.byref(shape), _dev(q, torch.bfloat16, "q", False),
-            _dev(k, torch.bfloat16, "k", False), _dev(v, torch.bfloat16, "v", False),
-            _dev(kept_idx, torch.int32, "kept_idx"), _dev(kept_count, torch.int32, "kept_count"),
-            float(scale)]
-    tail = [_dev(out, torch.bfloat16, "out", False), _dev(lse, torch.float32, "lse"), ws_ptr,
-            ws_bytes, _stream()]
-    if flags:
-        _check("heart_block_sparse_attn_flags",
-               lib.heart_block_sparse_attn_flags(*args, int(flags), *tail))
-    else:
-        _check("heart_block_sparse_attn", lib.heart_block_sparse_attn(*args, *tail))
+        if q.shape != k.shape or q.shape != v.shape:
+            raise ValueError("q, k, v must have the same shape")
+        workspace = torch.empty(heart_attn_workspace_bytes(q, block), dtype=torch.uint8, device=q.device)
+    rc = native.block_sparse_attn(q, k, v, block, kept_idx, kept_count, scale, flags, out, lse, workspace, _stream())
+    if rc:
+        _check("heart_block_sparse_attn_flags" if flags else "heart_block_sparse_attn", rc)
     return out
 
 
@@ -446,30 +397,17 @@ def heart_scores_antidiag(q, k, block: int, stride: int, scores=None, workspace=
     heart_mask_topp(scores_in=...).  workspace: a contiguous GPU tensor of at least
     heart_scores_antidiag_workspace_bytes, or None (a fresh tensor from torch's allocator);
     refresh: uint8 [B,H] or None: heads with 0 are skipped (their scores stay as they are)."""
-    lib = load_library()
-    if q.shape != k.shape:
-        raise ValueError("q and k must have the same shape")
-    B, H, N, D = q.shape
-    Nb = (N + block - 1) // block
-    if refresh is not None and refresh.shape != (B, H):
-        raise ValueError("refresh must be [B,H]")
-    shape = make_shape(q, k, block)
-    need = int(lib.heart_scores_antidiag_workspace_bytes(ctypes.byref(shape), int(stride)))
+    native = _native()
     if workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    if not workspace.is_cuda or not workspace.is_contiguous():
-        raise ValueError("workspace must be a contiguous GPU tensor")
+        workspace = torch.empty(heart_scores_antidiag_workspace_bytes(q, block, stride), dtype=torch.uint8,
+                                device=q.device)
     if scores is None:
+        B, H, N, _ = q.shape
+        Nb = (N + block - 1) // block
         scores = torch.empty((B, H, Nb, Nb), dtype=torch.float32, device=q.device)
-    elif scores.shape != (B, H, Nb, Nb):
-        raise ValueError("scores must be [B,H,Nb,Nb]")
-    rc = lib.heart_scores_antidiag(ctypes.byref(shape), _dev(q, torch.bfloat16, "q", False),
-                                   _dev(k, torch.bfloat16, "k", False), int(stride),
-                                   _dev(refresh, torch.uint8, "refresh"),
-                                   _dev(scores, torch.float32, "scores"),
-                                   workspace.data_ptr(),
-                                   workspace.nbytes, _stream())
-    _check("heart_scores_antidiag", rc)
+    rc = native.scores_antidiag(q, k, block, stride, scores, workspace, refresh, _stream())
+    if rc:
+        _check("heart_scores_antidiag", rc)
     return scores
 
 
@@ -481,23 +419,17 @@ def heart_ebc_band_error(err, dense, weights=(1.0, 0.5, 0.01, 0.01), epsilon: fl
                          workspace=None, out=None):
     """Frequency-weighted velocity error of fp32 GPU tensors [..., T, Y, X] (leading axes are
     summed over).  Returns a GPU float64 tensor [6]: error, E_LL, E_LH, E_HL, E_HH, dense energy."""
-    lib = load_library()
-    if err.shape != dense.shape or err.dim() < 3:
-        raise ValueError("err and dense must have the same shape [..., T, Y, X]")
-    T, Y, X = (int(v) for v in err.shape[-3:])
-    C = int(err.numel() // (T * Y * X))
-    need = int(lib.heart_ebc_workspace_bytes(C, T, Y, X))
+    native = _native()
     if workspace is None:
+        T, Y, X = (int(v) for v in err.shape[-3:])
+        need = heart_ebc_workspace_bytes(int(err.numel() // (T * Y * X)), T, Y, X)
         workspace = torch.empty(need, dtype=torch.uint8, device=err.device)
     if out is None:
         out = torch.empty(6, dtype=torch.float64, device=err.device)
-    w = (ctypes.c_double * 4)(*[float(x) for x in weights])
-    rc = lib.heart_ebc_band_error(C, T, Y, X, _dev(err, torch.float32, "err"),
-                                  _dev(dense, torch.float32, "dense"), w, float(epsilon),
-                                  _dev(workspace, workspace.dtype, "workspace"),
-                                  workspace.nbytes,
-                                  _dev(out, torch.float64, "out"), _stream())
-    _check("heart_ebc_band_error", rc)
+    w0, w1, w2, w3 = weights
+    rc = native.ebc_band_error(err, dense, w0, w1, w2, w3, epsilon, workspace, out, _stream())
+    if rc:
+        _check("heart_ebc_band_error", rc)
     return out
 
 

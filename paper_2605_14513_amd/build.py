@@ -1,14 +1,18 @@
-"""Builds libheart.so (the C-ABI HIP library) in-tree with hipcc for gfx950."""
+"""Builds libheart.so (the C-ABI HIP library) in-tree with hipcc for gfx950, and the extension module
+_native.so that calls it for binding.py."""
 from __future__ import annotations
 
 import os
 import subprocess
-import sys
+import sysconfig
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libheart.so")
+NATIVE = os.path.join(PKG, "_native.so")
+NATIVE_SOURCE = os.path.join(CSRC, "native_calls.cpp")
 SOURCES = ["heart_api.hip", "pool_qk.hip", "drift.hip", "mask_topp.hip", "attn_plan.hip",
            "block_sparse_attn.hip", "ubench.hip", "ebc.hip", "antidiag_scores.hip"]
 
@@ -25,29 +29,44 @@ def sources():
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(NATIVE):
         return True
-    t = os.path.getmtime(LIB)
-    deps = sources() + [os.path.join(CSRC, "heart_internal.h"),
+    t = min(os.path.getmtime(LIB), os.path.getmtime(NATIVE))
+    deps = sources() + [NATIVE_SOURCE, os.path.join(CSRC, "heart_internal.h"),
                         os.path.join(ROOT, "include", "heart.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 
 
-def build(force: bool = True, verbose: bool = False) -> str:
-    """Compile every HIP source into libheart.so.  Raises on failure."""
-    if not force and not is_stale():
-        return LIB
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc] + HIPCC_FLAGS + ["-o", LIB] + sources()
+def _run(cmd, verbose: bool) -> None:
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     out = "\n".join(l for l in res.stdout.splitlines()
                     if "is not a recognized feature for this target" not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError(f"{cmd[0]} failed:\n" + out)
     if verbose and out.strip():
         print(out)
+
+
+def build(force: bool = True, verbose: bool = False) -> str:
+    """Compile every HIP source into libheart.so and the extension module.  Raises on failure."""
+    if not force and not is_stale():
+        return LIB
+    from torch.utils.cpp_extension import include_paths, library_paths
+
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    obj = NATIVE[:-3] + ".o"
+    incs = [f"-isystem{p}" for p in include_paths() + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]]
+    with ThreadPoolExecutor(2) as ex:
+        jobs = [ex.submit(_run, [hipcc] + HIPCC_FLAGS + ["-o", LIB] + sources(), verbose),
+                ex.submit(_run, ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", *incs, "-c", NATIVE_SOURCE, "-o", obj], verbose)]
+        for j in jobs:
+            j.result()
+    # (torch's libraries are loaded already when the module is imported)
+    _run(["g++", "-shared", obj, "-L" + PKG, "-l:libheart.so", *[f"-L{p}" for p in library_paths()], "-ltorch_python",
+          "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN", "-o", NATIVE], verbose)
+    os.remove(obj)
     return LIB
 
 
