@@ -209,3 +209,14 @@ def test_product_does_not_import_the_oracle():
                 text = open(os.path.join(dirpath, f)).read()
                 assert "import oracle" not in text and "from oracle" not in text, f
                 assert "heart_oracle" not in text, f
+
+
+def test_extension_module_has_no_thread_local_data(lib):
+    """glibc (2.35) resolves every thread-local of a thread on a slow path once a library has been loaded whose own
+    ones the thread never touches; libheart's error text is touched by every call."""
+    import subprocess
+
+    from paper_2605_14513_amd import build as hb
+
+    out = subprocess.run(["readelf", "-lW", hb.NATIVE], stdout=subprocess.PIPE, check=True, text=True).stdout
+    assert "LOAD" in out and "TLS" not in out
