@@ -18,14 +18,17 @@
 //    all that is ever computed or stored of it: no transform, no projected tensor.
 //    The contractions run on the fp64 matrix cores (v_mfma_f64_16x16x4_f64: 16 coefficients
 //    of 16 lines, four elements of the lines a step); the sums of squares are taken from the
-//    accumulators and reduced in a fixed order.  Three launches:
+//    accumulators and reduced in a fixed order.  Two launches for latents:
 //      ebc_first   x coefficients of err with |err|^2, S_T of err, |dense|^2
+//      ebc_plane   y and t coefficients of the x coefficients with S_XY and S_XYT; its last workgroup adds everything up
+//    or, where t or y is longer than 63, in the place of the second
 //      ebc_second  y coefficients of the x coefficients with S_XY
 //      ebc_third   S_XYT; its last workgroup adds everything up
 //    Bound by latency: at 128 x 21 x 30 x 52 the matrix instructions are 7 us of the chip and the
-//    100 MB moved (half of them in the caches) some 20 us; the launches take 21 + 10 + 12 us, of
-//    which a table, a first load and a last sum each about 1 us.  Whole call 257 -> 42 us against
-//    twelve launches that convolved in fp64 on the vector units (results equal to 1e-15).
+//    90 MB moved (half of them in the caches) some 18 us; the launches take 21 + 12 us, of
+//    which a table, a first load and a last sum each about 1 us.  Whole call 41.6 -> 33.9 us against three
+//    launches that counted 400 workgroups on one ticket, 257 us with twelve launches that convolved in fp64 on the
+//    vector units (results equal to 1e-15); 128 x 33 x 45 x 80 134 -> 119 us, 16 x 21 x 30 x 52 21.8 -> 16.9 us.
 //    A calibration run evaluates this once per (head, candidate, prompt-step), off the serving path.
 //
 //  heart_ebc_select       the one-candidate-per-head selection of Eq. 5 (minimum summed
@@ -95,11 +98,13 @@ __device__ __forceinline__ long long ebc_div(long long a, long long b) {
 }
 
 // 32 lines as one wavefront contracts them: lane l16 = lane % 16 holds lines col0 + l16 and
-// col0 + 16 + l16, lane group g = lane / 16 their elements j = g mod 4.
+// col0 + 16 + l16, lane group g = lane / 16 their elements j = g mod 4; of lines whose elements lie side by side (kUnit)
+// instead elements 4 g .. 4 g + 3 of every whole 16, which are one load: the loads of single elements took four times
+// the instructions, and 16 wavefronts more lines than the 32 KB cache has (128 x 33 x 45 x 80: 124 -> 119 us).
 template <typename TIn>
 struct EbcTile {
   long long col0;
-  const TIn *src[2];  // this lane's first elements
+  const TIn *src[2];  // the lines (kUnit), or this lane's first elements
   bool ok[2];         // the line exists (others count as zeros)
 };
 template <typename TIn, bool kUnit>
@@ -112,7 +117,7 @@ __device__ __forceinline__ EbcTile<TIn> ebc_tile_at(const TIn *in, const EbcLine
     const long long col = t.col0 + 16 * c + l16;
     t.ok[c] = col < L.lines;
     const long long o = kUnit ? col : ebc_div(col, L.inner);
-    t.src[c] = in + (kUnit ? col * L.n + g : (o * L.n + g) * L.inner + (col - o * L.inner));
+    t.src[c] = in + (kUnit ? col * L.n : (o * L.n + g) * L.inner + (col - o * L.inner));
   }
   return t;
 }
@@ -122,13 +127,28 @@ template <typename TIn>
 struct EbcBatch {
   TIn v[kEbcBatch][2];
 };
+template <typename TIn>
+struct __attribute__((packed, aligned(sizeof(TIn)))) EbcQuad {
+  TIn v[kEbcBatch];
+};
 template <typename TIn, bool kUnit>
 __device__ __forceinline__ void ebc_load(EbcBatch<TIn> &d, const EbcTile<TIn> &t, const EbcLines &L, int j0) {
+  const int g = (int)((threadIdx.x & 63) >> 4);
+  if (kUnit && j0 + 4 * kEbcBatch <= L.n) {  // uniform
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      EbcQuad<TIn> x{};
+      if (t.ok[c]) x = *reinterpret_cast<const EbcQuad<TIn> *>(t.src[c] + j0 + 4 * g);
+#pragma unroll
+      for (int u = 0; u < kEbcBatch; ++u) d.v[u][c] = x.v[u];
+    }
+    return;
+  }
   const long long inner = kUnit ? 1 : L.inner;
-  const int last = L.n - (int)((threadIdx.x & 63) >> 4);
+  const int last = L.n - g;
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
-    const TIn *p = t.src[c] + j0 * inner;
+    const TIn *p = t.src[c] + j0 * inner + (kUnit ? g : 0);
 #pragma unroll
     for (int u = 0; u < kEbcBatch; ++u) d.v[u][c] = t.ok[c] && j0 + 4 * u < last ? p[4 * u * inner] : (TIn)0;
   }
@@ -144,14 +164,17 @@ __device__ __forceinline__ void ebc_tile(EbcBatch<TIn> &cur, const EbcTile<TIn> 
   const int lane = threadIdx.x & 63, l16 = lane & 15, g = lane >> 4;
   const int n = L.n;
   ebc_f64x4 acc[M][2];
-  int idx[M], step[M], part[M];  // (f * j) mod n at this lane's j, its step for j + 4, table half
+  // (f * j) mod n at this lane's j, its step to the j of the next contraction step (j + 4, or of a whole 16 of a unit line
+  // j + 1), table half; (unit lines) the step from a whole 16 to the next
+  int idx[M], step[M], part[M], jump[M];
 #pragma unroll
   for (int m = 0; m < M; ++m) {
     const int k = (kt + m) * 16 + l16;
     const int f = k < K ? (k + 1) >> 1 : 0;  // (coefficients past K are computed and dropped)
     part[m] = (k & 1) == 0 && k > 0 && k < K ? n : 0;
-    idx[m] = (int)((uint32_t)(f * g) % (uint32_t)n);
-    step[m] = (int)((uint32_t)(4 * f) % (uint32_t)n);
+    idx[m] = (int)((uint32_t)(f * (kUnit ? 4 * g : g)) % (uint32_t)n);
+    step[m] = (int)((uint32_t)(kUnit ? f : 4 * f) % (uint32_t)n);
+    jump[m] = (int)((uint32_t)(12 * f) % (uint32_t)n);
 #pragma unroll
     for (int c = 0; c < 2; ++c) acc[m][c] = ebc_f64x4{0.0, 0.0, 0.0, 0.0};
   }
@@ -159,6 +182,15 @@ __device__ __forceinline__ void ebc_tile(EbcBatch<TIn> &cur, const EbcTile<TIn> 
     EbcBatch<TIn> nxt;
     const bool more = j0 + 4 * kEbcBatch < n;
     ebc_load<TIn, kUnit>(nxt, more ? t : next, L, more ? j0 + 4 * kEbcBatch : 0);
+    if (kUnit && j0 + 4 * kEbcBatch > n) {  // the last elements of a unit line: j = j0 + g and every fourth
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const int k = (kt + m) * 16 + l16;
+        const int f = k < K ? (k + 1) >> 1 : 0;
+        idx[m] = (int)((uint32_t)(f * (j0 + g)) % (uint32_t)n);
+        step[m] = (int)((uint32_t)(4 * f) % (uint32_t)n);
+      }
+    }
 #pragma unroll
     for (int u = 0; u < kEbcBatch; ++u) {
       if (j0 + 4 * u >= n) break;  // uniform
@@ -176,6 +208,10 @@ __device__ __forceinline__ void ebc_tile(EbcBatch<TIn> &cur, const EbcTile<TIn> 
 #pragma unroll
         for (int c = 0; c < 2; ++c) acc[m][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b[c], acc[m][c], 0, 0, 0);
       }
+    }
+    if constexpr (kUnit) {
+#pragma unroll
+      for (int m = 0; m < M; ++m) idx[m] += jump[m], idx[m] -= idx[m] >= n ? n : 0;
     }
     cur = nxt;
   }
@@ -230,19 +266,35 @@ __device__ __forceinline__ void ebc_contract(const TIn *__restrict__ in, double 
         ebc_tile<2, TIn, kUnit, kStore, kSumIn>(cur, t, after(2 * share), out, L, tab, 0, K, e_out, e_in);
         kt = 2 * share;
       }
-      for (; kt < KT; kt += 2 * share)  // (rows of the last pair past K are dropped)
-        ebc_tile<2, TIn, kUnit, kStore, false>(cur, t, after(kt + 2 * share), out, L, tab, kt, K, e_out, e_in);
+      for (; kt < KT; kt += 2 * share) {
+        if (kt + 1 < KT)
+          ebc_tile<2, TIn, kUnit, kStore, false>(cur, t, after(kt + 2 * share), out, L, tab, kt, K, e_out, e_in);
+        else
+          ebc_tile<1, TIn, kUnit, kStore, false>(cur, t, after(kt + 2 * share), out, L, tab, kt, K, e_out, e_in);
+      }
     }
     t = next;
   }
 }
 
+// Tickets: atomics on one address are served one after another, some 35 ns each, which is 14 us with 400 workgroups and 30
+// with 864.  So a workgroup draws from one of 32 leaves (cache lines of their own), and the last of each leaf from the
+// root.  They lie in the halves of the partial sums that the first launch leaves unused, which zeroes them.
+constexpr int kEbcLeaves = 32, kEbcTicketLine = 16;  // (doubles)
+__host__ __device__ __forceinline__ unsigned *ebc_leaf(double *partials, int i) {
+  return reinterpret_cast<unsigned *>(partials + kEbcPartials / 2 + i * kEbcTicketLine);
+}
+__host__ __device__ __forceinline__ unsigned *ebc_root(double *partials) {
+  return reinterpret_cast<unsigned *>(partials + kEbcPartials + kEbcPartials / 2);
+}
+static_assert(kEbcLeaves * kEbcTicketLine <= kEbcPartials / 2, "room of the tickets");
+
 // Workgroups [0, gx): x coefficients of err -> cx, |err|^2.  [gx, gx + gt): S_T of err.  The rest:
-// |dense|^2.  ticket: zeroed for ebc_third.
+// |dense|^2.  The tickets of the last launch are zeroed.
 template <bool kShared>
 __global__ __launch_bounds__(kEbcThreads, 4) void ebc_first_kernel(
     const float *__restrict__ err, const float *__restrict__ dense, long long total, EbcLines lx, EbcLines lt,
-    int gx, int gt, double *__restrict__ cx, double *__restrict__ partials, unsigned *__restrict__ ticket) {
+    int gx, int gt, double *__restrict__ cx, double *__restrict__ partials) {
   __shared__ double tab[2 * kEbcMaxAxis];
   __shared__ double red[kEbcWaves];
   int blk = blockIdx.x;
@@ -253,8 +305,9 @@ __global__ __launch_bounds__(kEbcThreads, 4) void ebc_first_kernel(
     const double s = ebc_block_sum(e_in, red);
     if (threadIdx.x == 0) {
       partials[0 * kEbcPartials + blk] = s;
-      if (blk == 0) *ticket = 0u;
+      if (blk == 0) *ebc_root(partials) = 0u;
     }
+    if (blk == 0 && threadIdx.x < kEbcLeaves) *ebc_leaf(partials, (int)threadIdx.x) = 0u;
   } else if (blk < gx + gt) {
     blk -= gx;
     ebc_contract<kShared, float, false, false, false>(err, nullptr, lt, blk, gt, tab, e_out, e_in);
@@ -300,24 +353,24 @@ struct EbcFinish {
   double n_t, n_yx, w[4], epsilon;
 };
 
-// S_XYT; the workgroup that draws the last ticket adds up the partial sums and writes the result.
-// The partial sums of this launch cross workgroups of different XCDs and therefore move with
-// device-scope stores and loads; a workgroup takes its ticket after its store is acknowledged.
-template <bool kShared>
-__global__ __launch_bounds__(kEbcThreads, 3) void ebc_third_kernel(const double *__restrict__ cyx, EbcLines lt,
-                                                                double *__restrict__ partials,
-                                                                unsigned *__restrict__ ticket, EbcFinish f,
-                                                                double *__restrict__ out) {
-  __shared__ double tab[2 * kEbcMaxAxis];
-  __shared__ double red[kEbcWaves];
+// Ends a launch: this workgroup's sum of reduction 3 is `s` (and of reduction 2 `s_xy`, if kBoth); the workgroup that
+// draws the last ticket adds up all partial sums and writes the result.  The partial sums of this launch cross
+// workgroups of different XCDs and therefore move with device-scope stores and loads; a workgroup takes its
+// ticket after its stores are acknowledged.
+template <bool kBoth>
+__device__ __forceinline__ void ebc_finish(double s_xy, double s, double *__restrict__ partials, const EbcFinish &f,
+                                           double *__restrict__ out) {
   __shared__ int s_last;
-  double e_out = 0.0, e_in = 0.0;
-  ebc_contract<kShared, double, true, false, false>(cyx, nullptr, lt, blockIdx.x, gridDim.x, tab, e_out, e_in);
-  const double s = ebc_block_sum(e_out, red);
   if (threadIdx.x == 0) {
+    if constexpr (kBoth)
+      __hip_atomic_store(&partials[2 * kEbcPartials + blockIdx.x], s_xy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(&partials[3 * kEbcPartials + blockIdx.x], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    s_last = atomicAdd(ticket, 1u) == gridDim.x - 1;
+    const int leaf = (int)(blockIdx.x % kEbcLeaves), n_leaves = min((int)gridDim.x, kEbcLeaves);
+    const unsigned members = (gridDim.x - (unsigned)leaf + kEbcLeaves - 1) / kEbcLeaves;
+    bool last = atomicAdd(ebc_leaf(partials, leaf), 1u) == members - 1;
+    if (last) last = atomicAdd(ebc_root(partials), 1u) == (unsigned)n_leaves - 1;
+    s_last = last;
   }
   __syncthreads();
   if (!s_last) return;
@@ -358,7 +411,140 @@ __global__ __launch_bounds__(kEbcThreads, 3) void ebc_third_kernel(const double 
   }
 }
 
-// the two coefficient arrays (neither larger than the tensor), the partial sums, the ticket
+// S_XYT
+template <bool kShared>
+__global__ __launch_bounds__(kEbcThreads, 3) void ebc_third_kernel(const double *__restrict__ cyx, EbcLines lt,
+                                                                double *__restrict__ partials, EbcFinish f,
+                                                                double *__restrict__ out) {
+  __shared__ double tab[2 * kEbcMaxAxis];
+  __shared__ double red[kEbcWaves];
+  double e_out = 0.0, e_in = 0.0;
+  ebc_contract<kShared, double, true, false, false>(cyx, nullptr, lt, blockIdx.x, gridDim.x, tab, e_out, e_in);
+  ebc_finish<false>(0.0, ebc_block_sum(e_out, red), partials, f, out);
+}
+
+// The second and third step in one launch, for short t and y axes (at most kEbcPlaneAxis; latents have 21 to 33 and
+// 30 to 45): a wavefront takes a (t, y) plane of one x coefficient of one channel, contracts y and then t, and keeps
+// nothing but the two sums of squares.  With the plane's rows as the first operand and the table as the second the y
+// coefficients come out as (t = lane / 16 + 4 r, k = lane % 16) in register r, which is, unchanged, the second operand
+// of the t contraction's step r.  The table's operands over y stay in registers.  Bound by latency as the others: one
+// plane a wavefront at 128 x 21 x 30 x 52, 12 us in the place of two launches of 10 and 13 us and of 10 MB written and
+// read again (21 us with one ticket for its 864 workgroups and operands from LDS in every step).
+constexpr int kEbcPlaneAxis = 63;  // two tiles of 16 coefficients
+template <int M, int SY>  // tiles of y coefficients, contraction steps (of 4 elements) over y
+__global__ __launch_bounds__(kEbcThreads, SY > 8 ? 3 : 4) void ebc_plane_kernel(const double *__restrict__ cx, int C, int T, int Y,
+                                                                                int KX, double *__restrict__ partials,
+                                                                                EbcFinish f, double *__restrict__ out) {
+  __shared__ double tab_t[2 * kEbcPlaneAxis], tab_y[2 * kEbcPlaneAxis];
+  __shared__ double red[kEbcWaves];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, g = lane >> 4;
+  const int KY = ebc_coefs(Y), KT = ebc_coefs(T), PT = (KT + 15) / 16, TT = (T + 15) / 16, TY = T * Y;
+  const long long planes = (long long)KX * C, stride = (long long)gridDim.x * kEbcWaves;
+  long long p = (long long)blockIdx.x * kEbcWaves + wave;
+  // row l16 of t tile tt of plane pl, this lane's element of each step
+  auto load = [&](double (&v)[SY], long long pl, int tt) __attribute__((always_inline)) {
+    const int t = 16 * tt + l16;
+    const double *src = cx + pl * TY + t * Y + g;
+    const int last = pl < planes && t < T ? Y - g : 0;
+#pragma unroll
+    for (int u = 0; u < SY; ++u) v[u] = 4 * u < last ? src[4 * u] : 0.0;
+  };
+  double cur[SY];
+  load(cur, p, 0);
+  for (int m = threadIdx.x; m < T + Y; m += kEbcThreads) {  // (tables as ebc_table's)
+    const int n = m < T ? T : Y, i = m < T ? m : m - T;
+    double *tab = m < T ? tab_t : tab_y;
+    double c, sn;
+    sincospi(2.0 * (double)i / (double)n, &sn, &c);
+    tab[i] = c;
+    tab[n + i] = sn;
+  }
+  __syncthreads();
+  // this lane's coefficient of each tile: (f j) mod n at its first j, the step for j + 4, the half of the table
+  struct Walk { int at, step, half; };
+  auto walk = [&](int k, int K, int n) -> Walk {
+    const int fr = k < K ? (k + 1) >> 1 : 0;  // (coefficients past K are computed and dropped)
+    return Walk{(int)((uint32_t)(fr * g) % (uint32_t)n), (int)((uint32_t)(4 * fr) % (uint32_t)n), (k & 1) == 0 && k > 0 && k < K ? n : 0};
+  };
+  double by[M][SY];  // the table's operands of all steps over y
+#pragma unroll
+  for (int m = 0; m < M; ++m) {
+    Walk w = walk(16 * m + l16, KY, Y);
+#pragma unroll
+    for (int u = 0; u < SY; ++u) {
+      by[m][u] = tab_y[w.half + w.at];
+      w.at += w.step;
+      w.at -= w.at >= Y ? Y : 0;
+    }
+  }
+  Walk wt[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) wt[q] = walk(16 * q + l16, KT, T);
+  double s_xy = 0.0, s_xyt = 0.0;
+  for (; p < planes; p += stride) {
+    const double wx = p >= C ? 2.0 : 1.0;  // (plane = kx * C + channel)
+    ebc_f64x4 acc2[M][2];
+    int at_t[2] = {wt[0].at, wt[1].at};
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) acc2[m][q] = ebc_f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int tt = 0; tt < TT; ++tt) {
+      double nxt[SY];
+      const bool same = tt + 1 < TT;
+      load(nxt, same ? p : p + stride, same ? tt + 1 : 0);
+      ebc_f64x4 acc[M];
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        acc[m] = ebc_f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int u = 0; u < SY; ++u) acc[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(cur[u], by[m][u], acc[m], 0, 0, 0);
+      }
+#pragma unroll
+      for (int m = 0; m < M; ++m) {
+        const int ky = 16 * m + l16;
+        const double w = ky >= KY ? 0.0 : ky > 0 ? 2.0 * wx : wx;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s_xy = fma(w * acc[m][r], acc[m][r], s_xy);  // (rows past T are zero)
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        if (q >= PT) break;  // uniform
+        double a[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          a[r] = tab_t[wt[q].half + at_t[q]];
+          at_t[q] += wt[q].step;
+          at_t[q] -= at_t[q] >= T ? T : 0;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int m = 0; m < M; ++m) acc2[m][q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[r], acc[m][r], acc2[m][q], 0, 0, 0);
+      }
+#pragma unroll
+      for (int u = 0; u < SY; ++u) cur[u] = nxt[u];
+    }
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      const int ky = 16 * m + l16;
+      const double w = ky >= KY ? 0.0 : ky > 0 ? 2.0 * wx : wx;
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int kt = 16 * q + g + 4 * r;
+          const double v = acc2[m][q][r];
+          if (kt < KT) s_xyt = fma((kt > 0 ? 2.0 : 1.0) * w * v, v, s_xyt);
+        }
+    }
+  }
+  const double sum_xy = ebc_block_sum(s_xy, red);
+  const double sum = ebc_block_sum(s_xyt, red);
+  ebc_finish<true>(sum_xy, sum, partials, f, out);
+}
+
+// the two coefficient arrays (neither larger than the tensor), the partial sums with the tickets
 static size_t ebc_workspace_doubles(long long total, int T, int Y, int X) {
   return 2 * (size_t)total + (size_t)(T + Y + X) + kEbcSums * (size_t)kEbcPartials;
 }
@@ -369,7 +555,6 @@ int launch_ebc_band_error(long long C, int T, int Y, int X, const float *err, co
   const long long total = C * T * Y * X;
   const int KX = ebc_coefs(X), KY = ebc_coefs(Y);
   double *cx = ws, *cyx = cx + total, *partials = cyx + total;
-  unsigned *ticket = reinterpret_cast<unsigned *>(partials + kEbcSums * (size_t)kEbcPartials);
   EbcLines lx{X, 1, C * T * Y, 0, 1, 1};
   EbcLines lt{T, (long long)Y * X, C * Y * X, 0, 1, 1};
   EbcLines ly{Y, 1, (long long)KX * C * T, C * T, KX, 1};
@@ -389,16 +574,27 @@ int launch_ebc_band_error(long long C, int T, int Y, int X, const float *err, co
     const long long rounds = (g + most - 1) / most;
     return (int)((g + rounds - 1) / rounds);
   };
-  const int gx = groups(lx, 384), gt = groups(lt, 400), gy = groups(ly, 768), gyx = groups(lyx, 768);
+  const int gx = groups(lx, 384), gt = groups(lt, 400);
   const int gd = (int)std::min<long long>((total + 8 * kEbcThreads - 1) / (8 * kEbcThreads), 240);
-  const EbcFinish f{{gx, gt, gy, gyx, gd}, (double)T, (double)Y * X, {w[0], w[1], w[2], w[3]}, epsilon};
+  EbcFinish f{{gx, gt, 0, 0, gd}, (double)T, (double)Y * X, {w[0], w[1], w[2], w[3]}, epsilon};
   auto first = lx.share > 1 || lt.share > 1 ? ebc_first_kernel<true> : ebc_first_kernel<false>;
+  hipLaunchKernelGGL(first, dim3((unsigned)(gx + gt + gd)), dim3(kEbcThreads), 0, st, err, dense, total, lx, lt, gx, gt, cx,
+                     partials);
+  if (T <= kEbcPlaneAxis && Y <= kEbcPlaneAxis && C <= 0x7fffffff / KX) {
+    const long long want = ((long long)KX * C + kEbcWaves - 1) / kEbcWaves;
+    const int gp = (int)std::min<long long>(want, kEbcPartials);
+    f.count[2] = f.count[3] = gp;
+    auto plane = Y < 32 ? ebc_plane_kernel<1, 8> : Y <= 48 ? ebc_plane_kernel<2, 12> : ebc_plane_kernel<2, 16>;
+    hipLaunchKernelGGL(plane, dim3((unsigned)gp), dim3(kEbcThreads), 0, st, cx, (int)C, T, Y, KX, partials, f, out);
+    return check_launch("ebc kernels");
+  }
+  const int gy = groups(ly, 768), gyx = groups(lyx, 768);
+  f.count[2] = gy;
+  f.count[3] = gyx;
   auto second = ly.share > 1 ? ebc_second_kernel<true> : ebc_second_kernel<false>;
   auto third = lyx.share > 1 ? ebc_third_kernel<true> : ebc_third_kernel<false>;
-  hipLaunchKernelGGL(first, dim3((unsigned)(gx + gt + gd)), dim3(kEbcThreads), 0, st, err, dense, total, lx, lt, gx, gt, cx,
-                     partials, ticket);
   hipLaunchKernelGGL(second, dim3((unsigned)gy), dim3(kEbcThreads), 0, st, cx, ly, cyx, partials);
-  hipLaunchKernelGGL(third, dim3((unsigned)gyx), dim3(kEbcThreads), 0, st, cyx, lyx, partials, ticket, f, out);
+  hipLaunchKernelGGL(third, dim3((unsigned)gyx), dim3(kEbcThreads), 0, st, cyx, lyx, partials, f, out);
   return check_launch("ebc kernels");
 }
 

@@ -121,3 +121,20 @@ def test_thresholds_calibrated_on_the_tiny_workload():
     want_c, want_e = eo.select_bruteforce(E, S, budget)
     assert np.isclose(total, want_e, rtol=1e-12, atol=1e-18)
     print("calibrated thresholds", cands[choice], "error", total, "vs shared", E[:, shared].sum(), flush=True)
+
+
+# t and y axes that one launch contracts together, at the ends of its tiles (16 rows; 15 / 17 and 31 coefficients at 31 / 32
+# and 63 elements) and on either side of the longest axis it takes (63); more planes than wavefronts
+@pytest.mark.parametrize("shape", [(3, 16, 63, 9), (2, 17, 32, 7), (5, 63, 63, 5), (1, 64, 63, 4), (1, 63, 64, 4),
+                                   (2, 31, 31, 3), (1, 33, 1, 64), (300, 3, 5, 62)])
+def test_band_error_of_planes(shape):
+    import paper_2605_14513_amd as heart
+
+    rng = np.random.default_rng(sum(shape))
+    err, dense = (rng.standard_normal(shape).astype(np.float32) for _ in range(2))
+    print("ebc", shape, flush=True)
+    got = heart.heart_ebc_band_error(np_gpu(err), np_gpu(dense)).cpu().numpy()
+    want = eo.band_energies(err)
+    # (the bound of test_band_error_at_tile_edges: 64-bit sums of at most 1e6 terms)
+    assert np.abs(got[1:5] - want).max() <= 1e-13 * want.sum(), (got[1:5], want)
+    assert np.isclose(got[0], eo.band_error(err, dense), rtol=1e-12)
