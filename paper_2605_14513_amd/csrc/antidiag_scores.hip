@@ -15,14 +15,14 @@
 // (v_mfma_f32_32x32x16_bf16), MFMA-bound.
 //
 // Kernel 1 (antidiag_tile): one workgroup (8 wavefronts) per 256 x 256 tile of L (128 FLOP
-//   per operand byte, which keeps the operand stream from L2 below what it delivers).  The
+//   per operand byte, which keeps the operand stream from L2 below what it delivers), or (4) per 128 x 128.  The
 //   contraction runs in stages of 64 elements (half a token row at D = 128): both operand
 //   tiles go from global memory straight into LDS (`buffer_load ... lds`, 16-byte chunks
 //   XOR-swizzled by row so that the fragment reads are conflict free), double-buffered
-//   (128 KB), one barrier per stage, the loads of the next stage in flight during the MFMAs
-//   of the current one; fragments are
+//   (128 KB, 64 KB), one barrier per stage, the loads of the next stage in flight during the MFMAs
+//   of the current one (lines of later stages requested into the L2 as well: 613 -> 625 us); fragments are
 //   read one contraction step ahead and the barrier sits in the shadow of the last step's
-//   MFMAs.  A wavefront owns 64 reduced queries against 128 reduced keys (S^T layout: keys
+//   MFMAs.  A wavefront owns 64 (32) reduced queries against 128 reduced keys (S^T layout: keys
 //   along the accumulator rows), so a query's maximum over those keys is a per-lane
 //   reduction plus one exchange with the partner lane.  The epilogue writes one record per
 //   (reduced query, 128 keys): the maximum m and the 16 sums over 8 keys of exp2(L - m).
@@ -44,11 +44,11 @@ union AdFrag {
   ad_bf16x8 v;
 };
 
-constexpr int kAdTile = 256;                     // reduced rows per tile side
+constexpr int kAdTile = 256;                     // reduced rows per tile side (or half as many: launch_antidiag)
 constexpr int kAdRowB = 128;                     // bytes per tile row and stage (64 bf16)
-constexpr int kAdTileB = kAdTile * kAdRowB;      // bytes of one operand tile of one stage
 constexpr int kAdKeysPerBlock = 8;               // reduced keys per key block (block = 8 S)
-constexpr int kAdLds = 4 * kAdTileB;             // two stages x two operands (128 KB)
+constexpr int kAdLookHeads = 256;                // most heads whose refresh flags every workgroup looks at
+constexpr int ad_lds(int tile) { return 4 * tile * kAdRowB; }  // two stages x two operands (128 KB, 64 KB)
 
 // raw buffer descriptor (base, size in bytes) as four words in scalar registers, for the
 // hand-written LDS-direct loads; accesses past `bytes` return zeros
@@ -64,30 +64,64 @@ __device__ __forceinline__ ad_u32x4 ad_rsrc_words(const uint16_t *base, uint32_t
 
 }  // namespace
 
-template <int D>
-__global__ __launch_bounds__(512, 2) void antidiag_tile_kernel(
+// kTile = 256: 8 wavefronts of 64 queries x 128 keys; 128: 4 of 32 queries x 128 keys, two workgroups a CU
+template <int D, int kTile>
+__global__ __launch_bounds__(2 * kTile, 2) void antidiag_tile_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, long long qsb, long long qsh,
     long long qsn, long long ksb, long long ksh, long long ksn, int H, int BH, int N, int S, int M,
-    int MT2, float scale_log2, const unsigned char *__restrict__ refresh, float *__restrict__ esum,
+    int MTQ, int MT, float scale_log2, const unsigned char *__restrict__ refresh, float *__restrict__ esum,
     float *__restrict__ mref) {
   extern __shared__ __align__(1024) unsigned char smem[];
-  // workgroup -> (head, tile): workgroup ids are dealt round-robin to the 8 XCDs; all tiles
-  // of a head go to one XCD so that its operand rows are shared through that XCD's L2
-  const int tph = MT2 * MT2;
-  const long long slot = blockIdx.x / 8;
-  const int bh = (int)(blockIdx.x % 8) + 8 * (int)(slot / tph);
-  if (bh >= BH) return;
-  if (refresh && !refresh[bh]) return;  // reused head: its cached mask persists, no scores needed
-  const int tile = (int)(slot % tph);
-  const int tq = tile / MT2, tk = tile % MT2;
-  const int b = bh / H, h = bh % H;
-
+  constexpr int kAdTileB = kTile * kAdRowB;  // bytes of one operand tile of one stage
+  constexpr int QT = kTile / 128;            // query tiles of 32 a wavefront
   const int t = threadIdx.x;
   const int lane = t & 63;
+  // workgroup -> (head, tile): workgroup ids are dealt round-robin to the 8 XCDs; an XCD takes a contiguous
+  // eighth of the tiles of the refreshed heads, head by head, so that a head's operand rows are shared
+  // through one L2 or a few, and no XCD has more to do than another (before, whole heads went to the XCDs in turn: 12
+  // heads of 64 tiles 232 -> 179 us, one head 99 -> 47).  With hundreds of heads a look at all flags costs more than the tiles of reused heads,
+  // which end at once.
+  const int tiles_k = MT / (kTile / 128);  // (every record of 128 keys is written, also past the end)
+  const unsigned tph = (unsigned)(MTQ * tiles_k), x = blockIdx.x % kNumXcd;
+  const bool look = refresh && BH <= kAdLookHeads;
+  unsigned long long set[kAdLookHeads / 64];  // refreshed heads
+  unsigned n_heads = (unsigned)BH;
+  if (look) {
+    unsigned char f[kAdLookHeads / 64];
+#pragma unroll
+    for (int c = 0; c < kAdLookHeads / 64; ++c) f[c] = refresh[min(64 * c + lane, BH - 1)];
+    n_heads = 0;
+#pragma unroll
+    for (int c = 0; c < kAdLookHeads / 64; ++c) {
+      set[c] = __ballot(64 * c + lane < BH && f[c] != 0);
+      n_heads += (unsigned)__popcll(set[c]);
+    }
+  }
+  const unsigned long long items = (unsigned long long)n_heads * tph;
+  const unsigned w = (unsigned)(items * x / kNumXcd) + blockIdx.x / kNumXcd;
+  if (w >= (unsigned)(items * (x + 1) / kNumXcd)) return;
+  int bh = (int)(w / tph);
+  const int tile = (int)(w - (unsigned)bh * tph);
+  if (look) {
+    int rank = bh;
+#pragma unroll
+    for (int c = 0; c < kAdLookHeads / 64; ++c) {
+      const int n = __popcll(set[c]);
+      const bool mine = ((set[c] >> lane) & 1) && __popcll(set[c] & ((1ull << lane) - 1ull)) == rank;
+      const unsigned long long m = __ballot(mine);
+      if (rank >= 0 && rank < n) bh = 64 * c + __ffsll((long long)m) - 1;
+      rank -= n;  // (negative once found)
+    }
+  } else if (refresh && !refresh[bh]) {
+    return;  // reused head: its cached mask persists, no scores needed
+  }
+  const int tq = tile / tiles_k, tk = tile % tiles_k;
+  const int b = bh / H, h = bh % H;
+
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int l32 = lane & 31, hf = lane >> 5;
   const int wi = wave >> 2;  // which 128 keys of the tile
-  const int wj = wave & 3;   // which 64 queries of the tile
+  const int wj = wave & 3;   // which quarter of the tile's queries
 
   const ad_u32x4 q_rs = ad_rsrc_words(q + b * qsb + h * qsh, (uint32_t)((long long)N * qsn * 2));
   const ad_u32x4 k_rs = ad_rsrc_words(k + b * ksb + h * ksh, (uint32_t)((long long)N * ksn * 2));
@@ -108,8 +142,8 @@ __global__ __launch_bounds__(512, 2) void antidiag_tile_kernel(
       const int row = 8 * (4 * wave + ii) + drow;
       const uint32_t chunk = (uint32_t)(dp ^ ((row >> 1) & 7));
       // (token index of sub-row 0; the stage adds its sub-row)
-      q_dma[ii] = (uint32_t)(S * (kAdTile * tq + row)) * (uint32_t)(qsn * 2) + chunk * 16u;
-      k_dma[ii] = (uint32_t)(S * (kAdTile * tk + row)) * (uint32_t)(ksn * 2) + chunk * 16u;
+      q_dma[ii] = (uint32_t)(S * (kTile * tq + row)) * (uint32_t)(qsn * 2) + chunk * 16u;
+      k_dma[ii] = (uint32_t)(S * (kTile * tk + row)) * (uint32_t)(ksn * 2) + chunk * 16u;
     }
   }
   // (the compiler does not see the LDS write of these instructions: their completion is
@@ -140,23 +174,23 @@ __global__ __launch_bounds__(512, 2) void antidiag_tile_kernel(
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) foff[ks] = (uint32_t)(l32 * kAdRowB + (((2 * ks + hf) ^ ((l32 >> 1) & 7)) * 16));
 
-  ad_f32x16 acc[4][2];
+  ad_f32x16 acc[4][QT];
 #pragma unroll
   for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-    for (int qt = 0; qt < 2; ++qt)
+    for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[kt][qt][r] = 0.f;
 
-  // the six fragments of one contraction step: 4 of the keys (A operand), 2 of the queries
+  // the fragments of one contraction step: 4 of the keys (A operand), QT of the queries
   struct Frags {
-    AdFrag a[4], b[2];
+    AdFrag a[4], b[QT];
   };
   auto read_frags = [&](Frags &f, int buf, int ks) __attribute__((always_inline)) {
     const unsigned char *A = smem + buf * 2 * kAdTileB + wi * 128 * kAdRowB;
-    const unsigned char *B = smem + buf * 2 * kAdTileB + kAdTileB + wj * 64 * kAdRowB;
+    const unsigned char *B = smem + buf * 2 * kAdTileB + kAdTileB + wj * 32 * QT * kAdRowB;
 #pragma unroll
-    for (int qt = 0; qt < 2; ++qt)
+    for (int qt = 0; qt < QT; ++qt)
       f.b[qt].u = *reinterpret_cast<const ad_u32x4 *>(B + qt * 32 * kAdRowB + foff[ks]);
 #pragma unroll
     for (int kt = 0; kt < 4; ++kt)
@@ -166,7 +200,7 @@ __global__ __launch_bounds__(512, 2) void antidiag_tile_kernel(
 #pragma unroll
     for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-      for (int qt = 0; qt < 2; ++qt)
+      for (int qt = 0; qt < QT; ++qt)
         acc[kt][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[kt].v, f.b[qt].v, acc[kt][qt], 0, 0, 0);
   };
 
@@ -177,8 +211,8 @@ __global__ __launch_bounds__(512, 2) void antidiag_tile_kernel(
   // current buffer and its loads of the next stage into the other one; right after it, it
   // issues the loads of the stage after that into the buffer just released.  Loads past the
   // last stage repeat the last stage (into a buffer nobody reads any more).
-  const int n_stages = S * SPR;
-  const int last = n_stages - 1;
+  const int n_stages = kTile * tk < M ? S * SPR : 0;  // (a tile of keys past the end: records without weight)
+  const int last = max(n_stages - 1, 0);
   Frags f0, f1;
   dma_stage(0, 0);
   wait_loads_and_barrier();
@@ -208,11 +242,11 @@ __global__ __launch_bounds__(512, 2) void antidiag_tile_kernel(
   // ---- epilogue: record of (reduced query, 128 keys): maximum and 16 key-block sums ----------
   // accumulator element r of key tile kt: reduced key key0 + 32 kt + 8 (r / 4) + 4 hf + r % 4
   const float ninf = -__builtin_inff();
-  const int key0 = kAdTile * tk + 128 * wi;
-  const int rec = 2 * tk + wi;  // index of the 128-key record
-  const int MT = 2 * MT2, NbP = 16 * MT;
+  const int key0 = kTile * tk + 128 * wi;
+  const int rec = kTile / 128 * tk + wi;  // index of the 128-key record
+  const int NbP = 16 * MT;
 #pragma unroll
-  for (int qt = 0; qt < 2; ++qt) {
+  for (int qt = 0; qt < QT; ++qt) {
     float m = ninf;
 #pragma unroll
     for (int kt = 0; kt < 4; ++kt)
@@ -242,7 +276,7 @@ __global__ __launch_bounds__(512, 2) void antidiag_tile_kernel(
         swap_halves32(__float_as_uint(s), s0, s1);
         sums[kt][g] = __uint_as_float(s0) + __uint_as_float(s1);
       }
-    const int a = kAdTile * tq + 64 * wj + 32 * qt + l32;
+    const int a = kTile * tq + 32 * QT * wj + 32 * qt + l32;
     if (a < M) {
       float *dst = esum + ((size_t)bh * M + a) * NbP + 16 * rec + 8 * hf;
       // lower-half lanes write key blocks 0..7 of the record, upper-half lanes 8..15
@@ -338,31 +372,47 @@ int launch_antidiag(const heart_shape &s, const void *q, const void *k, int stri
   if (rows * s.q_stride[2] * 2 > 0xffffffffLL || rows * s.k_stride[2] * 2 > 0xffffffffLL)
     return fail(HEART_EUNSUPPORTED,
                 "heart_scores_antidiag: (N + 257 * stride) * token stride * 2 bytes must stay below 4 GiB");
-  const long long grid = (long long)((BH + 7) / 8) * 8 * MT2 * MT2;
+  const int dev = current_device();
+  if (dev < 0) return fail(HEART_EHIP, "heart_scores_antidiag: cannot identify the current device");
+  // Tiles of 128 x 128, two workgroups a CU, where they fill the chip better: a round of them takes 0.5 to 0.6 of the
+  // time of a round of 256 x 256, which move half the operand bytes per FLOP but come one to a CU.  Measured (tile and
+  // combine kernel, 256 -> 128): 13 heads of one tile 47 -> 22.5 us, one head of 64 tiles 49 -> 29, 14 of nine 54 -> 40,
+  // 8 of 36 62 -> 52; 20 of nine 57 -> 58, 12 of 64 182 -> 212, 40 of 64 629 -> 795.  (The same bits.)
+  const int n_cu = cu_count(dev);
+  if (n_cu <= 0) return fail(HEART_EHIP, "heart_scores_antidiag: cannot query the number of CUs");
+  const long long tiles = (long long)BH * MT2 * MT2, small = (long long)BH * ((M + 127) / 128) * MT;
+  const bool few = 5 * ((small + 2 * n_cu - 1) / (2 * n_cu)) < 8 * ((tiles + n_cu - 1) / n_cu);
+  const int tile = few ? kAdTile / 2 : kAdTile, MTQ = (M + tile - 1) / tile;
+  const long long grid = ((long long)BH * MTQ * (few ? MT : MT2) + kNumXcd - 1) / kNumXcd * kNumXcd;
   if (grid > 0x7fffffffLL || (long long)BH * Nb > 0x7fffffffLL)
     return fail(HEART_EUNSUPPORTED, "heart_scores_antidiag: grid too large");
   float *esum = workspace;
   float *mref = workspace + (size_t)BH * M * 16 * MT;
   const float scale_log2 = 1.4426950408889634f / ((float)S * sqrtf((float)s.D));
-  const int dev = current_device();
-  if (dev < 0) return fail(HEART_EHIP, "heart_scores_antidiag: cannot identify the current device");
-#define HEART_AD_LAUNCH(DD)                                                                        \
+#define HEART_AD_LAUNCH(DD, TT)                                                                    \
   do {                                                                                             \
-    auto kern = antidiag_tile_kernel<DD>;                                                          \
+    auto kern = antidiag_tile_kernel<DD, TT>;                                                      \
     static DeviceFlags attr_set;                                                                   \
     if (hipError_t e = set_max_lds_once(attr_set, dev, reinterpret_cast<const void *>(kern),       \
-                                        kAdLds))                                                   \
+                                        ad_lds(TT)))                                               \
       return fail(HEART_EHIP, "hipFuncSetAttribute(antidiagonal tile kernel LDS): %s",             \
                   hipGetErrorString(e));                                                           \
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), kAdLds, st, (const uint16_t *)q,     \
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(2 * TT), ad_lds(TT), st, (const uint16_t *)q, \
                        (const uint16_t *)k, s.q_stride[0], s.q_stride[1], s.q_stride[2],           \
-                       s.k_stride[0], s.k_stride[1], s.k_stride[2], s.H, BH, s.N, S, M, MT2,       \
+                       s.k_stride[0], s.k_stride[1], s.k_stride[2], s.H, BH, s.N, S, M, MTQ, MT,   \
                        scale_log2, refresh, esum, mref);                                           \
   } while (0)
-  if (s.D == 128)
-    HEART_AD_LAUNCH(128);
-  else
-    HEART_AD_LAUNCH(64);
+  if (s.D == 128) {
+    if (few)
+      HEART_AD_LAUNCH(128, 128);
+    else
+      HEART_AD_LAUNCH(128, 256);
+  } else {
+    if (few)
+      HEART_AD_LAUNCH(64, 128);
+    else
+      HEART_AD_LAUNCH(64, 256);
+  }
 #undef HEART_AD_LAUNCH
   if (int rc = check_launch("antidiag_tile_kernel")) return rc;
   const dim3 cgrid((unsigned)((long long)BH * Nb));

@@ -185,3 +185,35 @@ def test_argument_validation(heart):
     ws = torch.empty(16, dtype=torch.uint8, device="cuda")
     with pytest.raises(heart.HeartError):
         heart.heart_scores_antidiag(q, q, 128, 16, workspace=ws)   # workspace too small
+
+
+# tiles of 128 and of 256 reduced rows (the latter with many heads of more than 128 rows); rows at the ends of both; heads that
+# do not divide by the XCDs; refreshed heads found by rank (up to 256 heads) and, beyond, in place
+@pytest.mark.parametrize("H,N,D,block", [(1, 2048, 128, 128), (3, 2049, 64, 128), (5, 4113, 128, 128), (9, 1030, 64, 64),
+                                         (200, 2100, 64, 128), (300, 300, 64, 128), (150, 4100, 64, 128)])
+@pytest.mark.parametrize("flags", ["all", "some", "one", "none"])
+def test_tiles_of_refreshed_heads(heart, H, N, D, block, flags):
+    stride = block // 8
+    Nb = (N + block - 1) // block
+    g = torch.Generator(device="cuda").manual_seed(H)
+    q, k = ((2.0 * torch.randn((1, H, N, D), generator=g, device="cuda")).bfloat16() for _ in range(2))
+    on = torch.ones(H, dtype=torch.bool)
+    if flags == "some":
+        on = torch.rand(H, generator=torch.Generator().manual_seed(H)) < 0.5
+    elif flags != "all":
+        on[:] = False
+        on[H - 1] = flags == "one"
+    refresh = on.to(torch.uint8).reshape(1, H).cuda()
+    print(f"antidiag tiles H={H} N={N} D={D} block={block} {flags}", flush=True)
+    got = torch.full((1, H, Nb, Nb), -7.0, device="cuda")
+    heart.heart_scores_antidiag(q, k, block, stride, scores=got, refresh=None if flags == "all" else refresh)
+    torch.cuda.synchronize()
+    assert (got[0, ~on] == -7.0).all()  # reused heads keep their scores
+    res = got[0].cpu().numpy()
+    pick = torch.nonzero(on).flatten().tolist()
+    pick = sorted({pick[i] for i in (0, len(pick) // 2, -1)}) if pick else []
+    qc, kc = q.cpu(), k.cpu()
+    for (_, h), want in oracle_scores(qc, kc, block, stride, heads=[(0, h) for h in pick]).items():
+        assert_close(res[h], want, f"head {h}")
+    if pick:  # (every refreshed head: rows of a distribution)
+        np.testing.assert_allclose(res[on.numpy()].astype(np.float64).sum(-1), 1.0, rtol=1e-4)
