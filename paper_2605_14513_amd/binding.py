@@ -426,8 +426,11 @@ def heart_ebc_band_error(err, dense, weights=(1.0, 0.5, 0.01, 0.01), epsilon: fl
         workspace = torch.empty(need, dtype=torch.uint8, device=err.device)
     if out is None:
         out = torch.empty(6, dtype=torch.float64, device=err.device)
-    w0, w1, w2, w3 = weights
-    rc = native.ebc_band_error(err, dense, w0, w1, w2, w3, epsilon, workspace, out, _stream())
+    w = [float(x) for x in weights]
+    if len(w) > 4:
+        raise IndexError("more than four weights")
+    w += [0.0] * (4 - len(w))  # (bands that are not named do not count)
+    rc = native.ebc_band_error(err, dense, *w, epsilon, workspace, out, _stream())
     if rc:
         _check("heart_ebc_band_error", rc)
     return out

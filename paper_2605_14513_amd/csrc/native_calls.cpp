@@ -107,6 +107,11 @@ int integer32(PyObject *o) {
   if (v > INT_MAX || v < INT_MIN) value_error("integer argument out of range");
   return (int)v;
 }
+// tokens per block: a whole number, not one with a fraction cut off
+long block_of(PyObject *o) {
+  if (!PyIndex_Check(o)) type_error("block must be an integer");
+  return integer(o);
+}
 double real(PyObject *o) {
   const double v = PyFloat_AsDouble(o);
   if (v == -1.0 && PyErr_Occurred()) throw python_error();
@@ -137,7 +142,7 @@ PyObject *pool_drift(PyObject *, PyObject *const *a, Py_ssize_t n) {
   check_count(n, 18);
   const Tensor &q = some(a[0], "q"), &k = some(a[1], "k");
   if (q.sizes() != k.sizes()) value_error("q and k must have the same shape");
-  const heart_shape s = shape_of(q, k, integer(a[2]));
+  const heart_shape s = shape_of(q, k, block_of(a[2]));
   const int64_t means[3] = {s.B, s.H, s.D}, heads[2] = {s.B, s.H};
   if (some(a[6], "delta").numel() != s.H) value_error("delta must have H entries");
   const char *names[4] = {"qanchor", "kanchor", "qmean", "kmean"};
@@ -155,6 +160,7 @@ PyObject *pool_drift(PyObject *, PyObject *const *a, Py_ssize_t n) {
   float *drift = dev<float>(a[15], "drift");
   const float lo = (float)real(a[8]), hi = (float)real(a[9]);
   const int commit = PyObject_IsTrue(a[10]);
+  if (commit < 0) throw python_error();
   void *st = handle(a[17]);
   return call([&] {
     return heart_pool_drift(&s, qp, kp, qblk, kblk, qmean, kmean, qa, ka, has, delta, lo, hi, commit, drift, refresh, ws,
@@ -204,7 +210,7 @@ PyObject *block_sparse_attn(PyObject *, PyObject *const *a, Py_ssize_t n) {
   check_count(n, 12);
   const Tensor &q = some(a[0], "q"), &k = some(a[1], "k"), &v = some(a[2], "v"), &out = some(a[8], "out");
   if (q.sizes() != k.sizes() || q.sizes() != v.sizes()) value_error("q, k, v must have the same shape");
-  const heart_shape s = shape_of(q, k, integer(a[3]), &v, &out);
+  const heart_shape s = shape_of(q, k, block_of(a[3]), &v, &out);
   const int64_t Nb = blocks(s), square[4] = {s.B, s.H, Nb, Nb}, rows[3] = {s.B, s.H, s.N};
   if (some(a[4], "kept_idx").sizes() != Sizes(square) || some(a[5], "kept_count").sizes() != Sizes(square, 3))
     value_error("kept_idx must be [B,H,Nb,Nb] and kept_count [B,H,Nb]");
@@ -227,7 +233,7 @@ PyObject *scores_antidiag(PyObject *, PyObject *const *a, Py_ssize_t n) {
   check_count(n, 8);
   const Tensor &q = some(a[0], "q"), &k = some(a[1], "k");
   if (q.sizes() != k.sizes()) value_error("q and k must have the same shape");
-  const heart_shape s = shape_of(q, k, integer(a[2]));
+  const heart_shape s = shape_of(q, k, block_of(a[2]));
   const int stride = integer32(a[3]);
   const int64_t Nb = blocks(s), square[4] = {s.B, s.H, Nb, Nb}, heads[2] = {s.B, s.H};
   check_sizes(a[6], "refresh", heads, "refresh must be [B,H]");

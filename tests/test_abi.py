@@ -201,6 +201,21 @@ def test_binding_refuses_cpu_tensors(lib):
                           qmean=torch.zeros(1, 1, 128), kmean=torch.zeros(1, 1, 128))
 
 
+def test_binding_refuses_fractional_blocks(lib):
+    import torch
+
+    from paper_2605_14513_amd import binding
+
+    q, x, native = torch.zeros((1, 1, 128, 128), dtype=torch.bfloat16), torch.zeros(1), binding._native()
+    for block in (128.0, 128.5):
+        with pytest.raises(TypeError, match="block"):
+            native.block_sparse_attn(q, q, q, block, x, x, 0.0, 0, q, None, None, 0)
+        with pytest.raises(TypeError, match="block"):
+            native.pool_drift(q, q, block, x, x, x, x, x, 0.4, 0.8, True, x, x, x, x, x, x, 0)
+        with pytest.raises(TypeError, match="block"):
+            native.scores_antidiag(q, q, block, 16, x, x, None, 0)
+
+
 def test_product_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2605_14513_amd")
     for dirpath, _, files in os.walk(pkg):

@@ -138,3 +138,14 @@ def test_band_error_of_planes(shape):
     # (the bound of test_band_error_at_tile_edges: 64-bit sums of at most 1e6 terms)
     assert np.abs(got[1:5] - want).max() <= 1e-13 * want.sum(), (got[1:5], want)
     assert np.isclose(got[0], eo.band_error(err, dense), rtol=1e-12)
+
+
+def test_band_error_with_fewer_weights():
+    import paper_2605_14513_amd as heart
+
+    rng = np.random.default_rng(3)
+    err, dense = (np_gpu(rng.standard_normal((2, 5, 9, 12)).astype(np.float32)) for _ in range(2))
+    some = heart.heart_ebc_band_error(err, dense, weights=(1.0, 0.5)).cpu().numpy()
+    assert np.array_equal(some, heart.heart_ebc_band_error(err, dense, weights=(1.0, 0.5, 0.0, 0.0)).cpu().numpy())
+    with pytest.raises(IndexError):
+        heart.heart_ebc_band_error(err, dense, weights=(1.0,) * 5)
