@@ -29,8 +29,11 @@ __global__ __launch_bounds__(kThreads) void drift_kernel(
     unsigned char *__restrict__ has_anchor, const float *__restrict__ delta, float gate_lo,
     float gate_hi, int commit, float *__restrict__ drift, unsigned char *__restrict__ refresh) {
   extern __shared__ unsigned char smem[];  // [2 H]: marks, then final decisions
-  drift_workgroup(blockIdx.x, H, D, qmean, kmean, qanchor, kanchor, has_anchor, delta, gate_lo,
-                  gate_hi, commit, drift, refresh, smem);
+  const size_t item = (size_t)blockIdx.x * H * D;
+  DriftAnchors<0> anchors;
+  anchors.load(blockIdx.x, (int)(threadIdx.x >> 6) * kDriftHeadsPerPass, H, D, qanchor, kanchor, has_anchor, delta);
+  drift_workgroup<0, false>(blockIdx.x, H, D, DriftMeans{qmean + item, kmean + item}, anchors, qanchor, kanchor, has_anchor, delta,
+                     gate_lo, gate_hi, commit, drift, refresh, smem);
 }
 
 int launch_drift(int B, int H, int D, const float *qmean, const float *kmean, float *qanchor,

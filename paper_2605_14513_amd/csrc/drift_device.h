@@ -11,51 +11,85 @@ namespace heart {
 constexpr int kDriftMaxSlots = 8;  // D <= 512
 constexpr int kDriftHeadsPerPass = 4;
 
+// Where the token means of a batch item (offset o = h * D + d) come from; the values and the arithmetic are the same.
+struct DriftMeans {  // written before this launch, or by this workgroup
+  const float *q, *k;
+  __device__ __forceinline__ float qm(size_t o) const { return q[o]; }
+  __device__ __forceinline__ float km(size_t o) const { return k[o]; }
+};
+struct DriftMeansAcross {  // written by other workgroups of this launch, possibly on another XCD
+  const float *q, *k;
+  __device__ __forceinline__ float qm(size_t o) const { return __hip_atomic_load(q + o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+  __device__ __forceinline__ float km(size_t o) const { return __hip_atomic_load(k + o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+};
+
+// What the stage reads of a wavefront's heads h0 .. h0 + kDriftHeadsPerPass - 1 that no other workgroup of the launch writes
+// before the stage is over (of heads past the last: the last one's, which is computed and not stored).  All loads are issued
+// unconditionally (the anchor buffers always exist); a head without an anchor ignores the value.
+template <int kSlots>
+struct DriftAnchors {
+  static constexpr int kMost = kSlots ? kSlots : kDriftMaxSlots;
+  float q[kDriftHeadsPerPass][kMost], k[kDriftHeadsPerPass][kMost], delta[kDriftHeadsPerPass];
+  bool has[kDriftHeadsPerPass];
+  __device__ __forceinline__ void load(int b, int h0, int H, int D, const float *qanchor, const float *kanchor,
+                                       const unsigned char *has_anchor, const float *dl) {
+    const int lane = threadIdx.x & 63, slots = kSlots ? kSlots : D > 64 ? D / 64 : 1;
+#pragma unroll
+    for (int u = 0; u < kDriftHeadsPerPass; ++u) {
+      const int h = min(h0 + u, H - 1);
+      const size_t o = ((size_t)b * H + h) * D;
+      has[u] = has_anchor[(size_t)b * H + h] != 0;
+      delta[u] = dl[h];
+#pragma unroll
+      for (int c = 0; c < kMost; ++c) {
+        const int d = lane + 64 * c;
+        q[u][c] = c < slots && d < D ? qanchor[o + d] : 0.f;
+        k[u][c] = c < slots && d < D ? kanchor[o + d] : 0.f;
+      }
+    }
+  }
+};
+
 // lds: 2 H bytes of LDS (marks, then final decisions).  Every lane of the workgroup must
-// call this (it contains workgroup barriers).  kAcross: qmean and kmean were written by other
-// workgroups of the same launch, possibly on another XCD, and are read with device-scope
-// loads (same values, same arithmetic).
-template <bool kAcross = false>
+// call this (it contains workgroup barriers).  kSlots: D / 64 where D is known (64, 128), else 0.  kKeep: where
+// one pass takes all heads, the lanes keep the means that they compared, and the anchors are written from
+// registers instead of after a second pass of loads.  anchors: those of heads 4 * wavefront on, loaded.
+template <int kSlots, bool kKeep, class Means>
 __device__ __forceinline__ void drift_workgroup(
-    int b, int H, int D, const float *qmean, const float *kmean, float *qanchor, float *kanchor,
+    int b, int H, int D, const Means &mean, DriftAnchors<kSlots> &anchors, float *qanchor, float *kanchor,
     unsigned char *has_anchor, const float *delta, float gate_lo, float gate_hi, int commit,
     float *drift, unsigned char *refresh, unsigned char *lds) {
-  unsigned char *mark = lds;     // [H]
+  unsigned char *mark = lds;     // [H]: bit 0 the mark, bit 1 an anchor is there
   unsigned char *fin = lds + H;  // [H]
   __shared__ int n_mark_sh;
 
-  auto cur = [](const float *p) -> float {
-    if constexpr (kAcross)
-      return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else
-      return *p;
-  };
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n_waves = blockDim.x >> 6;
-  const int slots = D > 64 ? D / 64 : 1;
+  const int slots = kSlots ? kSlots : D > 64 ? D / 64 : 1;
+  constexpr int kMost = DriftAnchors<kSlots>::kMost, kKept = kKeep ? kSlots : 1;
+  static_assert(!kKeep || kSlots, "means are kept where D is known");
+  const bool keep = kKeep && H <= n_waves * kDriftHeadsPerPass;
+  float kept_q[kDriftHeadsPerPass][kKept], kept_k[kDriftHeadsPerPass][kKept];
+  const size_t item = (size_t)b * H * D;
 
   // A wavefront takes kDriftHeadsPerPass heads at a time and issues the loads of all of them
   // before it reduces any: the stage is bound by dependent memory round trips, not by bandwidth.
   for (int h0 = wave * kDriftHeadsPerPass; h0 < H; h0 += n_waves * kDriftHeadsPerPass) {
-    float a[kDriftHeadsPerPass][kDriftMaxSlots];
-    bool has[kDriftHeadsPerPass];
-    float dl[kDriftHeadsPerPass];
+    if (h0 >= n_waves * kDriftHeadsPerPass) anchors.load(b, h0, H, D, qanchor, kanchor, has_anchor, delta);
+    float a[kDriftHeadsPerPass][kMost];
 #pragma unroll
     for (int u = 0; u < kDriftHeadsPerPass; ++u) {
-      const int h = min(h0 + u, H - 1);  // (a repeated last head is computed and not stored)
-      const size_t o = ((size_t)b * H + h) * D;
-      // all loads are issued unconditionally (the anchor buffers always exist); a head
-      // without an anchor ignores the value
-      has[u] = has_anchor[(size_t)b * H + h] != 0;
-      dl[u] = delta[h];
+      const size_t o = (size_t)min(h0 + u, H - 1) * D;
 #pragma unroll
-      for (int c = 0; c < kDriftMaxSlots; ++c) {
+      for (int c = 0; c < kMost; ++c) {
         a[u][c] = 0.f;
         const int d = lane + 64 * c;
         if (c < slots && d < D) {
-          const float dq = fabsf(qanchor[o + d] - cur(qmean + o + d));
-          const float dk = fabsf(kanchor[o + d] - cur(kmean + o + d));
+          const float qv = mean.qm(o + d), kv = mean.km(o + d);
+          const float dq = fabsf(anchors.q[u][c] - qv);
+          const float dk = fabsf(anchors.k[u][c] - kv);
           a[u][c] = dq + dk;
+          if (kKeep) kept_q[u][c < kKept ? c : 0] = qv, kept_k[u][c < kKept ? c : 0] = kv;
         }
       }
     }
@@ -64,10 +98,10 @@ __device__ __forceinline__ void drift_workgroup(
       const int h = h0 + u;
       // steps with s >= 64: a[i] += a[i+s]  <=>  slot c += slot c + s/64
 #pragma unroll
-      for (int s = kDriftMaxSlots / 2; s >= 1; s >>= 1) {
+      for (int s = kMost / 2; s >= 1; s >>= 1) {
         if (s < slots) {
 #pragma unroll
-          for (int c = 0; c < kDriftMaxSlots / 2; ++c)
+          for (int c = 0; c < kMost / 2; ++c)
             if (c < s) a[u][c] = a[u][c] + a[u][c + s];
         }
       }
@@ -79,16 +113,16 @@ __device__ __forceinline__ void drift_workgroup(
         if (s < D) v = v + o2;
       }
       if (lane == 0 && h < H) {
-        float dv = has[u] ? v : __builtin_inff();
+        float dv = anchors.has[u] ? v : __builtin_inff();
         drift[(size_t)b * H + h] = dv;
-        mark[h] = (!has[u] || dv > dl[u]) ? 1 : 0;
+        mark[h] = ((!anchors.has[u] || dv > anchors.delta[u]) ? 1 : 0) | (anchors.has[u] ? 2 : 0);
       }
     }
   }
   __syncthreads();
   if (wave == 0) {
     uint32_t n = 0;
-    for (int h = lane; h < H; h += 64) n += mark[h];
+    for (int h = lane; h < H; h += 64) n += mark[h] & 1;
     n = wave_sum_u32(n);
     if (lane == 0) n_mark_sh = (int)n;
   }
@@ -97,16 +131,28 @@ __device__ __forceinline__ void drift_workgroup(
   for (int h = threadIdx.x; h < H; h += blockDim.x) {
     unsigned char r;
     if (frac < gate_lo)
-      r = has_anchor[(size_t)b * H + h] ? 0 : 1;
+      r = mark[h] & 2 ? 0 : 1;
     else if (frac > gate_hi)
       r = 1;
     else
-      r = mark[h];
+      r = mark[h] & 1;
     fin[h] = r;
     refresh[(size_t)b * H + h] = r;
   }
   __syncthreads();
-  if (commit) {
+  if (commit && keep) {
+#pragma unroll
+    for (int u = 0; u < kDriftHeadsPerPass; ++u) {
+      const int h = wave * kDriftHeadsPerPass + u;
+      if (h < H && fin[h]) {
+#pragma unroll
+        for (int c = 0; c < kKept; ++c) {
+          qanchor[item + (size_t)h * D + lane + 64 * c] = kept_q[u][c];
+          kanchor[item + (size_t)h * D + lane + 64 * c] = kept_k[u][c];
+        }
+      }
+    }
+  } else if (commit) {
     // (a lane loads its elements of a batch of passes before it stores any: the loads are
     // independent round trips, the stores conditional on the head's decision)
     constexpr int kBatch = 4;
@@ -116,23 +162,22 @@ __device__ __forceinline__ void drift_workgroup(
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
         const int e = min(e0 + u * (int)blockDim.x, n - 1);
-        const size_t o = (size_t)b * n + e;
-        qv[u] = cur(qmean + o);
-        kv[u] = cur(kmean + o);
+        qv[u] = mean.qm(e);
+        kv[u] = mean.km(e);
       }
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
         const int e = e0 + u * (int)blockDim.x;
         if (e < n && fin[e / D]) {
-          const size_t o = (size_t)b * n + e;
-          qanchor[o] = qv[u];
-          kanchor[o] = kv[u];
+          qanchor[item + e] = qv[u];
+          kanchor[item + e] = kv[u];
         }
       }
     }
+  }
+  if (commit)
     for (int h = threadIdx.x; h < H; h += blockDim.x)
       if (fin[h]) has_anchor[(size_t)b * H + h] = 1;
-  }
 }
 
 }  // namespace heart

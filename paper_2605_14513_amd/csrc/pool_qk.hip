@@ -2,7 +2,7 @@
 // (Alg. 1 step 1 and Eq. 4 for the token means; the block means feed the
 // block-level importance ranking).  heart_pool_drift: the same pass, with the token means,
 // the drift, the reuse rule and the layer gate (Eq. 4; Sec. 4.2; Alg. 1) together in ONE
-// second launch instead of two -- the paper notes that fixed per-layer cost such as kernel
+// second launch instead of two (with few blocks, in the same one) -- the paper notes that fixed per-layer cost such as kernel
 // launches caps what mask reuse can gain (Sec. 4.2, last paragraph).
 //
 // Bound by HBM reads: 2*B*H*N*D*2 bytes in, 2*B*H*(Nb+1)*D*4 bytes out.
@@ -26,7 +26,10 @@
 //   invalidates a whole L2, so the values that cross workgroups (the token means) move with
 //   device-scope atomic stores and loads instead; a workgroup waits for the acknowledgement of
 //   its stores before it takes its ticket.
-//   (Doing the same in the tail of pool_blocks_kernel, one ticket per block, was measured: a
+//   The anchors are written from the registers that were compared instead of after a second pass of
+//   loads (D = 128; 10.2 -> 9.3 us at 40 heads of 256 blocks).
+// pool_drift_small_kernel (heart_pool_drift of few blocks): everything in one launch.
+//   (Doing the same in the tail of pool_blocks_kernel at full size, one ticket per block, was measured: a
 //   device-wide fence per workgroup took the launch from 0.12 to 3.4 ms, device-scope stores
 //   with a ticket per workgroup to 0.23 ms -- under 6 TB/s of reads the store acknowledgement
 //   and the atomic's round trip double the lifetime of a workgroup -- so the pooling pass
@@ -118,33 +121,20 @@ struct PoolDriftArgs {  // what the drift stage needs beyond the token-mean argu
   unsigned *tickets;  // [B]; zero on entry, zero on return
 };
 
-template <int D>
-__global__ __launch_bounds__(kPoolThreads) void pool_blocks_kernel(
-    const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, long long qsb, long long qsh,
-    long long qsn, long long ksb, long long ksh, long long ksn, int H, int N, int block, int Nb,
-    float *__restrict__ qblk, float *__restrict__ kblk) {
+// Mean of one block, by kPoolThreads lanes (`t` = 0 .. kPoolThreads - 1) that all call it, of a head's rows n0 ..
+// n0 + nrows - 1 (at `base`, token stride sn); contains a barrier of the workgroup.  part: LDS, kPoolPart floats.
+// kAcross: dst is read by another workgroup of this launch.  nrows <= 0: no block for these lanes.  also(): called once the
+// loads are on their way.
+constexpr int kPoolPart = kPoolThreads * 8;
+template <int D, bool kAcross, class Also>
+__device__ __forceinline__ void block_mean(const uint16_t *base, int n0, long long sn, int nrows, float *dst, float *part, int t,
+                                           Also also) {
   constexpr int LPR = D / 8;               // lanes per token row
-  constexpr int RPP = kPoolThreads / LPR;  // rows per pass of the workgroup
+  constexpr int RPP = kPoolThreads / LPR;  // rows per pass
   constexpr int MAXP = 128 / RPP;          // passes for the largest block (128 tokens)
-  __shared__ float part[RPP * D];
-
-  // blockIdx.x enumerates (b*H+h, tensor, block) with the block index fastest so
-  // that consecutive workgroups stream consecutive memory.
-  long long wid = blockIdx.x;
-  int i = (int)(wid % Nb);
-  long long rest = wid / Nb;  // = 2 * (b*H+h) + tensor
-  int which = (int)(rest & 1);
-  long long bh = rest >> 1;
-  int b = (int)(bh / H), h = (int)(bh % H);
-
-  const uint16_t *base = which ? (k + b * ksb + h * ksh) : (q + b * qsb + h * qsh);
-  long long sn = which ? ksn : qsn;
-  float *outp = (which ? kblk : qblk) + ((size_t)bh * Nb + i) * D;
-
-  int n0 = i * block;
-  int nrows = min(block, N - n0);
-  int lane_col = (threadIdx.x % LPR) * 8;
-  int row0 = threadIdx.x / LPR;
+  static_assert(RPP * D == kPoolPart, "LDS of the block mean");
+  const int lane_col = (t % LPR) * 8;
+  const int row0 = t / LPR;
 
   uint4 v[MAXP];
 #pragma unroll
@@ -153,11 +143,11 @@ __global__ __launch_bounds__(kPoolThreads) void pool_blocks_kernel(
     v[p] = make_uint4(0u, 0u, 0u, 0u);
     if (r < nrows) {
       // streaming read: every byte is used once by this kernel
-      const u32x4 t = __builtin_nontemporal_load(
-          reinterpret_cast<const u32x4 *>(base + (long long)(n0 + r) * sn + lane_col));
-      v[p] = make_uint4(t.x, t.y, t.z, t.w);
+      const u32x4 x = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(base + (long long)(n0 + r) * sn + lane_col));
+      v[p] = make_uint4(x.x, x.y, x.z, x.w);
     }
   }
+  also();
   float acc[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = 0.f;
@@ -175,12 +165,37 @@ __global__ __launch_bounds__(kPoolThreads) void pool_blocks_kernel(
 #pragma unroll
   for (int e = 0; e < 8; ++e) part[row0 * D + lane_col + e] = acc[e];
   __syncthreads();
-  if (threadIdx.x < D) {
+  if (t < D && nrows > 0) {
     float s = 0.f;
 #pragma unroll
-    for (int r = 0; r < RPP; ++r) s += part[r * D + threadIdx.x];
-    outp[threadIdx.x] = s / (float)nrows;
+    for (int r = 0; r < RPP; ++r) s += part[r * D + t];
+    if constexpr (kAcross)
+      store_device_scope(dst + t, s / (float)nrows);
+    else
+      dst[t] = s / (float)nrows;
   }
+}
+
+template <int D>
+__global__ __launch_bounds__(kPoolThreads) void pool_blocks_kernel(
+    const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, long long qsb, long long qsh,
+    long long qsn, long long ksb, long long ksh, long long ksn, int H, int N, int block, int Nb,
+    float *__restrict__ qblk, float *__restrict__ kblk) {
+  __shared__ float part[kPoolPart];
+
+  // blockIdx.x enumerates (b*H+h, tensor, block) with the block index fastest so
+  // that consecutive workgroups stream consecutive memory.  (Divisions in 32 bits, which hold the
+  // grid: 13.85 -> 13.4 us for heart_pool_drift of two items of 10 heads of 101 blocks of 64.)
+  const unsigned rest = blockIdx.x / (unsigned)Nb;  // = 2 * (b*H+h) + tensor
+  const int i = (int)(blockIdx.x - rest * (unsigned)Nb), which = (int)(rest & 1u);
+  const unsigned bh = rest >> 1;
+  const int b = (int)(bh / (unsigned)H), h = (int)(bh - (unsigned)b * (unsigned)H);
+
+  const uint16_t *base = which ? (k + b * ksb + h * ksh) : (q + b * qsb + h * qsh);
+  long long sn = which ? ksn : qsn;
+  const int n0 = i * block;
+  block_mean<D, false>(base, n0, sn, min(block, N - n0),
+                       (which ? kblk : qblk) + ((size_t)bh * Nb + i) * D, part, (int)threadIdx.x, [] {});
 }
 
 // One workgroup per (tensor, b, h).
@@ -221,11 +236,83 @@ __global__ __launch_bounds__(kMeanThreads) void token_mean_drift_kernel(
   }
   __syncthreads();
   if (!s_last) return;
-  drift_workgroup<true>(b, H, D, qmean, kmean, fa.qanchor, fa.kanchor, fa.has_anchor, fa.delta,
-                        fa.gate_lo, fa.gate_hi, fa.commit, fa.drift, fa.refresh,
-                        reinterpret_cast<unsigned char *>(lds));
+  // (asked for before the block means, by every workgroup: 13.6 -> 14.1 us for a call of two items of 10 heads of 101 blocks)
+  DriftAnchors<D / 64> anchors;
+  anchors.load(b, (int)(threadIdx.x >> 6) * kDriftHeadsPerPass, H, D, fa.qanchor, fa.kanchor, fa.has_anchor, fa.delta);
+  const size_t item = (size_t)b * H * D;
+  // (at D = 64 few lanes would write the kept means: 13.7 -> 13.85 us for that call)
+  drift_workgroup<D / 64, D == 128>(b, H, D, DriftMeansAcross{qmean + item, kmean + item}, anchors, fa.qanchor, fa.kanchor, fa.has_anchor,
+                          fa.delta, fa.gate_lo, fa.gate_hi, fa.commit, fa.drift, fa.refresh,
+                          reinterpret_cast<unsigned char *>(lds));
 }
 
+// All of heart_pool_drift in one launch, for few blocks, where it is bound by launches and by a chain of memory round
+// trips (block, acknowledgement, ticket, block means, result; 7.7 us at two heads of 16 blocks): a workgroup pools kSmallBlocks blocks of a batch item, the
+// last one of the item computes its token means (in block order in fp64 as token_mean_workgroup does, which has at most one
+// block a slice here, so the bits are the same), keeps them in LDS and runs the drift stage.
+constexpr int kSmallBlocks = kMeanThreads / kPoolThreads;
+constexpr int kSmallMeans = kSmallBlocks * kPoolPart;  // token means that fit
+constexpr int kSmallMarks = 2 * kSmallMeans / (2 * 64);
+template <int D>
+__global__ __launch_bounds__(kMeanThreads) void pool_drift_small_kernel(
+    const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, long long qsb, long long qsh, long long qsn,
+    long long ksb, long long ksh, long long ksn, int H, int N, int block, int Nb, int per_item, float *qblk, float *kblk,
+    float *__restrict__ qmean, float *__restrict__ kmean, PoolDriftArgs fa) {
+  __shared__ float lds[kSmallMeans];
+  __shared__ unsigned char marks[kSmallMarks];
+  __shared__ int s_last;
+  const int b = (int)(blockIdx.x / per_item), group = threadIdx.x / kPoolThreads;
+  DriftAnchors<D / 64> anchors;  // (any workgroup may become the one that needs them)
+  {
+    const int p = (int)(blockIdx.x % per_item) * kSmallBlocks + group;  // (h, tensor, block)
+    const int i = p % Nb, which = (p / Nb) & 1, h = p / Nb >> 1, n0 = i * block;
+    const long long sn = which ? ksn : qsn;
+    const uint16_t *base = which ? (k + b * ksb + h * ksh) : (q + b * qsb + h * qsh);
+    block_mean<D, true>(base, n0, sn, h < H ? min(block, N - n0) : 0,
+                        (which ? kblk : qblk) + (((size_t)b * H + h) * Nb + i) * D, lds + group * kPoolPart,
+                        (int)(threadIdx.x % kPoolThreads), [&]() __attribute__((always_inline)) {
+                          anchors.load(b, (int)(threadIdx.x >> 6) * kDriftHeadsPerPass, H, D, fa.qanchor, fa.kanchor,
+                                       fa.has_anchor, fa.delta);
+                        });
+  }
+  wait_for_own_stores();
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned t = atomicAdd(&fa.tickets[b], 1u);
+    s_last = t == (unsigned)per_item - 1u;
+    if (s_last) atomicExch(&fa.tickets[b], 0u);
+  }
+  __syncthreads();
+  if (!s_last) return;
+  const size_t item = (size_t)b * H * D;
+  const int n = H * D;
+  for (int c = threadIdx.x; c < 2 * n; c += kMeanThreads) {
+    const int which = c >= n, o = c - which * n;
+    const float *src = (which ? kblk : qblk) + (item + (size_t)(o / D) * D) * Nb + o % D;
+    double s = 0.0;
+    for (int ib = 0; ib < Nb; ib += kTokenMeanBatch) {
+      float m[kTokenMeanBatch];
+#pragma unroll
+      for (int u = 0; u < kTokenMeanBatch; ++u)
+        m[u] = __hip_atomic_load(src + (size_t)min(ib + u, Nb - 1) * D, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int u = 0; u < kTokenMeanBatch; ++u)
+        if (ib + u < Nb) s += (double)m[u] * (double)min(block, N - (ib + u) * block);
+    }
+    const float mean = (float)(s / (double)N);
+    lds[c] = mean;
+    (which ? kmean : qmean)[item + o] = mean;
+  }
+  __syncthreads();
+  drift_workgroup<D / 64, true>(b, H, D, DriftMeans{lds, lds + n}, anchors, fa.qanchor, fa.kanchor, fa.has_anchor, fa.delta, fa.gate_lo,
+                          fa.gate_hi, fa.commit, fa.drift, fa.refresh, marks);
+}
+
+// Most workgroups of pool_drift_small_kernel for a batch item and in all.  One ticket each, served one after another, and the
+// last workgroup reads every block mean again.  heart_pool_drift in two launches -> in one, calls in a row: 2 workgroups 9.5 ->
+// 7.2 us, 16 9.1 -> 7.2, 32 (64 blocks of one head) 10.2 -> 9.4, 36 10.0 -> 9.7, 40 10.0 -> 8.0, 8 items of 32 13.2 -> 12.7; 64 10.5 -> 10.6,
+// 96 11.0 -> 12.6, 256 13.0 -> 21.8.
+constexpr int kSmallItem = 40, kSmallLaunch = 256;
 template <int D>
 static int launch_pool_t(const heart_shape &s, const uint16_t *qp, const uint16_t *kp, float *qblk,
                          float *kblk, float *qmean, float *kmean, const PoolDriftArgs *fused,
@@ -233,6 +320,15 @@ static int launch_pool_t(const heart_shape &s, const uint16_t *qp, const uint16_
   const int Nb = (s.N + s.block - 1) / s.block;
   const long long nwg = 2LL * s.B * s.H * Nb;
   if (nwg > 0x7fffffffLL) return fail(HEART_EUNSUPPORTED, "heart_pool_qk: grid too large");
+  // few blocks: at most one a slice of the token means, token means that fit the LDS
+  const long long per_item = (2LL * s.H * Nb + kSmallBlocks - 1) / kSmallBlocks;
+  if (fused && Nb <= kMeanThreads / (D / 4) && 2 * s.H * D <= kSmallMeans && per_item <= kSmallItem &&
+      s.B * per_item <= kSmallLaunch) {
+    hipLaunchKernelGGL(pool_drift_small_kernel<D>, dim3((unsigned)(s.B * per_item)), dim3(kMeanThreads), 0, st, qp, kp,
+                       s.q_stride[0], s.q_stride[1], s.q_stride[2], s.k_stride[0], s.k_stride[1], s.k_stride[2], s.H, s.N,
+                       s.block, Nb, (int)per_item, qblk, kblk, qmean, kmean, *fused);
+    return check_launch("pool_drift_small_kernel");
+  }
   const dim3 grid((unsigned)nwg), blk(kPoolThreads), grid2((unsigned)(2 * s.B * s.H)), blk2(kMeanThreads);
   hipLaunchKernelGGL(pool_blocks_kernel<D>, grid, blk, 0, st, qp, kp, s.q_stride[0], s.q_stride[1],
                      s.q_stride[2], s.k_stride[0], s.k_stride[1], s.k_stride[2], s.H, s.N, s.block,

@@ -194,6 +194,35 @@ def test_pool_drift_equals_the_two_calls(heart, name, gate):
         assert_means_close(fq, oqb, amax, "q block means")
 
 
+# one launch and two: a single block of one token; the most workgroups of one launch (40) and one more; the most blocks a
+# head (32 at D = 128, 64 at 64) and one more; the most heads (32, 64) and one more, where the drift stage takes two passes
+@pytest.mark.parametrize("B,H,Nb,D,block,tail", [(1, 1, 1, 64, 64, 63), (2, 5, 16, 128, 128, 3), (1, 27, 3, 64, 128, 0),
+                                                 (3, 1, 32, 128, 64, 1), (3, 1, 33, 128, 64, 1), (1, 1, 64, 64, 128, 100),
+                                                 (1, 1, 65, 64, 64, 0), (1, 32, 2, 128, 128, 17), (2, 33, 2, 128, 128, 17),
+                                                 (1, 64, 1, 64, 64, 2), (2, 70, 1, 64, 64, 2)])
+def test_pool_drift_of_few_blocks(heart, B, H, Nb, D, block, tail):
+    N = Nb * block - tail
+    g = torch.Generator(device="cuda").manual_seed(H * Nb)
+    state = [[torch.zeros((B, H, D), device="cuda"), torch.zeros((B, H, D), device="cuda"),
+              torch.zeros((B, H), dtype=torch.uint8, device="cuda")] for _ in range(2)]
+    ws = torch.zeros(heart.heart_pool_drift_workspace_bytes(B, H), dtype=torch.uint8, device="cuda")
+    base = torch.randn((2, B, N, H, D), generator=g, device="cuda")
+    delta = torch.full((H,), 2.0, device="cuda")
+    for step in range(3):
+        print(f"pool+drift B={B} H={H} Nb={Nb} D={D} block={block} step {step}", flush=True)
+        if step:  # about half of the heads move
+            base += (torch.rand((H, 1), generator=g, device="cuda") < 0.5) * (4.0 / D)
+        q, k = (x.bfloat16().transpose(1, 2) for x in base)
+        a, f = state
+        qblk, kblk, qmean, kmean = heart.heart_pool_qk(q, k, block)
+        d, r = heart.heart_drift(qmean, kmean, *a, delta, 0.1, 0.9)
+        got = heart.heart_pool_drift(q, k, block, *f, delta, ws, 0.1, 0.9)
+        torch.cuda.synchronize()
+        for x, y in zip([*got, *f], [qblk, kblk, qmean, kmean, d, r, *a]):
+            assert torch.equal(x, y)
+        assert not ws.any().item()
+
+
 def test_pool_drift_commit_off_and_validation(heart):
     g, st = case("small_d64")
     cfg = g.cfg
