@@ -503,9 +503,11 @@ __global__ __launch_bounds__(kEbcThreads, SY > 8 ? 3 : 4) void ebc_plane_kernel(
 #pragma unroll
       for (int m = 0; m < M; ++m) {
         const int ky = 16 * m + l16;
-        const double w = ky >= KY ? 0.0 : ky > 0 ? 2.0 * wx : wx;
+        const double w = ky > 0 ? 2.0 * wx : wx;
+        // (coefficients past KY are left out, not weighted with 0: they are infinite with an infinite element; rows past T are zero)
+        if (ky < KY)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) s_xy = fma(w * acc[m][r], acc[m][r], s_xy);  // (rows past T are zero)
+          for (int r = 0; r < 4; ++r) s_xy = fma(w * acc[m][r], acc[m][r], s_xy);
       }
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
@@ -528,14 +530,14 @@ __global__ __launch_bounds__(kEbcThreads, SY > 8 ? 3 : 4) void ebc_plane_kernel(
 #pragma unroll
     for (int m = 0; m < M; ++m) {
       const int ky = 16 * m + l16;
-      const double w = ky >= KY ? 0.0 : ky > 0 ? 2.0 * wx : wx;
+      const double w = ky > 0 ? 2.0 * wx : wx;
 #pragma unroll
       for (int q = 0; q < 2; ++q)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int kt = 16 * q + g + 4 * r;
           const double v = acc2[m][q][r];
-          if (kt < KT) s_xyt = fma((kt > 0 ? 2.0 : 1.0) * w * v, v, s_xyt);
+          if (ky < KY && kt < KT) s_xyt = fma((kt > 0 ? 2.0 : 1.0) * w * v, v, s_xyt);
         }
     }
   }

@@ -149,3 +149,19 @@ def test_band_error_with_fewer_weights():
     assert np.array_equal(some, heart.heart_ebc_band_error(err, dense, weights=(1.0, 0.5, 0.0, 0.0)).cpu().numpy())
     with pytest.raises(IndexError):
         heart.heart_ebc_band_error(err, dense, weights=(1.0,) * 5)
+
+
+# an infinite element makes every low coefficient infinite (axes of prime length: no table entry is zero but the first), and with
+# them their weighted sum of squares; y and t contracted in one launch, and in two
+@pytest.mark.parametrize("shape", [(2, 5, 7, 11), (1, 17, 47, 5), (1, 5, 67, 11)])
+def test_band_error_with_an_infinity(shape):
+    import paper_2605_14513_amd as heart
+
+    rng = np.random.default_rng(sum(shape))
+    err, dense = (rng.standard_normal(shape).astype(np.float32) for _ in range(2))
+    err[0, 2, 3, 4] = np.inf
+    print("ebc inf", shape, flush=True)
+    got = heart.heart_ebc_band_error(np_gpu(err), np_gpu(dense)).cpu().numpy()
+    assert np.isposinf(got[1]), got
+    # the other bands are differences of infinite sums
+    assert np.isnan(got[[0, 2, 3, 4]]).all() and np.isfinite(got[5]), got
