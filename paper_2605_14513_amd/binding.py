@@ -179,6 +179,10 @@ def heart_pool_qk(q: torch.Tensor, k: torch.Tensor, block: int, qblk=None, kblk=
     kblk = torch.empty((B, H, Nb, D), **f32) if kblk is None else kblk
     qmean = torch.empty((B, H, D), **f32) if qmean is None else qmean
     kmean = torch.empty((B, H, D), **f32) if kmean is None else kmean
+    for t, n, name in ((qblk, B * H * Nb * D, "qblk must hold [B,H,Nb,D]"), (kblk, B * H * Nb * D, "kblk must hold [B,H,Nb,D]"),
+                       (qmean, B * H * D, "qmean must hold [B,H,D]"), (kmean, B * H * D, "kmean must hold [B,H,D]")):
+        if t.numel() < n:
+            raise ValueError(name)
     shape = make_shape(q, k, block)
     rc = lib.heart_pool_qk(ctypes.byref(shape), _dev(q, torch.bfloat16, "q", False),
                            _dev(k, torch.bfloat16, "k", False), _dev(qblk, torch.float32, "qblk"),

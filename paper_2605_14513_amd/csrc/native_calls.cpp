@@ -64,6 +64,10 @@ void check_sizes(PyObject *o, const char *name, Sizes want, const char *msg) {
   const Tensor *t = tensor(o, name);
   if (t && t->sizes() != want) value_error(msg);
 }
+// `t` is read or written as `n` contiguous elements: fewer would leave it (more are left alone)
+void check_numel(const Tensor *t, int64_t n, const char *msg) {
+  if (t && t->numel() < n) value_error(msg);
+}
 // scratch memory: any type
 void *scratch(PyObject *o, size_t *bytes) {
   const Tensor &t = some(o, "workspace");
@@ -148,6 +152,9 @@ PyObject *pool_drift(PyObject *, PyObject *const *a, Py_ssize_t n) {
   const char *names[4] = {"qanchor", "kanchor", "qmean", "kmean"};
   PyObject *const vecs[4] = {a[3], a[4], a[13], a[14]};
   for (int i = 0; i < 4; ++i) check_sizes(vecs[i], names[i], means, (std::string(names[i]) + " must be [B,H,D]").c_str());
+  const int64_t n_blk = (int64_t)s.B * s.H * blocks(s) * s.D;
+  check_numel(tensor(a[11], "qblk"), n_blk, "qblk must hold [B,H,Nb,D]");
+  check_numel(tensor(a[12], "kblk"), n_blk, "kblk must hold [B,H,Nb,D]");
   PyObject *const flags[3] = {a[5], a[15], a[16]};
   for (PyObject *f : flags) check_sizes(f, "has_anchor, drift, refresh", heads, "has_anchor, drift, refresh must be [B,H]");
   size_t ws_bytes;
@@ -187,6 +194,7 @@ PyObject *mask_topp(PyObject *, PyObject *const *a, Py_ssize_t n) {
   check_sizes(a[11], "scores_out", square, "scores_out must be [B,H,Nb,Nb]");
   check_sizes(a[3], "refresh", heads, "refresh must be [B,H]");
   if (!scores && some(a[1], "kblk").sizes() != Sizes(means)) value_error("kblk must match qblk");
+  check_numel(scores, (int64_t)B * H * Nb * Nb, "scores_in must be [B,H,Nb,Nb]");
   const float *qp = dev<float>(a[0], "qblk"), *kp = dev<float>(a[1], "kblk"), *sp = dev<float>(a[4], "scores_in"),
               *tau = dev<float>(a[2], "tau");
   const unsigned char *refresh = dev<uint8_t>(a[3], "refresh");
@@ -214,6 +222,8 @@ PyObject *block_sparse_attn(PyObject *, PyObject *const *a, Py_ssize_t n) {
   const int64_t Nb = blocks(s), square[4] = {s.B, s.H, Nb, Nb}, rows[3] = {s.B, s.H, s.N};
   if (some(a[4], "kept_idx").sizes() != Sizes(square) || some(a[5], "kept_count").sizes() != Sizes(square, 3))
     value_error("kept_idx must be [B,H,Nb,Nb] and kept_count [B,H,Nb]");
+  for (int i = 0; i < 4; ++i)
+    if (out.size(i) < q.size(i)) value_error("out must hold the [B,H,N,D] of q");
   check_sizes(a[9], "lse", rows, "lse must be [B,H,N]");
   size_t ws_bytes = 0;
   void *ws = a[10] == Py_None ? nullptr : scratch(a[10], &ws_bytes);
@@ -253,6 +263,7 @@ PyObject *ebc_band_error(PyObject *, PyObject *const *a, Py_ssize_t n) {
   check_count(n, 10);
   const Tensor &err = some(a[0], "err"), &dense = some(a[1], "dense"), &w = some(a[7], "workspace");
   if (err.sizes() != dense.sizes() || err.dim() < 3) value_error("err and dense must have the same shape [..., T, Y, X]");
+  check_numel(&some(a[8], "out"), 6, "out must hold six values");
   int axis[3];
   for (int i = 0; i < 3; ++i) {
     if (err.size(i - 3) > INT_MAX) value_error("err is too large");

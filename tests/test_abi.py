@@ -216,6 +216,46 @@ def test_binding_refuses_fractional_blocks(lib):
             native.scores_antidiag(q, q, block, 16, x, x, None, 0)
 
 
+def test_binding_refuses_tensors_that_are_too_small(lib):
+    """What a kernel writes or reads has to be there (sizes are checked before devices are)."""
+    import torch
+
+    from paper_2605_14513_amd import binding
+
+    native = binding._native()
+    B, H, N, D, Nb = 2, 3, 300, 64, 3
+    bf = dict(dtype=torch.bfloat16)
+    q = torch.zeros((B, H, N, D), **bf)
+    idx, cnt = torch.zeros((B, H, Nb, Nb), dtype=torch.int32), torch.zeros((B, H, Nb), dtype=torch.int32)
+
+    def attn(out):
+        native.block_sparse_attn(q, q, q, 128, idx, cnt, 0.0, 0, out, None, None, 0)
+
+    for shape in ((B, H, N - 1, D), (B, H - 1, N, D), (1, H, N, D), (B, H, N, D // 2)):
+        with pytest.raises(ValueError, match="out"):
+            attn(torch.zeros(shape, **bf))
+    with pytest.raises(TypeError, match="GPU"):  # (room for more is no fault: the device is the next one)
+        attn(torch.zeros((B, H, N + 5, D), **bf))
+
+    blk, mean, bh = torch.zeros((B, H, Nb, D)), torch.zeros((B, H, D)), torch.zeros((B, H), dtype=torch.uint8)
+    drift, delta, few = torch.zeros((B, H)), torch.zeros(H), torch.zeros((B, H, Nb - 1, D))
+    for qblk, kblk in ((few, blk), (blk, few)):
+        with pytest.raises(ValueError, match="blk must hold"):
+            native.pool_drift(q, q, 128, mean, mean, bh, delta, bh, 0.4, 0.8, True, qblk, kblk, mean, mean, drift, bh, 0)
+        with pytest.raises(ValueError, match="blk must hold"):
+            binding.heart_pool_qk(q, q, 128, qblk, kblk, mean, mean)
+    for qmean, kmean in ((mean[:1], mean), (mean, mean[:1])):
+        with pytest.raises(ValueError, match="mean must hold"):
+            binding.heart_pool_qk(q, q, 128, blk, blk, qmean, kmean)
+
+    with pytest.raises(ValueError, match="scores_in"):
+        native.mask_topp(None, None, delta, None, torch.zeros((B, H, Nb, Nb - 1)), 0, 0, 1, idx, idx, cnt, None, None, 0)
+
+    x = torch.zeros((2, 3, 4, 5))
+    with pytest.raises(ValueError, match="out"):
+        native.ebc_band_error(x, x, 1.0, 1.0, 1.0, 1.0, 1e-8, x, torch.zeros(5, dtype=torch.float64), 0)
+
+
 def test_product_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2605_14513_amd")
     for dirpath, _, files in os.walk(pkg):
