@@ -82,7 +82,8 @@ void strides(const Tensor &t, const char *name, long long out[3]) {
 }
 heart_shape shape_of(const Tensor &q, const Tensor &k, long block, const Tensor *v = nullptr, const Tensor *o = nullptr) {
   if (q.dim() != 4) value_error("q must be [B,H,N,D] with a contiguous D axis");
-  if (block <= 0 || block > INT_MAX) value_error("block must be positive");
+  if (block == 0) raise(PyExc_ZeroDivisionError, "block must not be zero");
+  if (block > INT_MAX || block < -INT_MAX) value_error("block is too large");  // (negative ones: the library's error)
   for (int i = 0; i < 4; ++i)
     if (q.size(i) > INT_MAX) value_error("q is too large");
   heart_shape s{};
@@ -270,7 +271,8 @@ PyObject *ebc_band_error(PyObject *, PyObject *const *a, Py_ssize_t n) {
     axis[i] = (int)err.size(i - 3);
   }
   const int64_t plane = (int64_t)axis[0] * axis[1] * axis[2];
-  const long long C = plane > 0 ? err.numel() / plane : 0;
+  if (plane == 0) raise(PyExc_ZeroDivisionError, "err has an empty axis");
+  const long long C = err.numel() / plane;
   double weights[4];
   for (int i = 0; i < 4; ++i) weights[i] = real(a[2 + i]);
   const double epsilon = real(a[6]);

@@ -216,6 +216,26 @@ def test_binding_refuses_fractional_blocks(lib):
             native.scores_antidiag(q, q, block, 16, x, x, None, 0)
 
 
+def test_binding_errors_of_empty_divisors(lib):
+    """No blocks of no tokens and no empty axes: the division that counts them raises, as it does in Python."""
+    import torch
+
+    from paper_2605_14513_amd import binding
+
+    q, x, native = torch.zeros((1, 1, 128, 128), dtype=torch.bfloat16), torch.zeros(1), binding._native()
+    with pytest.raises(ZeroDivisionError):
+        native.block_sparse_attn(q, q, q, 0, x, x, 0.0, 0, q, None, None, 0)
+    with pytest.raises(ZeroDivisionError):
+        native.pool_drift(q, q, 0, x, x, x, x, x, 0.4, 0.8, True, x, x, x, x, x, x, 0)
+    with pytest.raises(ZeroDivisionError):
+        native.scores_antidiag(q, q, 0, 16, x, x, None, 0)
+    with pytest.raises(ValueError, match="kept_idx"):  # (no list has a negative number of blocks)
+        native.block_sparse_attn(q, q, q, -128, torch.zeros((1, 1, 1, 1)), torch.zeros((1, 1, 1)), 0.0, 0, q, None, None, 0)
+    e = torch.zeros((2, 0, 4, 5))
+    with pytest.raises(ZeroDivisionError):
+        native.ebc_band_error(e, e, 1.0, 1.0, 1.0, 1.0, 1e-8, x, torch.zeros(6, dtype=torch.float64), 0)
+
+
 def test_binding_refuses_tensors_that_are_too_small(lib):
     """What a kernel writes or reads has to be there (sizes are checked before devices are)."""
     import torch
