@@ -236,8 +236,9 @@ int heart_scores_antidiag(const heart_shape *shape, const void *q, const void *k
  * heart_attn_workspace_bytes is larger (35 MB at most); a workspace of that size then holds no
  * plan but the partial results of up to 16 workgroups per query block, which each take a
  * part of its kept list, and the results are those of the other cases up to rounding (fp32
- * sums in another order, each part with its own reference exponent).  A workspace of
- * heart_attn_balanced_workspace_bytes does the same for more sizes.  The contents need not
+ * sums in another order, each part with its own reference exponent).  workspace_bytes of exactly
+ * heart_attn_balanced_workspace_bytes does the same for more sizes; other larger sizes are as
+ * heart_attn_workspace_bytes.  The contents need not
  * be preserved between calls; two calls that run concurrently must not share a workspace.
  */
 int heart_block_sparse_attn(const heart_shape *shape, const void *q_bf16, const void *k_bf16,
@@ -289,12 +290,13 @@ size_t heart_workspace_bytes(int B, int H, int Nb, int D);
 size_t heart_attn_workspace_bytes(const heart_shape *shape);
 
 /*
- * Bytes with which heart_block_sparse_attn also divides the lists of launches in which a place for a workgroup (two
- * per CU, four at block = 64) works on at most 2 to 2.5 query blocks, so that uneven lists no longer decide when the
- * call ends.  Such a workspace holds no plan but the parts of the query blocks that were divided (71 MB at most), and the
- * results are those of a smaller workspace up to rounding.  Where that does not pay, and for other sizes, the same as
- * heart_attn_workspace_bytes; with dense != 0 (lists that keep every block) it pays less often.  0 for an
- * invalid shape.
+ * The workspace_bytes with which heart_block_sparse_attn also divides the lists of launches in which a place for a workgroup
+ * (two per CU, four at block = 64) works on at most 2 to 2.5 query blocks, so that uneven lists no longer decide when the
+ * call ends.  Exactly this size asks for it (a buffer that is larger is passed with this size).  Such a workspace holds
+ * no plan but the parts of the query blocks that were divided (71 MB at most), and the results are those of another
+ * size up to rounding; where lists are divided, and with it the rounding of a query block, depends on the kept counts of
+ * all heads of the call.  Where dividing does not pay, and for other shapes, the same as heart_attn_workspace_bytes; with
+ * dense != 0 (lists that keep every block) it pays less often.  0 for an invalid shape.
  */
 size_t heart_attn_balanced_workspace_bytes(const heart_shape *shape, int dense);
 

@@ -295,7 +295,7 @@ def heart_attn_workspace_bytes(q, block: int) -> int:
 
 
 def heart_attn_balanced_workspace_bytes(q, block: int, dense: bool = False) -> int:
-    """Bytes with which heart_block_sparse_attn also divides the lists of few rows evenly (dense: of full lists)."""
+    """The workspace size that asks heart_block_sparse_attn to also divide the lists of few rows evenly (dense: full lists)."""
     return int(load_library().heart_attn_balanced_workspace_bytes(ctypes.byref(make_shape(q, q, block)), int(dense)))
 
 
@@ -304,8 +304,8 @@ def heart_block_sparse_attn(q, k, v, block: int, kept_idx, kept_count, scale: fl
     """Block-sparse attention over the kept key blocks; returns bf16 out like q.
 
     workspace: a uint8/int32 GPU tensor of heart_attn_workspace_bytes (at least heart_workspace_bytes;
-    with few query blocks the full size splits their lists, heart_attn_balanced_workspace_bytes divides
-    those of a few rows a workgroup evenly), None (natural launch order), or "auto" (a
+    with few query blocks the full size splits their lists, one of exactly heart_attn_balanced_workspace_bytes
+    divides those of a few rows a workgroup evenly), None (natural launch order), or "auto" (a
     fresh tensor from torch's allocator).
     flags: 0 (heart_block_sparse_attn) or HEART_ATTN_FOLD_SCALE (heart_block_sparse_attn_flags)."""
     native = _native()

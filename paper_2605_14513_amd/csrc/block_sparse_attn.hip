@@ -1199,7 +1199,8 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
   const int BH = s.B * s.H;
   const int n_split = order ? attn_split(BH, Nb, D, BLK) : 1;
   const int n_share = order ? attn_shares(BH, Nb, D, BLK, false) : 0;
-  const bool share = n_share > 0 && order_bytes >= attn_balanced_bytes(BH, Nb, D, BLK, false);
+  // (exactly that size asks for shares: a larger buffer kept for several shapes is one that knows nothing of them)
+  const bool share = n_share > 0 && order_bytes == attn_balanced_bytes(BH, Nb, D, BLK, false);
   const bool split = !share && n_split > 1 && order_bytes >= attn_split_bytes(BH, Nb, D, BLK);
   const size_t lds = 4 * (size_t)kStageRows<D, BLK> * D * 2;  // >= BLK * (D + 8) * 2 of the output staging
   const AttnMode mode = share ? kSharedRows : split ? kSplitRows : kPlanned;

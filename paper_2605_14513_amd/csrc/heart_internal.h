@@ -284,7 +284,7 @@ size_t attn_split_bytes(long long BH, long long Nb, int D, int block);
 // Shares that the kept blocks of all rows are dealt out in (0 = not), and the bytes their parts take.
 int attn_shares(long long BH, long long Nb, int D, int block, bool dense);
 size_t attn_share_bytes(long long BH, long long Nb, int D, int block, bool dense);
-// What a call can use without shares, and with them (always more, so the size says which launch is meant).
+// What a call can use without shares, and the size that asks for them (always more, so it says which launch is meant).
 inline size_t attn_any_bytes(long long BH, long long Nb, int D, int block) {
   const size_t plan = attn_full_plan_bytes(BH, Nb), parts = attn_split_bytes(BH, Nb, D, block);
   return plan > parts ? plan : parts;

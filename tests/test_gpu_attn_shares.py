@@ -60,3 +60,25 @@ def test_shares_of_rows(B, H, Nb, D, block, tail, kind):
         if N * H * B <= 20000 and kind == "uneven" and not flags:
             want = np.nan_to_num(oracle.attn(u16(q.contiguous()), u16(k.contiguous()), u16(v.contiguous()), block, idx, cnt))
             assert np.abs(out.float().cpu().numpy() - want).max() <= 2e-2 * max(1.0, np.abs(want).max() / 2)
+
+
+# only the size that asks for it divides rows: a larger buffer, kept for several shapes, has the launch and the bits of
+# heart_attn_workspace_bytes (the first shape has a plan, the second split rows)
+@pytest.mark.parametrize("H,Nb,D,block", [(7, 67, 128, 128), (1, 200, 128, 64)])
+def test_larger_workspaces_do_not_divide_rows(H, Nb, D, block):
+    import paper_2605_14513_amd as heart
+
+    rng = np.random.default_rng(Nb)
+    cnt = rng.integers(1, Nb // 2, size=(1, H, Nb)).astype(np.int32)
+    idx = np.broadcast_to(np.arange(Nb, dtype=np.int32), (1, H, Nb, Nb)).copy()
+    g = torch.Generator(device="cuda").manual_seed(Nb)
+    q, k, v = (torch.randn((1, H, Nb * block, D), generator=g, device="cuda").bfloat16() for _ in range(3))
+    gi, gc = np_gpu(idx), np_gpu(cnt)
+    asked, usual = heart.heart_attn_balanced_workspace_bytes(q, block), heart.heart_attn_workspace_bytes(q, block)
+    assert asked > usual
+    print(f"H={H} Nb={Nb} D={D} block={block}", flush=True)
+    ws = torch.empty(2 * asked, dtype=torch.uint8, device="cuda")
+    want, divided = (heart.heart_block_sparse_attn(q, k, v, block, gi, gc, workspace=ws[:n]) for n in (usual, asked))
+    assert not torch.equal(divided, want)  # (sums in another order)
+    for n in (asked - 16, asked + 16, 2 * asked):
+        assert torch.equal(heart.heart_block_sparse_attn(q, k, v, block, gi, gc, workspace=ws[:n]), want), n
