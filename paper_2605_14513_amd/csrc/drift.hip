@@ -23,6 +23,7 @@ namespace heart {
 
 constexpr int kThreads = 1024; // 16 wavefronts: 16 heads in flight per pass
 
+template <int kSlots>  // D / 64, or 1
 __global__ __launch_bounds__(kThreads) void drift_kernel(
     int H, int D, const float *__restrict__ qmean, const float *__restrict__ kmean,
     float *__restrict__ qanchor, float *__restrict__ kanchor,
@@ -30,17 +31,17 @@ __global__ __launch_bounds__(kThreads) void drift_kernel(
     float gate_hi, int commit, float *__restrict__ drift, unsigned char *__restrict__ refresh) {
   extern __shared__ unsigned char smem[];  // [2 H]: marks, then final decisions
   const size_t item = (size_t)blockIdx.x * H * D;
-  DriftAnchors<0> anchors;
-  anchors.load(blockIdx.x, (int)(threadIdx.x >> 6) * kDriftHeadsPerPass, H, D, qanchor, kanchor, has_anchor, delta);
-  drift_workgroup<0, false>(blockIdx.x, H, D, DriftMeans{qmean + item, kmean + item}, anchors, qanchor, kanchor, has_anchor, delta,
-                     gate_lo, gate_hi, commit, drift, refresh, smem);
+  DriftAnchors<kSlots> anchors;
+  drift_workgroup<kSlots, false, false>(blockIdx.x, H, D, DriftMeans{qmean + item, kmean + item}, anchors, qanchor, kanchor,
+                                        has_anchor, delta, gate_lo, gate_hi, commit, drift, refresh, smem);
 }
 
 int launch_drift(int B, int H, int D, const float *qmean, const float *kmean, float *qanchor,
                  float *kanchor, unsigned char *has_anchor, const float *delta, float gate_lo,
                  float gate_hi, int commit, float *drift, unsigned char *refresh,
                  hipStream_t st) {
-  hipLaunchKernelGGL(drift_kernel, dim3(B), dim3(kThreads), (size_t)2 * H, st, H, D, qmean,
+  auto kern = D <= 64 ? drift_kernel<1> : D == 128 ? drift_kernel<2> : D == 256 ? drift_kernel<4> : drift_kernel<8>;
+  hipLaunchKernelGGL(kern, dim3(B), dim3(kThreads), (size_t)2 * H, st, H, D, qmean,
                      kmean, qanchor, kanchor, has_anchor, delta, gate_lo, gate_hi, commit, drift,
                      refresh);
   return check_launch("drift_kernel");

@@ -8,7 +8,6 @@
 
 namespace heart {
 
-constexpr int kDriftMaxSlots = 8;  // D <= 512
 constexpr int kDriftHeadsPerPass = 4;
 
 // Where the token means of a batch item (offset o = h * D + d) come from; the values and the arithmetic are the same.
@@ -28,33 +27,35 @@ struct DriftMeansAcross {  // written by other workgroups of this launch, possib
 // unconditionally (the anchor buffers always exist); a head without an anchor ignores the value.
 template <int kSlots>
 struct DriftAnchors {
-  static constexpr int kMost = kSlots ? kSlots : kDriftMaxSlots;
-  float q[kDriftHeadsPerPass][kMost], k[kDriftHeadsPerPass][kMost], delta[kDriftHeadsPerPass];
+  float q[kDriftHeadsPerPass][kSlots], k[kDriftHeadsPerPass][kSlots], delta[kDriftHeadsPerPass];
   bool has[kDriftHeadsPerPass];
+  __device__ __forceinline__ void load_head(int u, int b, int h0, int H, int D, const float *qanchor, const float *kanchor,
+                                            const unsigned char *has_anchor, const float *dl) {
+    const int lane = threadIdx.x & 63, h = min(h0 + u, H - 1);
+    const size_t o = ((size_t)b * H + h) * D;
+    has[u] = has_anchor[(size_t)b * H + h] != 0;
+    delta[u] = dl[h];
+#pragma unroll
+    for (int c = 0; c < kSlots; ++c) {
+      const int d = lane + 64 * c;
+      q[u][c] = d < D ? qanchor[o + d] : 0.f;
+      k[u][c] = d < D ? kanchor[o + d] : 0.f;
+    }
+  }
   __device__ __forceinline__ void load(int b, int h0, int H, int D, const float *qanchor, const float *kanchor,
                                        const unsigned char *has_anchor, const float *dl) {
-    const int lane = threadIdx.x & 63, slots = kSlots ? kSlots : D > 64 ? D / 64 : 1;
 #pragma unroll
-    for (int u = 0; u < kDriftHeadsPerPass; ++u) {
-      const int h = min(h0 + u, H - 1);
-      const size_t o = ((size_t)b * H + h) * D;
-      has[u] = has_anchor[(size_t)b * H + h] != 0;
-      delta[u] = dl[h];
-#pragma unroll
-      for (int c = 0; c < kMost; ++c) {
-        const int d = lane + 64 * c;
-        q[u][c] = c < slots && d < D ? qanchor[o + d] : 0.f;
-        k[u][c] = c < slots && d < D ? kanchor[o + d] : 0.f;
-      }
-    }
+    for (int u = 0; u < kDriftHeadsPerPass; ++u) load_head(u, b, h0, H, D, qanchor, kanchor, has_anchor, dl);
   }
 };
 
 // lds: 2 H bytes of LDS (marks, then final decisions).  Every lane of the workgroup must
-// call this (it contains workgroup barriers).  kSlots: D / 64 where D is known (64, 128), else 0.  kKeep: where
+// call this (it contains workgroup barriers).  kSlots: elements of a lane, D / 64 or 1.  kKeep: where
 // one pass takes all heads, the lanes keep the means that they compared, and the anchors are written from
-// registers instead of after a second pass of loads.  anchors: those of heads 4 * wavefront on, loaded.
-template <int kSlots, bool kKeep, class Means>
+// registers instead of after a second pass of loads.  kLoaded: anchors holds those of heads 4 * wavefront on already.
+// (Loaded ahead where nothing is done meanwhile, and with room for the largest D in every lane, they only cost
+// registers, 67 -> 128 and 24 bytes of scratch a lane: heart_drift of 40 heads of 128 5.9 -> 7.7 us, 5.6 like this.)
+template <int kSlots, bool kKeep, bool kLoaded, class Means>
 __device__ __forceinline__ void drift_workgroup(
     int b, int H, int D, const Means &mean, DriftAnchors<kSlots> &anchors, float *qanchor, float *kanchor,
     unsigned char *has_anchor, const float *delta, float gate_lo, float gate_hi, int commit,
@@ -65,9 +66,7 @@ __device__ __forceinline__ void drift_workgroup(
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n_waves = blockDim.x >> 6;
-  const int slots = kSlots ? kSlots : D > 64 ? D / 64 : 1;
-  constexpr int kMost = DriftAnchors<kSlots>::kMost, kKept = kKeep ? kSlots : 1;
-  static_assert(!kKeep || kSlots, "means are kept where D is known");
+  constexpr int kKept = kKeep ? kSlots : 1;
   const bool keep = kKeep && H <= n_waves * kDriftHeadsPerPass;
   float kept_q[kDriftHeadsPerPass][kKept], kept_k[kDriftHeadsPerPass][kKept];
   const size_t item = (size_t)b * H * D;
@@ -75,16 +74,17 @@ __device__ __forceinline__ void drift_workgroup(
   // A wavefront takes kDriftHeadsPerPass heads at a time and issues the loads of all of them
   // before it reduces any: the stage is bound by dependent memory round trips, not by bandwidth.
   for (int h0 = wave * kDriftHeadsPerPass; h0 < H; h0 += n_waves * kDriftHeadsPerPass) {
-    if (h0 >= n_waves * kDriftHeadsPerPass) anchors.load(b, h0, H, D, qanchor, kanchor, has_anchor, delta);
-    float a[kDriftHeadsPerPass][kMost];
+    if (kLoaded && h0 >= n_waves * kDriftHeadsPerPass) anchors.load(b, h0, H, D, qanchor, kanchor, has_anchor, delta);
+    float a[kDriftHeadsPerPass][kSlots];
 #pragma unroll
     for (int u = 0; u < kDriftHeadsPerPass; ++u) {
       const size_t o = (size_t)min(h0 + u, H - 1) * D;
+      if (!kLoaded) anchors.load_head(u, b, h0, H, D, qanchor, kanchor, has_anchor, delta);
 #pragma unroll
-      for (int c = 0; c < kMost; ++c) {
+      for (int c = 0; c < kSlots; ++c) {
         a[u][c] = 0.f;
         const int d = lane + 64 * c;
-        if (c < slots && d < D) {
+        if (d < D) {
           const float qv = mean.qm(o + d), kv = mean.km(o + d);
           const float dq = fabsf(anchors.q[u][c] - qv);
           const float dk = fabsf(anchors.k[u][c] - kv);
@@ -98,13 +98,10 @@ __device__ __forceinline__ void drift_workgroup(
       const int h = h0 + u;
       // steps with s >= 64: a[i] += a[i+s]  <=>  slot c += slot c + s/64
 #pragma unroll
-      for (int s = kMost / 2; s >= 1; s >>= 1) {
-        if (s < slots) {
+      for (int s = kSlots / 2; s >= 1; s >>= 1)
 #pragma unroll
-          for (int c = 0; c < kMost / 2; ++c)
-            if (c < s) a[u][c] = a[u][c] + a[u][c + s];
-        }
-      }
+        for (int c = 0; c < kSlots / 2; ++c)
+          if (c < s) a[u][c] = a[u][c] + a[u][c + s];
       float v = a[u][0];
       // steps with s < 64 (lanes >= D hold +0, adding it is exact)
 #pragma unroll

@@ -241,7 +241,7 @@ __global__ __launch_bounds__(kMeanThreads) void token_mean_drift_kernel(
   anchors.load(b, (int)(threadIdx.x >> 6) * kDriftHeadsPerPass, H, D, fa.qanchor, fa.kanchor, fa.has_anchor, fa.delta);
   const size_t item = (size_t)b * H * D;
   // (at D = 64 few lanes would write the kept means: 13.7 -> 13.85 us for that call)
-  drift_workgroup<D / 64, D == 128>(b, H, D, DriftMeansAcross{qmean + item, kmean + item}, anchors, fa.qanchor, fa.kanchor, fa.has_anchor,
+  drift_workgroup<D / 64, D == 128, true>(b, H, D, DriftMeansAcross{qmean + item, kmean + item}, anchors, fa.qanchor, fa.kanchor, fa.has_anchor,
                           fa.delta, fa.gate_lo, fa.gate_hi, fa.commit, fa.drift, fa.refresh,
                           reinterpret_cast<unsigned char *>(lds));
 }
@@ -304,7 +304,7 @@ __global__ __launch_bounds__(kMeanThreads) void pool_drift_small_kernel(
     (which ? kmean : qmean)[item + o] = mean;
   }
   __syncthreads();
-  drift_workgroup<D / 64, true>(b, H, D, DriftMeans{lds, lds + n}, anchors, fa.qanchor, fa.kanchor, fa.has_anchor, fa.delta, fa.gate_lo,
+  drift_workgroup<D / 64, true, true>(b, H, D, DriftMeans{lds, lds + n}, anchors, fa.qanchor, fa.kanchor, fa.has_anchor, fa.delta, fa.gate_lo,
                           fa.gate_hi, fa.commit, fa.drift, fa.refresh, marks);
 }
 

@@ -1,0 +1,21 @@
+"""What the compiler made of kernels whose time is a chain of memory round trips: scratch memory would lengthen it."""
+import re
+import subprocess
+
+from paper_2605_14513_amd import build as hb
+
+
+def scratch_of(source):
+    """Bytes of scratch a lane of every kernel of a source file."""
+    flags = [f for f in hb.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
+    asm = subprocess.run(["/opt/rocm/bin/hipcc", *flags, "--offload-device-only", "-S", "-o", "-", f"{hb.CSRC}/{source}"],
+                         stdout=subprocess.PIPE, stderr=subprocess.DEVNULL, check=True, text=True).stdout
+    names = re.findall(r"^\s*\.amdhsa_kernel (\S+)", asm, re.M)
+    sizes = re.findall(r"^\s*\.amdhsa_private_segment_fixed_size (\d+)", asm, re.M)
+    assert names and len(names) == len(sizes)
+    return dict(zip(names, map(int, sizes)))
+
+
+def test_drift_kernels_use_no_scratch_memory():
+    sizes = scratch_of("drift.hip")
+    assert not any(sizes.values()), sizes
