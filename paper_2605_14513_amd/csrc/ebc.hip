@@ -21,7 +21,7 @@
 //    accumulators and reduced in a fixed order.  Two launches for latents:
 //      ebc_first   x coefficients of err with |err|^2, S_T of err, |dense|^2
 //      ebc_plane   y and t coefficients of the x coefficients with S_XY and S_XYT; its last workgroup adds everything up
-//    or, where t or y is longer than 63, in the place of the second
+//    or, where t is longer than 63 or y than 48, in the place of the second
 //      ebc_second  y coefficients of the x coefficients with S_XY
 //      ebc_third   S_XYT; its last workgroup adds everything up
 //    Bound by latency: at 128 x 21 x 30 x 52 the matrix instructions are 7 us of the chip and the
@@ -423,19 +423,22 @@ __global__ __launch_bounds__(kEbcThreads, 3) void ebc_third_kernel(const double 
   ebc_finish<false>(0.0, ebc_block_sum(e_out, red), partials, f, out);
 }
 
-// The second and third step in one launch, for short t and y axes (at most kEbcPlaneAxis; latents have 21 to 33 and
-// 30 to 45): a wavefront takes a (t, y) plane of one x coefficient of one channel, contracts y and then t, and keeps
+// The second and third step in one launch, for short t and y axes (latents have 21 to 33 and 30 to 45): a wavefront takes a (t, y) plane of one x coefficient of one channel, contracts y and then t, and keeps
 // nothing but the two sums of squares.  With the plane's rows as the first operand and the table as the second the y
 // coefficients come out as (t = lane / 16 + 4 r, k = lane % 16) in register r, which is, unchanged, the second operand
 // of the t contraction's step r.  The table's operands over y stay in registers.  Bound by latency as the others: one
 // plane a wavefront at 128 x 21 x 30 x 52, 12 us in the place of two launches of 10 and 13 us and of 10 MB written and
 // read again (21 us with one ticket for its 864 workgroups and operands from LDS in every step).
-constexpr int kEbcPlaneAxis = 63;  // two tiles of 16 coefficients
+// Longest axes: two tiles of 16 coefficients over t; over y what the registers of a wavefront hold (16 steps took 35 of them to
+// scratch).  Whole call, three launches -> two, T = 3 to 63, X = 52: Y = 8 to 45 4 to 30 % faster at 16 and at 128 channels (16 x
+// 63 x 45 33.0 -> 30.8 us, 128 x 34 x 45 81.6 -> 78.7), Y = 49 to 63 up to 17 % slower (16 x 63 x 49 34.0 -> 40.0, 128 x 33 x 56
+// 85 -> 98).
+constexpr int kEbcPlaneT = 63, kEbcPlaneY = 48;
 template <int M, int SY>  // tiles of y coefficients, contraction steps (of 4 elements) over y
 __global__ __launch_bounds__(kEbcThreads, SY > 8 ? 3 : 4) void ebc_plane_kernel(const double *__restrict__ cx, int C, int T, int Y,
                                                                                 int KX, double *__restrict__ partials,
                                                                                 EbcFinish f, double *__restrict__ out) {
-  __shared__ double tab_t[2 * kEbcPlaneAxis], tab_y[2 * kEbcPlaneAxis];
+  __shared__ double tab_t[2 * kEbcPlaneT], tab_y[2 * kEbcPlaneY];
   __shared__ double red[kEbcWaves];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, g = lane >> 4;
   const int KY = ebc_coefs(Y), KT = ebc_coefs(T), PT = (KT + 15) / 16, TT = (T + 15) / 16, TY = T * Y;
@@ -582,11 +585,11 @@ int launch_ebc_band_error(long long C, int T, int Y, int X, const float *err, co
   auto first = lx.share > 1 || lt.share > 1 ? ebc_first_kernel<true> : ebc_first_kernel<false>;
   hipLaunchKernelGGL(first, dim3((unsigned)(gx + gt + gd)), dim3(kEbcThreads), 0, st, err, dense, total, lx, lt, gx, gt, cx,
                      partials);
-  if (T <= kEbcPlaneAxis && Y <= kEbcPlaneAxis && C <= 0x7fffffff / KX) {
+  if (T <= kEbcPlaneT && Y <= kEbcPlaneY && C <= 0x7fffffff / KX) {
     const long long want = ((long long)KX * C + kEbcWaves - 1) / kEbcWaves;
     const int gp = (int)std::min<long long>(want, kEbcPartials);
     f.count[2] = f.count[3] = gp;
-    auto plane = Y < 32 ? ebc_plane_kernel<1, 8> : Y <= 48 ? ebc_plane_kernel<2, 12> : ebc_plane_kernel<2, 16>;
+    auto plane = Y < 32 ? ebc_plane_kernel<1, 8> : ebc_plane_kernel<2, 12>;
     hipLaunchKernelGGL(plane, dim3((unsigned)gp), dim3(kEbcThreads), 0, st, cx, (int)C, T, Y, KX, partials, f, out);
     return check_launch("ebc kernels");
   }

@@ -124,9 +124,10 @@ def test_thresholds_calibrated_on_the_tiny_workload():
 
 
 # t and y axes that one launch contracts together, at the ends of its tiles (16 rows; 15 / 17 and 31 coefficients at 31 / 32
-# and 63 elements) and on either side of the longest axis it takes (63); more planes than wavefronts
+# and 63 elements) and on either side of the longest axes it takes (63 and 48; up to 64 x 64 besides); more planes than wavefronts
 @pytest.mark.parametrize("shape", [(3, 16, 63, 9), (2, 17, 32, 7), (5, 63, 63, 5), (1, 64, 63, 4), (1, 63, 64, 4),
-                                   (2, 31, 31, 3), (1, 33, 1, 64), (300, 3, 5, 62)])
+                                   (2, 31, 31, 3), (1, 33, 1, 64), (300, 3, 5, 62),
+                                   (3, 63, 48, 5), (2, 64, 48, 5), (2, 63, 49, 5), (1, 16, 47, 9)])
 def test_band_error_of_planes(shape):
     import paper_2605_14513_amd as heart
 
