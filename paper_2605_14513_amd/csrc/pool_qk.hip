@@ -247,12 +247,12 @@ __global__ __launch_bounds__(kMeanThreads) void token_mean_drift_kernel(
 }
 
 // All of heart_pool_drift in one launch, for few blocks, where it is bound by launches and by a chain of memory round
-// trips (block, acknowledgement, ticket, block means, result; 7.7 us at two heads of 16 blocks): a workgroup pools kSmallBlocks blocks of a batch item, the
+// trips (block, acknowledgement, ticket, block means, result; 7.1 us at two heads of 16 blocks of 64, D = 64): a workgroup pools kSmallBlocks blocks of a batch item, the
 // last one of the item computes its token means (in block order in fp64 as token_mean_workgroup does, which has at most one
 // block a slice here, so the bits are the same), keeps them in LDS and runs the drift stage.
 constexpr int kSmallBlocks = kMeanThreads / kPoolThreads;
 constexpr int kSmallMeans = kSmallBlocks * kPoolPart;  // token means that fit
-constexpr int kSmallMarks = 2 * kSmallMeans / (2 * 64);
+constexpr int kSmallMarks = 2 * 32;                   // two bytes a head, 32 heads
 template <int D>
 __global__ __launch_bounds__(kMeanThreads) void pool_drift_small_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, long long qsb, long long qsh, long long qsn,
@@ -308,11 +308,20 @@ __global__ __launch_bounds__(kMeanThreads) void pool_drift_small_kernel(
                           fa.gate_hi, fa.commit, fa.drift, fa.refresh, marks);
 }
 
-// Most workgroups of pool_drift_small_kernel for a batch item and in all.  One ticket each, served one after another, and the
-// last workgroup reads every block mean again.  heart_pool_drift in two launches -> in one, calls in a row: 2 workgroups 9.5 ->
-// 7.2 us, 16 9.1 -> 7.2, 32 (64 blocks of one head) 10.2 -> 9.4, 36 10.0 -> 9.7, 40 10.0 -> 8.0, 8 items of 32 13.2 -> 12.7; 64 10.5 -> 10.6,
-// 96 11.0 -> 12.6, 256 13.0 -> 21.8.
-constexpr int kSmallItem = 40, kSmallLaunch = 256;
+// Largest calls of pool_drift_small_kernel: workgroups of a batch item and in all (one ticket each, served one after another),
+// token means of a batch item (one workgroup makes them all, a lane one or two of them) and blocks a head (a chain of loads).
+// heart_pool_drift in two launches -> in one, us: D = 64, H x Nb = 2 x 16 7.9 -> 7.1, 8 x 8 (32 workgroups) 8.1 -> 7.2, 16 x
+// 4 (32 workgroups, 2048 means) 8.5 -> 8.1, 2 x 24 8.1 -> 7.4, six heads of 8 in 8 items (192 workgroups) 9.5 -> 9.0; beyond:
+// 3 x 26 (39) 8.0 -> 8.2, 25 x 1 (3200) 8.4 -> 8.7, 2 x 40 8.2 -> 8.4, 8 items of 32 9.5 -> 10.1.  D = 128, where the two launches
+// keep the means they compared: 2 x 16 8.2 -> 7.8, 4 x 8 (16 workgroups, 1024 means) 8.6 -> 7.9, 3 x 10 8.2 -> 8.1; beyond: 2 x 24
+// (24) 8.6 -> 8.8, 8 x 1 (2048 means) 7.8 -> 8.4, 25 x 3 8.8 -> 13.3.
+constexpr int kSmallLaunch = 192, kSmallNb = 24;
+template <int D>
+constexpr int kSmallItem = D == 64 ? 32 : 16;
+template <int D>
+constexpr int kSmallCols = D == 64 ? 2048 : 1024;
+static_assert(kSmallNb <= kMeanThreads / (128 / 4), "at most one block a slice of the token means");
+static_assert(kSmallCols<64> <= kSmallMeans && kSmallCols<64> / 64 <= kSmallMarks, "LDS");
 template <int D>
 static int launch_pool_t(const heart_shape &s, const uint16_t *qp, const uint16_t *kp, float *qblk,
                          float *kblk, float *qmean, float *kmean, const PoolDriftArgs *fused,
@@ -320,10 +329,8 @@ static int launch_pool_t(const heart_shape &s, const uint16_t *qp, const uint16_
   const int Nb = (s.N + s.block - 1) / s.block;
   const long long nwg = 2LL * s.B * s.H * Nb;
   if (nwg > 0x7fffffffLL) return fail(HEART_EUNSUPPORTED, "heart_pool_qk: grid too large");
-  // few blocks: at most one a slice of the token means, token means that fit the LDS
   const long long per_item = (2LL * s.H * Nb + kSmallBlocks - 1) / kSmallBlocks;
-  if (fused && Nb <= kMeanThreads / (D / 4) && 2 * s.H * D <= kSmallMeans && per_item <= kSmallItem &&
-      s.B * per_item <= kSmallLaunch) {
+  if (fused && Nb <= kSmallNb && 2 * s.H * D <= kSmallCols<D> && per_item <= kSmallItem<D> && s.B * per_item <= kSmallLaunch) {
     hipLaunchKernelGGL(pool_drift_small_kernel<D>, dim3((unsigned)(s.B * per_item)), dim3(kMeanThreads), 0, st, qp, kp,
                        s.q_stride[0], s.q_stride[1], s.q_stride[2], s.k_stride[0], s.k_stride[1], s.k_stride[2], s.H, s.N,
                        s.block, Nb, (int)per_item, qblk, kblk, qmean, kmean, *fused);

@@ -1,5 +1,7 @@
 """Helpers shared by the GPU parity tests (no method arithmetic here: every expected value
 comes from the `oracle` package)."""
+import ctypes
+
 import numpy as np
 import torch
 
@@ -180,3 +182,29 @@ class OracleChain:
         oracle.topp(self.scores, self.tau, refresh=r, n_always_kv=nt, n_dense_q=nt, mask=self.mask,
                     kept_idx=self.idx, kept_count=self.cnt)
         return d, r
+
+
+def captured_launches(fn):
+    """(workgroups, threads of one) of every kernel that fn enqueues, in order: fn is captured, not run."""
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    hip = ctypes.CDLL(path)  # (the one that is loaded)
+
+    class Params(ctypes.Structure):
+        _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                    ("grid", ctypes.c_uint * 3), ("params", ctypes.c_void_p), ("shared", ctypes.c_uint)]
+
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        fn()
+    raw, n = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(n)) == 0
+    out = []
+    for node in nodes:
+        kind, p = ctypes.c_int(-1), Params()
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0 and kind.value == 0  # kernels only
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        out.append((p.grid[0] * p.grid[1] * p.grid[2], p.block[0] * p.block[1] * p.block[2]))
+    return out

@@ -21,7 +21,7 @@ import torch
 import oracle
 from heart_synth import make_generator
 from heart_testlib import (ATTN_ATOL, OracleChain, assert_lists_equal, assert_masks_equal_up_to_threshold,
-                           assert_means_close, assert_scores_close, attn_atol, check_attn_plan, gpu,
+                           assert_means_close, assert_scores_close, attn_atol, captured_launches, check_attn_plan, gpu,
                            np_gpu, pooled_mean_score_shift, u16)
 
 pytestmark = pytest.mark.gpu
@@ -194,13 +194,17 @@ def test_pool_drift_equals_the_two_calls(heart, name, gate):
         assert_means_close(fq, oqb, amax, "q block means")
 
 
-# one launch and two: a single block of one token; the most workgroups of one launch (40) and one more; the most blocks a
-# head (32 at D = 128, 64 at 64) and one more; the most heads (32, 64) and one more, where the drift stage takes two passes
-@pytest.mark.parametrize("B,H,Nb,D,block,tail", [(1, 1, 1, 64, 64, 63), (2, 5, 16, 128, 128, 3), (1, 27, 3, 64, 128, 0),
-                                                 (3, 1, 32, 128, 64, 1), (3, 1, 33, 128, 64, 1), (1, 1, 64, 64, 128, 100),
-                                                 (1, 1, 65, 64, 64, 0), (1, 32, 2, 128, 128, 17), (2, 33, 2, 128, 128, 17),
-                                                 (1, 64, 1, 64, 64, 2), (2, 70, 1, 64, 64, 2)])
-def test_pool_drift_of_few_blocks(heart, B, H, Nb, D, block, tail):
+# one launch and two (`one`): a single block of one token; the most workgroups of one launch (D = 128: 16, D = 64: 32) and one
+# more; the most blocks a head (24) and one more; the most heads (4, 16) and one more; the most workgroups in all (192) and more;
+# two passes of the drift stage (65 heads and more)
+@pytest.mark.parametrize("B,H,Nb,D,block,tail,one", [
+    (1, 1, 1, 64, 64, 63, True), (2, 5, 16, 128, 128, 3, False), (1, 27, 3, 64, 128, 0, False), (3, 1, 24, 128, 64, 1, True),
+    (3, 1, 25, 128, 64, 1, False), (1, 1, 24, 64, 128, 100, True), (1, 1, 25, 64, 64, 0, False), (1, 4, 8, 128, 128, 17, True),
+    (1, 3, 11, 128, 128, 17, False), (1, 5, 2, 128, 128, 17, False), (2, 33, 2, 128, 128, 17, False), (1, 16, 4, 64, 64, 2, True),
+    (1, 16, 5, 64, 64, 2, False), (1, 17, 1, 64, 64, 2, False), (6, 8, 8, 64, 64, 9, True), (7, 8, 8, 64, 64, 9, False),
+    (2, 70, 1, 64, 64, 2, False), (1, 32, 2, 128, 128, 17, False), (1, 64, 1, 64, 64, 2, False), (3, 1, 33, 128, 64, 1, False),
+    (1, 1, 65, 64, 64, 0, False), (3, 1, 32, 128, 64, 1, False), (1, 1, 64, 64, 128, 100, False)])
+def test_pool_drift_of_few_blocks(heart, B, H, Nb, D, block, tail, one):
     N = Nb * block - tail
     g = torch.Generator(device="cuda").manual_seed(H * Nb)
     state = [[torch.zeros((B, H, D), device="cuda"), torch.zeros((B, H, D), device="cuda"),
@@ -221,6 +225,9 @@ def test_pool_drift_of_few_blocks(heart, B, H, Nb, D, block, tail):
         for x, y in zip([*got, *f], [qblk, kblk, qmean, kmean, d, r, *a]):
             assert torch.equal(x, y)
         assert not ws.any().item()
+    outs = dict(zip(("qblk", "kblk", "qmean", "kmean", "drift", "refresh"), got))
+    calls = captured_launches(lambda: heart.heart_pool_drift(q, k, block, *f, delta, ws, 0.1, 0.9, **outs))
+    assert len(calls) == (1 if one else 2), calls
 
 
 def test_pool_drift_commit_off_and_validation(heart):
