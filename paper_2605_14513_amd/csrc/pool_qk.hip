@@ -236,12 +236,15 @@ __global__ __launch_bounds__(kMeanThreads) void token_mean_drift_kernel(
   }
   __syncthreads();
   if (!s_last) return;
-  // (asked for before the block means, by every workgroup: 13.6 -> 14.1 us for a call of two items of 10 heads of 101 blocks)
+  // (asked for before the block means, by every workgroup: 13.6 -> 14.1 us for a call of two items of 10 heads of 101 blocks.  At D =
+  // 64 they are loaded with the means: ahead of them 72 heads of one block took 11.3 instead of 10.9 us, 200 of ten 22.5
+  // instead of 21.6; at D = 128 it is the other way round, 12.6 against 13.1 and 38.8 against 39.6)
   DriftAnchors<D / 64> anchors;
-  anchors.load(b, (int)(threadIdx.x >> 6) * kDriftHeadsPerPass, H, D, fa.qanchor, fa.kanchor, fa.has_anchor, fa.delta);
+  if constexpr (D == 128)
+    anchors.load(b, (int)(threadIdx.x >> 6) * kDriftHeadsPerPass, H, D, fa.qanchor, fa.kanchor, fa.has_anchor, fa.delta);
   const size_t item = (size_t)b * H * D;
   // (at D = 64 few lanes would write the kept means: 13.7 -> 13.85 us for that call)
-  drift_workgroup<D / 64, D == 128, true>(b, H, D, DriftMeansAcross{qmean + item, kmean + item}, anchors, fa.qanchor, fa.kanchor, fa.has_anchor,
+  drift_workgroup<D / 64, D == 128, D == 128>(b, H, D, DriftMeansAcross{qmean + item, kmean + item}, anchors, fa.qanchor, fa.kanchor, fa.has_anchor,
                           fa.delta, fa.gate_lo, fa.gate_hi, fa.commit, fa.drift, fa.refresh,
                           reinterpret_cast<unsigned char *>(lds));
 }
