@@ -380,8 +380,16 @@ int launch_antidiag(const heart_shape &s, const void *q, const void *k, int stri
   // 8 of 36 62 -> 52; 20 of nine 57 -> 58, 12 of 64 182 -> 212, 40 of 64 629 -> 795.  (The same bits.)
   const int n_cu = cu_count(dev);
   if (n_cu <= 0) return fail(HEART_EHIP, "heart_scores_antidiag: cannot query the number of CUs");
-  const long long tiles = (long long)BH * MT2 * MT2, small = (long long)BH * ((M + 127) / 128) * MT;
-  const bool few = 5 * ((small + 2 * n_cu - 1) / (2 * n_cu)) < 8 * ((tiles + n_cu - 1) / n_cu);
+  // Only the device knows how many heads `refresh` names, so small tiles then have to be the better ones for any number of
+  // them, that is for the most heads of every number of rounds of large ones (30 heads of nine tiles, of which 16 refresh: 52
+  // us, 59 with small tiles, which are better for all 30).
+  const long long large_h = (long long)MT2 * MT2, small_h = (long long)((M + 127) / 128) * MT;  // tiles of a head
+  auto rounds = [](long long n, long long places) { return (n + places - 1) / places; };
+  bool few = true;
+  for (long long r = refresh ? rounds(large_h, n_cu) : rounds(BH * large_h, n_cu), heads = 0; few && heads < BH; ++r) {
+    heads = refresh ? std::min<long long>(BH, r * n_cu / large_h) : BH;
+    few = 5 * rounds(heads * small_h, 2 * n_cu) < 8 * r;
+  }
   const int tile = few ? kAdTile / 2 : kAdTile, MTQ = (M + tile - 1) / tile;
   const long long grid = ((long long)BH * MTQ * (few ? MT : MT2) + kNumXcd - 1) / kNumXcd * kNumXcd;
   if (grid > 0x7fffffffLL || (long long)BH * Nb > 0x7fffffffLL)

@@ -15,7 +15,7 @@ import torch
 import oracle
 from oracle import antidiag_oracle as ao
 from heart_synth import make_generator
-from heart_testlib import assert_lists_equal, np_gpu
+from heart_testlib import assert_lists_equal, captured_launches, np_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -217,3 +217,22 @@ def test_tiles_of_refreshed_heads(heart, H, N, D, block, flags):
         assert_close(res[h], want, f"head {h}")
     if pick:  # (every refreshed head: rows of a distribution)
         np.testing.assert_allclose(res[on.numpy()].astype(np.float64).sum(-1), 1.0, rtol=1e-4)
+
+
+# tiles of 256 reduced rows come in workgroups of 512 threads, tiles of 128 in workgroups of 256.  Thirty heads of 737 reduced rows:
+# two rounds of large tiles, three of small ones, which are shorter; with 28 heads or fewer refreshed one round and two, which are not
+@pytest.mark.parametrize("H,N,flags,small", [(30, 11784, False, True), (30, 11784, True, False), (14, 11784, True, True),
+                                             (1, 2000, True, True), (40, 3500, True, True), (20, 11784, False, False)])
+def test_small_tiles_for_any_number_of_refreshed_heads(heart, H, N, flags, small):
+    q = torch.zeros((1, H, N, 128), dtype=torch.bfloat16, device="cuda")
+    Nb = (N + 127) // 128
+    refresh = torch.ones((1, H), dtype=torch.uint8, device="cuda") if flags else None
+    scores = torch.empty((1, H, Nb, Nb), device="cuda")
+    ws = torch.empty(heart.heart_scores_antidiag_workspace_bytes(q, 128, 16), dtype=torch.uint8, device="cuda")
+
+    def call():
+        heart.heart_scores_antidiag(q, q, 128, 16, scores=scores, workspace=ws, refresh=refresh)
+
+    call()  # (attributes of a kernel are set on its first call)
+    print(f"antidiag H={H} N={N} flags={flags}", flush=True)
+    assert captured_launches(call)[0][1] == (256 if small else 512)
