@@ -377,7 +377,8 @@ int launch_antidiag(const heart_shape &s, const void *q, const void *k, int stri
   // Tiles of 128 x 128, two workgroups a CU, where they fill the chip better: a round of them takes 0.5 to 0.6 of the
   // time of a round of 256 x 256, which move half the operand bytes per FLOP but come one to a CU.  Measured (tile and
   // combine kernel, 256 -> 128): 13 heads of one tile 47 -> 22.5 us, one head of 64 tiles 49 -> 29, 14 of nine 54 -> 40,
-  // 8 of 36 62 -> 52; 20 of nine 57 -> 58, 12 of 64 182 -> 212, 40 of 64 629 -> 795.  (The same bits.)
+  // 8 of 36 62 -> 52; 20 of nine 57 -> 58, 12 of 64 182 -> 212, 40 of 64 629 -> 795.  (The same bits.)  Three rounds in the place
+  // of two: 1.16 times as fast with 16 stages, 0.96 to 1.04 with 32 (D = 128, stride 16); four of three 1.11 to 1.23.
   const int n_cu = cu_count(dev);
   if (n_cu <= 0) return fail(HEART_EHIP, "heart_scores_antidiag: cannot query the number of CUs");
   // Only the device knows how many heads `refresh` names, so small tiles then have to be the better ones for any number of
@@ -388,7 +389,7 @@ int launch_antidiag(const heart_shape &s, const void *q, const void *k, int stri
   bool few = true;
   for (long long r = refresh ? rounds(large_h, n_cu) : rounds(BH * large_h, n_cu), heads = 0; few && heads < BH; ++r) {
     heads = refresh ? std::min<long long>(BH, r * n_cu / large_h) : BH;
-    few = 5 * rounds(heads * small_h, 2 * n_cu) < 8 * r;
+    few = 10 * rounds(heads * small_h, 2 * n_cu) < (s.D * S >= 2048 ? 15 : 16) * r;
   }
   const int tile = few ? kAdTile / 2 : kAdTile, MTQ = (M + tile - 1) / tile;
   const long long grid = ((long long)BH * MTQ * (few ? MT : MT2) + kNumXcd - 1) / kNumXcd * kNumXcd;

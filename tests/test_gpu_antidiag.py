@@ -220,11 +220,13 @@ def test_tiles_of_refreshed_heads(heart, H, N, D, block, flags):
 
 
 # tiles of 256 reduced rows come in workgroups of 512 threads, tiles of 128 in workgroups of 256.  Thirty heads of 737 reduced rows:
-# two rounds of large tiles, three of small ones, which are shorter; with 28 heads or fewer refreshed one round and two, which are not
-@pytest.mark.parametrize("H,N,flags,small", [(30, 11784, False, True), (30, 11784, True, False), (14, 11784, True, True),
-                                             (1, 2000, True, True), (40, 3500, True, True), (20, 11784, False, False)])
-def test_small_tiles_for_any_number_of_refreshed_heads(heart, H, N, flags, small):
-    q = torch.zeros((1, H, N, 128), dtype=torch.bfloat16, device="cuda")
+# two rounds of large tiles, three of small ones, which are shorter at D = 64; with 28 heads or fewer refreshed one round and two,
+# which are not.  33 heads of 789 (16 tiles): three rounds and four
+@pytest.mark.parametrize("H,N,D,flags,small", [
+    (30, 11784, 64, False, True), (30, 11784, 64, True, False), (30, 11784, 128, False, False), (14, 11784, 128, True, True),
+    (1, 2000, 128, True, True), (40, 3500, 128, True, True), (20, 11784, 128, False, False), (33, 12614, 128, False, True)])
+def test_small_tiles_for_any_number_of_refreshed_heads(heart, H, N, D, flags, small):
+    q = torch.zeros((1, H, N, D), dtype=torch.bfloat16, device="cuda")
     Nb = (N + 127) // 128
     refresh = torch.ones((1, H), dtype=torch.uint8, device="cuda") if flags else None
     scores = torch.empty((1, H, Nb, Nb), device="cuda")
@@ -234,5 +236,5 @@ def test_small_tiles_for_any_number_of_refreshed_heads(heart, H, N, flags, small
         heart.heart_scores_antidiag(q, q, 128, 16, scores=scores, workspace=ws, refresh=refresh)
 
     call()  # (attributes of a kernel are set on its first call)
-    print(f"antidiag H={H} N={N} flags={flags}", flush=True)
+    print(f"antidiag H={H} N={N} D={D} flags={flags}", flush=True)
     assert captured_launches(call)[0][1] == (256 if small else 512)
