@@ -314,13 +314,13 @@ __global__ __launch_bounds__(kMeanThreads) void pool_drift_small_kernel(
 // Largest calls of pool_drift_small_kernel: workgroups of a batch item and in all (one ticket each, served one after another),
 // token means of a batch item (one workgroup makes them all, a lane one or two of them) and blocks a head (a chain of loads).
 // heart_pool_drift in two launches -> in one, us: D = 64, H x Nb = 2 x 16 7.9 -> 7.1, 8 x 8 (32 workgroups) 8.1 -> 7.2, 16 x
-// 4 (32 workgroups, 2048 means) 8.5 -> 8.1, 2 x 24 8.1 -> 7.4, six heads of 8 in 8 items (192 workgroups) 9.5 -> 9.0; beyond:
-// 3 x 26 (39) 8.0 -> 8.2, 25 x 1 (3200) 8.4 -> 8.7, 2 x 40 8.2 -> 8.4, 8 items of 32 9.5 -> 10.1.  D = 128, where the two launches
+// 4 (32 workgroups, 2048 means) 8.5 -> 8.1, 10 x 8 (40) 8.0 -> 7.6, 2 x 24 8.1 -> 7.4, six heads of 8 in 8 items (192 workgroups)
+// 9.5 -> 9.0; beyond: 10 x 9 (45) 8.1 -> 8.5, 25 x 1 (3200) 8.2 -> 8.7, 2 x 40 8.0 -> 8.4, 8 items of 32 9.5 -> 10.1.  D = 128, where the two launches
 // keep the means they compared: 2 x 16 8.2 -> 7.8, 4 x 8 (16 workgroups, 1024 means) 8.6 -> 7.9, 3 x 10 8.2 -> 8.1; beyond: 2 x 24
 // (24) 8.6 -> 8.8, 8 x 1 (2048 means) 7.8 -> 8.4, 25 x 3 8.8 -> 13.3.
 constexpr int kSmallLaunch = 192, kSmallNb = 24;
 template <int D>
-constexpr int kSmallItem = D == 64 ? 32 : 16;
+constexpr int kSmallItem = D == 64 ? 40 : 16;
 template <int D>
 constexpr int kSmallCols = D == 64 ? 2048 : 1024;
 static_assert(kSmallNb <= kMeanThreads / (128 / 4), "at most one block a slice of the token means");
