@@ -296,7 +296,8 @@ size_t heart_attn_workspace_bytes(const heart_shape *shape);
  * no plan but the parts of the query blocks that were divided (71 MB at most), and the results are those of another
  * size up to rounding; where lists are divided, and with it the rounding of a query block, depends on the kept counts of
  * all heads of the call.  Where dividing does not pay, and for other shapes, the same as heart_attn_workspace_bytes; with
- * dense != 0 (lists that keep every block) it pays less often.  0 for an invalid shape.
+ * dense != 0 (lists that keep every block) it pays less often.  Only lists of uneven length gain: a call whose lists
+ * are all about equally long can take up to a fifth longer than with heart_attn_workspace_bytes.  0 for an invalid shape.
  */
 size_t heart_attn_balanced_workspace_bytes(const heart_shape *shape, int dense);
 

@@ -191,8 +191,10 @@ __device__ __forceinline__ int share_blocks(int d, int cnt) {
 // to 30 heads: with more rows the workgroups of an XCD are at places of K/V that are too far apart for its L2 and the
 // rows level out by themselves (D = 128, block 128: 1.04 to 1.85 times as fast up to 2 rows a place, 0.95 to 1.04 at 3; D =
 // 64: 1.0 to 2.6 times up to 2.5).  Four workgroups a CU with long lists at D = 128, block 64 feel that most (two heads of 585
-// rows 0.90, four of 293 1.19 times as fast).  Rows of at most 15 blocks a part of kSplitRows are left to that.
-// Dense lists need no levelling: only where a last round of whole rows would leave many places empty.
+// rows 0.90, four of 293 1.19 times as fast).  Rows of few blocks a part of kSplitRows are left to that.
+// Dense lists need no levelling: only where a last round of whole rows would leave many places empty.  (Lists that are nearly full
+// and of nearly equal length without the caller's saying so: 0.79 to 1.6 times as fast, the least with 1.6 to 2 rows a place at D =
+// 128, block 64.)
 int attn_shares(long long BH, long long Nb, int D, int block, bool dense) {
   const long long places = attn_places(D, block);
   if (BH > kShareMaxRows || Nb > kShareMaxRows || BH * Nb > kShareMaxRows) return 0;
@@ -201,7 +203,12 @@ int attn_shares(long long BH, long long Nb, int D, int block, bool dense) {
   const bool near = D == 64 || block == 128 || rows * Nb <= 300 * places;
   if (rows > places && !near) return 0;
   const int s = attn_split(BH, Nb, D, block);
-  if (s > 1 && (dense || Nb <= 15 * s)) return 0;
+  // Short rows in many parts each: what a workgroup takes to find its part costs more than even parts give.  Lists of the timed
+  // fields, kSplitRows -> shares us: D = 64, block 64, one head of 167 rows (six parts) 19.8 -> 22.8, two of 115 (four) 23.7 -> 24.4,
+  // but one of 197 (five) 28.5 -> 26.2, two of 165 (three) 31.4 -> 23.8; D = 128, block 64, three of 80 (four) 23.2 -> 26.1, two of
+  // 105 (four) 27.6 -> 25.1, four of 77 (three) 37.3 -> 29.9; two parts, and blocks of 128, 1.0 to 2 times as fast from 15 on.
+  const int few_blocks = block == 128 || s < 3 ? 15 : D == 64 ? 30 : s < 4 ? 15 : 24;  // a part
+  if (s > 1 && (dense || Nb <= few_blocks * s)) return 0;
   if (dense && (!near || (rows > places && 8 * rows > (D == 64 ? 13 : 10) * places))) return 0;
   const long long most = rows * (Nb / kSharePart + 1);
   return (int)((most < places ? most : places) + kNumXcd - 1) / kNumXcd * kNumXcd;

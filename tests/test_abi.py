@@ -276,6 +276,23 @@ def test_binding_refuses_tensors_that_are_too_small(lib):
         native.ebc_band_error(x, x, 1.0, 1.0, 1.0, 1.0, 1e-8, x, torch.zeros(5, dtype=torch.float64), 0)
 
 
+# (B, H, Nb, D, block): a size of its own asks for divided rows, or there is none.  Parts of split rows with few blocks are left as
+# they are: 15 a part in two parts or at blocks of 128, 30 at D = 64 and 24 at D = 128 in more parts
+@pytest.mark.parametrize("B,H,Nb,D,block,divided", [
+    (1, 1, 167, 64, 64, False), (2, 1, 115, 64, 64, False), (1, 1, 150, 64, 64, False), (1, 1, 197, 64, 64, True),
+    (1, 2, 165, 64, 64, True), (1, 12, 34, 64, 64, True), (1, 3, 80, 128, 64, False), (1, 2, 105, 128, 64, True),
+    (1, 4, 77, 128, 64, True), (1, 1, 102, 128, 128, True), (1, 1, 75, 128, 128, False), (1, 3, 50, 64, 128, True),
+    (2, 10, 101, 64, 64, True), (1, 40, 256, 128, 128, False)])
+def test_size_that_asks_for_divided_rows(lib, B, H, Nb, D, block, divided):
+    from paper_2605_14513_amd.binding import HeartShape
+
+    s = HeartShape(B, H, Nb * block, D, block)
+    usual = lib.heart_attn_workspace_bytes(ctypes.byref(s))
+    asks, dense = (lib.heart_attn_balanced_workspace_bytes(ctypes.byref(s), d) for d in (0, 1))
+    assert (asks > usual) == divided
+    assert dense in (usual, asks)
+
+
 def test_product_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2605_14513_amd")
     for dirpath, _, files in os.walk(pkg):
