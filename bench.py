@@ -448,9 +448,9 @@ def main():
     import paper_2605_14513_amd as heart
     from heart_synth import make_generator
 
-    if not os.path.exists(heart.lib_path()):
-        from paper_2605_14513_amd import build as hb
+    from paper_2605_14513_amd import build as hb
 
+    if not hb.is_built():
         hb.build(force=True)
     heart.load_library()
     assert torch.cuda.is_available(), "bench.py needs a GPU"

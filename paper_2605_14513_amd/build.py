@@ -28,13 +28,27 @@ def sources():
     return [os.path.join(CSRC, s) for s in SOURCES]
 
 
+def is_built() -> bool:
+    """Both the library and the extension module are there."""
+    return os.path.exists(LIB) and os.path.exists(NATIVE)
+
+
+def _torch_mark() -> str:
+    # (the extension module is bound to the C++ ABI of the torch that it was compiled against)
+    import torch
+
+    return f"built for torch {torch.__version__}"
+
+
 def is_stale() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(NATIVE):
+    if not is_built():
         return True
     t = min(os.path.getmtime(LIB), os.path.getmtime(NATIVE))
-    deps = sources() + [NATIVE_SOURCE, os.path.join(CSRC, "heart_internal.h"),
-                        os.path.join(ROOT, "include", "heart.h")]
-    return any(os.path.getmtime(d) > t for d in deps)
+    deps = [os.path.join(d, f) for d in (CSRC, os.path.join(ROOT, "include")) for f in os.listdir(d)]
+    if any(os.path.getmtime(d) > t for d in deps):
+        return True
+    with open(NATIVE, "rb") as f:
+        return _torch_mark().encode() not in f.read()
 
 
 def _run(cmd, verbose: bool) -> None:
@@ -63,8 +77,8 @@ def build(force: bool = True, verbose: bool = False) -> str:
                 # (NDEBUG: without it pybind11's headers leave a thread-local counter, and a library with thread-local
                 # data that a thread never touches puts all its other thread-locals on glibc's slow path: every torch
                 # operation took 0.4 us longer once the module was imported)
-                ex.submit(_run, ["g++", "-O2", "-DNDEBUG", "-std=c++17", "-fPIC", "-Wall", *incs, "-c", NATIVE_SOURCE,
-                                 "-o", obj], verbose)]
+                ex.submit(_run, ["g++", "-O2", "-DNDEBUG", "-std=c++17", "-fPIC", "-Wall", f'-DHEART_TORCH="{_torch_mark()}"',
+                                 *incs, "-c", NATIVE_SOURCE, "-o", obj], verbose)]
         for j in jobs:
             j.result()
     # (torch's libraries are loaded already when the module is imported)

@@ -294,7 +294,7 @@ PyMethodDef methods[] = {
     {"scores_antidiag", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(scores_antidiag)), METH_FASTCALL, nullptr},
     {"ebc_band_error", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(ebc_band_error)), METH_FASTCALL, nullptr},
     {nullptr, nullptr, 0, nullptr}};
-PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", HEART_TORCH, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
 

@@ -303,6 +303,28 @@ def test_product_does_not_import_the_oracle():
                 assert "heart_oracle" not in text, f
 
 
+def test_build_knows_when_it_is_stale(lib, monkeypatch, tmp_path):
+    """Every source and header counts, and the torch that the extension module was compiled against."""
+    import torch
+
+    from paper_2605_14513_amd import build as hb
+
+    assert hb.is_built() and not hb.is_stale()
+    built = min(os.path.getmtime(hb.LIB), os.path.getmtime(hb.NATIVE))
+    for name in sorted(os.listdir(hb.CSRC)) + ["heart.h", "heart_diag.h"]:
+        real = os.path.getmtime
+        monkeypatch.setattr(os.path, "getmtime", lambda p: built + 1 if os.path.basename(p) == name else real(p))
+        assert hb.is_stale(), name
+        monkeypatch.undo()
+    monkeypatch.setattr(torch, "__version__", "0.0.0")
+    assert hb.is_stale()
+    monkeypatch.undo()
+    for artefact in ("LIB", "NATIVE"):
+        monkeypatch.setattr(hb, artefact, str(tmp_path / "none.so"))
+        assert hb.is_stale() and not hb.is_built()
+        monkeypatch.undo()
+
+
 def test_extension_module_has_no_thread_local_data(lib):
     """glibc (2.35) resolves every thread-local of a thread on a slow path once a library has been loaded whose own
     ones the thread never touches; libheart's error text is touched by every call."""

@@ -36,7 +36,7 @@ def heart():
 
     if not torch.cuda.is_available():
         pytest.fail("GPU tests need a GPU")
-    if hb.is_stale() and not __import__("os").path.exists(pkg.lib_path()):
+    if not hb.is_built():
         hb.build(force=True)
     pkg.load_library()
     return pkg
