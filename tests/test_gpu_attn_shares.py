@@ -11,11 +11,13 @@ pytestmark = pytest.mark.gpu
 
 
 # rows: one; as few as two shares; groups of 256 rows with a remainder; the most there are (D = 64, block 64: 2560) and one
-# head more than that, which has a plan.  kinds: uneven with rows of no and one block; no blocks at all; all blocks
+# head more than that, which has a plan; at D = 128 more rows than places (512, 1024 of the small workgroups), so that a share
+# ends a row that another began, takes whole ones and begins the next, and the most rows a place (2).  kinds: uneven with rows of no and one block; no blocks at all; all blocks
 @pytest.mark.parametrize("kind", ["uneven", "empty", "full"])
 @pytest.mark.parametrize("B,H,Nb,D,block,tail", [(1, 1, 1, 128, 128, 5), (1, 1, 150, 64, 64, 0), (1, 1, 197, 64, 64, 0), (2, 3, 6, 128, 128, 78),
                                                  (1, 1, 200, 128, 64, 63), (2, 7, 67, 64, 128, 1), (1, 3, 171, 64, 64, 7),
-                                                 (2, 20, 64, 64, 64, 0), (1, 41, 64, 64, 64, 33)])
+                                                 (2, 20, 64, 64, 64, 0), (1, 41, 64, 64, 64, 33),
+                                                 (1, 6, 88, 128, 128, 40), (1, 7, 146, 128, 128, 0), (1, 21, 74, 128, 64, 9)])
 def test_shares_of_rows(B, H, Nb, D, block, tail, kind):
     import paper_2605_14513_amd as heart
 
@@ -85,3 +87,111 @@ def test_larger_workspaces_do_not_divide_rows(H, Nb, D, block):
     assert not torch.equal(divided, want)  # (sums in another order)
     for n in (asked - 16, asked + 16, 2 * asked):
         assert torch.equal(heart.heart_block_sparse_attn(q, k, v, block, gi, gc, workspace=ws[:n]), want), n
+
+
+# rows of 84 blocks, cut in five parts each ("parts": one head), in some twenty with short rows around them ("few"), and, with more
+# rows than places, by shares ("shares": six heads)
+@pytest.mark.parametrize("kind,H", [("parts", 1), ("few", 1), ("shares", 6)])
+@pytest.mark.parametrize("flags", [0, 1])
+def test_divided_rows_show_non_finite_inputs(kind, H, flags):
+    """A NaN or an infinity that reaches a row of the undivided launch reaches it in the divided one, and no other row."""
+    import paper_2605_14513_amd as heart
+
+    Nb, D, block = 88, 128, 128
+    N = Nb * block
+    g = torch.Generator(device="cuda").manual_seed(H)
+    q, k, v = (torch.randn((1, H, N, D), generator=g, device="cuda").bfloat16() for _ in range(3))
+    blk = lambda i: slice(i * block, (i + 1) * block)
+    nan_k, neg_k, inf_v, low = 30, 51, 70, 12  # key blocks that only some rows keep
+    k[0, 0, blk(nan_k).start + 3] = float("nan")
+    k[0, 0, blk(neg_k), 0] = float("-inf")
+    v[0, 0, blk(inf_v), 2] = float("inf")
+    k[0, 0, blk(low), 1], v[0, 0, blk(low), 2] = -400.0, float("nan")
+    q[0, 0, blk(0).start + 5] = float("nan")
+    q[0, 0, blk(2), 0] = q[0, 0, blk(3), 0] = 1.0
+    q[0, 0, blk(4), 0] = -1.0
+    q[0, 0, blk(6), 1] = 8.0
+    plain = [j for j in range(Nb) if j not in (nan_k, neg_k, inf_v, low)]
+    first = [plain, sorted(plain + [nan_k]), sorted(plain + [neg_k]), [neg_k], sorted(plain + [neg_k]), sorted(plain + [inf_v]),
+             sorted(plain + [low]), plain]
+    idx, cnt = np.zeros((1, H, Nb, Nb), np.int32), np.zeros((1, H, Nb), np.int32)
+    for h in range(H):
+        for i in range(Nb):
+            r = first[i] if h == 0 and i < len(first) else plain if kind == "parts" else [plain[(h + i) % len(plain)]]
+            idx[0, h, i, :len(r)], cnt[0, h, i] = r, len(r)
+    gi, gc = np_gpu(idx), np_gpu(cnt)
+    n_bytes = heart.heart_attn_balanced_workspace_bytes(q, block)
+    assert n_bytes > heart.heart_attn_workspace_bytes(q, block)
+    print(f"non-finite {kind} H={H} flags={flags}", flush=True)
+    res = []
+    for ws in (torch.full((n_bytes,), 255, dtype=torch.uint8, device="cuda"), None):
+        lse = torch.empty((1, H, N), device="cuda")
+        out = heart.heart_block_sparse_attn(q, k, v, block, gi, gc, workspace=ws, flags=flags, lse=lse)
+        res.append((out.float().cpu().numpy()[0], lse.cpu().numpy()[0]))
+    (out, lse), (one, lse1) = res
+    for h in range(H):
+        for i in range(Nb):
+            a, b = out[h, blk(i)], one[h, blk(i)]
+            assert np.array_equal(np.isnan(a), np.isnan(b)) and np.array_equal(np.isinf(a), np.isinf(b)), f"row {h} {i}"
+            assert np.array_equal(np.isneginf(lse[h, blk(i)]), np.isneginf(lse1[h, blk(i)])), f"row {h} {i}: lse"
+    # what the rows above must show, whichever launch
+    one = one[0]
+    assert np.isnan(one[blk(0)][5]).all() and np.isfinite(np.delete(one[blk(0)], 5, 0)).all()
+    assert np.isnan(one[blk(1)]).all() and np.isfinite(one[blk(2)]).all() and (one[blk(3)] == 0).all()
+    assert np.isnan(one[blk(4)]).all() and not np.isfinite(one[blk(5)][:, 2]).any()
+    assert np.isnan(one[blk(6)][:, 2]).all() and np.isfinite(one[7 * block:]).all()
+
+
+# counts outside of [0, Nb] count as its ends: in the search for a share as in the row itself
+@pytest.mark.parametrize("H,Nb,D,block", [(1, 200, 128, 64), (6, 88, 128, 128), (20, 64, 64, 64)])
+def test_divided_rows_clamp_the_counts(H, Nb, D, block):
+    import paper_2605_14513_amd as heart
+
+    rng = np.random.default_rng(H)
+    cnt = rng.integers(-3, Nb + 6, size=(1, H, Nb)).astype(np.int32)
+    cnt[0, 0, :2], cnt[0, -1, -2:] = (-3, Nb + 5), (Nb + 5, -3)
+    idx = rng.permuted(np.broadcast_to(np.arange(Nb, dtype=np.int32), (1, H, Nb, Nb)), axis=-1)
+    g = torch.Generator(device="cuda").manual_seed(H)
+    q, k, v = (torch.randn((1, H, Nb * block, D), generator=g, device="cuda").bfloat16() for _ in range(3))
+    ws = torch.empty(heart.heart_attn_balanced_workspace_bytes(q, block), dtype=torch.uint8, device="cuda")
+    assert ws.numel() > heart.heart_attn_workspace_bytes(q, block)
+    print(f"clamped counts H={H} Nb={Nb} D={D} block={block}", flush=True)
+    got, want = (heart.heart_block_sparse_attn(q, k, v, block, np_gpu(idx), np_gpu(c), workspace=ws)
+                 for c in (cnt, cnt.clip(0, Nb)))
+    assert torch.equal(got, want)
+
+
+def test_divided_rows_in_a_captured_graph():
+    """Captured once, replayed on other counts each time (other rows are divided elsewhere): the eager bits."""
+    import paper_2605_14513_amd as heart
+
+    H, Nb, D, block = 6, 88, 128, 128
+    g = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v = (torch.randn((1, H, Nb * block, D), generator=g, device="cuda").bfloat16() for _ in range(3))
+    idx = torch.arange(Nb, dtype=torch.int32, device="cuda").expand(1, H, Nb, Nb).contiguous()
+    counts = [torch.randint(0, Nb // d, (1, H, Nb), generator=g, dtype=torch.int32, device="cuda") for d in (2, 8, 1, 2)]
+    cnt, out = counts[0].clone(), torch.empty_like(q)
+    n_bytes = heart.heart_attn_balanced_workspace_bytes(q, block)
+    ws, ws2 = (torch.full((n_bytes,), 255, dtype=torch.uint8, device="cuda") for _ in range(2))
+
+    def call():
+        heart.heart_block_sparse_attn(q, k, v, block, idx, cnt, out=out, workspace=ws)
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        call()
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        call()
+    for i, c in enumerate(counts):
+        want = heart.heart_block_sparse_attn(q, k, v, block, idx, c, workspace=ws2)
+        cnt.copy_(c)
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        print(f"replay {i}", flush=True)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), f"replay {i}"
