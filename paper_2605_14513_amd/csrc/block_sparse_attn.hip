@@ -159,8 +159,8 @@ size_t attn_split_bytes(long long BH, long long Nb, int D, int block) {
 }
 
 // Shared rows.  Where a place works on at most a few rows, their uneven lengths decide when a launch ends: the
-// longest row alone takes as long as several of the mean.  With room for the parts
-// (heart_attn_balanced_workspace_bytes) lists are divided there, by one of three rules, and attn_merge_kernel adds up
+// longest row alone takes as long as several of the mean.  Where the caller asks for it (workspace_bytes of
+// heart_attn_balanced_workspace_bytes) lists are divided there, by one of three rules, and attn_merge_kernel adds up
 // the rows that were:
 //   shares  the kept blocks of all rows, row after row, are one sequence (lengths in half blocks) that is cut into equal
 //           shares, one per place
@@ -170,9 +170,10 @@ size_t attn_split_bytes(long long BH, long long Nb, int D, int block) {
 // Every workgroup finds the rule and its part or share from the kept counts by itself (read once, 16 KB at most), so there
 // is no plan, no queue and no atomic, and what is divided where, and with it the bits, is a function of the counts alone.
 // XCD x takes the x-th eighth of the parts or shares, so it sees an eighth of the heads.
-// What it costs: 1.5 to 3 us until a workgroup knows its share, and the merge (4 to 10 us).  Attention with its plan ->
-// with shares, lists of the timed fields: 20 heads of 101 rows (D = 64, block 64) 122 -> 92 us; D = 128, block 128: six
-// heads of 88 rows 153 -> 93, two of 248 436 -> 236, 21 of 74 164 -> 148; dense lists, four heads of 147 rows 760 -> 659.
+// What it costs: 1.5 to 3 us until a workgroup knows its share, and the merge (4 to 10 us).  Calls with a plan -> with
+// shares, lists of the timed fields, several seeds: 20 heads of 101 rows (D = 64, block 64) 99 to 127 -> 74 to 111 us; D = 128,
+// block 128: six heads of 88 rows 193 to 224 -> 146 to 159, two of 247 375 -> 204 to 237; D = 128, block 64: 21 heads of 73
+// rows 110 to 118 -> 96; dense lists, four heads of 147 rows (D = 128, block 128) 726 -> 669.
 constexpr int kShareGroup = 256, kShareMaxRows = 16 * kShareGroup;  // rows; counts are summed up in groups, four rows a lane
 constexpr int kShareMin = 8;       // shortest share
 constexpr int kSharePart = 2;      // fewest blocks of a part: a cut closer to an end of its row goes there

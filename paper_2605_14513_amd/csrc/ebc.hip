@@ -25,10 +25,10 @@
 //      ebc_second  y coefficients of the x coefficients with S_XY
 //      ebc_third   S_XYT; its last workgroup adds everything up
 //    Bound by latency: at 128 x 21 x 30 x 52 the matrix instructions are 7 us of the chip and the
-//    90 MB moved (half of them in the caches) some 18 us; the launches take 21 + 12 us, of
-//    which a table, a first load and a last sum each about 1 us.  Whole call 41.6 -> 33.9 us against three
+//    90 MB moved (half of them in the caches) some 18 us; the launches take 20 + 13 us, of
+//    which a table, a first load and a last sum each about 1 us.  Whole call 41.6 -> 33.0 us against three
 //    launches that counted 400 workgroups on one ticket, 257 us with twelve launches that convolved in fp64 on the
-//    vector units (results equal to 1e-15); 128 x 33 x 45 x 80 134 -> 119 us, 16 x 21 x 30 x 52 21.8 -> 16.9 us.
+//    vector units (results equal to 1e-15); 128 x 33 x 45 x 80 134 -> 119 us, 16 x 21 x 30 x 52 21.3 -> 16.7 us.
 //    A calibration run evaluates this once per (head, candidate, prompt-step), off the serving path.
 //
 //  heart_ebc_select       the one-candidate-per-head selection of Eq. 5 (minimum summed
@@ -424,12 +424,13 @@ __global__ __launch_bounds__(kEbcThreads, 3) void ebc_third_kernel(const double 
   ebc_finish<false>(0.0, ebc_block_sum(e_out, red), partials, f, out);
 }
 
-// The second and third step in one launch, for short t and y axes (latents have 21 to 33 and 30 to 45): a wavefront takes a (t, y) plane of one x coefficient of one channel, contracts y and then t, and keeps
+// The second and third step in one launch, for short t and y axes (latents have 21 to 33 and 30 to 45): a wavefront
+// takes a (t, y) plane of one x coefficient of one channel, contracts y and then t, and keeps
 // nothing but the two sums of squares.  With the plane's rows as the first operand and the table as the second the y
 // coefficients come out as (t = lane / 16 + 4 r, k = lane % 16) in register r, which is, unchanged, the second operand
 // of the t contraction's step r.  The table's operands over y stay in registers.  Bound by latency as the others: one
-// plane a wavefront at 128 x 21 x 30 x 52, 12 us in the place of two launches of 10 and 13 us and of 10 MB written and
-// read again (21 us with one ticket for its 864 workgroups and operands from LDS in every step).
+// plane a wavefront at 128 x 21 x 30 x 52, 13 us (14.7 under the profiler) in the place of two launches of 10 and 13 us and
+// of 10 MB written and read again (21 us with one ticket for its 864 workgroups and operands from LDS in every step).
 // Longest axes: two tiles of 16 coefficients over t; over y what the registers of a wavefront hold (16 steps took 35 of them to
 // scratch).  Whole call, three launches -> two, T = 3 to 63, X = 52: Y = 8 to 45 4 to 30 % faster at 16 and at 128 channels (16 x
 // 63 x 45 33.0 -> 30.8 us, 128 x 34 x 45 81.6 -> 78.7), Y = 49 to 63 up to 17 % slower (16 x 63 x 49 34.0 -> 40.0, 128 x 33 x 56
