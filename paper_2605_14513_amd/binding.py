@@ -174,15 +174,17 @@ def heart_pool_qk(q: torch.Tensor, k: torch.Tensor, block: int, qblk=None, kblk=
         raise ValueError("q and k must have the same shape")
     B, H, N, D = q.shape
     Nb = (N + block - 1) // block
-    f32 = dict(dtype=torch.float32, device=q.device)
-    qblk = torch.empty((B, H, Nb, D), **f32) if qblk is None else qblk
-    kblk = torch.empty((B, H, Nb, D), **f32) if kblk is None else kblk
-    qmean = torch.empty((B, H, D), **f32) if qmean is None else qmean
-    kmean = torch.empty((B, H, D), **f32) if kmean is None else kmean
-    for t, n, name in ((qblk, B * H * Nb * D, "qblk must hold [B,H,Nb,D]"), (kblk, B * H * Nb * D, "kblk must hold [B,H,Nb,D]"),
-                       (qmean, B * H * D, "qmean must hold [B,H,D]"), (kmean, B * H * D, "kmean must hold [B,H,D]")):
-        if t.numel() < n:
-            raise ValueError(name)
+    if qblk is None or kblk is None or qmean is None or kmean is None:
+        f32 = dict(dtype=torch.float32, device=q.device)
+        qblk = torch.empty((B, H, Nb, D), **f32) if qblk is None else qblk
+        kblk = torch.empty((B, H, Nb, D), **f32) if kblk is None else kblk
+        qmean = torch.empty((B, H, D), **f32) if qmean is None else qmean
+        kmean = torch.empty((B, H, D), **f32) if kmean is None else kmean
+    n = B * H * D
+    if qblk.numel() < n * Nb or kblk.numel() < n * Nb:
+        raise ValueError("qblk and kblk must hold [B,H,Nb,D]")
+    if qmean.numel() < n or kmean.numel() < n:
+        raise ValueError("qmean and kmean must hold [B,H,D]")
     shape = make_shape(q, k, block)
     rc = lib.heart_pool_qk(ctypes.byref(shape), _dev(q, torch.bfloat16, "q", False),
                            _dev(k, torch.bfloat16, "k", False), _dev(qblk, torch.float32, "qblk"),
