@@ -21,8 +21,12 @@
 //   XOR-swizzled by row so that the fragment reads are conflict free), double-buffered
 //   (128 KB, 64 KB), one barrier per stage, the loads of the next stage in flight during the MFMAs
 //   of the current one (lines of later stages requested into the L2 as well: 613 -> 625 us); fragments are
-//   read one contraction step ahead and the barrier sits in the shadow of the last step's
-//   MFMAs.  A wavefront owns 64 (32) reduced queries against 128 reduced keys (S^T layout: keys
+//   read one contraction step ahead, and fragment reads and loads are issued between the MFMAs, one or two
+//   behind each: all eight loads of a wavefront in one go, right after the barrier, held the MFMAs behind them
+//   back until the address unit had taken them (estimator and selection, 40 heads of 32760 tokens 674 -> 656 us,
+//   10 of 75600 960 -> 917, 20 of 32760 at D = 64 200 -> 184, 12 of 20280 in blocks of 64 193 -> 180, six of 3565 29.3 -> 26.8).  Not the flight time of the loads: stages of half the
+//   depth, five buffers and four stages ahead took 709 to 720 us in the place of 660, four wavefronts of 128 x 128,
+//   one a SIMD, 730.  A wavefront owns 64 (32) reduced queries against 128 reduced keys (S^T layout: keys
 //   along the accumulator rows), so a query's maximum over those keys is a per-lane
 //   reduction plus one exchange with the partner lane.  The epilogue writes one record per
 //   (reduced query, 128 keys): the maximum m and the 16 sums over 8 keys of exp2(L - m).
@@ -148,21 +152,21 @@ __global__ __launch_bounds__(2 * kTile, 2) void antidiag_tile_kernel(
   }
   // (the compiler does not see the LDS write of these instructions: their completion is
   // awaited explicitly before the barrier that publishes the stage)
-  auto dma_stage = [&](int st, int buf) __attribute__((always_inline)) {
-    const int r = st / SPR, d0 = (st % SPR) * 64;
-    const uint32_t qo = (uint32_t)(S - 1 - r) * (uint32_t)(qsn * 2) + (uint32_t)d0 * 2u;
-    const uint32_t ko = (uint32_t)r * (uint32_t)(ksn * 2) + (uint32_t)d0 * 2u;
-#pragma unroll
-    for (int ii = 0; ii < 4; ++ii) {
-      const uint32_t dst_a = smem_lds + (uint32_t)(buf * 2 * kAdTileB + (4 * wave + ii) * 1024);
-      const uint32_t dst_b = dst_a + (uint32_t)kAdTileB;
-      uint32_t m0_saved;  // (M0 carries the LDS destination; saved and restored for the compiler)
+  constexpr int kLoads = 8;  // of a stage and wavefront: the keys' and the queries' in turn
+  auto dma = [&](int st, int buf, int i) __attribute__((always_inline)) {
+    const int r = st / SPR, d0 = (st % SPR) * 64, ii = i >> 1;
+    const uint32_t dst = smem_lds + (uint32_t)((buf * 2 + (i & 1)) * kAdTileB + (4 * wave + ii) * 1024);
+    uint32_t m0_saved;  // (M0 carries the LDS destination; saved and restored for the compiler)
+    if (i & 1) {
+      const uint32_t qo = (uint32_t)(S - 1 - r) * (uint32_t)(qsn * 2) + (uint32_t)d0 * 2u;
       asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
                    "buffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
-                   : "=&s"(m0_saved) : "s"(dst_a), "v"(k_dma[ii] + ko), "s"(k_rs) : "memory");
+                   : "=&s"(m0_saved) : "s"(dst), "v"(q_dma[ii] + qo), "s"(q_rs) : "memory");
+    } else {
+      const uint32_t ko = (uint32_t)r * (uint32_t)(ksn * 2) + (uint32_t)d0 * 2u;
       asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
                    "buffer_load_dwordx4 %2, %3, 0 offen lds\n\ts_mov_b32 m0, %0"
-                   : "=&s"(m0_saved) : "s"(dst_b), "v"(q_dma[ii] + qo), "s"(q_rs) : "memory");
+                   : "=&s"(m0_saved) : "s"(dst), "v"(k_dma[ii] + ko), "s"(k_rs) : "memory");
     }
   };
   auto wait_loads_and_barrier = [&]() __attribute__((always_inline)) {
@@ -186,55 +190,63 @@ __global__ __launch_bounds__(2 * kTile, 2) void antidiag_tile_kernel(
   struct Frags {
     AdFrag a[4], b[QT];
   };
-  auto read_frags = [&](Frags &f, int buf, int ks) __attribute__((always_inline)) {
+  constexpr int kFrags = 4 + QT, kMfmas = 4 * QT;
+  auto read_frag = [&](Frags &f, int buf, int ks, int i) __attribute__((always_inline)) {
     const unsigned char *A = smem + buf * 2 * kAdTileB + wi * 128 * kAdRowB;
     const unsigned char *B = smem + buf * 2 * kAdTileB + kAdTileB + wj * 32 * QT * kAdRowB;
-#pragma unroll
-    for (int qt = 0; qt < QT; ++qt)
-      f.b[qt].u = *reinterpret_cast<const ad_u32x4 *>(B + qt * 32 * kAdRowB + foff[ks]);
-#pragma unroll
-    for (int kt = 0; kt < 4; ++kt)
-      f.a[kt].u = *reinterpret_cast<const ad_u32x4 *>(A + kt * 32 * kAdRowB + foff[ks]);
+    if (i < QT)
+      f.b[i].u = *reinterpret_cast<const ad_u32x4 *>(B + i * 32 * kAdRowB + foff[ks]);
+    else
+      f.a[i - QT].u = *reinterpret_cast<const ad_u32x4 *>(A + (i - QT) * 32 * kAdRowB + foff[ks]);
   };
-  auto mfma8 = [&](const Frags &f) __attribute__((always_inline)) {
+  // The MFMAs of one contraction step; behind those of the first half the reads of the next step's fragments (step ks of
+  // buffer `buf`), behind each what extra(i) issues.
+  auto step = [&](const Frags &f, Frags &next, int buf, int ks, auto &&extra) __attribute__((always_inline)) {
 #pragma unroll
-    for (int kt = 0; kt < 4; ++kt)
+    for (int i = 0; i < kMfmas; ++i) {
+      acc[i / QT][i % QT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i / QT].v, f.b[i % QT].v, acc[i / QT][i % QT], 0, 0, 0);
 #pragma unroll
-      for (int qt = 0; qt < QT; ++qt)
-        acc[kt][qt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[kt].v, f.b[qt].v, acc[kt][qt], 0, 0, 0);
+      for (int j = 0; j < kFrags; ++j)
+        if (j * (kMfmas / 2) / kFrags == i) read_frag(next, buf, ks, j);
+      extra(i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   };
 
-  // Per stage: the fragments of a contraction step are read one step before their MFMAs, and
-  // the barrier that hands over the next stage sits between the reads of the stage's last
-  // step and its MFMAs, so that the barrier and the first LDS reads of the next stage run in
-  // the shadow of eight MFMAs.  By the barrier a wavefront has completed all its reads of the
-  // current buffer and its loads of the next stage into the other one; right after it, it
-  // issues the loads of the stage after that into the buffer just released.  Loads past the
-  // last stage repeat the last stage (into a buffer nobody reads any more).
+  // Per stage: the barrier that hands over the next stage sits before the MFMAs of the stage's last step.  By then a
+  // wavefront has completed all its reads of the current buffer and its loads of the next stage into the other one;
+  // behind those MFMAs it issues the first half of the loads of the stage after that into the buffer just released, behind
+  // those of the next step the other half (the later a load, the shorter its flight: all within the
+  // first step, or three quarters, 0.5 to 2 % slower).  Loads past the last stage repeat the last stage (into a buffer
+  // nobody reads any more).
   const int n_stages = kTile * tk < M ? S * SPR : 0;  // (a tile of keys past the end: records without weight)
   const int last = max(n_stages - 1, 0);
+  constexpr int kHalf = kLoads / 2;
   Frags f0, f1;
-  dma_stage(0, 0);
+#pragma unroll
+  for (int i = 0; i < kLoads; ++i) dma(0, 0, i);
   wait_loads_and_barrier();
-  dma_stage(min(1, last), 1);
-  read_frags(f0, 0, 0);
+#pragma unroll
+  for (int i = 0; i < kHalf; ++i) dma(min(1, last), 1, i);
+#pragma unroll
+  for (int j = 0; j < kFrags; ++j) read_frag(f0, 0, 0, j);
+  auto no_extra = [](int) {};
   for (int st = 0; st < n_stages; ++st) {
-    const int buf = st & 1;
-    read_frags(f1, buf, 1);
-    mfma8(f0);
-    __builtin_amdgcn_sched_barrier(0);
-    read_frags(f0, buf, 2);
-    mfma8(f1);
-    __builtin_amdgcn_sched_barrier(0);
-    read_frags(f1, buf, 3);
-    mfma8(f0);
-    __builtin_amdgcn_sched_barrier(0);
+    const int buf = st & 1, st1 = min(st + 1, last), st2 = min(st + 2, last);
+    step(f0, f1, buf, 1, [&](int i) {
+#pragma unroll
+      for (int j = 0; j < kHalf; ++j)
+        if (j * kMfmas / kHalf == i) dma(st1, buf ^ 1, kHalf + j);
+    });
+    step(f1, f0, buf, 2, no_extra);
+    step(f0, f1, buf, 3, no_extra);
     wait_loads_and_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    dma_stage(min(st + 2, last), buf);
-    read_frags(f0, buf ^ 1, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    mfma8(f1);
+    step(f1, f0, buf ^ 1, 0, [&](int i) {
+#pragma unroll
+      for (int j = 0; j < kHalf; ++j)
+        if (j * kMfmas / kHalf == i) dma(st2, buf, j);
+    });
   }
   // loads of the repeated last stage may still be in flight towards LDS
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -247,20 +259,24 @@ __global__ __launch_bounds__(2 * kTile, 2) void antidiag_tile_kernel(
   const int NbP = 16 * MT;
 #pragma unroll
   for (int qt = 0; qt < QT; ++qt) {
+    if (key0 + 128 > M) {  // (uniform: the records of the last keys)
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (key0 + 32 * kt + 8 * (r >> 2) + 4 * hf + (r & 3) >= M) acc[kt][qt][r] = ninf;
+    }
+    // The maximum of the logits as they come out of the matrix cores, and exp2(scale L - scale max) in one fused
+    // operation each (one rounding less than scaled logits and their difference, and two instructions).
     float m = ninf;
 #pragma unroll
     for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = key0 + 32 * kt + 8 * (r >> 2) + 4 * hf + (r & 3);
-        const float x = key < M ? acc[kt][qt][r] * scale_log2 : ninf;
-        acc[kt][qt][r] = x;
-        m = fmaxf(m, x);
-      }
+      for (int r = 0; r < 16; ++r) m = fmaxf(m, acc[kt][qt][r]);
     {
       uint32_t s0, s1;
       swap_halves32(__float_as_uint(m), s0, s1);
-      m = fmaxf(__uint_as_float(s0), __uint_as_float(s1));
+      m = fmaxf(__uint_as_float(s0), __uint_as_float(s1)) * scale_log2;
     }
     // (a record whose 128 keys are all past the end has m = -inf and all sums zero)
     const float mm = m == ninf ? 0.f : m;
@@ -271,7 +287,7 @@ __global__ __launch_bounds__(2 * kTile, 2) void antidiag_tile_kernel(
       for (int g = 0; g < 4; ++g) {
         float s = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s += __builtin_amdgcn_exp2f(acc[kt][qt][4 * g + i] - mm);
+        for (int i = 0; i < 4; ++i) s += __builtin_amdgcn_exp2f(fmaf(acc[kt][qt][4 * g + i], scale_log2, -mm));
         uint32_t s0, s1;
         swap_halves32(__float_as_uint(s), s0, s1);
         sums[kt][g] = __uint_as_float(s0) + __uint_as_float(s1);
