@@ -49,6 +49,7 @@
 // workspace an XCD works on a contiguous eighth of the query blocks of every head, in index
 // order.  With fewer query blocks than places for workgroups the lists themselves are split
 // (kSplit below).
+#include <chrono>
 #include <type_traits>
 
 #include "heart_internal.h"
@@ -120,7 +121,7 @@ constexpr int kHeadsInTurn = 2;
 // Split rows.  A launch with fewer rows than the chip has places for workgroups (two per CU, four
 // of the small ones at block 64) would leave the rest idle while each row walks its list
 // alone; there S workgroups take a part of each list and write their unnormalised outputs, and
-// attn_merge_kernel adds them up.  S is as many as there are places for, with at least kSplitMinBlocks
+// attn_merge_kernel (or, of two parts, the second of them) adds them up.  S is as many as there are places for, with at least kSplitMinBlocks
 // blocks a part where lists are full: a part costs about 10 us beside its blocks (launch, first
 // loads, 64 KB written and read again), a block 0.8 us (64 keys, D = 64) to 1.7 us (128 keys,
 // D = 128).  All parts start at once, so such a launch needs no plan.  A function of the sizes only.
@@ -133,6 +134,16 @@ constexpr int kLdsPerCu = 160 * 1024;
 // floats of one wavefront's part: accumulators, reference exponent and row sum of every lane
 template <int D>
 constexpr int kPartFloats = 64 * (D / 2) + 128;
+// Rows of few parts are added up by the workgroup that leaves the last of them (kSplitMerged, kSharedMerged).  That saves a
+// launch, and of the two parts at a cut the one that ends later, mostly the end of a share, stays in registers: a 64 KB part (D =
+// 128, block 128) is written and read once in the place of twice, which bound the launch (11.7 us for 512 cuts, 5.7 TB/s).  It
+// reads one part after the other, though, and of many parts a launch of a wavefront for 32 columns of 32 rows is the faster
+// way.  Steps and calls with the launch -> without, us: 18 heads of 33 rows (D = 128, block 128) 91.1 -> 85.1, four of 58 (two
+// shares a row) 44.0 -> 37.7, two of five (three) 31.8 -> 29.7, 20 of 101 (D = 64, block 64) 101.0 -> 96.4, two of 604 140 -> 137;
+// 18 of eleven in two split parts 48.4 -> 44.9; but six of six in four shares a row 33.4 -> 34.5, two of 16 in four split
+// parts at D = 64 21.9 -> 23.6.
+constexpr int kMergeParts = 2;     // split rows
+constexpr int kMergeShares = 4;    // more shares for a row than this
 constexpr float kNoKeys = -1.f;  // in the place of the row sum: a part without keys (a sum is not negative, but may be NaN)
 
 // places for workgroups on the chip
@@ -160,8 +171,8 @@ size_t attn_split_bytes(long long BH, long long Nb, int D, int block) {
 
 // Shared rows.  Where a place works on at most a few rows, their uneven lengths decide when a launch ends: the
 // longest row alone takes as long as several of the mean.  Where the caller asks for it (workspace_bytes of
-// heart_attn_balanced_workspace_bytes) lists are divided there, by one of three rules, and attn_merge_kernel adds up
-// the rows that were:
+// heart_attn_balanced_workspace_bytes) lists are divided there, by one of three rules, and the rows that were
+// are added up by the workgroup that leaves the last part, or by attn_merge_kernel (kMergeShares):
 //   shares  the kept blocks of all rows, row after row, are one sequence (lengths in half blocks) that is cut into equal
 //           shares, one per place
 //   parts   every row is split into parts of at most L blocks, L as small as the places allow; each workgroup has one
@@ -170,7 +181,7 @@ size_t attn_split_bytes(long long BH, long long Nb, int D, int block) {
 // Every workgroup finds the rule and its part or share from the kept counts by itself (read once, 16 KB at most), so there
 // is no plan, no queue and no atomic, and what is divided where, and with it the bits, is a function of the counts alone.
 // XCD x takes the x-th eighth of the parts or shares, so it sees an eighth of the heads.
-// What it costs: 1.5 to 3 us until a workgroup knows its share, and the merge (4 to 10 us).  Calls with a plan -> with
+// What it costs: 1.5 to 3 us until a workgroup knows its share, and the merge (2 to 4 us in the workgroups, 4 to 13 as a launch).  Calls with a plan -> with
 // shares, lists of the timed fields, several seeds: 20 heads of 101 rows (D = 64, block 64) 99 to 127 -> 74 to 111 us; D = 128,
 // block 128: six heads of 88 rows 193 to 224 -> 146 to 159, two of 247 375 -> 204 to 237; D = 128, block 64: 21 heads of 73
 // rows 110 to 118 -> 96; dense lists, four heads of 147 rows (D = 128, block 128) 726 -> 669.
@@ -215,7 +226,7 @@ int attn_shares(long long BH, long long Nb, int D, int block, bool dense) {
   return (int)((most < places ? most : places) + kNumXcd - 1) / kNumXcd * kNumXcd;
 }
 
-// owners of split rows (row, further parts, share), then two parts per share: the one a share starts with and the one it ends with
+// owners of divided rows (row, further parts, share) or tickets, then two parts per share: the one a share starts with and the one it ends with
 size_t attn_share_bytes(long long BH, long long Nb, int D, int block, bool dense) {
   const int n = attn_shares(BH, Nb, D, block, dense);
   if (n == 0) return 0;
@@ -223,7 +234,7 @@ size_t attn_share_bytes(long long BH, long long Nb, int D, int block, bool dense
   return (size_t)n * (sizeof(int4) + 2 * (size_t)(block / 32) * part * sizeof(float));
 }
 
-// Adds up the parts of a row: one wavefront per (32 query rows, 32 columns of the output), lanes
+// Adds up the parts of rows where attn_kernel leaves that to a second launch: one wavefront per (32 query rows, 32 columns of the output), lanes
 // as in attn_kernel.  Parts of item i are i * n_split .. ; of shared rows (`owner` given) the last part of share k
 // and the first ones of the shares after it.  Bound by latency (the parts come from the L2s and the memory-side
 // cache): four parts at a time.
@@ -305,9 +316,16 @@ __global__ __launch_bounds__(D * 2) void attn_merge_kernel(const float *__restri
   }
 }
 
+// Tickets of divided rows: `mark`, which no other call has, with the number of parts that are there in its lowest bits, so that
+// memory of any contents is a ticket without parts.  The workgroup that finds all others there sets it back to zero: the
+// next replay of a captured call has the same mark.
+constexpr unsigned kMarkCount = 0xffff;
+static_assert(kShareMaxRows <= (int)kMarkCount && kMergeParts == 2, "parts of a row");
+
 // kMode: kPlanned, rows as a plan (or, without one, the workgroup's number) says; kSplitRows: a workgroup takes part of
 // one row's list and leaves it in `part`; kSharedRows: a share of all rows
-enum AttnMode { kPlanned, kSplitRows, kSharedRows };
+// kSplitMerged, kSharedMerged: the same, and the workgroup that leaves the last part of a row adds them up
+enum AttnMode { kPlanned, kSplitRows, kSharedRows, kSplitMerged, kSharedMerged };
 template <int D, int BLK, bool kExact, AttnMode kMode>
 __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k,
@@ -316,8 +334,10 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     long long vsn, long long osb, long long osh, long long osn, int H, int BH, int N, int Nb,
     const int *__restrict__ kept_idx, const int *__restrict__ kept_count, float scale_log2e,
     float *__restrict__ lse, int *__restrict__ plan, const int *__restrict__ seq, int *__restrict__ cursors,
-    int cursor_step, float *__restrict__ part, int4 *__restrict__ owner, int n_split, int n_few) {
-  constexpr bool kSplit = kMode == kSplitRows, kShare = kMode == kSharedRows;
+    int cursor_step, float *__restrict__ part, int4 *__restrict__ owner, int n_split, int n_few,
+    unsigned long long mark) {
+  constexpr bool kSplit = kMode == kSplitRows || kMode == kSplitMerged, kShare = kMode == kSharedRows || kMode == kSharedMerged;
+  constexpr bool kMerge = kMode == kSplitMerged || kMode == kSharedMerged;
   constexpr int NT = BLK * 2;            // threads
   constexpr int NW = NT / 64;            // wavefronts
   constexpr int DT = D / 32;             // 32-wide d tiles of the output
@@ -467,8 +487,8 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     const size_t row = (size_t)bh * Nb + qb;
     idx = kept_idx + row * Nb;
     if constexpr (kShare) {
-      cnt = e_end - e_begin;
-      idx += e_begin;
+      cnt = __builtin_amdgcn_readfirstlane(e_end - e_begin);
+      idx += __builtin_amdgcn_readfirstlane(e_begin);
     } else {
       cnt = min(kept_count[row], Nb);
     }
@@ -910,7 +930,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     } else {
       e_begin = share_blocks(cut0 - row0, row_cnt);
     }
-    if (t == 0) owner[blockIdx.x] = int4{-1, 0, 0, 0};
+    if (!kMerge && t == 0) owner[blockIdx.x] = int4{-1, 0, 0, 0};
     if (share >= s1) return;
     if (!parts && e_begin > 0 && e_begin == row_cnt) next_row();
   } else if (kMode == kPlanned && plan) {
@@ -940,7 +960,46 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     const int qb0 = x0 * per + (int)(slot % per);
     if (qb0 < Nb) item = (int)(slot / per) * Nb + qb0;  // else: padding of the last eighth
   }
+  // (kMerge) The parts of a row are n, this one is number `mine`; the first is that of share k0.  The end of a share is mostly the
+  // last of two parts: if the other one is there this one stays in registers.  (Asked while the last loads are awaited.)
+  int n = n_split, mine = split, k0 = share;
+  bool last = false;
+  auto ticket = [&]() __attribute__((always_inline)) -> unsigned long long * {
+    // (one reference exponent per query: the upper half of its 64 places in a row's first part holds the row's ticket)
+    return kShare ? reinterpret_cast<unsigned long long *>(owner + k0)
+                  : reinterpret_cast<unsigned long long *>(part + (size_t)item * n_split * NW * kPartFloats<D> + 64 * 16 * DT + 32);
+  };
+  auto arrived = [&](unsigned long long v) __attribute__((always_inline)) -> int {
+    return (v & ~(unsigned long long)kMarkCount) == mark && (int)(v & kMarkCount) < n ? (int)(v & kMarkCount) : 0;
+  };
+  // (an empty part, cnt = 0, comes from split rows only)
+  auto partial = [&]() __attribute__((always_inline)) -> bool { return kSplit || (kShare && e_end - e_begin < row_cnt); };
+  auto find_parts = [&]() __attribute__((always_inline)) {
+    last = false;
+    if constexpr (kShare) {
+      if (parts) {
+        n = parts;
+        mine = share - row0;
+        k0 = row0;
+      } else {
+        k0 = share;
+        while (share_blocks(share_cut(k0) - row0, row_cnt) > 0) --k0;
+        mine = share - k0;
+        n = mine + 1;
+        // (a part has two blocks at least, so the row has two: cuts behind it give all of its blocks, and the loop ends)
+        for (int k = share + 1; share_blocks(share_cut(k) - row0, row_cnt) < row_cnt; ++k) ++n;
+      }
+      n = __builtin_amdgcn_readfirstlane(n);
+      k0 = __builtin_amdgcn_readfirstlane(k0);
+      mine = __builtin_amdgcn_readfirstlane(mine);
+      if (mine == 0 && n == 2) {
+        if (t == 0) s_item = arrived(__hip_atomic_load(ticket(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 1;
+        last = true;  // (if s_item says so)
+      }
+    }
+  };
   while (kShare ? in_share() : item >= 0 && item < BH * Nb) {
+  if constexpr (kMode == kSharedMerged) item = __builtin_amdgcn_readfirstlane(item);
   begin_item(item);
   // (thread 0) cursor value and item id of the NEXT item.  The cursor is advanced only in
   // the last loop body, not earlier: items are then started in list order up to about a
@@ -1113,6 +1172,8 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
 #pragma unroll
       for (int i = 0; i < EPB; ++i) jb[NE - EPB + i] = jn[i];
     }
+    if constexpr (kMerge)
+      if (partial()) find_parts();
     // loads of stages past the end may still be in flight towards LDS
     wait_loads_and_barrier();
   }
@@ -1125,8 +1186,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     }
   }
 
-  const bool partial = kSplit || (kShare && e_end - e_begin < row_cnt);
-  if (partial) {
+  if (!kMerge && partial()) {
     // ---- part of a row: unnormalised output and its softmax state, as the lanes hold them ----
     const int slot = kShare ? 2 * share + (e_begin == 0) : item * n_split + split;
     float *dst = part + ((size_t)slot * NW + wave) * kPartFloats<D>;
@@ -1152,6 +1212,115 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     if (kSplit || parts || e_end < row_cnt) break;
     next_row();
     continue;
+  }
+
+  if constexpr (kMerge) if (partial()) {
+    // ---- the same part, or, if the others are there, their sum -------------------------------
+    constexpr int kAgent = 16;  // (sc1: past the L2 of this XCD, where the workgroups of all XCDs meet)
+    constexpr int kStateB = 64 * 16 * DT * 4;  // byte offset of the state behind the accumulators
+    auto part_rsrc = [&](int s) __attribute__((always_inline)) -> __amdgpu_buffer_rsrc_t {
+      const int slot = kShare ? 2 * (k0 + s) + (s == 0) : item * n_split + s;
+      return head_rsrc(reinterpret_cast<const uint16_t *>(part + (size_t)slot * NW * kPartFloats<D>),
+                       (uint32_t)(NW * kPartFloats<D> * sizeof(float)));
+    };
+    uint32_t ln = (uint32_t)lane;
+    asm volatile("" : "+v"(ln));  // (offsets made here: kept through the MFMA stream they would cost it registers)
+    const uint32_t part_off = (uint32_t)(wave * kPartFloats<D> * sizeof(float)) + 16u * ln;
+    const uint32_t state_off = (uint32_t)(wave * kPartFloats<D> * sizeof(float)) + (uint32_t)kStateB + 4u * ln;
+    const uint32_t ref_off = state_off - 4u * (ln & 32u);
+    last = last && __builtin_amdgcn_readfirstlane(s_item) != 0;
+    if (!last) {
+      const __amdgpu_buffer_rsrc_t dst = part_rsrc(mine);
+      if (ln < 32u) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(m_ref), dst, ref_off, 0, kAgent);
+      __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(cnt > 0 ? l_run : kNoKeys), dst, state_off + 256u, 0, kAgent);
+      if (cnt > 0) {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const f32x4_t x = {o[dt][4 * g], o[dt][4 * g + 1], o[dt][4 * g + 2], o[dt][4 * g + 3]};
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, x), dst, part_off + (uint32_t)((4 * dt + g) * 1024), 0, kAgent);
+          }
+      }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      if (t == 0) {
+        unsigned long long v = __hip_atomic_load(ticket(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int c;
+        do {
+          c = arrived(v);
+        } while (!__hip_atomic_compare_exchange_strong(ticket(), &v, mark | (unsigned long long)(c + 1), __ATOMIC_RELAXED,
+                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        s_item = c == n - 1;
+      }
+      __syncthreads();
+      last = __builtin_amdgcn_readfirstlane(s_item) != 0;
+      __syncthreads();
+    }
+    if (!last) {
+      if (kSplit || parts || e_end < row_cnt) break;
+      next_row();
+      continue;
+    }
+    if (t == 0) __hip_atomic_store(ticket(), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // ---- the last part of a row: the sum of all, in their order whichever was the last --------
+    // One of two parts is added to the registers; of more, this one too is read again (one more array of accumulators does not
+    // fit the registers).  (A part whose logits are all NaN or -inf keeps the reference -inf: its weight is 0, but its sums
+    // count, because a NaN among them has to reach the result.)
+    f32x16_t x[DT];
+    float ms, ls;
+    auto load_part = [&](int s) __attribute__((always_inline)) {
+      const __amdgpu_buffer_rsrc_t src = part_rsrc(s);
+      ms = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(src, ref_off, 0, kAgent));
+      ls = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(src, state_off + 256u, 0, kAgent));
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4_t y = __builtin_bit_cast(
+              f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(src, part_off + (uint32_t)((4 * dt + g) * 1024), 0, kAgent));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[dt][4 * g + e] = y[e];
+        }
+    };
+    // (accumulators of a part without keys are not written)
+    auto has_keys = [&](float sum) -> bool {
+      return __builtin_amdgcn_readfirstlane(__float_as_int(sum)) != __float_as_int(kNoKeys);
+    };
+    if (kSplit || n == 2) {
+      load_part(1 - mine);
+      if (has_keys(ls)) {
+        // (products rounded on their mine: their sum does not depend on which of the two is the own part)
+#pragma clang fp contract(off)
+        const float m_new = fmaxf(m_ref, ms), m_fin = m_new == -__builtin_inff() ? 0.f : m_new;
+        const float w = __builtin_amdgcn_exp2f(m_ref - m_fin), wx = __builtin_amdgcn_exp2f(ms - m_fin);
+        l_run = l_run * w + ls * wx;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[dt][r] = o[dt][r] * w + x[dt][r] * wx;
+        m_ref = m_new;
+      }
+    } else {
+      m_ref = -__builtin_inff();
+      l_run = 0.f;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
+      for (int s = 0; s < n; ++s) {
+        load_part(s);
+        if (!has_keys(ls)) continue;
+        const float m_new = fmaxf(m_ref, ms), m_fin = m_new == -__builtin_inff() ? 0.f : m_new;
+        const float alpha = __builtin_amdgcn_exp2f(m_ref - m_fin), w = __builtin_amdgcn_exp2f(ms - m_fin);
+        l_run = fmaf(ls, w, l_run * alpha);
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[dt][r] = fmaf(x[dt][r], w, o[dt][r] * alpha);
+        m_ref = m_new;
+      }
+    }
   }
 
   // ---- epilogue: normalise, stage through LDS, coalesced bf16 store -----------------------
@@ -1189,7 +1358,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     __syncthreads();  // everyone has read the output staging before the next row's loads
     continue;
   }
-  if (!plan) break;
+  if (kSplit || !plan) break;
   if (wave == 0) {
     if (item_next < 0) item_next = take();
     if (lane == 0) s_item = item_next;
@@ -1199,29 +1368,48 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   }  // work loop
 }
 
+// A mark that no other call has (kMarkCount: its low bits are zero): counted from a place that the clock and the address space
+// of the process choose.
+static unsigned long long call_mark() {
+  static std::atomic<unsigned long long> next{0};
+  unsigned long long m = next.load(std::memory_order_relaxed);
+  if (m == 0) {
+    unsigned long long x = (unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count() ^
+                           (unsigned long long)reinterpret_cast<uintptr_t>(&next);
+    x = (x ^ (x >> 30)) * 0xbf58476d1ce4e5b9ull;  // (the finaliser of SplitMix64, Steele et al. 2014)
+    x = (x ^ (x >> 27)) * 0x94d049bb133111ebull;
+    next.compare_exchange_strong(m, ((x ^ (x >> 31)) & ~(unsigned long long)kMarkCount) | (kMarkCount + 1ull));
+  }
+  return next.fetch_add(kMarkCount + 1ull, std::memory_order_relaxed);
+}
+
 template <int D, int BLK, bool kExact>
 static int launch_attn_t(const heart_shape &s, const void *q, const void *k, const void *v,
                          const int *kept_idx, const int *kept_count, float scale, void *out,
                          float *lse, int *order, size_t order_bytes, hipStream_t st) {
   const int Nb = (s.N + BLK - 1) / BLK;
   const int BH = s.B * s.H;
+  const long long n_items = (long long)BH * Nb;
   const int n_split = order ? attn_split(BH, Nb, D, BLK) : 1;
   const int n_share = order ? attn_shares(BH, Nb, D, BLK, false) : 0;
   // (exactly that size asks for shares: a larger buffer kept for several shapes is one that knows nothing of them)
   const bool share = n_share > 0 && order_bytes == attn_balanced_bytes(BH, Nb, D, BLK, false);
   const bool split = !share && n_split > 1 && order_bytes >= attn_split_bytes(BH, Nb, D, BLK);
   const size_t lds = 4 * (size_t)kStageRows<D, BLK> * D * 2;  // >= BLK * (D + 8) * 2 of the output staging
-  const AttnMode mode = share ? kSharedRows : split ? kSplitRows : kPlanned;
-  auto kern = share ? attn_kernel<D, BLK, kExact, kSharedRows>
-              : split ? attn_kernel<D, BLK, kExact, kSplitRows> : attn_kernel<D, BLK, kExact, kPlanned>;
+  const bool merged = (share && n_share < kMergeShares * n_items) || (split && n_split <= kMergeParts);
+  const AttnMode mode = share ? (merged ? kSharedMerged : kSharedRows) : split ? (merged ? kSplitMerged : kSplitRows) : kPlanned;
+  auto kern = mode == kSharedMerged  ? attn_kernel<D, BLK, kExact, kSharedMerged>
+              : mode == kSharedRows  ? attn_kernel<D, BLK, kExact, kSharedRows>
+              : mode == kSplitMerged ? attn_kernel<D, BLK, kExact, kSplitMerged>
+              : mode == kSplitRows   ? attn_kernel<D, BLK, kExact, kSplitRows>
+                                     : attn_kernel<D, BLK, kExact, kPlanned>;
   const int dev = current_device();
   if (dev < 0) return fail(HEART_EHIP, "heart_block_sparse_attn: cannot identify the current device");
-  static DeviceFlags attr_set[3];  // per instantiation: the attribute is per function and device
+  static DeviceFlags attr_set[5];  // per instantiation: the attribute is per function and device
   if (hipError_t e = set_max_lds_once(attr_set[mode], dev, reinterpret_cast<const void *>(kern), (int)lds))
     return fail(HEART_EHIP, "hipFuncSetAttribute(max dynamic LDS %zu): %s", lds, hipGetErrorString(e));
   const float sc = scale > 0.f ? scale : 1.0f / sqrtf((float)D);
   const float scale_log2e = sc * 1.4426950408889634f;
-  const long long n_items = (long long)BH * Nb;
   long long grid = (long long)BH * ((Nb + kNumXcd - 1) / kNumXcd) * kNumXcd;
   int n_few = 0;  // (a plan: see working_groups)
   float *part = nullptr;
@@ -1261,9 +1449,9 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
                      s.k_stride[1], s.k_stride[2], s.v_stride[0], s.v_stride[1], s.v_stride[2],
                      s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, BH, s.N, Nb, kept_idx,
                      kept_count, scale_log2e, lse, order, seq, spread ? spread : order,
-                     spread ? kCursorSpread : 1, part, owner, n_split, n_few);
+                     spread ? kCursorSpread : 1, part, owner, n_split, n_few, merged ? call_mark() : 0ull);
   if (int rc = check_launch("attn_kernel")) return rc;
-  if (!split && !share) return HEART_OK;
+  if ((!split && !share) || merged) return HEART_OK;
   hipLaunchKernelGGL((attn_merge_kernel<D, BLK>), dim3((unsigned)((share ? n_share : n_items) * (BLK / 32))), dim3(D * 2), 0, st, part,
                      owner, n_split, (uint16_t *)out, s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, s.N, Nb, lse);
   return check_launch("attn_merge_kernel");

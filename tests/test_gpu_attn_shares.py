@@ -195,3 +195,45 @@ def test_divided_rows_in_a_captured_graph():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, want), f"replay {i}"
+
+
+# parts that are added up where the last of them is left (two split parts; shares, of which the first shape has rows of three and
+# more parts): whatever the workspace holds, eagerly and in replays, in between other calls with the same memory
+@pytest.mark.parametrize("H,Nb,D,block", [(2, 5, 128, 128), (18, 11, 128, 128), (40, 10, 64, 64), (6, 88, 128, 64), (20, 64, 64, 64)])
+def test_merged_parts_in_memory_of_any_contents(H, Nb, D, block):
+    import paper_2605_14513_amd as heart
+
+    N = Nb * block - 3
+    rng = np.random.default_rng(H)
+    cnt = np_gpu(rng.integers(Nb // 2, Nb + 1, size=(1, H, Nb)).astype(np.int32))
+    idx = torch.arange(Nb, dtype=torch.int32, device="cuda").expand(1, H, Nb, Nb).contiguous()
+    g = torch.Generator(device="cuda").manual_seed(H)
+    q, k, v = (torch.randn((1, H, N, D), generator=g, device="cuda").bfloat16() for _ in range(3))
+    ws = torch.zeros(heart.heart_attn_balanced_workspace_bytes(q, block), dtype=torch.uint8, device="cuda")
+    out, lse = torch.empty_like(q), torch.empty((1, H, N), device="cuda")
+
+    def call():
+        heart.heart_block_sparse_attn(q, k, v, block, idx, cnt, out=out, lse=lse, workspace=ws)
+
+    print(f"merged H={H} Nb={Nb} D={D} block={block}", flush=True)
+    call()
+    want, want_lse = out.clone(), lse.clone()
+    one = heart.heart_block_sparse_attn(q, k, v, block, idx, cnt, workspace=None)
+    mass = heart.heart_block_sparse_attn(q, k, v.abs(), block, idx, cnt, workspace=None).float()
+    # (two roundings of a weight, one of the output, a tenth more for fp32: as above)
+    assert ((want.float() - one.float()).abs() <= 1.1 * 2.0 ** -8 * (mass + one.float().abs()) * 1.01).all()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        call()
+    for i in range(6):
+        if i % 3 == 0:
+            ws.fill_(0 if i else 255)
+        elif i % 3 == 1:
+            ws.copy_(torch.randint(0, 256, ws.shape, generator=g, dtype=torch.uint8, device="cuda"))
+        for run in (call, graph.replay):
+            out.fill_(float("nan"))
+            lse.fill_(float("nan"))
+            run()
+            torch.cuda.synchronize()
+            assert torch.equal(out, want) and torch.equal(lse, want_lse), f"round {i}"
