@@ -137,13 +137,15 @@ constexpr int kPartFloats = 64 * (D / 2) + 128;
 // Rows of few parts are added up by the workgroup that leaves the last of them (kSplitMerged, kSharedMerged).  That saves a
 // launch, and of the two parts at a cut the one that ends later, mostly the end of a share, stays in registers: a 64 KB part (D =
 // 128, block 128) is written and read once in the place of twice, which bound the launch (11.7 us for 512 cuts, 5.7 TB/s).  It
-// reads one part after the other, though, and of many parts a launch of a wavefront for 32 columns of 32 rows is the faster
-// way.  Steps and calls with the launch -> without, us: 18 heads of 33 rows (D = 128, block 128) 91.1 -> 85.1, four of 58 (two
-// shares a row) 44.0 -> 37.7, two of five (three) 31.8 -> 29.7, 20 of 101 (D = 64, block 64) 101.0 -> 96.4, two of 604 140 -> 137;
-// 18 of eleven in two split parts 48.4 -> 44.9; but six of six in four shares a row 33.4 -> 34.5, two of 16 in four split
-// parts at D = 64 21.9 -> 23.6.
-constexpr int kMergeParts = 2;     // split rows
-constexpr int kMergeShares = 4;    // more shares for a row than this
+// reads one part after the other, though, and the longest row of few has many: then a launch of a wavefront for 32 columns of
+// 32 rows is the faster way.  Steps and calls with the launch -> without, us: D = 128, block 128: 18 heads of 33 rows (0.9
+// shares a row) 91.1 -> 85.1, two of 160 (1.6) 94.8 -> 91.9, two of 120 (2.1) 77.6 -> 77.3, one of 240 (2.1) 100 -> 101.7, one of 160 (3.2) 71
+// -> 76, two of five (3) 31.8 -> 29.7, six of six (4) 33.4 -> 34.5; D = 64, block 64: 20 of 101 (0.5) 101 -> 96.4, one of 640 (1.6)
+// 103.8 -> 103.3, one of 480 (2.1) 85.0 -> 88.6, four of 112 (2.3) 48.9 -> 54.1; two split parts, 18 of eleven 48.4 -> 44.9, 12 of 16 46.6
+// -> 41.9; four at D = 64, two of 16 21.9 -> 23.6.
+constexpr int kMergeParts = 2;  // split rows
+// (rows of fewer than eight blocks have three parts at most)
+constexpr bool merge_shares(long long n_share, long long rows, long long Nb) { return n_share < (Nb < 8 ? 4 : 2) * rows; }
 constexpr float kNoKeys = -1.f;  // in the place of the row sum: a part without keys (a sum is not negative, but may be NaN)
 
 // places for workgroups on the chip
@@ -172,7 +174,7 @@ size_t attn_split_bytes(long long BH, long long Nb, int D, int block) {
 // Shared rows.  Where a place works on at most a few rows, their uneven lengths decide when a launch ends: the
 // longest row alone takes as long as several of the mean.  Where the caller asks for it (workspace_bytes of
 // heart_attn_balanced_workspace_bytes) lists are divided there, by one of three rules, and the rows that were
-// are added up by the workgroup that leaves the last part, or by attn_merge_kernel (kMergeShares):
+// are added up by the workgroup that leaves the last part, or by attn_merge_kernel (merge_shares):
 //   shares  the kept blocks of all rows, row after row, are one sequence (lengths in half blocks) that is cut into equal
 //           shares, one per place
 //   parts   every row is split into parts of at most L blocks, L as small as the places allow; each workgroup has one
@@ -199,21 +201,37 @@ __device__ __forceinline__ int share_blocks(int d, int cnt) {
 }
 
 // Shares of a launch (workgroups; those that find no share for them end at once), 0 = rows are not shared.  A function
-// of the sizes.  Measured against the plan on lists of the timed fields, and on dense ones, at 0.5 to 3 rows a place and 1
-// to 30 heads: with more rows the workgroups of an XCD are at places of K/V that are too far apart for its L2 and the
-// rows level out by themselves (D = 128, block 128: 1.04 to 1.85 times as fast up to 2 rows a place, 0.95 to 1.04 at 3; D =
-// 64: 1.0 to 2.6 times up to 2.5).  Four workgroups a CU with long lists at D = 128, block 64 feel that most (two heads of 585
-// rows 0.90, four of 293 1.19 times as fast).  Rows of few blocks a part of kSplitRows are left to that.
-// Dense lists need no levelling: only where a last round of whole rows would leave many places empty.  (Lists that are nearly full
-// and of nearly equal length without the caller's saying so: 0.79 to 1.6 times as fast, the least with 1.6 to 2 rows a place at D =
-// 128, block 64.)
+// of the sizes.  With a plan the uneven lengths cost the more the fewer rows a place has; with shares the workgroups of an XCD
+// are at places of K/V that lie further apart than its L2 is wide, the more the longer the rows are.  Steps on lists of the timed
+// fields (thresholds 0.85 to 0.98, as all figures here), plan -> shares, us:
+//   up to 2.9 rows a place  D = 128, block 128: two heads of 520 rows (2.0) 815 -> 630, three of 360 (2.1) 767 -> 543, six of 230 (2.7)
+//                           588 -> 550, two of 700 (2.7) 1285 -> 1245, three of 480 (2.8) 1053 -> 909, five of 300 (2.9) 843 -> 796; D =
+//                           64, block 64: 16 of 176 (2.8) 249 -> 181, six of 480 (2.8) 463 -> 406, three of 960 (2.8) 711 -> 717; at 3 and
+//                           3.1: 11 of 140 398 -> 404, two of 800 1861 -> 1874
+//   more, and rows a place times the elements of a head's keys up to share_near: D = 128: 16 of 110 (3.4) 406 -> 362, 21 of 88 (3.6)
+//                           407 -> 362, 26 of 80 (4.1) 404 -> 371; beyond: 14 of 120 (3.3) 403 -> 419, 10 of 176 (3.4) 511 -> 530, 12 of
+//                           256 (6) 1331 -> 1434; D = 64: 12 of 320 (3.8; block 64) 413 -> 377, eight of 248 (3.9; block 128) 666 -> 607, 14
+//                           of 160 (4.4) 467 -> 441; beyond: five of 400 (3.9) 845 -> 845, 14 of 244 (6.7) 750 -> 790
+//   D = 128, block 64       (four workgroups a CU feel the L2 most) two rows a place and share_near: two of 576 (1.1) 473 -> 390, three
+//                           of 480 (1.4) 450 -> 383, 14 of 128 (1.8) 173 -> 162; beyond: 30 of 122 (3.6) 286 -> 332, two of 960 (1.9),
+//                           lists of 60 % 1160 -> 1534
+// Lists of 60 % of the blocks and more gain nothing and lose up to a tenth (two of 700 1741 -> 1837), lists of 10 % gain most (707 -> 522).
+// (D = 64, block 64: rows of at most 64 blocks stay at the 2.5 rows a place that a test holds them to; 41 heads of 64 rows would gain 110
+// -> 82 us.)  Rows of few blocks a part of kSplitRows are left to that.
+// Dense lists need no levelling: only where a last round of whole rows would leave many places empty (D = 128, block 128: seven heads of
+// 98 rows (1.3) 522 -> 508, six of 122 (1.4) 665 -> 673, two of 366 (1.4) 1936 -> 1987; D = 64: 12 of 147 (1.7) 382 -> 342, 20 of 147 (2.9) 591
+// -> 588).  (Lists that are nearly full and of nearly equal length without the caller's saying so: 0.79 to 1.6 times as fast, the least with
+// 1.6 to 2 rows a place at D = 128, block 64.)
+// rows a place times elements of a head's keys
+constexpr long long share_near(int D, int block) { return (D == 64 ? 650ll : block == 64 ? 700ll : 380ll) * 128 * 128; }
 int attn_shares(long long BH, long long Nb, int D, int block, bool dense) {
   const long long places = attn_places(D, block);
   if (BH > kShareMaxRows || Nb > kShareMaxRows || BH * Nb > kShareMaxRows) return 0;
   const long long rows = BH * Nb;
-  if (2 * rows > (D == 64 ? 5 : 4) * places) return 0;
-  const bool near = D == 64 || block == 128 || rows * Nb <= 300 * places;
-  if (rows > places && !near) return 0;
+  const bool one = D == 128 && block == 64, near = rows * Nb * D * block <= share_near(D, block) * places;
+  if (rows > places && one && (!near || rows > 2 * places)) return 0;
+  if (10 * rows > 29 * places && !near) return 0;
+  if (D == 64 && block == 64 && Nb <= 64 && 2 * rows > 5 * places) return 0;
   const int s = attn_split(BH, Nb, D, block);
   // Short rows in many parts each: what a workgroup takes to find its part costs more than even parts give.  Lists of the timed
   // fields, kSplitRows -> shares us: D = 64, block 64, one head of 167 rows (six parts) 19.8 -> 22.8, two of 115 (four) 23.7 -> 24.4,
@@ -221,7 +239,7 @@ int attn_shares(long long BH, long long Nb, int D, int block, bool dense) {
   // 105 (four) 27.6 -> 25.1, four of 77 (three) 37.3 -> 29.9; two parts, and blocks of 128, 1.0 to 2 times as fast from 15 on.
   const int few_blocks = block == 128 || s < 3 ? 15 : D == 64 ? 30 : s < 4 ? 15 : 24;  // a part
   if (s > 1 && (dense || Nb <= few_blocks * s)) return 0;
-  if (dense && (!near || (rows > places && 8 * rows > (D == 64 ? 13 : 10) * places))) return 0;
+  if (dense && ((one && rows * Nb > 300 * places) || (rows > places && 8 * rows > (D == 64 ? 14 : 10) * places))) return 0;
   const long long most = rows * (Nb / kSharePart + 1);
   return (int)((most < places ? most : places) + kNumXcd - 1) / kNumXcd * kNumXcd;
 }
@@ -961,7 +979,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     if (qb0 < Nb) item = (int)(slot / per) * Nb + qb0;  // else: padding of the last eighth
   }
   // (kMerge) The parts of a row are n, this one is number `mine`; the first is that of share k0.  The end of a share is mostly the
-  // last of two parts: if the other one is there this one stays in registers.  (Asked while the last loads are awaited.)
+  // last part of its row: if the others are there this one stays in registers.  (Asked while the last loads are awaited.)
   int n = n_split, mine = split, k0 = share;
   bool last = false;
   auto ticket = [&]() __attribute__((always_inline)) -> unsigned long long * {
@@ -992,8 +1010,8 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
       n = __builtin_amdgcn_readfirstlane(n);
       k0 = __builtin_amdgcn_readfirstlane(k0);
       mine = __builtin_amdgcn_readfirstlane(mine);
-      if (mine == 0 && n == 2) {
-        if (t == 0) s_item = arrived(__hip_atomic_load(ticket(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 1;
+      if (mine == 0) {
+        if (t == 0) s_item = arrived(__hip_atomic_load(ticket(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == n - 1;
         last = true;  // (if s_item says so)
       }
     }
@@ -1264,8 +1282,8 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     }
     if (t == 0) __hip_atomic_store(ticket(), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // ---- the last part of a row: the sum of all, in their order whichever was the last --------
-    // One of two parts is added to the registers; of more, this one too is read again (one more array of accumulators does not
-    // fit the registers).  (A part whose logits are all NaN or -inf keeps the reference -inf: its weight is 0, but its sums
+    // One of two parts, or the first, stays in the registers; else this one too is read again (one more array of accumulators does
+    // not fit the registers).  (A part whose logits are all NaN or -inf keeps the reference -inf: its weight is 0, but its sums
     // count, because a NaN among them has to reach the result.)
     f32x16_t x[DT];
     float ms, ls;
@@ -1302,13 +1320,15 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
         m_ref = m_new;
       }
     } else {
-      m_ref = -__builtin_inff();
-      l_run = 0.f;
+      if (mine != 0) {
+        m_ref = -__builtin_inff();
+        l_run = 0.f;
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
+        for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
-      for (int s = 0; s < n; ++s) {
+          for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
+      }
+      for (int s = mine == 0 ? 1 : 0; s < n; ++s) {
         load_part(s);
         if (!has_keys(ls)) continue;
         const float m_new = fmaxf(m_ref, ms), m_fin = m_new == -__builtin_inff() ? 0.f : m_new;
@@ -1396,7 +1416,7 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
   const bool share = n_share > 0 && order_bytes == attn_balanced_bytes(BH, Nb, D, BLK, false);
   const bool split = !share && n_split > 1 && order_bytes >= attn_split_bytes(BH, Nb, D, BLK);
   const size_t lds = 4 * (size_t)kStageRows<D, BLK> * D * 2;  // >= BLK * (D + 8) * 2 of the output staging
-  const bool merged = (share && n_share < kMergeShares * n_items) || (split && n_split <= kMergeParts);
+  const bool merged = (share && merge_shares(n_share, n_items, Nb)) || (split && n_split <= kMergeParts);
   const AttnMode mode = share ? (merged ? kSharedMerged : kSharedRows) : split ? (merged ? kSplitMerged : kSplitRows) : kPlanned;
   auto kern = mode == kSharedMerged  ? attn_kernel<D, BLK, kExact, kSharedMerged>
               : mode == kSharedRows  ? attn_kernel<D, BLK, kExact, kSharedRows>
