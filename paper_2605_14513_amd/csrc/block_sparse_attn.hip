@@ -352,8 +352,8 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     long long vsn, long long osb, long long osh, long long osn, int H, int BH, int N, int Nb,
     const int *__restrict__ kept_idx, const int *__restrict__ kept_count, float scale_log2e,
     float *__restrict__ lse, int *__restrict__ plan, const int *__restrict__ seq, int *__restrict__ cursors,
-    int cursor_step, float *__restrict__ part, int4 *__restrict__ owner, int n_split, int n_few,
-    unsigned long long mark) {
+    int cursor_step, float *__restrict__ part, int4 *__restrict__ owner,
+    unsigned long long mark, int n_split, int n_few) {
   constexpr bool kSplit = kMode == kSplitRows || kMode == kSplitMerged, kShare = kMode == kSharedRows || kMode == kSharedMerged;
   constexpr bool kMerge = kMode == kSplitMerged || kMode == kSharedMerged;
   constexpr int NT = BLK * 2;            // threads
@@ -1469,7 +1469,8 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
                      s.k_stride[1], s.k_stride[2], s.v_stride[0], s.v_stride[1], s.v_stride[2],
                      s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, BH, s.N, Nb, kept_idx,
                      kept_count, scale_log2e, lse, order, seq, spread ? spread : order,
-                     spread ? kCursorSpread : 1, part, owner, n_split, n_few, merged ? call_mark() : 0ull);
+                     spread ? kCursorSpread : 1, part, owner, merged ? call_mark() : 0ull,
+                     n_split, n_few);
   if (int rc = check_launch("attn_kernel")) return rc;
   if ((!split && !share) || merged) return HEART_OK;
   hipLaunchKernelGGL((attn_merge_kernel<D, BLK>), dim3((unsigned)((share ? n_share : n_items) * (BLK / 32))), dim3(D * 2), 0, st, part,

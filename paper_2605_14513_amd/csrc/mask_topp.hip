@@ -310,12 +310,147 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
   const float tau_h = tau[h];
   const unsigned long long lt_mask = (1ull << lane) - 1ull;
 
-  if (!scores_in) {
-    // ---- Phases B and C, two rows per wavefront (scores from phase A) ----------------------
+  // (a score stage of its own: no scores are handed in)
+  const bool given = NF4T == 0 && !kInt8 && scores_in;
+  // A row of scores handed in with a sum of about two and more: the whole wavefront, 64-bit masses.
+  auto any_row = [&](int r) {
+    const int i = i0 + r;
+    if (i >= Nb) return;  // wave-uniform
+    const size_t row = (size_t)bh * Nb + i;
+    float p[CMAX];
+#pragma unroll
+    for (int c = 0; c < CMAX; ++c) {
+      int j = lane + 64 * c;
+      p[c] = j < Nb ? scores_in[row * Nb + j] : 0.f;
+    }
+    if (scores_out) {
+#pragma unroll
+      for (int c = 0; c < CMAX; ++c) {
+        int j = lane + 64 * c;
+        if (j < Nb) scores_out[row * Nb + j] = p[c];
+      }
+    }
+
+    // ---- Phase C: top-p selection ------------------------------------------------
+    uint32_t e[CMAX], u[CMAX];
+    unsigned long long my_u = 0;
+#pragma unroll
+    for (int c = 0; c < CMAX; ++c) {
+      int j = lane + 64 * c;
+      // (scores handed in may be anything: negative values and NaN count as 0, values above
+      // 1 as 1, so the fixed-point conversion below cannot overflow)
+      float pc = (j < Nb && p[c] > 0.f) ? fminf(p[c], 1.0f) : 0.f;
+      e[c] = __float_as_uint(pc);
+      u[c] = (uint32_t)floorf(pc * 1073741824.0f);  // exact: power-of-two scaling
+      my_u += u[c];
+    }
+    const unsigned long long U = wave_sum_u64(my_u);
+    const bool keep_all = tau_h >= 1.0f;
+    uint32_t vf = 0;   // threshold bit pattern
+    int cf = 0;        // number of lowest-index ties at vf to keep
+    if (!keep_all) {
+      const unsigned long long T =
+          tau_h > 0.f ? (unsigned long long)floorf(tau_h * 16777216.0f) : 0ull;
+      const unsigned long long need = (T * U + 16777215ull) >> 24;
+      // v* = largest bit pattern v with mass(scores >= v) >= need, built from the top
+      // bit down.  Invariant: mass(>= v) >= need > mass(>= v + 2^(bit+1)); the scores in
+      // [v, v + 2^(bit+1)) are undecided.  As soon as a single score is undecided it IS
+      // v* (keeping it reaches the mass, dropping it does not), so the loop stops early:
+      // typically after about a dozen steps instead of 31.  need == 0 keeps nothing here.
+      // (a score that carries mass is at least 2^-30 and none exceeds 1, so bits 30..28 of the
+      // threshold are known: 011)
+      uint32_t v = need == 0 ? 0x7fffffffu : 0x30000000u;
+      for (int bit = 27; bit >= 0 && need != 0; --bit) {
+        const uint32_t cand = v | (1u << bit);
+        unsigned long long s = 0;
+#pragma unroll
+        for (int c = 0; c < CMAX; ++c) s += e[c] >= cand ? u[c] : 0u;
+        s = wave_sum_u64(s);
+        if (s >= need) v = cand;
+        // undecided scores: [v, v + 2^bit) after this step (wave ballots, scalar counts)
+        const uint32_t top = v + (1u << bit);  // exclusive; bit patterns stay below 2^31
+        int n_und = 0;
+        uint32_t und = 0;
+#pragma unroll
+        for (int c = 0; c < CMAX; ++c) {
+          const bool in = e[c] >= v && e[c] < top;
+          n_und += __popcll(__ballot(in));
+          und = in ? e[c] : und;
+        }
+        if (n_und == 1) {
+          uint32_t x = und;  // the one lane that holds it has und != 0 unless it is 0
+          HEART_WAVE_REDUCE(uint32_t, x, HEART_OP_UMAX);
+          v = x > v ? x : v;
+          break;
+        }
+      }
+      unsigned long long s_gt = 0;
+      int n_gt = 0;
+#pragma unroll
+      for (int c = 0; c < CMAX; ++c) {
+        bool gt = e[c] > v;
+        s_gt += gt ? u[c] : 0u;
+        n_gt += gt ? 1 : 0;
+      }
+      s_gt = wave_sum_u64(s_gt);
+      n_gt = wave_sum_i32(n_gt);
+      int c_m = 0;
+      if (need > s_gt) {
+        const unsigned long long ustar =
+            (unsigned long long)floorf(__uint_as_float(v) * 1073741824.0f);
+        c_m = (int)((need - s_gt + ustar - 1ull) / ustar);
+      }
+      int k_mass = n_gt + c_m;
+      int k_min = min(max(1, min_keep), Nb);
+      vf = v;
+      cf = c_m;
+      if (k_mass < k_min) {
+        // the floor on the number of kept blocks wins: take the k_min best-ranked
+        uint32_t v2 = 0;
+        for (int bit = 30; bit >= 0; --bit) {
+          const uint32_t cand = v2 | (1u << bit);
+          int cnt = 0;
+#pragma unroll
+          for (int c = 0; c < CMAX; ++c) cnt += e[c] >= cand ? 1 : 0;
+          cnt = wave_sum_i32(cnt);
+          if (cnt >= k_min) v2 = cand;
+        }
+        int n_gt2 = 0;
+#pragma unroll
+        for (int c = 0; c < CMAX; ++c) n_gt2 += (lane + 64 * c < Nb && e[c] > v2) ? 1 : 0;
+        n_gt2 = wave_sum_i32(n_gt2);
+        vf = v2;
+        cf = k_min - n_gt2;
+      }
+    }
+
+    const bool dense_row = i < n_dense_q;
+    int tie_run = 0, out_run = 0;
+#pragma unroll
+    for (int c = 0; c < CMAX; ++c) {
+      const int j = lane + 64 * c;
+      const bool valid = j < Nb;
+      const bool tie = valid && e[c] == vf;
+      const unsigned long long tb = __ballot(tie);
+      const int tie_rank = tie_run + __popcll(tb & lt_mask);
+      tie_run += __popcll(tb);
+      bool keep = valid && (keep_all || dense_row || j < n_always_kv || e[c] > vf ||
+                            (tie && tie_rank < cf));
+      const unsigned long long kb = __ballot(keep);
+      const int pos = out_run + __popcll(kb & lt_mask);
+      out_run += __popcll(kb);
+      if (valid) mask[row * Nb + j] = keep ? 1 : 0;
+      if (keep) kept_idx[row * Nb + pos] = j;
+    }
+    if (lane == 0) kept_count[row] = out_run;
+  };
+
+  // ---- Phases B and C, two rows per wavefront --------------------------------------------
     // Each half of the wavefront (32 lanes) owns one row: the selection is bound by the
     // number of vector instructions, and with 32 lanes per row every search step serves two
-    // rows and its reductions take five exchanges instead of six.  The scores of a row sum to
-    // one, so every partial sum of the fixed-point masses stays below 2^31: the mass
+    // rows and its reductions take five exchanges instead of six.  The kernel's own scores of a row sum to
+    // one, and of those handed in only rows with a sum below 1.9 come here (half a wavefront a row in the place of a whole one with 64-bit masses; estimator and selection, 40 heads of 256
+    // rows 649 -> 627 us, 20 of 256 181 -> 171, six of 28 26.9 -> 24.8), so every partial sum of the fixed-point masses stays below 2^31: the mass
     // arithmetic is 32-bit here (same integers as in the general path below, hence the same
     // kept sets).  The per-row state (v, top, counts) is replicated over the lanes of a half.
     constexpr int EPL = 2 * CMAX;  // elements per lane: element c is key block l32 + 32 c
@@ -328,7 +463,21 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
     const bool row_ok = i < Nb;
     const size_t row = (size_t)bh * Nb + (row_ok ? i : 0);
     float p[EPL];
-    {
+    if (given) {
+      float z = 0.f;
+#pragma unroll
+      for (int c = 0; c < EPL; ++c) {
+        const int j = l32 + 32 * c;
+        p[c] = (row_ok && j < Nb) ? scores_in[row * Nb + j] : 0.f;
+        z += p[c] > 0.f ? fminf(p[c], 1.f) : 0.f;
+      }
+      z = half_sum_f32(z);
+      if (!__all(z < 1.9f)) {
+        any_row(r - hfw);
+        any_row(r - hfw + 1);
+        continue;
+      }
+    } else {
       float m = -__builtin_inff();
 #pragma unroll
       for (int c = 0; c < EPL; ++c) {
@@ -362,7 +511,8 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
 #pragma unroll
     for (int c = 0; c < EPL; ++c) {
       const int j = l32 + 32 * c;
-      const float pc = (j < Nb && p[c] > 0.f) ? p[c] : 0.f;
+      // (scores handed in may be anything: negative values and NaN count as 0, values above 1 as 1)
+      const float pc = (j < Nb && p[c] > 0.f) ? (given ? fminf(p[c], 1.f) : p[c]) : 0.f;
       e[c] = __float_as_uint(pc);
       u[c] = (uint32_t)floorf(pc * 1073741824.0f);
       my_u += u[c];
@@ -499,163 +649,6 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
     }
     if (l32 == 0 && row_ok) kept_count[row] = out_run;
     }  // selection passes
-    return;
-  }
-
-  for (int r = wave; r < kRows; r += kWaves) {
-    const int i = i0 + r;
-    if (i >= Nb) break;  // wave-uniform
-    const size_t row = (size_t)bh * Nb + i;
-
-    float p[CMAX];
-    if (scores_in) {
-#pragma unroll
-      for (int c = 0; c < CMAX; ++c) {
-        int j = lane + 64 * c;
-        p[c] = j < Nb ? scores_in[row * Nb + j] : 0.f;
-      }
-    } else {
-      // ---- Phase B: softmax of the row ------------------------------------------
-      float m = -__builtin_inff();
-#pragma unroll
-      for (int c = 0; c < CMAX; ++c) {
-        int j = lane + 64 * c;
-        p[c] = j < Nb ? sP[r * NBP + j] : -__builtin_inff();
-        m = fmaxf(m, p[c]);
-      }
-      m = wave_max_f32(m);
-      float z = 0.f;
-#pragma unroll
-      for (int c = 0; c < CMAX; ++c) {
-        int j = lane + 64 * c;
-        p[c] = j < Nb ? expf(p[c] - m) : 0.f;
-        z += p[c];
-      }
-      z = wave_sum_f32(z);
-#pragma unroll
-      for (int c = 0; c < CMAX; ++c) p[c] = __fdiv_rn(p[c], z);
-    }
-    if (scores_out) {
-#pragma unroll
-      for (int c = 0; c < CMAX; ++c) {
-        int j = lane + 64 * c;
-        if (j < Nb) scores_out[row * Nb + j] = p[c];
-      }
-    }
-
-    // ---- Phase C: top-p selection ------------------------------------------------
-    uint32_t e[CMAX], u[CMAX];
-    unsigned long long my_u = 0;
-#pragma unroll
-    for (int c = 0; c < CMAX; ++c) {
-      int j = lane + 64 * c;
-      // (scores handed in may be anything: negative values and NaN count as 0, values above
-      // 1 as 1, so the fixed-point conversion below cannot overflow)
-      float pc = (j < Nb && p[c] > 0.f) ? fminf(p[c], 1.0f) : 0.f;
-      e[c] = __float_as_uint(pc);
-      u[c] = (uint32_t)floorf(pc * 1073741824.0f);  // exact: power-of-two scaling
-      my_u += u[c];
-    }
-    const unsigned long long U = wave_sum_u64(my_u);
-    const bool keep_all = tau_h >= 1.0f;
-    uint32_t vf = 0;   // threshold bit pattern
-    int cf = 0;        // number of lowest-index ties at vf to keep
-    if (!keep_all) {
-      const unsigned long long T =
-          tau_h > 0.f ? (unsigned long long)floorf(tau_h * 16777216.0f) : 0ull;
-      const unsigned long long need = (T * U + 16777215ull) >> 24;
-      // v* = largest bit pattern v with mass(scores >= v) >= need, built from the top
-      // bit down.  Invariant: mass(>= v) >= need > mass(>= v + 2^(bit+1)); the scores in
-      // [v, v + 2^(bit+1)) are undecided.  As soon as a single score is undecided it IS
-      // v* (keeping it reaches the mass, dropping it does not), so the loop stops early:
-      // typically after about a dozen steps instead of 31.  need == 0 keeps nothing here.
-      // (a score that carries mass is at least 2^-30 and none exceeds 1, so bits 30..28 of the
-      // threshold are known: 011)
-      uint32_t v = need == 0 ? 0x7fffffffu : 0x30000000u;
-      for (int bit = 27; bit >= 0 && need != 0; --bit) {
-        const uint32_t cand = v | (1u << bit);
-        unsigned long long s = 0;
-#pragma unroll
-        for (int c = 0; c < CMAX; ++c) s += e[c] >= cand ? u[c] : 0u;
-        s = wave_sum_u64(s);
-        if (s >= need) v = cand;
-        // undecided scores: [v, v + 2^bit) after this step (wave ballots, scalar counts)
-        const uint32_t top = v + (1u << bit);  // exclusive; bit patterns stay below 2^31
-        int n_und = 0;
-        uint32_t und = 0;
-#pragma unroll
-        for (int c = 0; c < CMAX; ++c) {
-          const bool in = e[c] >= v && e[c] < top;
-          n_und += __popcll(__ballot(in));
-          und = in ? e[c] : und;
-        }
-        if (n_und == 1) {
-          uint32_t x = und;  // the one lane that holds it has und != 0 unless it is 0
-          HEART_WAVE_REDUCE(uint32_t, x, HEART_OP_UMAX);
-          v = x > v ? x : v;
-          break;
-        }
-      }
-      unsigned long long s_gt = 0;
-      int n_gt = 0;
-#pragma unroll
-      for (int c = 0; c < CMAX; ++c) {
-        bool gt = e[c] > v;
-        s_gt += gt ? u[c] : 0u;
-        n_gt += gt ? 1 : 0;
-      }
-      s_gt = wave_sum_u64(s_gt);
-      n_gt = wave_sum_i32(n_gt);
-      int c_m = 0;
-      if (need > s_gt) {
-        const unsigned long long ustar =
-            (unsigned long long)floorf(__uint_as_float(v) * 1073741824.0f);
-        c_m = (int)((need - s_gt + ustar - 1ull) / ustar);
-      }
-      int k_mass = n_gt + c_m;
-      int k_min = min(max(1, min_keep), Nb);
-      vf = v;
-      cf = c_m;
-      if (k_mass < k_min) {
-        // the floor on the number of kept blocks wins: take the k_min best-ranked
-        uint32_t v2 = 0;
-        for (int bit = 30; bit >= 0; --bit) {
-          const uint32_t cand = v2 | (1u << bit);
-          int cnt = 0;
-#pragma unroll
-          for (int c = 0; c < CMAX; ++c) cnt += e[c] >= cand ? 1 : 0;
-          cnt = wave_sum_i32(cnt);
-          if (cnt >= k_min) v2 = cand;
-        }
-        int n_gt2 = 0;
-#pragma unroll
-        for (int c = 0; c < CMAX; ++c) n_gt2 += (lane + 64 * c < Nb && e[c] > v2) ? 1 : 0;
-        n_gt2 = wave_sum_i32(n_gt2);
-        vf = v2;
-        cf = k_min - n_gt2;
-      }
-    }
-
-    const bool dense_row = i < n_dense_q;
-    int tie_run = 0, out_run = 0;
-#pragma unroll
-    for (int c = 0; c < CMAX; ++c) {
-      const int j = lane + 64 * c;
-      const bool valid = j < Nb;
-      const bool tie = valid && e[c] == vf;
-      const unsigned long long tb = __ballot(tie);
-      const int tie_rank = tie_run + __popcll(tb & lt_mask);
-      tie_run += __popcll(tb);
-      bool keep = valid && (keep_all || dense_row || j < n_always_kv || e[c] > vf ||
-                            (tie && tie_rank < cf));
-      const unsigned long long kb = __ballot(keep);
-      const int pos = out_run + __popcll(kb & lt_mask);
-      out_run += __popcll(kb);
-      if (valid) mask[row * Nb + j] = keep ? 1 : 0;
-      if (keep) kept_idx[row * Nb + pos] = j;
-    }
-    if (lane == 0) kept_count[row] = out_run;
-  }
 }
 
 template <int CMAX, int NF4T, bool kInt8>

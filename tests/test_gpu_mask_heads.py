@@ -70,3 +70,28 @@ def test_as_many_workgroups_as_a_launch_holds():
     heart.heart_mask_topp(x, x, tau, mask=mask, kept_idx=idx, kept_count=cnt)
     torch.cuda.synchronize()
     assert (mask == 1).all() and (idx == 0).all() and (cnt == 1).all()
+
+
+# scores handed in: rows whose sum lies around the two that 32-bit masses hold, next to each other in every order, with ties, empty
+# rows, negative scores, NaN and scores above one (which count as 0, 0 and 1); one slot a lane, several, all; an odd last row
+@pytest.mark.parametrize("Nb", [1, 15, 64, 65, 255, 300, 1000])
+def test_scores_of_any_sum(Nb):
+    import paper_2605_14513_amd as heart
+
+    H = 3
+    rng = np.random.default_rng(Nb)
+    s = rng.exponential(size=(1, H, Nb, Nb)) ** 3
+    s[rng.random(s.shape) < 0.2] = 1.0  # ties
+    s = s / s.sum(-1, keepdims=True) * rng.choice([0.0, 0.3, 1.0, 1.89, 1.91, 2.1, 8.0, 300.0], size=(1, H, Nb, 1))
+    s = s.astype(np.float32)
+    counts = s.clip(0.0, 1.0)
+    low = rng.random(s.shape) < 0.05
+    given = np.where(low, np.where(rng.random(s.shape) < 0.5, np.float32(np.nan), np.float32(-0.5)), s)
+    counts[low] = 0.0
+    tau = np.array([0.4, 0.9, 0.999], np.float32)
+    for keep in (1, 5):
+        m, i, c = (x.cpu().numpy() for x in heart.heart_mask_topp(None, None, np_gpu(tau), scores_in=np_gpu(given), min_keep=keep))
+        om, oi, oc = oracle.topp(counts, tau, min_keep=keep)
+        assert np.array_equal(m, om) and np.array_equal(c, oc)
+        listed = np.arange(Nb) < oc[..., None]
+        assert np.array_equal(i[listed], oi[listed])
