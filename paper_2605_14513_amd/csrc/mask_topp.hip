@@ -20,8 +20,7 @@
 //            exact integers (v_mfma_i32_16x16x64_i8), and the slice pairs are put together
 //            in fp64.
 //   Phase B  row softmax, fp32 with the accurate expf: half a wavefront per row (two rows at
-//            a time) when the scores are the kernel's own, one wavefront per row for scores
-//            passed in.
+//            a time); rows of scores passed in with a sum of 1.9 and more have a wavefront each.
 //   Phase C  top-p selection, same lanes as phase B, without sorting: the kept set
 //            is "every score above a threshold value v*, plus the lowest-index
 //            ties at v*", and v* is found by a 31-step bitwise search on the fp32
@@ -170,6 +169,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
     if (refresh && !refresh[bh]) return;  // reused head: cached mask persists
   }
   const int h = (int)(bh % H);
+  const bool given = NF4T == 0 && scores_in;  // (the kernels of a head dimension have no scores handed in)
 
   if constexpr (kInt8) {
     // ---- Phase A on the int8 matrix cores (launched only without scores_in) -------- -----------------------------------------
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
       ekc = ekn;
     }
     __syncthreads();
-  } else if (!scores_in) {
+  } else if (!given) {
     // ---- Phase A: logits -------------------------------------------------------
     // MFMA operand layout (16x16x4 fp64): A lane L = (row L%16, k L/16), B lane L =
     // (k L/16, column L%16), D lane L register r = (row L/16 + 4 r, column L%16).
@@ -310,8 +310,6 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
   const float tau_h = tau[h];
   const unsigned long long lt_mask = (1ull << lane) - 1ull;
 
-  // (a score stage of its own: no scores are handed in)
-  const bool given = NF4T == 0 && !kInt8 && scores_in;
   // A row of scores handed in with a sum of about two and more: the whole wavefront, 64-bit masses.
   auto any_row = [&](int r) {
     const int i = i0 + r;
@@ -449,9 +447,9 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
     // Each half of the wavefront (32 lanes) owns one row: the selection is bound by the
     // number of vector instructions, and with 32 lanes per row every search step serves two
     // rows and its reductions take five exchanges instead of six.  The kernel's own scores of a row sum to
-    // one, and of those handed in only rows with a sum below 1.9 come here (half a wavefront a row in the place of a whole one with 64-bit masses; estimator and selection, 40 heads of 256
-    // rows 649 -> 627 us, 20 of 256 181 -> 171, six of 28 26.9 -> 24.8), so every partial sum of the fixed-point masses stays below 2^31: the mass
-    // arithmetic is 32-bit here (same integers as in the general path below, hence the same
+    // one, and of those handed in only rows with a sum below 1.9 come here (before, a whole wavefront and
+    // 64-bit masses a row: estimator and selection of 40 heads of 256 rows 644 -> 627 us, 20 of 256 184 -> 171, six
+    // of 28 26.8 -> 24.8), so every partial sum of the fixed-point masses stays below 2^31: the mass arithmetic is 32-bit here (same integers as in the general path below, hence the same
     // kept sets).  The per-row state (v, top, counts) is replicated over the lanes of a half.
     constexpr int EPL = 2 * CMAX;  // elements per lane: element c is key block l32 + 32 c
     const int l32 = lane & 31, hfw = lane >> 5;
