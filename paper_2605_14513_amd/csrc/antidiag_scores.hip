@@ -19,7 +19,7 @@
 //   contraction runs in stages of 64 elements (half a token row at D = 128): both operand
 //   tiles go from global memory straight into LDS (`buffer_load ... lds`, 16-byte chunks
 //   XOR-swizzled by row so that the fragment reads are conflict free), double-buffered
-//   (128 KB, 64 KB), one barrier per stage, the loads of the next stage in flight during the MFMAs
+//   (128 KB, 64 KB; 128 KB in four buffers for one small tile a CU), one barrier per stage, the loads of the next stage in flight during the MFMAs
 //   of the current one (lines of later stages requested into the L2 as well: 613 -> 625 us); fragments are
 //   read one contraction step ahead, and fragment reads and loads are issued between the MFMAs, one or two
 //   behind each: all eight loads of a wavefront in one go, right after the barrier, held the MFMAs behind them
@@ -52,7 +52,7 @@ constexpr int kAdTile = 256;                     // reduced rows per tile side (
 constexpr int kAdRowB = 128;                     // bytes per tile row and stage (64 bf16)
 constexpr int kAdKeysPerBlock = 8;               // reduced keys per key block (block = 8 S)
 constexpr int kAdLookHeads = 256;                // most heads whose refresh flags every workgroup looks at
-constexpr int ad_lds(int tile) { return 4 * tile * kAdRowB; }  // two stages x two operands (128 KB, 64 KB)
+constexpr int ad_lds(int tile, int bufs) { return 2 * bufs * tile * kAdRowB; }  // stages x two operands (128 KB, 64 KB)
 
 // raw buffer descriptor (base, size in bytes) as four words in scalar registers, for the
 // hand-written LDS-direct loads; accesses past `bytes` return zeros
@@ -68,8 +68,8 @@ __device__ __forceinline__ ad_u32x4 ad_rsrc_words(const uint16_t *base, uint32_t
 
 }  // namespace
 
-// kTile = 256: 8 wavefronts of 64 queries x 128 keys; 128: 4 of 32 queries x 128 keys, two workgroups a CU
-template <int D, int kTile>
+// kTile = 256: 8 wavefronts of 64 queries x 128 keys; 128: 4 of 32 queries x 128 keys, two workgroups a CU (kBufs stage buffers; 4: one)
+template <int D, int kTile, int kBufs>
 __global__ __launch_bounds__(2 * kTile, 2) void antidiag_tile_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, long long qsb, long long qsh,
     long long qsn, long long ksb, long long ksh, long long ksn, int H, int BH, int N, int S, int M,
@@ -170,7 +170,8 @@ __global__ __launch_bounds__(2 * kTile, 2) void antidiag_tile_kernel(
     }
   };
   auto wait_loads_and_barrier = [&]() __attribute__((always_inline)) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // (the loads of the next stage; those of the stages behind it may be in flight)
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kBufs - 2) * kLoads) : "memory");
     __syncthreads();
   };
   // fragment of contraction step ks (16 elements) of tile row 32 x + l32: chunk 2 ks + hf
@@ -215,7 +216,7 @@ __global__ __launch_bounds__(2 * kTile, 2) void antidiag_tile_kernel(
 
   // Per stage: the barrier that hands over the next stage sits before the MFMAs of the stage's last step.  By then a
   // wavefront has completed all its reads of the current buffer and its loads of the next stage into the other one;
-  // behind those MFMAs it issues the first half of the loads of the stage after that into the buffer just released, behind
+  // behind those MFMAs it issues the first half of the loads of the stage kBufs on into the buffer just released, behind
   // those of the next step the other half (the later a load, the shorter its flight: all within the
   // first step, or three quarters, 0.5 to 2 % slower).  Loads past the last stage repeat the last stage (into a buffer
   // nobody reads any more).
@@ -224,25 +225,28 @@ __global__ __launch_bounds__(2 * kTile, 2) void antidiag_tile_kernel(
   constexpr int kHalf = kLoads / 2;
   Frags f0, f1;
 #pragma unroll
-  for (int i = 0; i < kLoads; ++i) dma(0, 0, i);
+  for (int st = 0; st < kBufs - 1; ++st)
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) dma(min(st, last), st, i);
   wait_loads_and_barrier();
 #pragma unroll
-  for (int i = 0; i < kHalf; ++i) dma(min(1, last), 1, i);
+  for (int i = 0; i < kHalf; ++i) dma(min(kBufs - 1, last), kBufs - 1, i);
 #pragma unroll
   for (int j = 0; j < kFrags; ++j) read_frag(f0, 0, 0, j);
   auto no_extra = [](int) {};
   for (int st = 0; st < n_stages; ++st) {
-    const int buf = st & 1, st1 = min(st + 1, last), st2 = min(st + 2, last);
+    const int buf = st % kBufs, buf1 = (st + 1) % kBufs, bufp = (st + kBufs - 1) % kBufs;
+    const int st1 = min(st + kBufs - 1, last), st2 = min(st + kBufs, last);
     step(f0, f1, buf, 1, [&](int i) {
 #pragma unroll
       for (int j = 0; j < kHalf; ++j)
-        if (j * kMfmas / kHalf == i) dma(st1, buf ^ 1, kHalf + j);
+        if (j * kMfmas / kHalf == i) dma(st1, bufp, kHalf + j);
     });
     step(f1, f0, buf, 2, no_extra);
     step(f0, f1, buf, 3, no_extra);
     wait_loads_and_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    step(f1, f0, buf ^ 1, 0, [&](int i) {
+    step(f1, f0, buf1, 0, [&](int i) {
 #pragma unroll
       for (int j = 0; j < kHalf; ++j)
         if (j * kMfmas / kHalf == i) dma(st2, buf, j);
@@ -411,32 +415,40 @@ int launch_antidiag(const heart_shape &s, const void *q, const void *k, int stri
   const long long grid = ((long long)BH * MTQ * (few ? MT : MT2) + kNumXcd - 1) / kNumXcd * kNumXcd;
   if (grid > 0x7fffffffLL || (long long)BH * Nb > 0x7fffffffLL)
     return fail(HEART_EUNSUPPORTED, "heart_scores_antidiag: grid too large");
+  // One small tile a CU: four buffers, since nothing else is there to cover the flight of the loads
+  // (estimator and selection, inputs from HBM, two buffers -> four: six heads of 5250 tokens 41.4 -> 27.6 us, 13 of 1590 33.3 -> 26.4;
+  // inputs in the caches 31.7 -> 25.1, 26.2 -> 26.3).
+  const bool alone = grid <= n_cu;
   float *esum = workspace;
   float *mref = workspace + (size_t)BH * M * 16 * MT;
   const float scale_log2 = 1.4426950408889634f / ((float)S * sqrtf((float)s.D));
-#define HEART_AD_LAUNCH(DD, TT)                                                                    \
+#define HEART_AD_LAUNCH(DD, TT, BB)                                                                \
   do {                                                                                             \
-    auto kern = antidiag_tile_kernel<DD, TT>;                                                      \
+    auto kern = antidiag_tile_kernel<DD, TT, BB>;                                                  \
     static DeviceFlags attr_set;                                                                   \
     if (hipError_t e = set_max_lds_once(attr_set, dev, reinterpret_cast<const void *>(kern),       \
-                                        ad_lds(TT)))                                               \
+                                        ad_lds(TT, BB)))                                           \
       return fail(HEART_EHIP, "hipFuncSetAttribute(antidiagonal tile kernel LDS): %s",             \
                   hipGetErrorString(e));                                                           \
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(2 * TT), ad_lds(TT), st, (const uint16_t *)q, \
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(2 * TT), ad_lds(TT, BB), st, (const uint16_t *)q, \
                        (const uint16_t *)k, s.q_stride[0], s.q_stride[1], s.q_stride[2],           \
                        s.k_stride[0], s.k_stride[1], s.k_stride[2], s.H, BH, s.N, S, M, MTQ, MT,   \
                        scale_log2, refresh, esum, mref);                                           \
   } while (0)
   if (s.D == 128) {
-    if (few)
-      HEART_AD_LAUNCH(128, 128);
+    if (few && alone)
+      HEART_AD_LAUNCH(128, 128, 4);
+    else if (few)
+      HEART_AD_LAUNCH(128, 128, 2);
     else
-      HEART_AD_LAUNCH(128, 256);
+      HEART_AD_LAUNCH(128, 256, 2);
   } else {
-    if (few)
-      HEART_AD_LAUNCH(64, 128);
+    if (few && alone)
+      HEART_AD_LAUNCH(64, 128, 4);
+    else if (few)
+      HEART_AD_LAUNCH(64, 128, 2);
     else
-      HEART_AD_LAUNCH(64, 256);
+      HEART_AD_LAUNCH(64, 256, 2);
   }
 #undef HEART_AD_LAUNCH
   if (int rc = check_launch("antidiag_tile_kernel")) return rc;
