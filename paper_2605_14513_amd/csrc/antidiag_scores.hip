@@ -313,15 +313,17 @@ __global__ __launch_bounds__(2 * kTile, 2) void antidiag_tile_kernel(
 // block's 8 reduced queries on its own (global maximum over the records, normaliser, both
 // wave-wide reductions; the loads of both rows are issued before either is reduced), leaves
 // the normalised key-block masses in LDS, and after one barrier the workgroup averages the
-// 8 rows.  JPL = key blocks per lane (16 MT <= 64 JPL).
-template <int JPL>
+// 8 rows.  A lane has four key blocks at a time (one load; they share a record, whose maximum is one more), JQ times: 16 MT <=
+// 256 JQ.  Bound by the records' bytes at many heads, by latency at few (estimator and selection with one key block a load -> four:
+// 40 heads of 256 blocks 627 -> 619 us; eight heads of 13230 tokens at D = 64, inputs from HBM, 33.9 -> 33.1, six of 5250 27.6 -> 27.1).
+template <int JQ>
 __global__ __launch_bounds__(256) void antidiag_combine_kernel(int Nb, int M, int MT,
                                                               const unsigned char *__restrict__ refresh,
                                                               const float *__restrict__ esum,
                                                               const float *__restrict__ mref,
                                                               float *__restrict__ scores) {
   constexpr int RQ = kAdKeysPerBlock;       // reduced queries per query block
-  extern __shared__ float s_w[];            // [RQ][NbP]
+  extern __shared__ __align__(16) float s_w[];  // [RQ][NbP]
   const int I = blockIdx.x % Nb;
   const long long bh = blockIdx.x / Nb;
   if (refresh && !refresh[bh]) return;
@@ -329,16 +331,17 @@ __global__ __launch_bounds__(256) void antidiag_combine_kernel(int Nb, int M, in
   const int a0 = I * RQ;
   const int na = min(RQ, M - a0);
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  float mr[2], w[2][JPL], mj[2][JPL];
+  float mr[2], mj[2][JQ];
+  float4 w[2][JQ];
 #pragma unroll
   for (int x = 0; x < 2; ++x) {
     const int rr = wave + 4 * x;
     const size_t row = (size_t)bh * M + a0 + (rr < na ? rr : 0);  // (rows past the end: loads of row 0, unused)
     mr[x] = lane < MT ? mref[row * MT + lane] : -__builtin_inff();
 #pragma unroll
-    for (int u = 0; u < JPL; ++u) {
-      const int J = lane + 64 * u;
-      w[x][u] = J < NbP ? esum[row * NbP + J] : 0.f;
+    for (int u = 0; u < JQ; ++u) {
+      const int J = 4 * (lane + 64 * u);
+      w[x][u] = J < NbP ? *reinterpret_cast<const float4 *>(esum + row * NbP + J) : make_float4(0.f, 0.f, 0.f, 0.f);
       mj[x][u] = J < NbP ? mref[row * MT + (J >> 4)] : 0.f;
     }
   }
@@ -348,16 +351,18 @@ __global__ __launch_bounds__(256) void antidiag_combine_kernel(int Nb, int M, in
     const float m = wave_max_f32(mr[x]);
     float part = 0.f;
 #pragma unroll
-    for (int u = 0; u < JPL; ++u) {
-      const int J = lane + 64 * u;
-      w[x][u] = J < NbP ? w[x][u] * __builtin_amdgcn_exp2f(mj[x][u] - m) : 0.f;
-      part += w[x][u];
+    for (int u = 0; u < JQ; ++u) {
+      const float f = 4 * (lane + 64 * u) < NbP ? __builtin_amdgcn_exp2f(mj[x][u] - m) : 0.f;
+      w[x][u] = make_float4(w[x][u].x * f, w[x][u].y * f, w[x][u].z * f, w[x][u].w * f);
+      part += (w[x][u].x + w[x][u].y) + (w[x][u].z + w[x][u].w);
     }
     const float inv = rr < na ? 1.f / wave_sum_f32(part) : 0.f;
 #pragma unroll
-    for (int u = 0; u < JPL; ++u) {
-      const int J = lane + 64 * u;
-      if (J < NbP) s_w[rr * NbP + J] = w[x][u] * inv;
+    for (int u = 0; u < JQ; ++u) {
+      const int J = 4 * (lane + 64 * u);
+      if (J < NbP)
+        *reinterpret_cast<float4 *>(s_w + rr * NbP + J) =
+            make_float4(w[x][u].x * inv, w[x][u].y * inv, w[x][u].z * inv, w[x][u].w * inv);
     }
   }
   __syncthreads();
@@ -455,13 +460,13 @@ int launch_antidiag(const heart_shape &s, const void *q, const void *k, int stri
   const dim3 cgrid((unsigned)((long long)BH * Nb));
   const size_t clds = (size_t)kAdKeysPerBlock * 16 * MT * sizeof(float);
   if (MT <= 16)
-    hipLaunchKernelGGL(antidiag_combine_kernel<4>, cgrid, dim3(256), clds, st, Nb, M, MT, refresh, esum,
+    hipLaunchKernelGGL(antidiag_combine_kernel<1>, cgrid, dim3(256), clds, st, Nb, M, MT, refresh, esum,
                        mref, scores);
   else if (MT <= 32)
-    hipLaunchKernelGGL(antidiag_combine_kernel<8>, cgrid, dim3(256), clds, st, Nb, M, MT, refresh, esum,
+    hipLaunchKernelGGL(antidiag_combine_kernel<2>, cgrid, dim3(256), clds, st, Nb, M, MT, refresh, esum,
                        mref, scores);
   else
-    hipLaunchKernelGGL(antidiag_combine_kernel<16>, cgrid, dim3(256), clds, st, Nb, M, MT, refresh, esum,
+    hipLaunchKernelGGL(antidiag_combine_kernel<4>, cgrid, dim3(256), clds, st, Nb, M, MT, refresh, esum,
                        mref, scores);
   return check_launch("antidiag_combine_kernel");
 }
