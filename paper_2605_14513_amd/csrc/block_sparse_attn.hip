@@ -343,6 +343,8 @@ static_assert(kShareMaxRows <= (int)kMarkCount && kMergeParts == 2, "parts of a 
 // kMode: kPlanned, rows as a plan (or, without one, the workgroup's number) says; kSplitRows: a workgroup takes part of
 // one row's list and leaves it in `part`; kSharedRows: a share of all rows
 // kSplitMerged, kSharedMerged: the same, and the workgroup that leaves the last part of a row adds them up
+// (instantiations of their own: with a branch at run time the others took 0.5 to 1 us longer; at D = 128 kSharedMerged keeps two
+// registers in scratch memory while it adds up, behind the MFMA stream)
 enum AttnMode { kPlanned, kSplitRows, kSharedRows, kSplitMerged, kSharedMerged };
 template <int D, int BLK, bool kExact, AttnMode kMode>
 __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
