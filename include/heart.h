@@ -291,8 +291,8 @@ size_t heart_attn_workspace_bytes(const heart_shape *shape);
 
 /*
  * The workspace_bytes with which heart_block_sparse_attn also divides the lists of launches in which a place for a workgroup
- * (two per CU, four at block = 64) works on at most 2 to 2.5 query blocks, so that uneven lists no longer decide when the
- * call ends.  Exactly this size asks for it (a buffer that is larger is passed with this size).  Such a workspace holds
+ * (two per CU, four at block = 64) works on few query blocks (up to 2.9; 2 at D = 128, block = 64; more where the heads
+ * are short), so that uneven lists no longer decide when the call ends.  Exactly this size asks for it (a buffer that is larger is passed with this size).  Such a workspace holds
  * no plan but the parts of the query blocks that were divided (71 MB at most), and the results are those of another
  * size up to rounding; where lists are divided, and with it the rounding of a query block, depends on the kept counts of
  * all heads of the call.  Where dividing does not pay, and for other shapes, the same as heart_attn_workspace_bytes; with

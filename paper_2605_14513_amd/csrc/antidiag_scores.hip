@@ -24,8 +24,8 @@
 //   read one contraction step ahead, and fragment reads and loads are issued between the MFMAs, one or two
 //   behind each: all eight loads of a wavefront in one go, right after the barrier, held the MFMAs behind them
 //   back until the address unit had taken them (estimator and selection, 40 heads of 32760 tokens 674 -> 656 us,
-//   10 of 75600 960 -> 917, 20 of 32760 at D = 64 200 -> 184, 12 of 20280 in blocks of 64 193 -> 180, six of 3565 29.3 -> 26.8).  Not the flight time of the loads: stages of half the
-//   depth, five buffers and four stages ahead took 709 to 720 us in the place of 660, four wavefronts of 128 x 128,
+//   10 of 75600 960 -> 917, 20 of 32760 at D = 64 200 -> 184, 12 of 20280 in blocks of 64 193 -> 180, six of 3565
+//   29.3 -> 26.8).  With a full chip the flight time of the loads does not count: stages of half the depth, five buffers and four stages ahead took 709 to 720 us in the place of 660, four wavefronts of 128 x 128,
 //   one a SIMD, 730.  A wavefront owns 64 (32) reduced queries against 128 reduced keys (S^T layout: keys
 //   along the accumulator rows), so a query's maximum over those keys is a per-lane
 //   reduction plus one exchange with the partner lane.  The epilogue writes one record per
