@@ -238,3 +238,24 @@ def test_small_tiles_for_any_number_of_refreshed_heads(heart, H, N, D, flags, sm
     call()  # (attributes of a kernel are set on its first call)
     print(f"antidiag H={H} N={N} D={D} flags={flags}", flush=True)
     assert captured_launches(call)[0][1] == (256 if small else 512)
+
+
+# logits around and far beyond 2^31 (log2 units), where the exponential of a logit's own rounding no longer fits fp32: all mass lies on
+# the keys nearest to the top, as in fp64.  A tile with a ragged end, small tiles and large ones, logits of either sign
+@pytest.mark.parametrize("H,N,D,block", [(2, 1000, 128, 128), (1, 2048, 64, 64), (150, 4100, 64, 128)])
+@pytest.mark.parametrize("amp", [2.0 ** 4, 2.0 ** 9, 2.0 ** 13, 2.0 ** 15, 2.0 ** 40])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_large_finite_inputs(heart, H, N, D, block, amp, sign):
+    Nb = (N + block - 1) // block
+    g = torch.Generator().manual_seed(N)
+    q = (amp * (1.0 + torch.rand((1, 1, N, 1), generator=g))).expand(1, H, N, D).bfloat16()
+    k = sign * amp * (1.0 + torch.rand((1, 1, N, 1), generator=g))
+    hot = Nb // 2 * block  # (one block apart from the others, its keys alike: fp32 sums cannot change who is on top)
+    k[0, 0, hot:hot + block] = sign * amp * (8.0 if sign > 0 else 0.125)
+    k = k.expand(1, H, N, D).bfloat16()
+    print(f"antidiag large H={H} N={N} D={D} amp={amp} sign={sign}", flush=True)
+    got = heart.heart_scores_antidiag(q.cuda(), k.cuda(), block, block // 8)
+    torch.cuda.synchronize()
+    want = oracle_scores(q, k, block, block // 8, heads={(0, 0)})[(0, 0)]
+    assert_close(got[0, 0].cpu().numpy(), want, f"amp {amp} sign {sign}")
+    assert torch.equal(got, got[:, :1].expand_as(got))
