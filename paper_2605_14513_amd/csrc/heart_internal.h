@@ -115,14 +115,6 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
   HEART_WAVE_REDUCE(uint32_t, v, HEART_OP_ADD);
   return v;
 }
-// Sum of per-lane masses below 2^40: two 32-bit reductions over the low 20 bits and the
-// rest (each stays below 2^32 for 64 lanes), recombined exactly.
-__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
-  uint32_t lo = (uint32_t)v & 0xfffffu, hi = (uint32_t)(v >> 20);
-  HEART_WAVE_REDUCE(uint32_t, lo, HEART_OP_ADD);
-  HEART_WAVE_REDUCE(uint32_t, hi, HEART_OP_ADD);
-  return ((unsigned long long)hi << 20) + lo;
-}
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
   HEART_WAVE_REDUCE(uint32_t, v, HEART_OP_UMAX);
   return v;
@@ -143,9 +135,17 @@ __device__ __forceinline__ int wave_scan_i32(int v) {
   return v;
 }
 __device__ __forceinline__ int wave_sum_i32(int v) { return (int)wave_sum_u32((uint32_t)v); }
-__device__ __forceinline__ uint32_t half_sum_u32(uint32_t v) {
+__device__ __forceinline__ uint32_t half_sum(uint32_t v) {
   HEART_HALF_REDUCE(uint32_t, v, HEART_OP_ADD);
   return v;
+}
+// Sum of per-lane masses below 2^40: two 32-bit reductions over the low 20 bits and the
+// rest (each stays below 2^32), recombined exactly.
+__device__ __forceinline__ unsigned long long half_sum(unsigned long long v) {
+  uint32_t lo = (uint32_t)v & 0xfffffu, hi = (uint32_t)(v >> 20);
+  HEART_HALF_REDUCE(uint32_t, lo, HEART_OP_ADD);
+  HEART_HALF_REDUCE(uint32_t, hi, HEART_OP_ADD);
+  return ((unsigned long long)hi << 20) + lo;
 }
 __device__ __forceinline__ uint32_t half_max_u32(uint32_t v) {
   HEART_HALF_REDUCE(uint32_t, v, HEART_OP_UMAX);

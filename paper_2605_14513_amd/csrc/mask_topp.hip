@@ -20,7 +20,7 @@
 //            exact integers (v_mfma_i32_16x16x64_i8), and the slice pairs are put together
 //            in fp64.
 //   Phase B  row softmax, fp32 with the accurate expf: half a wavefront per row (two rows at
-//            a time); rows of scores passed in with a sum of 1.9 and more have a wavefront each.
+//            a time).
 //   Phase C  top-p selection, same lanes as phase B, without sorting: the kept set
 //            is "every score above a threshold value v*, plus the lowest-index
 //            ties at v*", and v* is found by a 31-step bitwise search on the fp32
@@ -308,159 +308,23 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
   }
 
   const float tau_h = tau[h];
-  const unsigned long long lt_mask = (1ull << lane) - 1ull;
-
-  // A row of scores handed in with a sum of about two and more: the whole wavefront, 64-bit masses.
-  auto any_row = [&](int r) {
-    const int i = i0 + r;
-    if (i >= Nb) return;  // wave-uniform
-    const size_t row = (size_t)bh * Nb + i;
-    float p[CMAX];
-#pragma unroll
-    for (int c = 0; c < CMAX; ++c) {
-      int j = lane + 64 * c;
-      p[c] = j < Nb ? scores_in[row * Nb + j] : 0.f;
-    }
-    if (scores_out) {
-#pragma unroll
-      for (int c = 0; c < CMAX; ++c) {
-        int j = lane + 64 * c;
-        if (j < Nb) scores_out[row * Nb + j] = p[c];
-      }
-    }
-
-    // ---- Phase C: top-p selection ------------------------------------------------
-    uint32_t e[CMAX], u[CMAX];
-    unsigned long long my_u = 0;
-#pragma unroll
-    for (int c = 0; c < CMAX; ++c) {
-      int j = lane + 64 * c;
-      // (scores handed in may be anything: negative values and NaN count as 0, values above
-      // 1 as 1, so the fixed-point conversion below cannot overflow)
-      float pc = (j < Nb && p[c] > 0.f) ? fminf(p[c], 1.0f) : 0.f;
-      e[c] = __float_as_uint(pc);
-      u[c] = (uint32_t)floorf(pc * 1073741824.0f);  // exact: power-of-two scaling
-      my_u += u[c];
-    }
-    const unsigned long long U = wave_sum_u64(my_u);
-    const bool keep_all = tau_h >= 1.0f;
-    uint32_t vf = 0;   // threshold bit pattern
-    int cf = 0;        // number of lowest-index ties at vf to keep
-    if (!keep_all) {
-      const unsigned long long T =
-          tau_h > 0.f ? (unsigned long long)floorf(tau_h * 16777216.0f) : 0ull;
-      const unsigned long long need = (T * U + 16777215ull) >> 24;
-      // v* = largest bit pattern v with mass(scores >= v) >= need, built from the top
-      // bit down.  Invariant: mass(>= v) >= need > mass(>= v + 2^(bit+1)); the scores in
-      // [v, v + 2^(bit+1)) are undecided.  As soon as a single score is undecided it IS
-      // v* (keeping it reaches the mass, dropping it does not), so the loop stops early:
-      // typically after about a dozen steps instead of 31.  need == 0 keeps nothing here.
-      // (a score that carries mass is at least 2^-30 and none exceeds 1, so bits 30..28 of the
-      // threshold are known: 011)
-      uint32_t v = need == 0 ? 0x7fffffffu : 0x30000000u;
-      for (int bit = 27; bit >= 0 && need != 0; --bit) {
-        const uint32_t cand = v | (1u << bit);
-        unsigned long long s = 0;
-#pragma unroll
-        for (int c = 0; c < CMAX; ++c) s += e[c] >= cand ? u[c] : 0u;
-        s = wave_sum_u64(s);
-        if (s >= need) v = cand;
-        // undecided scores: [v, v + 2^bit) after this step (wave ballots, scalar counts)
-        const uint32_t top = v + (1u << bit);  // exclusive; bit patterns stay below 2^31
-        int n_und = 0;
-        uint32_t und = 0;
-#pragma unroll
-        for (int c = 0; c < CMAX; ++c) {
-          const bool in = e[c] >= v && e[c] < top;
-          n_und += __popcll(__ballot(in));
-          und = in ? e[c] : und;
-        }
-        if (n_und == 1) {
-          uint32_t x = und;  // the one lane that holds it has und != 0 unless it is 0
-          HEART_WAVE_REDUCE(uint32_t, x, HEART_OP_UMAX);
-          v = x > v ? x : v;
-          break;
-        }
-      }
-      unsigned long long s_gt = 0;
-      int n_gt = 0;
-#pragma unroll
-      for (int c = 0; c < CMAX; ++c) {
-        bool gt = e[c] > v;
-        s_gt += gt ? u[c] : 0u;
-        n_gt += gt ? 1 : 0;
-      }
-      s_gt = wave_sum_u64(s_gt);
-      n_gt = wave_sum_i32(n_gt);
-      int c_m = 0;
-      if (need > s_gt) {
-        const unsigned long long ustar =
-            (unsigned long long)floorf(__uint_as_float(v) * 1073741824.0f);
-        c_m = (int)((need - s_gt + ustar - 1ull) / ustar);
-      }
-      int k_mass = n_gt + c_m;
-      int k_min = min(max(1, min_keep), Nb);
-      vf = v;
-      cf = c_m;
-      if (k_mass < k_min) {
-        // the floor on the number of kept blocks wins: take the k_min best-ranked
-        uint32_t v2 = 0;
-        for (int bit = 30; bit >= 0; --bit) {
-          const uint32_t cand = v2 | (1u << bit);
-          int cnt = 0;
-#pragma unroll
-          for (int c = 0; c < CMAX; ++c) cnt += e[c] >= cand ? 1 : 0;
-          cnt = wave_sum_i32(cnt);
-          if (cnt >= k_min) v2 = cand;
-        }
-        int n_gt2 = 0;
-#pragma unroll
-        for (int c = 0; c < CMAX; ++c) n_gt2 += (lane + 64 * c < Nb && e[c] > v2) ? 1 : 0;
-        n_gt2 = wave_sum_i32(n_gt2);
-        vf = v2;
-        cf = k_min - n_gt2;
-      }
-    }
-
-    const bool dense_row = i < n_dense_q;
-    int tie_run = 0, out_run = 0;
-#pragma unroll
-    for (int c = 0; c < CMAX; ++c) {
-      const int j = lane + 64 * c;
-      const bool valid = j < Nb;
-      const bool tie = valid && e[c] == vf;
-      const unsigned long long tb = __ballot(tie);
-      const int tie_rank = tie_run + __popcll(tb & lt_mask);
-      tie_run += __popcll(tb);
-      bool keep = valid && (keep_all || dense_row || j < n_always_kv || e[c] > vf ||
-                            (tie && tie_rank < cf));
-      const unsigned long long kb = __ballot(keep);
-      const int pos = out_run + __popcll(kb & lt_mask);
-      out_run += __popcll(kb);
-      if (valid) mask[row * Nb + j] = keep ? 1 : 0;
-      if (keep) kept_idx[row * Nb + pos] = j;
-    }
-    if (lane == 0) kept_count[row] = out_run;
-  };
 
   // ---- Phases B and C, two rows per wavefront --------------------------------------------
-    // Each half of the wavefront (32 lanes) owns one row: the selection is bound by the
-    // number of vector instructions, and with 32 lanes per row every search step serves two
-    // rows and its reductions take five exchanges instead of six.  The kernel's own scores of a row sum to
-    // one, and of those handed in only rows with a sum below 1.9 come here (before, a whole wavefront and
-    // 64-bit masses a row: estimator and selection of 40 heads of 256 rows 644 -> 627 us, 20 of 256 184 -> 171, six
-    // of 28 26.8 -> 24.8), so every partial sum of the fixed-point masses stays below 2^31: the mass arithmetic is 32-bit here (same integers as in the general path below, hence the same
-    // kept sets).  The per-row state (v, top, counts) is replicated over the lanes of a half.
-    constexpr int EPL = 2 * CMAX;  // elements per lane: element c is key block l32 + 32 c
-    const int l32 = lane & 31, hfw = lane >> 5;
-    const uint32_t lt32 = (1u << l32) - 1u;
-    static_assert(kRows % (2 * kWaves) == 0, "rows per selection pass");
-    for (int rp = 0; rp < kRows / (2 * kWaves); ++rp) {
+  // Each half of the wavefront (32 lanes) owns one row: the selection is bound by the
+  // number of vector instructions, and with 32 lanes per row every search step serves two
+  // rows and its reductions take five exchanges instead of six.  The per-row state (v, top, counts)
+  // is replicated over the lanes of a half.
+  constexpr int EPL = 2 * CMAX;  // elements per lane: element c is key block l32 + 32 c
+  const int l32 = lane & 31, hfw = lane >> 5;
+  const uint32_t lt32 = (1u << l32) - 1u;
+  static_assert(kRows % (2 * kWaves) == 0, "rows per selection pass");
+  for (int rp = 0; rp < kRows / (2 * kWaves); ++rp) {
     const int r = 2 * (wave + rp * kWaves) + hfw;
     const int i = i0 + r;
     const bool row_ok = i < Nb;
     const size_t row = (size_t)bh * Nb + (row_ok ? i : 0);
     float p[EPL];
+    bool small = true;  // (uniform) no sum of masses reaches 2^31
     if (given) {
       float z = 0.f;
 #pragma unroll
@@ -469,12 +333,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
         p[c] = (row_ok && j < Nb) ? scores_in[row * Nb + j] : 0.f;
         z += p[c] > 0.f ? fminf(p[c], 1.f) : 0.f;
       }
-      z = half_sum_f32(z);
-      if (!__all(z < 1.9f)) {
-        any_row(r - hfw);
-        any_row(r - hfw + 1);
-        continue;
-      }
+      small = __all(half_sum_f32(z) < 1.9f);
     } else {
       float m = -__builtin_inff();
 #pragma unroll
@@ -505,27 +364,38 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
       }
     }
     uint32_t e[EPL], u[EPL];
-    uint32_t my_u = 0;
 #pragma unroll
     for (int c = 0; c < EPL; ++c) {
       const int j = l32 + 32 * c;
-      // (scores handed in may be anything: negative values and NaN count as 0, values above 1 as 1)
+      // (scores handed in may be anything: negative values and NaN count as 0, values above 1 as 1, so the fixed-point
+      // conversion cannot overflow)
       const float pc = (j < Nb && p[c] > 0.f) ? (given ? fminf(p[c], 1.f) : p[c]) : 0.f;
       e[c] = __float_as_uint(pc);
-      u[c] = (uint32_t)floorf(pc * 1073741824.0f);
-      my_u += u[c];
+      u[c] = (uint32_t)floorf(pc * 1073741824.0f);  // exact: power-of-two scaling
     }
-    const uint32_t U = half_sum_u32(my_u);
     const bool keep_all = tau_h >= 1.0f;  // (uniform: one head per workgroup)
-    uint32_t vf = 0;
-    int cf = 0;
-    if (!keep_all) {
+    uint32_t vf = 0;  // threshold bit pattern
+    int cf = 0;       // number of lowest-index ties at vf to keep
+    // Mass: a sum of masses.  The kernel's own scores of a row sum to one, and so do most that are handed in: every
+    // partial sum of their fixed-point masses stays below 2^31.  Rows handed in with a sum of 1.9 and more, and the row beside
+    // such a one, have 64-bit sums of the same integers, hence the same kept sets.  Selection from given scores, rows with a sum
+    // of one and of 2.5 (a whole wavefront a row and 64 bits for all -> this): 40 heads of 256 rows 27.6 and 26.9 -> 17.6 and 19.6
+    // us, 24 of 931 133 and 132 -> 84.4 and 102, 12 of 400 29.7 and 29.1 -> 18.6 and 21.3, six of 28 8.4 and 8.6 -> 6.0 and 6.9.
+    auto search = [&](auto zero) __attribute__((always_inline)) {
+      using Mass = decltype(zero);
+      Mass my_u = 0;
+#pragma unroll
+      for (int c = 0; c < EPL; ++c) my_u += u[c];
+      const Mass U = half_sum(my_u);
       const unsigned long long T =
           tau_h > 0.f ? (unsigned long long)floorf(tau_h * 16777216.0f) : 0ull;
-      const uint32_t need = (uint32_t)((T * (unsigned long long)U + 16777215ull) >> 24);
-      // The same bitwise search as in the general path, shortened at the top: a score that
-      // carries mass is at least 2^-30, so mass(>= 2^-31) is the whole row (>= need) and bits
-      // 30..28 of the threshold are known (011); the exponent bits 27..23 are probed on masses
+      const Mass need = (Mass)((T * (unsigned long long)U + 16777215ull) >> 24);
+      // v* = largest bit pattern v with mass(scores >= v) >= need, built from the top bit down.  Invariant: mass(>= v) >=
+      // need > mass(>= v + 2^(bit+1)); the scores in [v, v + 2^(bit+1)) are undecided.  As soon as a single score is
+      // undecided it IS v* (keeping it reaches the mass, dropping it does not), so the loop stops early: typically after
+      // about a dozen steps instead of 31.  need == 0 keeps nothing here.
+      // Shortened at the top: a score that carries mass is at least 2^-30 and none exceeds 1, so mass(>= 2^-31) is the
+      // whole row (>= need) and bits 30..28 of the threshold are known (011); the exponent bits 27..23 are probed on masses
       // alone (a binade holds many scores, the early exit below never fires there); from bit 22
       // on the count of undecided scores is kept incrementally: n_v = #(scores >= v),
       // n_top = #(scores >= top).
@@ -534,10 +404,10 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
       for (int bit = 27; bit >= 23; --bit) {
         if (!__any(active)) break;
         const uint32_t cand = v | (1u << bit);
-        uint32_t s = 0;
+        Mass s = 0;
 #pragma unroll
         for (int c = 0; c < EPL; ++c) s += e[c] >= cand ? u[c] : 0u;
-        s = half_sum_u32(s);
+        s = half_sum(s);
         if (active && s >= need) v = cand;
       }
       uint32_t n_v = 0, n_top = 0;
@@ -548,21 +418,22 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
           n_v += e[c] >= v ? 1u : 0u;
           n_top += e[c] >= top ? 1u : 0u;
         }
-        n_v = half_sum_u32(n_v);
-        n_top = half_sum_u32(n_top);
+        n_v = half_sum(n_v);
+        n_top = half_sum(n_top);
       }
       for (int bit = 22; bit >= 0; --bit) {
         if (!__any(active)) break;
         const uint32_t cand = v | (1u << bit);
-        uint32_t s = 0, cn = 0;
+        Mass s = 0;
+        uint32_t cn = 0;
 #pragma unroll
         for (int c = 0; c < EPL; ++c) {
           const bool ge = e[c] >= cand;
           s += ge ? u[c] : 0u;
           cn += ge ? 1u : 0u;
         }
-        s = half_sum_u32(s);
-        cn = half_sum_u32(cn);
+        s = half_sum(s);
+        cn = half_sum(cn);
         if (active) {
           if (s >= need) {
             v = cand;
@@ -585,24 +456,33 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
           }
         }
       }
-      uint32_t s_gt = 0, n_gt = 0;
+      Mass s_gt = 0;
+      uint32_t n_gt = 0;
 #pragma unroll
       for (int c = 0; c < EPL; ++c) {
         const bool gt = e[c] > v;
         s_gt += gt ? u[c] : 0u;
         n_gt += gt ? 1u : 0u;
       }
-      s_gt = half_sum_u32(s_gt);
-      n_gt = half_sum_u32(n_gt);
-      uint32_t c_m = 0;
+      s_gt = half_sum(s_gt);
+      n_gt = half_sum(n_gt);
+      Mass c_m = 0;
       if (need > s_gt) {
         const uint32_t ustar = (uint32_t)floorf(__uint_as_float(v) * 1073741824.0f);
         c_m = (need - s_gt + ustar - 1u) / (ustar > 0u ? ustar : 1u);
       }
-      const int k_mass = (int)(n_gt + c_m);
-      const int k_min = min(max(1, min_keep), Nb);
       vf = v;
       cf = (int)c_m;
+      return (int)n_gt;
+    };
+    if (!keep_all) {
+      int n_gt;
+      if (__builtin_expect(!given || small, 1))
+        n_gt = search(0u);
+      else
+        n_gt = search(0ull);
+      const int k_mass = n_gt + cf;
+      const int k_min = min(max(1, min_keep), Nb);
       const bool floor_wins = k_mass < k_min;
       if (__any(floor_wins)) {
         // the floor on the number of kept blocks: the k_min best-ranked of such a row
@@ -612,13 +492,13 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
           uint32_t cn = 0;
 #pragma unroll
           for (int c = 0; c < EPL; ++c) cn += e[c] >= cand ? 1u : 0u;
-          cn = half_sum_u32(cn);
+          cn = half_sum(cn);
           if ((int)cn >= k_min) v2 = cand;
         }
         uint32_t n_gt2 = 0;
 #pragma unroll
         for (int c = 0; c < EPL; ++c) n_gt2 += (l32 + 32 * c < Nb && e[c] > v2) ? 1u : 0u;
-        n_gt2 = half_sum_u32(n_gt2);
+        n_gt2 = half_sum(n_gt2);
         if (floor_wins) {
           vf = v2;
           cf = k_min - (int)n_gt2;
@@ -646,7 +526,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
       if (keep) kept_idx[row * Nb + pos] = j;
     }
     if (l32 == 0 && row_ok) kept_count[row] = out_run;
-    }  // selection passes
+  }  // selection passes
 }
 
 template <int CMAX, int NF4T, bool kInt8>

@@ -95,3 +95,18 @@ def test_scores_of_any_sum(Nb):
         assert np.array_equal(m, om) and np.array_equal(c, oc)
         listed = np.arange(Nb) < oc[..., None]
         assert np.array_equal(i[listed], oi[listed])
+
+
+# the largest masses there are: every score counts as one, and the first half of the blocks has half of the mass.  One slot a lane and
+# 32, beside a row without mass
+@pytest.mark.parametrize("Nb", [31, 64, 257, 1024])
+def test_scores_all_above_one(Nb):
+    import paper_2605_14513_amd as heart
+
+    s = torch.full((1, 1, Nb, Nb), 3.0, device="cuda")
+    s[0, 0, 1::2] = 0.0
+    print(f"scores all above one Nb={Nb}", flush=True)
+    m, i, c = (x.cpu().numpy()[0, 0] for x in heart.heart_mask_topp(None, None, torch.full((1,), 0.5, device="cuda"), scores_in=s))
+    half = (Nb + 1) // 2
+    assert (c[::2] == half).all() and (c[1::2] == 1).all()
+    assert (m[::2] == (np.arange(Nb) < half)).all() and (i[::2, :half] == np.arange(half)).all()
