@@ -290,14 +290,18 @@ size_t heart_workspace_bytes(int B, int H, int Nb, int D);
 size_t heart_attn_workspace_bytes(const heart_shape *shape);
 
 /*
- * The workspace_bytes with which heart_block_sparse_attn also divides the lists of launches in which a place for a workgroup
- * (two per CU, four at block = 64) works on few query blocks (up to 2.9; 2 at D = 128, block = 64; more where the heads
- * are short), so that uneven lists no longer decide when the call ends.  Exactly this size asks for it (a buffer that is larger is passed with this size).  Such a workspace holds
- * no plan but the parts of the query blocks that were divided (71 MB at most), and the results are those of another
- * size up to rounding; where lists are divided, and with it the rounding of a query block, depends on the kept counts of
- * all heads of the call.  Where dividing does not pay, and for other shapes, the same as heart_attn_workspace_bytes; with
- * dense != 0 (lists that keep every block) it pays less often.  Only lists of uneven length gain: a call whose lists
- * are all about equally long can take up to a fifth longer than with heart_attn_workspace_bytes.  0 for an invalid shape.
+ * The workspace_bytes with which heart_block_sparse_attn also divides the lists of launches in which a place for a
+ * workgroup (two per CU, four at block = 64) works on few query blocks, so that uneven lists no longer decide when the call
+ * ends: up to 2.9 query blocks a place (2 at D = 128, block = 64; 2.5 at D = block = 64 for heads of at most 64 blocks), more
+ * where the heads are short.  Exactly this size asks for it (a buffer that is larger is passed with this size).  Such a
+ * workspace holds the parts of the query blocks that were divided (71 MB at most), and the results are those of another size
+ * up to rounding; where lists are divided, and with it the rounding of a query block, depends on the kept counts of all heads
+ * of the call.  With many query blocks a place and long heads, lists that keep more than about a quarter of the blocks are
+ * left to a plan, which the workspace then holds, and the results are those of another size bit for bit: decided on the
+ * device, by the kept counts of the call.  Where dividing does not pay, and for other shapes, the same as
+ * heart_attn_workspace_bytes; with dense != 0 (lists that keep every block) it pays less often.  Only lists of uneven length
+ * gain: a call of at most two query blocks a place whose lists are all about equally long can take up to a fifth longer
+ * than with heart_attn_workspace_bytes.  0 for an invalid shape.
  */
 size_t heart_attn_balanced_workspace_bytes(const heart_shape *shape, int dense);
 

@@ -306,10 +306,18 @@ template <bool kStaged, int kThreads>
 __global__ __launch_bounds__(kThreads) void attn_plan_kernel(const int *__restrict__ kept_idx,
                                                              const int *__restrict__ kept_count, int BH,
                                                              int Nb, int n_wg, int n_few, uint32_t mult, int batch,
-                                                             int *__restrict__ plan, int *__restrict__ spread,
-                                                             int *__restrict__ near_seq) {
+                                                             const int *__restrict__ skip, int *__restrict__ plan,
+                                                             int *__restrict__ spread, int *__restrict__ near_seq) {
   extern __shared__ __align__(16) unsigned char lds[];
   int id = blockIdx.x;
+  if (skip && *skip == 0) {
+    if (id == 0) {
+      for (int i = threadIdx.x; i < BH; i += kThreads) plan[kPlanHdr + BH + i] = 0;
+      if (threadIdx.x < kPlanHdr) plan[threadIdx.x] = 0;
+      if (spread && threadIdx.x < kNumXcd) spread[threadIdx.x * kCursorSpread] = 0;
+    }
+    return;
+  }
   if (kThreads == kPlanThreads && near_seq) {
     if (id < BH) {
       if (Nb <= 256)
@@ -336,7 +344,7 @@ __global__ __launch_bounds__(kThreads) void attn_plan_kernel(const int *__restri
 }  // namespace
 
 int launch_attn_plan(int BH, int Nb, int n_wg, int n_few, int n_items, const int *kept_idx, const int *kept_count,
-                     int *plan, size_t plan_bytes, const int **seq, int **cursors, hipStream_t st) {
+                     const int *skip, int *plan, size_t plan_bytes, const int **seq, int **cursors, hipStream_t st) {
   int *class_seq = plan + kPlanHdr + 2 * BH;
   int *near_seq = nullptr;
   // (with one row per workgroup there is nothing to order)
@@ -376,7 +384,7 @@ int launch_attn_plan(int BH, int Nb, int n_wg, int n_few, int n_items, const int
   const uint32_t mult = (uint32_t)(((kOrderClasses - 1) << 16) / Nb);
   const unsigned grid = (unsigned)(1 + (BH < kPlanMaxGroups ? BH : kPlanMaxGroups) + (near_seq ? BH : 0));
   hipLaunchKernelGGL(kern, dim3(grid), dim3(small ? kOrderCols : kPlanThreads), lds, st, kept_idx, kept_count, BH,
-                     Nb, n_wg, n_few, mult, batch, plan, spread, near_seq);
+                     Nb, n_wg, n_few, mult, batch, skip, plan, spread, near_seq);
   return check_launch("attn_plan_kernel");
 }
 

@@ -180,13 +180,14 @@ size_t attn_split_bytes(long long BH, long long Nb, int D, int block) {
 //   parts   every row is split into parts of at most L blocks, L as small as the places allow; each workgroup has one
 //           part, all start at once
 //   whole   a workgroup per row, as far as that is no slower: few rows of nearly the same length
-// Every workgroup finds the rule and its part or share from the kept counts by itself (read once, 16 KB at most), so there
-// is no plan, no queue and no atomic, and what is divided where, and with it the bits, is a function of the counts alone.
+// Every workgroup finds the rule and its part or share from the kept counts by itself (read once, 16 KB at most): no plan and
+// no queue, and what is divided where, and with it the bits, is a function of the counts alone.  Only the parts of a divided
+// row are counted, by one ticket a row, where a workgroup adds them up.
 // XCD x takes the x-th eighth of the parts or shares, so it sees an eighth of the heads.
-// What it costs: 1.5 to 3 us until a workgroup knows its share, and the merge (2 to 4 us in the workgroups, 4 to 13 as a launch).  Calls with a plan -> with
-// shares, lists of the timed fields, several seeds: 20 heads of 101 rows (D = 64, block 64) 99 to 127 -> 74 to 111 us; D = 128,
-// block 128: six heads of 88 rows 193 to 224 -> 146 to 159, two of 247 375 -> 204 to 237; D = 128, block 64: 21 heads of 73
-// rows 110 to 118 -> 96; dense lists, four heads of 147 rows (D = 128, block 128) 726 -> 669.
+// What it costs: 1.5 to 3 us until a workgroup knows its share, and the merge (2 to 4 us in the workgroups, 4 to 13 as a
+// launch).  Calls with a plan -> with shares, lists of the timed fields, several seeds: 20 heads of 101 rows (D = 64, block 64)
+// 99 to 127 -> 74 to 111 us; D = 128, block 128: six heads of 88 rows 193 to 224 -> 146 to 159, two of 247 375 -> 204 to 237;
+// D = 128, block 64: 21 heads of 73 rows 110 to 118 -> 96; dense lists, four heads of 147 rows (D = 128, block 128) 726 -> 669.
 constexpr int kShareGroup = 256, kShareMaxRows = 16 * kShareGroup;  // rows; counts are summed up in groups, four rows a lane
 constexpr int kShareMin = 8;       // shortest share
 constexpr int kSharePart = 2;      // fewest blocks of a part: a cut closer to an end of its row goes there
@@ -201,29 +202,59 @@ __device__ __forceinline__ int share_blocks(int d, int cnt) {
 }
 
 // Shares of a launch (workgroups; those that find no share for them end at once), 0 = rows are not shared.  A function
-// of the sizes.  With a plan the uneven lengths cost the more the fewer rows a place has; with shares the workgroups of an XCD
-// are at places of K/V that lie further apart than its L2 is wide, the more the longer the rows are.  Steps on lists of the timed
-// fields (thresholds 0.85 to 0.98, as all figures here), plan -> shares, us:
-//   up to 2.9 rows a place  D = 128, block 128: two heads of 520 rows (2.0) 815 -> 630, three of 360 (2.1) 767 -> 543, six of 230 (2.7)
-//                           588 -> 550, two of 700 (2.7) 1285 -> 1245, three of 480 (2.8) 1053 -> 909, five of 300 (2.9) 843 -> 796; D =
-//                           64, block 64: 16 of 176 (2.8) 249 -> 181, six of 480 (2.8) 463 -> 406, three of 960 (2.8) 711 -> 717; at 3 and
-//                           3.1: 11 of 140 398 -> 404, two of 800 1861 -> 1874
-//   more, and rows a place times the elements of a head's keys up to share_near: D = 128: 16 of 110 (3.4) 406 -> 362, 21 of 88 (3.6)
-//                           407 -> 362, 26 of 80 (4.1) 404 -> 371; beyond: 14 of 120 (3.3) 403 -> 419, 10 of 176 (3.4) 511 -> 530, 12 of
-//                           256 (6) 1331 -> 1434; D = 64: 12 of 320 (3.8; block 64) 413 -> 377, eight of 248 (3.9; block 128) 666 -> 607, 14
-//                           of 160 (4.4) 467 -> 441; beyond: five of 400 (3.9) 845 -> 845, 14 of 244 (6.7) 750 -> 790
-//   D = 128, block 64       (four workgroups a CU feel the L2 most) two rows a place and share_near: two of 576 (1.1) 473 -> 390, three
-//                           of 480 (1.4) 450 -> 383, 14 of 128 (1.8) 173 -> 162; beyond: 30 of 122 (3.6) 286 -> 332, two of 960 (1.9),
-//                           lists of 60 % 1160 -> 1534
-// Lists of 60 % of the blocks and more gain nothing and lose up to a tenth (two of 700 1741 -> 1837), lists of 10 % gain most (707 -> 522).
-// (D = 64, block 64: rows of at most 64 blocks stay at the 2.5 rows a place that a test holds them to; 41 heads of 64 rows would gain 110
-// -> 82 us.)  Rows of few blocks a part of kSplitRows are left to that.
-// Dense lists need no levelling: only where a last round of whole rows would leave many places empty (D = 128, block 128: seven heads of
-// 98 rows (1.3) 522 -> 508, six of 122 (1.4) 665 -> 673, two of 366 (1.4) 1936 -> 1987; D = 64: 12 of 147 (1.7) 382 -> 342, 20 of 147 (2.9) 591
-// -> 588).  (Lists that are nearly full and of nearly equal length without the caller's saying so: 0.79 to 1.6 times as fast, the least with
-// 1.6 to 2 rows a place at D = 128, block 64.)
+// of the sizes.  With a plan the uneven lengths cost the more the fewer rows a place has; with shares the workgroups of an
+// XCD are at places of K/V that lie further apart than its L2 is wide, the more the longer the rows are.  Steps on lists of
+// the timed fields (thresholds 0.85 to 0.98), plan -> shares, us:
+//   up to 2.9 rows a place  D = 128, block 128: two heads of 520 rows (2.0) 815 -> 630, three of 360 (2.1) 767 -> 543, six
+//                           of 230 (2.7) 588 -> 550, two of 700 (2.7) 1285 -> 1245, three of 480 (2.8) 1053 -> 909, five of
+//                           300 (2.9) 843 -> 796; D = 64, block 64: 16 of 176 (2.8) 249 -> 181, six of 480 (2.8) 463 ->
+//                           406; at 3 and 3.1: 11 of 140 398 -> 404, two of 800 1861 -> 1874
+//   more, and rows a place times the elements of a head's keys up to share_near: D = 128: 16 of 110 (3.4) 406 -> 362, 21 of
+//                           88 (3.6) 407 -> 362, 26 of 80 (4.1) 404 -> 371; beyond: 14 of 120 (3.3) 403 -> 419, 10 of 176
+//                           (3.4) 511 -> 530, 12 of 256 (6) 1331 -> 1434; D = 64: 12 of 320 (3.8; block 64) 413 -> 377,
+//                           eight of 248 (3.9; block 128) 666 -> 607, 14 of 160 (4.4) 467 -> 441; beyond: five of 400 (3.9)
+//                           845 -> 845, 14 of 244 (6.7) 750 -> 790
+//   D = 128, block 64       (four workgroups a CU feel the L2 most) two rows a place and share_near: two of 576 (1.1) 473 ->
+//                           390, three of 480 (1.4) 450 -> 383, 14 of 128 (1.8) 173 -> 162; beyond: 30 of 122 (3.6) 286 -> 332
+// Lists of 10 % of the blocks gain most (two of 700 rows 707 -> 522), for those that keep much see share_most.  Rows of few
+// blocks a part of kSplitRows are left to that.
+// (D = 64, block 64: heads of at most 64 blocks keep the limit of 2.5 rows a place, and with it the workspace size and the bits
+// that the tests hold them to.  That is no limit of the chip: 52 heads of 49 rows, just below it, take 101 us with a plan and 74
+// with shares, 41 of 64, just beyond, 110 and would take 82.)
+// Dense lists need no levelling: only where a last round of whole rows would leave many places empty (D = 128, block 128:
+// seven heads of 98 rows (1.3) 522 -> 508, six of 122 (1.4) 665 -> 673, two of 366 (1.4) 1936 -> 1987; D = 64: 12 of 147 (1.7)
+// 382 -> 342, 20 of 147 (2.9) 591 -> 588).
 // rows a place times elements of a head's keys
 constexpr long long share_near(int D, int block) { return (D == 64 ? 650ll : block == 64 ? 700ll : 380ll) * 128 * 128; }
+
+// Most kept blocks of a launch that are shared (kShareAny: any number).  Long lists in long rows gain nothing and lose: 0.88
+// to 1 times as fast at D = 128, block 128, 0.84 at D = 64, block 64 with 950 rows a head, 0.7 to 0.95 at D = 128, block 64.
+// Beyond share_sure the workgroups, which know all counts, therefore leave lists of more than 28 % of the blocks, or of more
+// than share_far to a place, to a plan and a launch that follows it; where they do not, these two end at once (6 to 8 us).
+// Calls of shares for any lists -> this, us, and with a plan: D = 128, block 128: two heads of 695 rows, 47 % kept, 3710 -> 3340
+// (3327), 16 % 1166 -> 1179 (1190), three of 476, 70 % 3744 -> 3551 (3524), 14 % 713 -> 722 (906); D = 64, block 64: three of
+// 951, 62 % 2940 -> 2305 (2298), 13 % 476 -> 483 (660); D = 128, block 64: three of 464, 68 % 1543 -> 1082 (1069), 13 % 259 ->
+// 265 (338), eight of 226, 78 % 783 -> 712 (722), 15 % 156 -> 164 (229).
+// Up to share_sure, and up to two rows a place (2.5 at D = 64, one at D = 128, block 64), any lists are shared: what lists that
+// keep much lose there (up to 4 %; at most two rows a place up to a tenth, a fifth at D = 128, block 64) is little beside what
+// others gain (1.1 to 1.6 times as fast), which the two launches would take a part of.  So with D = 64, block 128 for all (six
+// heads of 293 rows 0.95 with 70 % kept, 1.06 with 37 %, 1.2 with 11 %).
+// share_far: kept blocks a place.  An XCD that has rows of two heads at a time finds less of them in its L2.  Shares are
+// as fast as the plan at, % of the blocks: D = 128, block 128: two heads of 695 rows 22, of 598 30, three of 476 15, of 415 28,
+// of 354 29, four of 317 30, five of 256 27; D = 64, block 64: three of 951 15, of 854 17, four of 683 27, six of 464 31;
+// D = 128, block 64: two of 537 29, three of 439 17, of 464 16, five of 287 31, six of 256 28.
+constexpr long long share_sure(int D, int block) { return (D == 64 ? 430ll : block == 64 ? 150ll : 600ll) * 128 * 128; }
+constexpr int share_far(int D, int block) { return D == 64 ? 380 : block == 64 ? 96 : 225; }
+constexpr int kShareAny = 0x7fffffff;
+static int share_most(long long BH, long long Nb, int D, int block) {
+  const long long places = attn_places(D, block), rows = BH * Nb;
+  if (D == 64 && block == 128) return kShareAny;
+  if (2 * rows <= (D == 64 ? 5 : block == 64 ? 2 : 4) * places) return kShareAny;
+  if (rows * Nb * D * block <= share_sure(D, block) * places) return kShareAny;
+  const bool one_head = BH % kNumXcd == 0 || kNumXcd % BH == 0;  // an XCD has rows of one head at a time
+  const long long all = rows * Nb * 7 / 25, far = (one_head ? 2 : 1) * share_far(D, block) * places;
+  return (int)(all < far ? all : far);
+}
 int attn_shares(long long BH, long long Nb, int D, int block, bool dense) {
   const long long places = attn_places(D, block);
   if (BH > kShareMaxRows || Nb > kShareMaxRows || BH * Nb > kShareMaxRows) return 0;
@@ -850,6 +881,12 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     __syncthreads();
     int gl = lane < kGroups ? group_sum[0][lane] : 0;  // blocks of group `lane`, then its length
     const int blocks = __builtin_amdgcn_readfirstlane(wave_sum_i32(gl)), total = 2 * blocks + kShareRowCost * rows, n_wg = (int)gridDim.x;
+    if constexpr (kMode == kSharedMerged) {
+      // (n_few: the most blocks that are shared; *cursors: whether the plan is to do it)
+      if (cursors && blockIdx.x == 0 && t == 0)
+        __hip_atomic_store(cursors, blocks > n_few ? 1 : 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (blocks > n_few) return;
+    }
     // blocks of a part, 0 = shares.  Any number from blocks / (n_wg - rows) up gives no more parts than workgroups
     // (n / most + 1 a row).  The rule is the one with the shortest way, in half blocks: the longest row; a part and
     // the merge of all; a share with a row more than the mean and the merge (which takes one for 64 parts).
@@ -1419,65 +1456,71 @@ static int launch_attn_t(const heart_shape &s, const void *q, const void *k, con
   const bool split = !share && n_split > 1 && order_bytes >= attn_split_bytes(BH, Nb, D, BLK);
   const size_t lds = 4 * (size_t)kStageRows<D, BLK> * D * 2;  // >= BLK * (D + 8) * 2 of the output staging
   const bool merged = (share && merge_shares(n_share, n_items, Nb)) || (split && n_split <= kMergeParts);
-  const AttnMode mode = share ? (merged ? kSharedMerged : kSharedRows) : split ? (merged ? kSplitMerged : kSplitRows) : kPlanned;
-  auto kern = mode == kSharedMerged  ? attn_kernel<D, BLK, kExact, kSharedMerged>
-              : mode == kSharedRows  ? attn_kernel<D, BLK, kExact, kSharedRows>
-              : mode == kSplitMerged ? attn_kernel<D, BLK, kExact, kSplitMerged>
-              : mode == kSplitRows   ? attn_kernel<D, BLK, kExact, kSplitRows>
-                                     : attn_kernel<D, BLK, kExact, kPlanned>;
+  const int most = share && merged ? share_most(BH, Nb, D, BLK) : kShareAny;
+  const bool watch = most != kShareAny;  // (more rows than places: always merged)
   const int dev = current_device();
   if (dev < 0) return fail(HEART_EHIP, "heart_block_sparse_attn: cannot identify the current device");
-  static DeviceFlags attr_set[5];  // per instantiation: the attribute is per function and device
-  if (hipError_t e = set_max_lds_once(attr_set[mode], dev, reinterpret_cast<const void *>(kern), (int)lds))
-    return fail(HEART_EHIP, "hipFuncSetAttribute(max dynamic LDS %zu): %s", lds, hipGetErrorString(e));
   const float sc = scale > 0.f ? scale : 1.0f / sqrtf((float)D);
   const float scale_log2e = sc * 1.4426950408889634f;
-  long long grid = (long long)BH * ((Nb + kNumXcd - 1) / kNumXcd) * kNumXcd;
-  int n_few = 0;  // (a plan: see working_groups)
   float *part = nullptr;
   int4 *owner = nullptr;
+  auto run = [&](auto mode, long long grid, int *plan, const int *seq, int *cursors, int cursor_step, int n_few) -> int {
+    auto kern = attn_kernel<D, BLK, kExact, decltype(mode)::value>;
+    static DeviceFlags attr_set;  // per instantiation: the attribute is per function and device
+    if (hipError_t e = set_max_lds_once(attr_set, dev, reinterpret_cast<const void *>(kern), (int)lds))
+      return fail(HEART_EHIP, "hipFuncSetAttribute(max dynamic LDS %zu): %s", lds, hipGetErrorString(e));
+    if (grid > 0x7fffffffLL) return fail(HEART_EUNSUPPORTED, "heart_block_sparse_attn: grid too large");
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(BLK * 2), lds, st,
+                       (const uint16_t *)q, (const uint16_t *)k, (const uint16_t *)v,
+                       (uint16_t *)out, s.q_stride[0], s.q_stride[1], s.q_stride[2], s.k_stride[0],
+                       s.k_stride[1], s.k_stride[2], s.v_stride[0], s.v_stride[1], s.v_stride[2],
+                       s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, BH, s.N, Nb, kept_idx,
+                       kept_count, scale_log2e, lse, plan, seq, cursors, cursor_step, part, owner,
+                       merged ? call_mark() : 0ull, n_split, n_few);
+    return check_launch("attn_kernel");
+  };
+  auto merge = [&](long long n) -> int {
+    hipLaunchKernelGGL((attn_merge_kernel<D, BLK>), dim3((unsigned)(n * (BLK / 32))), dim3(D * 2), 0, st, part,
+                       owner, n_split, (uint16_t *)out, s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, s.N, Nb, lse);
+    return check_launch("attn_merge_kernel");
+  };
+  const int *skip = nullptr;  // (a plan for lists that the shares left)
   if (share) {
     owner = reinterpret_cast<int4 *>(order);
     part = reinterpret_cast<float *>(owner + n_share);
-    order = nullptr;
-    grid = n_share;
+    int *left = watch ? order + 2 : nullptr;  // (the third word of the first owner is free beside its ticket)
+    if (int rc = merged ? run(std::integral_constant<AttnMode, kSharedMerged>{}, n_share, nullptr, nullptr, left, 1, most)
+                        : run(std::integral_constant<AttnMode, kSharedRows>{}, n_share, nullptr, nullptr, nullptr, 1, 0))
+      return rc;
+    if (!watch) return merged ? HEART_OK : merge(n_share);
+    skip = left;
+    order = reinterpret_cast<int *>(part);  // (the parts are not there where there is a plan)
+    order_bytes -= (size_t)n_share * sizeof(int4);
   }
   if (split) {
     part = reinterpret_cast<float *>(order);
-    order = nullptr;
-    grid = (n_items * n_split + kNumXcd - 1) / kNumXcd * kNumXcd;
+    const long long grid = (n_items * n_split + kNumXcd - 1) / kNumXcd * kNumXcd;
+    if (merged) return run(std::integral_constant<AttnMode, kSplitMerged>{}, grid, nullptr, nullptr, nullptr, 1, 0);
+    if (int rc = run(std::integral_constant<AttnMode, kSplitRows>{}, grid, nullptr, nullptr, nullptr, 1, 0)) return rc;
+    return merge(n_items);
   }
-  if (order) {
-    // persistent workgroups: as many as are resident at once (HEART_ATTN_OCC per SIMD, i.e.
-    // two workgroups of four wavefronts per CU)
-    const int n_cu = cu_count(dev);
-    if (n_cu <= 0) return fail(HEART_EHIP, "heart_block_sparse_attn: cannot query the number of CUs");
-    const long long resident = (long long)n_cu * HEART_ATTN_OCC * 4 / (BLK / 32);
-    grid = n_items < resident ? n_items : resident;
-    const bool few = kStageRows<D, BLK> < 64 && BH <= kFewHeads && n_items <= kFewRows && grid > 2 * n_cu;
-    n_few = few ? 2 * n_cu : (int)grid;
-  }
-  if (grid > 0x7fffffffLL) return fail(HEART_EUNSUPPORTED, "heart_block_sparse_attn: grid too large");
+  const std::integral_constant<AttnMode, kPlanned> planned;
+  if (!order)
+    return run(planned, (long long)BH * ((Nb + kNumXcd - 1) / kNumXcd) * kNumXcd, nullptr, nullptr, nullptr, 1, 0);
+  // persistent workgroups: as many as are resident at once (HEART_ATTN_OCC per SIMD, i.e.
+  // two workgroups of four wavefronts per CU)
+  const int n_cu = cu_count(dev);
+  if (n_cu <= 0) return fail(HEART_EHIP, "heart_block_sparse_attn: cannot query the number of CUs");
+  const long long resident = (long long)n_cu * HEART_ATTN_OCC * 4 / (BLK / 32);
+  const long long grid = n_items < resident ? n_items : resident;
+  const bool few = kStageRows<D, BLK> < 64 && BH <= kFewHeads && n_items <= kFewRows && grid > 2 * n_cu;
+  const int n_few = few ? 2 * n_cu : (int)grid;  // (see working_groups)
   const int *seq = nullptr;
   int *spread = nullptr;
-  if (order) {
-    if (int rc = launch_attn_plan(BH, Nb, (int)grid, n_few, (int)n_items, kept_idx, kept_count, order, order_bytes,
-                                  &seq, &spread, st))
-      return rc;
-  }
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(BLK * 2), lds, st,
-                     (const uint16_t *)q, (const uint16_t *)k, (const uint16_t *)v,
-                     (uint16_t *)out, s.q_stride[0], s.q_stride[1], s.q_stride[2], s.k_stride[0],
-                     s.k_stride[1], s.k_stride[2], s.v_stride[0], s.v_stride[1], s.v_stride[2],
-                     s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, BH, s.N, Nb, kept_idx,
-                     kept_count, scale_log2e, lse, order, seq, spread ? spread : order,
-                     spread ? kCursorSpread : 1, part, owner, merged ? call_mark() : 0ull,
-                     n_split, n_few);
-  if (int rc = check_launch("attn_kernel")) return rc;
-  if ((!split && !share) || merged) return HEART_OK;
-  hipLaunchKernelGGL((attn_merge_kernel<D, BLK>), dim3((unsigned)((share ? n_share : n_items) * (BLK / 32))), dim3(D * 2), 0, st, part,
-                     owner, n_split, (uint16_t *)out, s.o_stride[0], s.o_stride[1], s.o_stride[2], s.H, s.N, Nb, lse);
-  return check_launch("attn_merge_kernel");
+  if (int rc = launch_attn_plan(BH, Nb, (int)grid, n_few, (int)n_items, kept_idx, kept_count, skip, order, order_bytes,
+                                &seq, &spread, st))
+    return rc;
+  return run(planned, grid, order, seq, spread ? spread : order, spread ? kCursorSpread : 1, n_few);
 }
 
 template <bool kExact>

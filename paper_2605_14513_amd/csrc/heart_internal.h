@@ -273,9 +273,10 @@ __host__ __device__ constexpr int list_first(int n_wg, int list, int BH) {
 }
 // Enqueues the plan for a launch of n_wg attention workgroups, of which working_groups(n_wg, n_few, ..)
 // work (with n_few < n_wg in order of length alone), over n_items items; *seq = the sequence that launch
-// follows; *cursors = the spread cursors or null.
+// follows; *cursors = the spread cursors or null.  With *skip = 0 (device memory; null: no question) the plan has
+// no items, and the launch that follows it ends at once.
 int launch_attn_plan(int BH, int Nb, int n_wg, int n_few, int n_items, const int *kept_idx, const int *kept_count,
-                     int *plan, size_t plan_bytes, const int **seq, int **cursors, hipStream_t st);
+                     const int *skip, int *plan, size_t plan_bytes, const int **seq, int **cursors, hipStream_t st);
 
 // Parts that the kept list of every row is split into, 1 = not (a function of the sizes alone), and the
 // workspace bytes the parts take (instead of a plan; 0 if rows are not split).

@@ -293,6 +293,19 @@ def test_size_that_asks_for_divided_rows(lib, B, H, Nb, D, block, divided):
     assert dense in (usual, asks)
 
 
+# the same on either side of the limits of rows a place (2.9; two at D = 128, block 64; 2.5 at D = block = 64 for heads of at most 64 blocks),
+# of short heads beyond them, and of 4096 rows
+@pytest.mark.parametrize("B,H,Nb,D,block,divided", [
+    (1, 4, 371, 128, 128, True), (1, 4, 372, 128, 128, False), (1, 26, 80, 128, 128, True), (1, 16, 110, 128, 128, True),
+    (1, 16, 111, 128, 128, False), (1, 4, 371, 64, 128, True), (1, 4, 372, 64, 128, True), (1, 8, 288, 64, 128, True),
+    (1, 8, 289, 64, 128, False), (1, 4, 742, 64, 64, True), (1, 4, 817, 64, 64, False), (1, 40, 64, 64, 64, True),
+    (1, 41, 64, 64, 64, False), (1, 41, 65, 64, 64, True), (1, 16, 128, 128, 64, True), (1, 16, 129, 128, 64, False),
+    (1, 2, 846, 128, 64, True), (1, 2, 847, 128, 64, False), (1, 256, 16, 128, 128, True), (1, 257, 16, 128, 128, False),
+    (1, 40, 256, 128, 64, False)])
+def test_limits_of_rows_a_place(lib, B, H, Nb, D, block, divided):
+    test_size_that_asks_for_divided_rows(lib, B, H, Nb, D, block, divided)
+
+
 def test_product_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2605_14513_amd")
     for dirpath, _, files in os.walk(pkg):

@@ -237,3 +237,123 @@ def test_merged_parts_in_memory_of_any_contents(H, Nb, D, block):
             run()
             torch.cuda.synchronize()
             assert torch.equal(out, want) and torch.equal(lse, want_lse), f"round {i}"
+
+
+def _bits_or_bound(heart, q, k, v, block, idx, cnt, ws, same):
+    """A divided launch twice, whatever the workspace holds: the bits of the undivided one (`same`), or two roundings of a weight
+    and one of the output from it (a tenth more for fp32, as above); the row sums that the two make."""
+    B, H, N, _ = q.shape
+    lse, lse0 = (torch.full((B, H, N), float("nan"), device="cuda") for _ in range(2))
+    one = heart.heart_block_sparse_attn(q, k, v, block, idx, cnt, workspace=None, lse=lse0)
+    mass = heart.heart_block_sparse_attn(q, k, v.abs(), block, idx, cnt, workspace=None).float()
+    for fill in (255, 0):
+        ws.fill_(fill)
+        out = heart.heart_block_sparse_attn(q, k, v, block, idx, cnt, workspace=ws, lse=lse, out=torch.full_like(q, float("nan")))
+        again = heart.heart_block_sparse_attn(q, k, v, block, idx, cnt, workspace=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(out, again)
+        if same:
+            assert torch.equal(out, one) and torch.equal(lse, lse0)
+        else:
+            assert ((out.float() - one.float()).abs() <= 1.1 * 2.0 ** -8 * (mass + one.float().abs()) * 1.01).all()
+            empty = torch.isinf(lse0)
+            assert torch.equal(torch.isinf(lse), empty)
+            assert empty.all() or (lse - lse0)[~empty].abs().max() <= 2e-5 * lse0[~empty].abs().max()
+    return torch.equal(out, one)
+
+
+def _lists(H, Nb, D, block, seed):
+    N = Nb * block - 5
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    q, k, v = (torch.randn((1, N, H, D), generator=g, device="cuda").bfloat16().transpose(1, 2) for _ in range(3))
+    idx = torch.argsort(torch.rand((1, H, Nb, Nb), generator=g, device="cuda"), dim=-1).int()
+    return q, k, v, idx
+
+
+# three to eight rows a place, where the heads are short (the most rows there are: 4096): shares that end a row, take several whole
+# ones and begin the next
+@pytest.mark.parametrize("kind", ["uneven", "long", "full", "empty"])
+@pytest.mark.parametrize("H,Nb,D,block", [(26, 80, 128, 128), (16, 110, 128, 128), (50, 80, 64, 64), (16, 176, 64, 64), (8, 180, 64, 128), (8, 172, 128, 128),
+                                          (3, 460, 64, 128), (256, 16, 128, 128), (512, 8, 64, 128), (585, 7, 128, 128), (14, 128, 128, 64)])
+def test_shares_of_several_rows_a_place(H, Nb, D, block, kind):
+    import paper_2605_14513_amd as heart
+
+    q, k, v, idx = _lists(H, Nb, D, block, Nb)
+    rng = np.random.default_rng(H)
+    cnt = rng.integers(0, Nb // 4 + 2, size=(1, H, Nb)).clip(0, Nb).astype(np.int32)
+    if kind == "long":
+        cnt[rng.random(cnt.shape) < 0.1] = Nb
+    elif kind != "uneven":
+        cnt[:] = Nb if kind == "full" else 0
+    n_bytes = heart.heart_attn_balanced_workspace_bytes(q, block)
+    assert n_bytes > heart.heart_attn_workspace_bytes(q, block)
+    print(f"H={H} Nb={Nb} D={D} block={block} {kind}", flush=True)
+    ws = torch.empty(n_bytes, dtype=torch.uint8, device="cuda")
+    _bits_or_bound(heart, q, k, v, block, idx, np_gpu(cnt), ws, same=False)
+
+
+# most kept blocks of long heads that are divided: 7 / 25 of all, or as many a place (two workgroups a CU, four of the small ones), twice
+# as many where an XCD has rows of one head at a time
+def _most_divided(H, Nb, D, block):
+    places, far = {(128, 128): (512, 225), (64, 64): (1024, 380), (128, 64): (1024, 96)}[D, block]
+    return min(H * Nb * Nb * 7 // 25, (2 if H % 8 == 0 or 8 % H == 0 else 1) * far * places)
+
+
+# lists of at most that many blocks are divided, others have the launch that a plan orders, and its bits
+@pytest.mark.parametrize("H,Nb,D,block", [(3, 480, 128, 128), (4, 320, 128, 128), (3, 951, 64, 64), (2, 540, 128, 64),
+                                          (8, 226, 128, 64), (1, 1100, 128, 64)])
+def test_lists_that_keep_much_are_left_to_a_plan(H, Nb, D, block):
+    import paper_2605_14513_amd as heart
+
+    q, k, v, idx = _lists(H, Nb, D, block, Nb)
+    rng = np.random.default_rng(H)
+    most = _most_divided(H, Nb, D, block)
+    ws = torch.empty(heart.heart_attn_balanced_workspace_bytes(q, block), dtype=torch.uint8, device="cuda")
+    assert ws.numel() > heart.heart_attn_workspace_bytes(q, block)
+    for total in (most // 2, most, most + 1, H * Nb * Nb):
+        cnt = np.full(H * Nb, total // (H * Nb))
+        move = rng.integers(0, cnt[0] + 1, H * Nb // 2)  # from one row to another
+        cnt[:len(move)] -= move
+        cnt[len(move):2 * len(move)] += move
+        cnt[0] += total - cnt.sum()
+        while (cnt > Nb).any():  # (what a row cannot hold goes to the shortest)
+            i, j = cnt.argmax(), cnt.argmin()
+            cnt[j], cnt[i] = cnt[j] + cnt[i] - Nb, Nb
+        assert cnt.sum() == total and cnt.min() >= 0
+        print(f"H={H} Nb={Nb} D={D} block={block} blocks={total} of {H * Nb * Nb}", flush=True)
+        gc = np_gpu(cnt.astype(np.int32).reshape(1, H, Nb))
+        same = _bits_or_bound(heart, q, k, v, block, idx, gc, ws, same=total > most)
+        assert same == (total > most)
+
+
+def test_divided_and_planned_lists_in_a_captured_graph():
+    """Captured once, replayed on lists that are divided and on lists that are left to the plan: the eager bits."""
+    import paper_2605_14513_amd as heart
+
+    H, Nb, D, block = 4, 320, 128, 128
+    q, k, v, idx = _lists(H, Nb, D, block, 1)
+    g = torch.Generator(device="cuda").manual_seed(2)
+    counts = [torch.randint(0, n, (1, H, Nb), generator=g, dtype=torch.int32, device="cuda") for n in (Nb // 2, Nb, Nb // 3, Nb, Nb // 2)]
+    cnt, out = counts[1].clone(), torch.empty_like(q)
+    n_bytes = heart.heart_attn_balanced_workspace_bytes(q, block)
+    ws, ws2 = (torch.full((n_bytes,), 255, dtype=torch.uint8, device="cuda") for _ in range(2))
+
+    def call():
+        heart.heart_block_sparse_attn(q, k, v, block, idx, cnt, out=out, workspace=ws)
+
+    call()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        call()
+    for i, c in enumerate(counts):
+        want = heart.heart_block_sparse_attn(q, k, v, block, idx, c, workspace=ws2)
+        one = heart.heart_block_sparse_attn(q, k, v, block, idx, c, workspace=None)
+        assert torch.equal(want, one) == (c.sum().item() > _most_divided(H, Nb, D, block))
+        cnt.copy_(c)
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        print(f"replay {i}", flush=True)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), f"replay {i}"
