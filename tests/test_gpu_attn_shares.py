@@ -10,9 +10,10 @@ from heart_testlib import np_gpu, u16
 pytestmark = pytest.mark.gpu
 
 
-# rows: one; as few as two shares; groups of 256 rows with a remainder; the most there are (D = 64, block 64: 2560) and one
-# head more than that, which has a plan; at D = 128 more rows than places (512, 1024 of the small workgroups), so that a share
-# ends a row that another began, takes whole ones and begins the next, and the most rows a place (2).  kinds: uneven with rows of no and one block; no blocks at all; all blocks
+# rows: one; as few as two shares; groups of 256 rows with a remainder; the most there are in heads of 64 blocks at D = 64,
+# block 64 (2560) and one head more than that, which has a plan; at D = 128 more rows than places (512, 1024 of the small
+# workgroups), so that a share ends a row that another began, takes whole ones and begins the next, and two rows a place (more:
+# below).  kinds: uneven with rows of no and one block; no blocks at all; all blocks
 @pytest.mark.parametrize("kind", ["uneven", "empty", "full"])
 @pytest.mark.parametrize("B,H,Nb,D,block,tail", [(1, 1, 1, 128, 128, 5), (1, 1, 150, 64, 64, 0), (1, 1, 197, 64, 64, 0), (2, 3, 6, 128, 128, 78),
                                                  (1, 1, 200, 128, 64, 63), (2, 7, 67, 64, 128, 1), (1, 3, 171, 64, 64, 7),
@@ -357,3 +358,55 @@ def test_divided_and_planned_lists_in_a_captured_graph():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, want), f"replay {i}"
+
+
+# rows split in two parts, which the workgroup that leaves the second adds up: what stands in either part, in both or in one without
+# keys reaches the row, whichever of them comes last, and no other row
+@pytest.mark.parametrize("H,Nb,D,block", [(18, 11, 128, 128), (40, 10, 64, 64), (34, 12, 128, 64), (20, 12, 64, 128)])
+@pytest.mark.parametrize("flags", [0, 1])
+def test_rows_in_two_parts_show_non_finite_inputs(H, Nb, D, block, flags):
+    import paper_2605_14513_amd as heart
+
+    N = Nb * block
+    g = torch.Generator(device="cuda").manual_seed(H)
+    q, k, v = (torch.randn((1, H, N, D), generator=g, device="cuda").bfloat16() for _ in range(3))
+    blk = lambda i: slice(i * block, (i + 1) * block)
+    nan_k, neg_k, inf_v, nan_v = 0, 1, 2, 3  # key blocks that only some rows keep
+    q[..., 0] = q[..., 0].abs() + 0.5        # (so the logits of block neg_k are -inf)
+    k[0, :, blk(nan_k).start + 3] = float("nan")
+    k[0, :, blk(neg_k), 0] = float("-inf")
+    v[0, :, blk(inf_v), 2] = float("inf")
+    v[0, :, blk(nan_v), 1] = float("nan")
+    a, b, c, d = range(4, 8)  # blocks of finite values
+    rows = [[a, b, c, d], [nan_k, a, b, c], [a, b, c, nan_k], [neg_k, neg_k, a, b], [a, b, neg_k, neg_k], [neg_k, neg_k], [neg_k],
+            [inf_v, a, b, c], [a, b, inf_v, c], [nan_v, a]][:Nb - 2] + [[], [a]]
+    idx, cnt = np.zeros((1, H, Nb, Nb), np.int32), np.zeros((1, H, Nb), np.int32)
+    for h in range(H):
+        for i in range(Nb):
+            r = rows[(h + i) % len(rows)]
+            idx[0, h, i, :len(r)], cnt[0, h, i] = r, len(r)
+    gi, gc = np_gpu(idx), np_gpu(cnt)
+    print(f"two parts H={H} Nb={Nb} D={D} block={block} flags={flags}", flush=True)
+    n_bytes = heart.heart_attn_workspace_bytes(q, block)
+    # (room for two parts a row)
+    assert n_bytes == 2 * H * Nb * (block // 32) * (32 * D + 128) * 4
+    res = []
+    for fill in (255, 0, None):
+        ws = None if fill is None else torch.full((n_bytes,), fill, dtype=torch.uint8, device="cuda")
+        lse = torch.empty((1, H, N), device="cuda")
+        out = heart.heart_block_sparse_attn(q, k, v, block, gi, gc, workspace=ws, flags=flags, lse=lse)
+        res.append((out.float().cpu().numpy()[0], lse.cpu().numpy()[0]))
+    (out, lse), (out0, lse0), (one, lse1) = res
+    assert np.array_equal(out, out0, equal_nan=True) and np.array_equal(lse, lse0, equal_nan=True)
+    assert np.array_equal(np.isnan(out), np.isnan(one)) and np.array_equal(np.isinf(out), np.isinf(one))
+    assert np.array_equal(np.isneginf(lse), np.isneginf(lse1)) and np.array_equal(np.isnan(lse), np.isnan(lse1))
+    ok = np.isfinite(one)
+    # (weights of at most four blocks of values below 6, two roundings of 2^-9 each and one of the output)
+    assert np.abs(out[ok] - one[ok]).max() <= 1.1 * 2.0 ** -8 * 2 * 6
+    for h in range(H):  # what the rows must show, whichever launch
+        for i in range(Nb):
+            r, x = rows[(h + i) % len(rows)], one[h, blk(i)]
+            assert np.isnan(x).all() == (nan_k in r)
+            assert (x == 0).all() == (set(r) <= {neg_k})
+            assert np.isposinf(x[:, 2]).all() == (inf_v in r)
+            assert np.isnan(x[:, 1]).all() == (nan_v in r or nan_k in r)

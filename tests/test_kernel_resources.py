@@ -24,3 +24,10 @@ def test_drift_kernels_use_no_scratch_memory():
 def test_band_error_kernels_use_no_scratch_memory():
     sizes = scratch_of("ebc.hip")
     assert not any(sizes.values()), sizes
+
+
+def test_attention_kernels_use_no_scratch_memory():
+    """But the merged shares at D = 128 (mode 4), which keep up to four registers there while they add up parts, behind the MFMA
+    stream.  (Not for the time: a reload whose wait also waits for the loads in flight towards LDS would stall that stream.)"""
+    sizes = {n: b for n, b in scratch_of("block_sparse_attn.hip").items() if b}
+    assert all(re.search(r"attn_kernelILi128ELi(64|128)ELb[01]ELNS_8AttnModeE4E", n) and b <= 16 for n, b in sizes.items()), sizes
