@@ -227,9 +227,9 @@ def heart_pool_drift_workspace_bytes(B: int, H: int) -> int:
 def heart_pool_drift(q, k, block: int, qanchor, kanchor, has_anchor, delta, workspace,
                      gate_lo: float = 0.4, gate_hi: float = 0.8, commit: bool = True, qblk=None,
                      kblk=None, qmean=None, kmean=None, drift=None, refresh=None):
-    """heart_pool_qk and heart_drift with one launch fewer (token means and drift share a launch; with few blocks it is one in all).  workspace: a GPU tensor of at least
-    heart_pool_drift_workspace_bytes(B, H) bytes that was zero before its first use (the call
-    leaves it zero).  Returns (qblk, kblk, qmean, kmean, drift, refresh)."""
+    """heart_pool_qk and heart_drift with one launch fewer (token means and drift share a launch; with few blocks it is
+    one in all).  workspace: a GPU tensor of at least heart_pool_drift_workspace_bytes(B, H) bytes that was zero before its
+    first use (the call leaves it zero).  Returns (qblk, kblk, qmean, kmean, drift, refresh)."""
     native = _native()
     if qblk is None or kblk is None or qmean is None or kmean is None or drift is None or refresh is None:
         B, H, N, D = q.shape

@@ -19,14 +19,15 @@
 //   contraction runs in stages of 64 elements (half a token row at D = 128): both operand
 //   tiles go from global memory straight into LDS (`buffer_load ... lds`, 16-byte chunks
 //   XOR-swizzled by row so that the fragment reads are conflict free), double-buffered
-//   (128 KB, 64 KB; 128 KB in four buffers for one small tile a CU), one barrier per stage, the loads of the next stage in flight during the MFMAs
-//   of the current one (lines of later stages requested into the L2 as well: 613 -> 625 us); fragments are
-//   read one contraction step ahead, and fragment reads and loads are issued between the MFMAs, one or two
+//   (128 KB, 64 KB; 128 KB in four buffers for one small tile a CU), one barrier per stage, the loads of the next
+//   stage in flight during the MFMAs of the current one (lines of later stages requested into the L2 as well: 613 ->
+//   625 us); fragments are read one contraction step ahead, and fragment reads and loads are issued between the MFMAs, one or two
 //   behind each: all eight loads of a wavefront in one go, right after the barrier, held the MFMAs behind them
 //   back until the address unit had taken them (estimator and selection, 40 heads of 32760 tokens 674 -> 656 us,
 //   10 of 75600 960 -> 917, 20 of 32760 at D = 64 200 -> 184, 12 of 20280 in blocks of 64 193 -> 180, six of 3565
-//   29.3 -> 26.8).  With a full chip the flight time of the loads does not count: stages of half the depth, five buffers and four stages ahead took 709 to 720 us in the place of 660, four wavefronts of 128 x 128,
-//   one a SIMD, 730.  A wavefront owns 64 (32) reduced queries against 128 reduced keys (S^T layout: keys
+//   29.3 -> 26.8).  With a full chip the flight time of the loads does not count: stages of half the depth, five
+//   buffers and four stages ahead took 709 to 720 us in the place of 660, four wavefronts of 128 x 128, one a SIMD,
+//   730.  A wavefront owns 64 (32) reduced queries against 128 reduced keys (S^T layout: keys
 //   along the accumulator rows), so a query's maximum over those keys is a per-lane
 //   reduction plus one exchange with the partner lane.  The epilogue writes one record per
 //   (reduced query, 128 keys): the maximum m and the 16 sums over 8 keys of exp2(L - m).
@@ -84,8 +85,8 @@ __global__ __launch_bounds__(2 * kTile, 2) void antidiag_tile_kernel(
   // workgroup -> (head, tile): workgroup ids are dealt round-robin to the 8 XCDs; an XCD takes a contiguous
   // eighth of the tiles of the refreshed heads, head by head, so that a head's operand rows are shared
   // through one L2 or a few, and no XCD has more to do than another (before, whole heads went to the XCDs in turn: 12
-  // heads of 64 tiles 232 -> 179 us, one head 99 -> 47).  With hundreds of heads a look at all flags costs more than the tiles of reused heads,
-  // which end at once.
+  // heads of 64 tiles 232 -> 179 us, one head 99 -> 47).  With hundreds of heads a look at all flags costs more than
+  // the tiles of reused heads, which end at once.
   const int tiles_k = MT / (kTile / 128);  // (every record of 128 keys is written, also past the end)
   const unsigned tph = (unsigned)(MTQ * tiles_k), x = blockIdx.x % kNumXcd;
   const bool look = refresh && BH <= kAdLookHeads;

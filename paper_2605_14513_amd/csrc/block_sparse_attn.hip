@@ -121,10 +121,10 @@ constexpr int kHeadsInTurn = 2;
 // Split rows.  A launch with fewer rows than the chip has places for workgroups (two per CU, four
 // of the small ones at block 64) would leave the rest idle while each row walks its list
 // alone; there S workgroups take a part of each list and write their unnormalised outputs, and
-// attn_merge_kernel (or, of two parts, the second of them) adds them up.  S is as many as there are places for, with at least kSplitMinBlocks
-// blocks a part where lists are full: a part costs about 10 us beside its blocks (launch, first
-// loads, 64 KB written and read again), a block 0.8 us (64 keys, D = 64) to 1.7 us (128 keys,
-// D = 128).  All parts start at once, so such a launch needs no plan.  A function of the sizes only.
+// attn_merge_kernel (or, of two parts, the second of them) adds them up.  S is as many as there are
+// places for, with at least kSplitMinBlocks blocks a part where lists are full: a part costs about
+// 10 us beside its blocks (launch, first loads, 64 KB written and read again), a block 0.8 us (64
+// keys, D = 64) to 1.7 us (128 keys, D = 128).  All parts start at once, so such a launch needs no plan.  A function of the sizes only.
 // Measured, whole call: dense 38 -> 19 us, a step at two heads of 16 rows 36 -> 31.5 us (which the
 // host now bounds), steps of 100 to 250 rows 67 -> 33, 88 -> 38, 88 -> 43 us.
 constexpr int kSplitCus = 256;        // CUs the places are counted for
@@ -135,16 +135,16 @@ constexpr int kLdsPerCu = 160 * 1024;
 template <int D>
 constexpr int kPartFloats = 64 * (D / 2) + 128;
 // Rows of few parts are added up by the workgroup that leaves the last of them (kSplitMerged, kSharedMerged).  That saves a
-// launch, and of the two parts at a cut the one that ends later, mostly the end of a share, stays in registers: a 64 KB part (D =
-// 128, block 128) is written and read once in the place of twice, which bound the launch (11.7 us for 512 cuts, 5.7 TB/s).  It
-// reads one part after the other, though, and the longest row of few has many: then a launch of a wavefront for 32 columns of
-// 32 rows is the faster way.  Steps and calls with the launch -> without, us: D = 128, block 128: 18 heads of 33 rows (0.9
-// shares a row) 91.1 -> 85.1, two of 160 (1.6) 94.8 -> 91.9, two of 120 (2.1) 77.6 -> 77.3, one of 240 (2.1) 100 -> 101.7, one of 160 (3.2) 71
-// -> 76, two of five (3) 31.8 -> 29.7, six of six (4) 33.4 -> 34.5; D = 64, block 64: 20 of 101 (0.5) 101 -> 96.4, one of 640 (1.6)
-// 103.8 -> 103.3, one of 480 (2.1) 85.0 -> 88.6, four of 112 (2.3) 48.9 -> 54.1; two split parts, 18 of eleven 48.4 -> 44.9, 12 of 16 46.6
-// -> 41.9; four at D = 64, two of 16 21.9 -> 23.6.
+// launch, and of the two parts at a cut the one that ends later, mostly the end of a share, stays in registers: a 64 KB part
+// (D = 128, block 128) is written and read once in the place of twice, which bound the launch (11.7 us for 512 cuts, 5.7
+// TB/s).  It reads one part after the other, though, and the longest row of few has many: then a launch of a wavefront for 32
+// columns of 32 rows is the faster way.  Steps and calls with the launch -> without, us: D = 128, block 128: 18 heads of 33
+// rows (0.9 shares a row) 91.1 -> 85.1, two of 160 (1.6) 94.8 -> 91.9, two of 120 (2.1) 77.6 -> 77.3, one of 240 (2.1) 100 ->
+// 101.7, one of 160 (3.2) 71 -> 76, two of five (3) 31.8 -> 29.7, six of six (4) 33.4 -> 34.5; D = 64, block 64: 20 of 101
+// (0.5) 101 -> 96.4, one of 640 (1.6) 103.8 -> 103.3, one of 480 (2.1) 85.0 -> 88.6, four of 112 (2.3) 48.9 -> 54.1; two split
+// parts, 18 of eleven 48.4 -> 44.9, 12 of 16 46.6 -> 41.9; four at D = 64, two of 16 21.9 -> 23.6.
 constexpr int kMergeParts = 2;  // split rows
-// (rows of fewer than eight blocks have three parts at most)
+// (rows of fewer than eight blocks have four parts at most: seven blocks in parts of two)
 constexpr bool merge_shares(long long n_share, long long rows, long long Nb) { return n_share < (Nb < 8 ? 4 : 2) * rows; }
 constexpr float kNoKeys = -1.f;  // in the place of the row sum: a part without keys (a sum is not negative, but may be NaN)
 
@@ -275,7 +275,8 @@ int attn_shares(long long BH, long long Nb, int D, int block, bool dense) {
   return (int)((most < places ? most : places) + kNumXcd - 1) / kNumXcd * kNumXcd;
 }
 
-// owners of divided rows (row, further parts, share) or tickets, then two parts per share: the one a share starts with and the one it ends with
+// owners of divided rows (row, further parts, share) or tickets, then two parts per share: the one a share starts with and the
+// one it ends with
 size_t attn_share_bytes(long long BH, long long Nb, int D, int block, bool dense) {
   const int n = attn_shares(BH, Nb, D, block, dense);
   if (n == 0) return 0;
@@ -283,8 +284,8 @@ size_t attn_share_bytes(long long BH, long long Nb, int D, int block, bool dense
   return (size_t)n * (sizeof(int4) + 2 * (size_t)(block / 32) * part * sizeof(float));
 }
 
-// Adds up the parts of rows where attn_kernel leaves that to a second launch: one wavefront per (32 query rows, 32 columns of the output), lanes
-// as in attn_kernel.  Parts of item i are i * n_split .. ; of shared rows (`owner` given) the last part of share k
+// Adds up the parts of rows where attn_kernel leaves that to a second launch: one wavefront per (32 query rows, 32 columns of
+// the output), lanes as in attn_kernel.  Parts of item i are i * n_split .. ; of shared rows (`owner` given) the last part of share k
 // and the first ones of the shares after it.  Bound by latency (the parts come from the L2s and the memory-side
 // cache): four parts at a time.
 template <int D, int BLK>
@@ -843,7 +844,8 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
   };
   if constexpr (kShare) {
     constexpr int kGroups = kShareMaxRows / kShareGroup, GPW = kGroups / NW;
-    constexpr int PG = (kNumXcd * kPlacesXcd + kShareGroup * NW - 1) / (kShareGroup * NW);  // groups a wavefront has of as many rows as places
+    // groups a wavefront has of as many rows as places
+    constexpr int PG = (kNumXcd * kPlacesXcd + kShareGroup * NW - 1) / (kShareGroup * NW);
     __shared__ int group_sum[2][kGroups];
     __shared__ int wave_longest[NW];
     __shared__ int found[4];
@@ -1296,7 +1298,8 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
             const f32x4_t x = {o[dt][4 * g], o[dt][4 * g + 1], o[dt][4 * g + 2], o[dt][4 * g + 3]};
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, x), dst, part_off + (uint32_t)((4 * dt + g) * 1024), 0, kAgent);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, x), dst,
+                                                   part_off + (uint32_t)((4 * dt + g) * 1024), 0, kAgent);
           }
       }
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1347,7 +1350,7 @@ __global__ __launch_bounds__(BLK * 2, HEART_ATTN_OCC) void attn_kernel(
     if (kSplit || n == 2) {
       load_part(1 - mine);
       if (has_keys(ls)) {
-        // (products rounded on their mine: their sum does not depend on which of the two is the own part)
+        // (products rounded on their own: their sum does not depend on which of the two is the own part)
 #pragma clang fp contract(off)
         const float m_new = fmaxf(m_ref, ms), m_fin = m_new == -__builtin_inff() ? 0.f : m_new;
         const float w = __builtin_amdgcn_exp2f(m_ref - m_fin), wx = __builtin_amdgcn_exp2f(ms - m_fin);

@@ -244,15 +244,16 @@ __global__ __launch_bounds__(kMeanThreads) void token_mean_drift_kernel(
     anchors.load(b, (int)(threadIdx.x >> 6) * kDriftHeadsPerPass, H, D, fa.qanchor, fa.kanchor, fa.has_anchor, fa.delta);
   const size_t item = (size_t)b * H * D;
   // (at D = 64 few lanes would write the kept means: 13.7 -> 13.85 us for that call)
-  drift_workgroup<D / 64, D == 128, D == 128>(b, H, D, DriftMeansAcross{qmean + item, kmean + item}, anchors, fa.qanchor, fa.kanchor, fa.has_anchor,
-                          fa.delta, fa.gate_lo, fa.gate_hi, fa.commit, fa.drift, fa.refresh,
-                          reinterpret_cast<unsigned char *>(lds));
+  drift_workgroup<D / 64, D == 128, D == 128>(b, H, D, DriftMeansAcross{qmean + item, kmean + item}, anchors, fa.qanchor,
+                                              fa.kanchor, fa.has_anchor, fa.delta, fa.gate_lo, fa.gate_hi, fa.commit,
+                                              fa.drift, fa.refresh, reinterpret_cast<unsigned char *>(lds));
 }
 
 // All of heart_pool_drift in one launch, for few blocks, where it is bound by launches and by a chain of memory round
-// trips (block, acknowledgement, ticket, block means, result; 7.1 us at two heads of 16 blocks of 64, D = 64): a workgroup pools kSmallBlocks blocks of a batch item, the
-// last one of the item computes its token means (in block order in fp64 as token_mean_workgroup does, which has at most one
-// block a slice here, so the bits are the same), keeps them in LDS and runs the drift stage.
+// trips (block, acknowledgement, ticket, block means, result; 7.1 us at two heads of 16 blocks of 64, D = 64): a workgroup
+// pools kSmallBlocks blocks of a batch item, the last one of the item computes its token means (in block order in fp64 as
+// token_mean_workgroup does, which has at most one block a slice here, so the bits are the same), keeps them in LDS and runs
+// the drift stage.
 constexpr int kSmallBlocks = kMeanThreads / kPoolThreads;
 constexpr int kSmallMeans = kSmallBlocks * kPoolPart;  // token means that fit
 constexpr int kSmallMarks = 2 * 32;                   // two bytes a head, 32 heads
@@ -307,17 +308,17 @@ __global__ __launch_bounds__(kMeanThreads) void pool_drift_small_kernel(
     (which ? kmean : qmean)[item + o] = mean;
   }
   __syncthreads();
-  drift_workgroup<D / 64, true, true>(b, H, D, DriftMeans{lds, lds + n}, anchors, fa.qanchor, fa.kanchor, fa.has_anchor, fa.delta, fa.gate_lo,
-                          fa.gate_hi, fa.commit, fa.drift, fa.refresh, marks);
+  drift_workgroup<D / 64, true, true>(b, H, D, DriftMeans{lds, lds + n}, anchors, fa.qanchor, fa.kanchor, fa.has_anchor,
+                                      fa.delta, fa.gate_lo, fa.gate_hi, fa.commit, fa.drift, fa.refresh, marks);
 }
 
 // Largest calls of pool_drift_small_kernel: workgroups of a batch item and in all (one ticket each, served one after another),
 // token means of a batch item (one workgroup makes them all, a lane one or two of them) and blocks a head (a chain of loads).
 // heart_pool_drift in two launches -> in one, us: D = 64, H x Nb = 2 x 16 7.9 -> 7.1, 8 x 8 (32 workgroups) 8.1 -> 7.2, 16 x
 // 4 (32 workgroups, 2048 means) 8.5 -> 8.1, 10 x 8 (40) 8.0 -> 7.6, 2 x 24 8.1 -> 7.4, six heads of 8 in 8 items (192 workgroups)
-// 9.5 -> 9.0; beyond: 10 x 9 (45) 8.1 -> 8.5, 25 x 1 (3200) 8.2 -> 8.7, 2 x 40 8.0 -> 8.4, 8 items of 32 9.5 -> 10.1.  D = 128, where the two launches
-// keep the means they compared: 2 x 16 8.2 -> 7.8, 4 x 8 (16 workgroups, 1024 means) 8.6 -> 7.9, 3 x 10 8.2 -> 8.1; beyond: 2 x 24
-// (24) 8.6 -> 8.8, 8 x 1 (2048 means) 7.8 -> 8.4, 25 x 3 8.8 -> 13.3.
+// 9.5 -> 9.0; beyond: 10 x 9 (45) 8.1 -> 8.5, 25 x 1 (3200) 8.2 -> 8.7, 2 x 40 8.0 -> 8.4, 8 items of 32 9.5 -> 10.1.  D = 128,
+// where the two launches keep the means they compared: 2 x 16 8.2 -> 7.8, 4 x 8 (16 workgroups, 1024 means) 8.6 -> 7.9, 3 x
+// 10 8.2 -> 8.1; beyond: 2 x 24 (24) 8.6 -> 8.8, 8 x 1 (2048 means) 7.8 -> 8.4, 25 x 3 8.8 -> 13.3.
 constexpr int kSmallLaunch = 192, kSmallNb = 24;
 template <int D>
 constexpr int kSmallItem = D == 64 ? 40 : 16;

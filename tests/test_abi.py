@@ -293,8 +293,8 @@ def test_size_that_asks_for_divided_rows(lib, B, H, Nb, D, block, divided):
     assert dense in (usual, asks)
 
 
-# the same on either side of the limits of rows a place (2.9; two at D = 128, block 64; 2.5 at D = block = 64 for heads of at most 64 blocks),
-# of short heads beyond them, and of 4096 rows
+# the same on either side of the limits of rows a place (2.9; two at D = 128, block 64; 2.5 at D = block = 64 for heads of at
+# most 64 blocks), of short heads beyond them, and of 4096 rows
 @pytest.mark.parametrize("B,H,Nb,D,block,divided", [
     (1, 4, 371, 128, 128, True), (1, 4, 372, 128, 128, False), (1, 26, 80, 128, 128, True), (1, 16, 110, 128, 128, True),
     (1, 16, 111, 128, 128, False), (1, 4, 371, 64, 128, True), (1, 4, 372, 64, 128, True), (1, 8, 288, 64, 128, True),
