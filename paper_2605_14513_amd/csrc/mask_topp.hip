@@ -381,6 +381,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void mask_topp_kernel(
     // such a one, have 64-bit sums of the same integers, hence the same kept sets.  Selection from given scores, rows with a sum
     // of one and of 2.5 (a whole wavefront a row and 64 bits for all -> this): 40 heads of 256 rows 27.6 and 26.9 -> 17.6 and 19.6
     // us, 24 of 931 133 and 132 -> 84.4 and 102, 12 of 400 29.7 and 29.1 -> 18.6 and 21.3, six of 28 8.4 and 8.6 -> 6.0 and 6.9.
+    // (Above 896 blocks the two searches keep seven registers in scratch memory.)
     auto search = [&](auto zero) __attribute__((always_inline)) {
       using Mass = decltype(zero);
       Mass my_u = 0;
