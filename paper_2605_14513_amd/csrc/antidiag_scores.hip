@@ -32,7 +32,7 @@
 //   buffers and four stages ahead took 709 to 720 us in the place of 660, four wavefronts of 128 x 128, one a SIMD,
 //   730.  A wavefront owns 64 (32) reduced queries against 128 reduced keys (S^T layout: keys
 //   along the accumulator rows), so a query's maximum over those keys is a per-lane
-//   reduction plus two exchanges among the four lanes that share the query.  The epilogue writes one record per
+//   reduction plus two exchanges among the four lanes that share the query (one between two, in the small tiles).  The epilogue writes one record per
 //   (reduced query, 128 keys): the maximum m and the 16 sums over 8 keys of exp2(L - m).
 //   Tiles are independent.
 // Kernel 2 (antidiag_combine): one workgroup per query block: global maximum and
@@ -47,6 +47,7 @@ namespace {
 typedef __attribute__((ext_vector_type(4))) uint32_t ad_u32x4;
 typedef __attribute__((ext_vector_type(8))) __bf16 ad_bf16x8;
 typedef __attribute__((ext_vector_type(4))) float ad_f32x4;
+typedef __attribute__((ext_vector_type(16))) float ad_f32x16;
 union AdFrag {
   ad_u32x4 u;
   ad_bf16x8 v;
@@ -82,8 +83,6 @@ __global__ __launch_bounds__(2 * kTile, 2) void antidiag_tile_kernel(
     float *__restrict__ mref) {
   extern __shared__ __align__(1024) unsigned char smem[];
   constexpr int kAdTileB = kTile * kAdRowB;  // bytes of one operand tile of one stage
-  constexpr int QT = kTile / 64;             // query tiles of 16 a wavefront
-  constexpr int KT = 8;                      // key tiles of 16
   const int t = threadIdx.x;
   const int lane = t & 63;
   // workgroup -> (head, tile): workgroup ids are dealt round-robin to the 8 XCDs; an XCD takes a contiguous
@@ -129,7 +128,6 @@ __global__ __launch_bounds__(2 * kTile, 2) void antidiag_tile_kernel(
   const int b = bh / H, h = bh % H;
 
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int l16 = lane & 15, grp = lane >> 4;
   const int wi = wave >> 2;  // which 128 keys of the tile
   const int wj = wave & 3;   // which quarter of the tile's queries
 
@@ -180,51 +178,12 @@ __global__ __launch_bounds__(2 * kTile, 2) void antidiag_tile_kernel(
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kBufs - 2) * kLoads) : "memory");
     __syncthreads();
   };
-  // fragment of contraction step ks (32 elements) of tile row 16 x + l16: chunk 4 ks + grp
-  uint32_t foff[2];
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks) foff[ks] = (uint32_t)(l16 * kAdRowB + (((4 * ks + grp) ^ ((l16 >> 1) & 7)) * 16));
-
-  ad_f32x4 acc[KT][QT];
-#pragma unroll
-  for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-    for (int qt = 0; qt < QT; ++qt) acc[kt][qt] = ad_f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // Fragments: of the queries (B operand) those of a whole stage, of the keys (A operand) those of two key tiles and, arriving, of
-  // the next two.  A pair of key tiles is worked on query tile by query tile, both contraction steps of an accumulator after one
-  // another (two MFMAs in a row on one accumulator take less power than on two).
-  AdFrag fb[QT][2], fa[2][2][2];  // [tile][step], [pair][tile][step]
-  constexpr int kMfmas = 4 * QT;  // of a pair of key tiles
-  auto read_a = [&](int buf, int pair, int i) __attribute__((always_inline)) {  // i: tile and step
-    const unsigned char *A = smem + buf * 2 * kAdTileB + wi * 128 * kAdRowB;
-    fa[pair & 1][i >> 1][i & 1].u = *reinterpret_cast<const ad_u32x4 *>(A + (2 * pair + (i >> 1)) * 16 * kAdRowB + foff[i & 1]);
-  };
-  auto read_b = [&](int buf, int qt, int ks) __attribute__((always_inline)) {
-    const unsigned char *B = smem + buf * 2 * kAdTileB + kAdTileB + wj * 16 * QT * kAdRowB;
-    fb[qt][ks].u = *reinterpret_cast<const ad_u32x4 *>(B + qt * 16 * kAdRowB + foff[ks]);
-  };
-  // The MFMAs of one pair of key tiles; behind the i-th what extra(i) issues, behind the first ones the reads of the next pair's
-  // fragments (of buffer `buf`).
-  auto pair_step = [&](int pair, int buf, auto &&extra) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < kMfmas; ++i) {
-      const int qt = i >> 2, kt = (i >> 1) & 1, ks = i & 1;
-      acc[2 * pair + kt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[pair & 1][kt][ks].v, fb[qt][ks].v,
-                                                                       acc[2 * pair + kt][qt], 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (j * (kMfmas / 2) / 4 == i) read_a(buf, (pair + 1) & 3, j);
-      extra(i);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-
-  // Per stage: the barrier that hands over the next stage sits before the MFMAs of the stage's last pair.  By then a
+  // Per stage: the barrier that hands over the next stage sits before the MFMAs of the stage's last quarter.  By then a
   // wavefront has completed all its reads of the current buffer and its loads of the next stage into the other one;
-  // behind those MFMAs it reads the queries of the next stage, each tile when its last MFMA has been issued, and issues the first
-  // half of the loads of the stage kBufs on into the buffer just released, behind those of the next pair the other half (the
-  // later a load, the shorter its flight).  Loads past the last stage repeat the last stage (into a buffer nobody reads any more).
+  // behind those MFMAs it issues the first half of the loads of the stage kBufs on into the buffer just released, behind
+  // those of the next quarter the other half (the later a load, the shorter its flight: all within the
+  // first quarter, or three, 0.5 to 2 % slower).  Loads past the last stage repeat the last stage (into a buffer
+  // nobody reads any more).
   const int n_stages = kTile * tk < M ? S * SPR : 0;  // (a tile of keys past the end: records without weight)
   const int last = max(n_stages - 1, 0);
   constexpr int kHalf = kLoads / 2;
@@ -235,96 +194,255 @@ __global__ __launch_bounds__(2 * kTile, 2) void antidiag_tile_kernel(
   wait_loads_and_barrier();
 #pragma unroll
   for (int i = 0; i < kHalf; ++i) dma(min(kBufs - 1, last), kBufs - 1, i);
-#pragma unroll
-  for (int j = 0; j < 4; ++j) read_a(0, 0, j);
-#pragma unroll
-  for (int j = 0; j < 2 * QT; ++j) read_b(0, j >> 1, j & 1);
   auto no_extra = [](int) {};
-  for (int st = 0; st < n_stages; ++st) {
-    const int buf = st % kBufs, buf1 = (st + 1) % kBufs, bufp = (st + kBufs - 1) % kBufs;
-    const int st1 = min(st + kBufs - 1, last), st2 = min(st + kBufs, last);
-    pair_step(0, buf, [&](int i) {
-#pragma unroll
-      for (int j = 0; j < kHalf; ++j)
-        if (j * kMfmas / kHalf == i) dma(st1, bufp, kHalf + j);
-    });
-    pair_step(1, buf, no_extra);
-    pair_step(2, buf, no_extra);
-    wait_loads_and_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    pair_step(3, buf1, [&](int i) {
-      if ((i & 2) != 0) read_b(buf1, i >> 2, i & 1);  // (tile i / 4 has no MFMA after this one that reads step i % 2)
-#pragma unroll
-      for (int j = 0; j < kHalf; ++j)
-        if (j * kMfmas / kHalf == i) dma(st2, buf, j);
-    });
-  }
-  // loads of the repeated last stage may still be in flight towards LDS
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-
   // ---- epilogue: record of (reduced query, 128 keys): maximum and 16 key-block sums ----------
-  // accumulator element r of key tile kt: reduced key key0 + 16 kt + 4 grp + r
   const float ninf = -__builtin_inff();
   const int key0 = kTile * tk + 128 * wi;
   const int rec = kTile / 128 * tk + wi;  // index of the 128-key record
   const int NbP = 16 * MT;
+
+  if constexpr (kTile == 256) {
+    constexpr int QT = 4, KT = 8;  // tiles of 16: of the queries, of the keys
+    const int l16 = lane & 15, grp = lane >> 4;
+    // fragment of contraction step ks (32 elements) of tile row 16 x + l16: chunk 4 ks + grp
+    uint32_t foff[2];
 #pragma unroll
-  for (int qt = 0; qt < QT; ++qt) {
-    if (key0 + 128 > M) {  // (uniform: the records of the last keys)
-#pragma unroll
-      for (int kt = 0; kt < KT; ++kt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (key0 + 16 * kt + 4 * grp + r >= M) acc[kt][qt][r] = ninf;
-    }
-    // The maximum of the logits as they come out of the matrix cores, and exp2(scale L - scale max) in one fused
-    // operation each (one rounding less than scaled logits and their difference, and two instructions).
-    float m = ninf;
+    for (int ks = 0; ks < 2; ++ks) foff[ks] = (uint32_t)(l16 * kAdRowB + (((4 * ks + grp) ^ ((l16 >> 1) & 7)) * 16));
+
+    ad_f32x4 acc[KT][QT];
 #pragma unroll
     for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) m = fmaxf(m, acc[kt][qt][r]);
+      for (int qt = 0; qt < QT; ++qt) acc[kt][qt] = ad_f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // Fragments: of the queries (B operand) those of a whole stage, of the keys (A operand) those of two key tiles and, arriving, of
+    // the next two.  A pair of key tiles is worked on query tile by query tile, both contraction steps of an accumulator after one
+    // another (two MFMAs in a row on one accumulator take less power than on two).  Behind the last pair of a stage, each when its
+    // last MFMA has been issued, the queries of the next stage are read.
+    AdFrag fb[QT][2], fa[2][2][2];  // [tile][step], [pair][tile][step]
+    constexpr int kMfmas = 4 * QT;  // of a pair of key tiles
+    auto read_a = [&](int buf, int pair, int i) __attribute__((always_inline)) {  // i: tile and step
+      const unsigned char *A = smem + buf * 2 * kAdTileB + wi * 128 * kAdRowB;
+      fa[pair & 1][i >> 1][i & 1].u = *reinterpret_cast<const ad_u32x4 *>(A + (2 * pair + (i >> 1)) * 16 * kAdRowB + foff[i & 1]);
+    };
+    auto read_b = [&](int buf, int qt, int ks) __attribute__((always_inline)) {
+      const unsigned char *B = smem + buf * 2 * kAdTileB + kAdTileB + wj * 16 * QT * kAdRowB;
+      fb[qt][ks].u = *reinterpret_cast<const ad_u32x4 *>(B + qt * 16 * kAdRowB + foff[ks]);
+    };
+    // The MFMAs of one pair of key tiles; behind the i-th what extra(i) issues, behind the first ones the reads of the next pair's
+    // fragments (of buffer `buf`).
+    auto pair_step = [&](int pair, int buf, auto &&extra) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < kMfmas; ++i) {
+        const int qt = i >> 2, kt = (i >> 1) & 1, ks = i & 1;
+        acc[2 * pair + kt][qt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[pair & 1][kt][ks].v, fb[qt][ks].v,
+                                                                         acc[2 * pair + kt][qt], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (j * (kMfmas / 2) / 4 == i) read_a(buf, (pair + 1) & 3, j);
+        extra(i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+
+#pragma unroll
+    for (int j = 0; j < 4; ++j) read_a(0, 0, j);
+#pragma unroll
+    for (int j = 0; j < 2 * QT; ++j) read_b(0, j >> 1, j & 1);
+    for (int st = 0; st < n_stages; ++st) {
+      const int buf = st % kBufs, buf1 = (st + 1) % kBufs, bufp = (st + kBufs - 1) % kBufs;
+      const int st1 = min(st + kBufs - 1, last), st2 = min(st + kBufs, last);
+      pair_step(0, buf, [&](int i) {
+#pragma unroll
+        for (int j = 0; j < kHalf; ++j)
+          if (j * kMfmas / kHalf == i) dma(st1, bufp, kHalf + j);
+      });
+      pair_step(1, buf, no_extra);
+      pair_step(2, buf, no_extra);
+      wait_loads_and_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      pair_step(3, buf1, [&](int i) {
+        if ((i & 2) != 0) read_b(buf1, i >> 2, i & 1);  // (tile i / 4 has no MFMA after this one that reads step i % 2)
+#pragma unroll
+        for (int j = 0; j < kHalf; ++j)
+          if (j * kMfmas / kHalf == i) dma(st2, buf, j);
+      });
+    }
+    // loads of the repeated last stage may still be in flight towards LDS
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // accumulator element r of key tile kt: reduced key key0 + 16 kt + 4 grp + r
+#pragma unroll
+    for (int qt = 0; qt < QT; ++qt) {
+      if (key0 + 128 > M) {  // (uniform: the records of the last keys)
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (key0 + 16 * kt + 4 * grp + r >= M) acc[kt][qt][r] = ninf;
+      }
+      // The maximum of the logits as they come out of the matrix cores, and exp2(scale L - scale max) in one fused
+      // operation each (one rounding less than scaled logits and their difference, and two instructions).
+      float m = ninf;
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m = fmaxf(m, acc[kt][qt][r]);
+      {
+        uint32_t s0, s1;
+        swap_rows16(__float_as_uint(m), s0, s1);
+        m = fmaxf(__uint_as_float(s0), __uint_as_float(s1));
+        swap_halves32(__float_as_uint(m), s0, s1);
+        m = fmaxf(__uint_as_float(s0), __uint_as_float(s1)) * scale_log2;
+      }
+      // The fused operation keeps what `m` was rounded by (up to 2^-24 of it), and from |m| = 2^31 on its exponential leaves
+      // fp32: logits that large are scaled and rounded first, so that the largest is exactly its own reference.  (No time: estimator and
+      // selection of 40 heads of 256 blocks 620.5 and 620.6 us.)
+      float scale = scale_log2;
+      if (__any(fabsf(m) > kAdFused)) {
+        scale = 1.f;
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt) acc[kt][qt] *= scale_log2;
+      }
+      // (a record whose 128 keys are all past the end has m = -inf and all sums zero)
+      const float mm = m == ninf ? 0.f : m;
+      // Sums over the 8 keys of a key block: two lane groups hold four each (block 2 kt: groups 0 and 1).  z[p], of the key tiles
+      // 2 p and 2 p + 1, has the sums of the blocks 4 p + 0, 2, 1, 3 in the groups 0 to 3; transposed, group g has blocks 4 g ..
+      uint32_t z[4];
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        float s[2] = {0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) s[j] += __builtin_amdgcn_exp2f(fmaf(acc[2 * p + j][qt][i], scale, -mm));
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(s[0]), __float_as_uint(s[1]), false, false);
+        z[p] = __float_as_uint(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+      }
+      const auto h0 = __builtin_amdgcn_permlane32_swap(z[0], z[2], false, false);
+      const auto h1 = __builtin_amdgcn_permlane32_swap(z[1], z[3], false, false);
+      const auto v0 = __builtin_amdgcn_permlane16_swap(h0[0], h1[0], false, false);
+      const auto v1 = __builtin_amdgcn_permlane16_swap(h0[1], h1[1], false, false);
+      const int a = kTile * tq + 16 * QT * wj + 16 * qt + l16;
+      if (a < M) {
+        float *dst = esum + ((size_t)bh * M + a) * NbP + 16 * rec + 4 * grp;
+        *reinterpret_cast<float4 *>(dst) = make_float4(__uint_as_float(v0[0]), __uint_as_float(v1[0]),
+                                                       __uint_as_float(v0[1]), __uint_as_float(v1[1]));
+        if (grp == 0) mref[((size_t)bh * M + a) * MT + rec] = m;
+      }
+    }
+  } else {
+    // (the same in tiles of 32: with few tiles power is not what counts, and reads and small MFMAs get in each other's way: six heads of
+    // 5000 tokens 25.5 us, 26.6 with the tiles of 16; 24 heads of 6400 37.3, 40.0)
+    const int l32 = lane & 31, hf = lane >> 5;
+    // fragment of contraction step ks (16 elements) of tile row 32 x + l32: chunk 2 ks + hf
+    uint32_t foff[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) foff[ks] = (uint32_t)(l32 * kAdRowB + (((2 * ks + hf) ^ ((l32 >> 1) & 7)) * 16));
+
+    ad_f32x16 acc[4];
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[kt][r] = 0.f;
+
+    // the fragments of one contraction step: 4 of the keys (A operand), one of the queries
+    struct Frags {
+      AdFrag a[4], b;
+    };
+    constexpr int kFrags = 5, kMfmas = 4;
+    auto read_frag = [&](Frags &f, int buf, int ks, int i) __attribute__((always_inline)) {
+      const unsigned char *A = smem + buf * 2 * kAdTileB + wi * 128 * kAdRowB;
+      const unsigned char *B = smem + buf * 2 * kAdTileB + kAdTileB + wj * 32 * kAdRowB;
+      if (i == 0)
+        f.b.u = *reinterpret_cast<const ad_u32x4 *>(B + foff[ks]);
+      else
+        f.a[i - 1].u = *reinterpret_cast<const ad_u32x4 *>(A + (i - 1) * 32 * kAdRowB + foff[ks]);
+    };
+    // The MFMAs of one contraction step; behind those of the first half the reads of the next step's fragments (step ks of
+    // buffer `buf`), behind each what extra(i) issues.
+    auto step = [&](const Frags &f, Frags &next, int buf, int ks, auto &&extra) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = 0; i < kMfmas; ++i) {
+        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i].v, f.b.v, acc[i], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < kFrags; ++j)
+          if (j * (kMfmas / 2) / kFrags == i) read_frag(next, buf, ks, j);
+        extra(i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+
+    Frags f0, f1;
+#pragma unroll
+    for (int j = 0; j < kFrags; ++j) read_frag(f0, 0, 0, j);
+    for (int st = 0; st < n_stages; ++st) {
+      const int buf = st % kBufs, buf1 = (st + 1) % kBufs, bufp = (st + kBufs - 1) % kBufs;
+      const int st1 = min(st + kBufs - 1, last), st2 = min(st + kBufs, last);
+      step(f0, f1, buf, 1, [&](int i) {
+#pragma unroll
+        for (int j = 0; j < kHalf; ++j)
+          if (j * kMfmas / kHalf == i) dma(st1, bufp, kHalf + j);
+      });
+      step(f1, f0, buf, 2, no_extra);
+      step(f0, f1, buf, 3, no_extra);
+      wait_loads_and_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      step(f1, f0, buf1, 0, [&](int i) {
+#pragma unroll
+        for (int j = 0; j < kHalf; ++j)
+          if (j * kMfmas / kHalf == i) dma(st2, buf, j);
+      });
+    }
+    // loads of the repeated last stage may still be in flight towards LDS
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // accumulator element r of key tile kt: reduced key key0 + 32 kt + 8 (r / 4) + 4 hf + r % 4
+    if (key0 + 128 > M) {  // (uniform: the records of the last keys)
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (key0 + 32 * kt + 8 * (r >> 2) + 4 * hf + (r & 3) >= M) acc[kt][r] = ninf;
+    }
+    float m = ninf;
+#pragma unroll
+    for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) m = fmaxf(m, acc[kt][r]);
     {
       uint32_t s0, s1;
-      swap_rows16(__float_as_uint(m), s0, s1);
-      m = fmaxf(__uint_as_float(s0), __uint_as_float(s1));
       swap_halves32(__float_as_uint(m), s0, s1);
       m = fmaxf(__uint_as_float(s0), __uint_as_float(s1)) * scale_log2;
     }
-    // The fused operation keeps what `m` was rounded by (up to 2^-24 of it), and from |m| = 2^31 on its exponential leaves
-    // fp32: logits that large are scaled and rounded first, so that the largest is exactly its own reference.  (No time: estimator and
-    // selection of 40 heads of 256 blocks 620.5 and 620.6 us.)
     float scale = scale_log2;
     if (__any(fabsf(m) > kAdFused)) {
       scale = 1.f;
 #pragma unroll
-      for (int kt = 0; kt < KT; ++kt) acc[kt][qt] *= scale_log2;
+      for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[kt][r] *= scale_log2;
     }
-    // (a record whose 128 keys are all past the end has m = -inf and all sums zero)
     const float mm = m == ninf ? 0.f : m;
-    // Sums over the 8 keys of a key block: two lane groups hold four each (block 2 kt: groups 0 and 1).  z[p], of the key tiles
-    // 2 p and 2 p + 1, has the sums of the blocks 4 p + 0, 2, 1, 3 in the groups 0 to 3; transposed, group g has blocks 4 g ..
-    uint32_t z[4];
+    float sums[4][4];
 #pragma unroll
-    for (int p = 0; p < 4; ++p) {
-      float s[2] = {0.f, 0.f};
+    for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int g = 0; g < 4; ++g) {
+        float s = 0.f;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s[j] += __builtin_amdgcn_exp2f(fmaf(acc[2 * p + j][qt][i], scale, -mm));
-      const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(s[0]), __float_as_uint(s[1]), false, false);
-      z[p] = __float_as_uint(__uint_as_float(r[0]) + __uint_as_float(r[1]));
-    }
-    const auto h0 = __builtin_amdgcn_permlane32_swap(z[0], z[2], false, false);
-    const auto h1 = __builtin_amdgcn_permlane32_swap(z[1], z[3], false, false);
-    const auto v0 = __builtin_amdgcn_permlane16_swap(h0[0], h1[0], false, false);
-    const auto v1 = __builtin_amdgcn_permlane16_swap(h0[1], h1[1], false, false);
-    const int a = kTile * tq + 16 * QT * wj + 16 * qt + l16;
+        for (int i = 0; i < 4; ++i) s += __builtin_amdgcn_exp2f(fmaf(acc[kt][4 * g + i], scale, -mm));
+        uint32_t s0, s1;
+        swap_halves32(__float_as_uint(s), s0, s1);
+        sums[kt][g] = __uint_as_float(s0) + __uint_as_float(s1);
+      }
+    const int a = kTile * tq + 32 * wj + l32;
     if (a < M) {
-      float *dst = esum + ((size_t)bh * M + a) * NbP + 16 * rec + 4 * grp;
-      *reinterpret_cast<float4 *>(dst) = make_float4(__uint_as_float(v0[0]), __uint_as_float(v1[0]),
-                                                     __uint_as_float(v0[1]), __uint_as_float(v1[1]));
-      if (grp == 0) mref[((size_t)bh * M + a) * MT + rec] = m;
+      float *dst = esum + ((size_t)bh * M + a) * NbP + 16 * rec + 8 * hf;
+      // lower-half lanes write key blocks 0..7 of the record, upper-half lanes 8..15
+      *reinterpret_cast<float4 *>(dst) = hf ? make_float4(sums[2][0], sums[2][1], sums[2][2], sums[2][3])
+                                            : make_float4(sums[0][0], sums[0][1], sums[0][2], sums[0][3]);
+      *reinterpret_cast<float4 *>(dst + 4) = hf ? make_float4(sums[3][0], sums[3][1], sums[3][2], sums[3][3])
+                                                : make_float4(sums[1][0], sums[1][1], sums[1][2], sums[1][3]);
+      if (hf == 0) mref[((size_t)bh * M + a) * MT + rec] = m;
     }
   }
 }
