@@ -18,17 +18,19 @@
 //    all that is ever computed or stored of it: no transform, no projected tensor.
 //    The contractions run on the fp64 matrix cores (v_mfma_f64_16x16x4_f64: 16 coefficients
 //    of 16 lines, four elements of the lines a step); the sums of squares are taken from the
-//    accumulators and reduced in a fixed order.  Two launches for latents:
-//      ebc_first   x coefficients of err with |err|^2, S_T of err, |dense|^2
-//      ebc_plane   y and t coefficients of the x coefficients with S_XY and S_XYT; its last workgroup adds everything up
+//    accumulators and reduced in a fixed order.  One launch and the total where there are enough channels:
+//      ebc_channel everything: a channel's planes from the tensor to S_XY and S_XYT, |err|^2 and S_T, |dense|^2 in its workgroups
+//      ebc_total  one workgroup adds up
+//    or, of few channels and short axes, two launches with the x coefficients between them:
+//      ebc_first  x coefficients of err with |err|^2, S_T of err, |dense|^2
+//      ebc_plane  y and t coefficients of the x coefficients with S_XY and S_XYT; its last workgroup adds everything up
 //    or, where t is longer than 63 or y than 48, in the place of the second
-//      ebc_second  y coefficients of the x coefficients with S_XY
-//      ebc_third   S_XYT; its last workgroup adds everything up
-//    Bound by latency: at 128 x 21 x 30 x 52 the matrix instructions are 7 us of the chip and the
-//    90 MB moved (half of them in the caches) some 18 us; the launches take 20 + 13 us, of
-//    which a table, a first load and a last sum each about 1 us.  Whole call 41.6 -> 33.0 us against three
-//    launches that counted 400 workgroups on one ticket, 257 us with twelve launches that convolved in fp64 on the
-//    vector units (results equal to 1e-15); 128 x 33 x 45 x 80 134 -> 119 us, 16 x 21 x 30 x 52 21.3 -> 16.7 us.
+//      ebc_second y coefficients of the x coefficients with S_XY
+//      ebc_third  S_XYT; its last workgroup adds everything up
+//    Bound by latency and, with many channels, the bytes of err and dense: 128 x 21 x 30 x 52 33.1 -> 21.4 us with one launch (15 us
+//    of it the planes: 3 until the operands are there, 2.5 a plane, 1.3 over t; 18 the lines of S_T beside them and |dense|^2), of
+//    which the matrix instructions are 3 and the bytes 6 to 8.  Before: 41.6 us with three launches that counted
+//    400 workgroups on one ticket, 257 with twelve that convolved in fp64 on the vector units (results equal to 1e-15).
 //    A calibration run evaluates this once per (head, candidate, prompt-step), off the serving path.
 //
 //  heart_ebc_select       the one-candidate-per-head selection of Eq. 5 (minimum summed
@@ -56,8 +58,9 @@ typedef __attribute__((ext_vector_type(4))) double ebc_f64x4;
 __host__ __device__ constexpr int ebc_coefs(int n) { return 2 * (n / 4) + 1; }
 
 // cos(2 pi m / n) in tab[m], sin(2 pi m / n) in tab[n + m], by the whole workgroup
+template <int kThreads = kEbcThreads>
 __device__ __forceinline__ void ebc_table(int n, double *tab) {
-  for (int m = threadIdx.x; m < n; m += kEbcThreads) {
+  for (int m = threadIdx.x; m < n; m += kThreads) {
     double c, s;
     sincospi(2.0 * (double)m / (double)n, &s, &c);
     tab[m] = c;
@@ -66,7 +69,8 @@ __device__ __forceinline__ void ebc_table(int n, double *tab) {
   __syncthreads();
 }
 
-// sum over the workgroup in a fixed order, valid in thread 0; red: kEbcWaves doubles of LDS
+// sum over the workgroup in a fixed order, valid in thread 0; red: a double of LDS per wavefront
+template <int kThreads = kEbcThreads>
 __device__ __forceinline__ double ebc_block_sum(double v, double *red) {
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
@@ -75,7 +79,7 @@ __device__ __forceinline__ double ebc_block_sum(double v, double *red) {
   __syncthreads();
   double s = red[0];
 #pragma unroll
-  for (int w = 1; w < kEbcWaves; ++w) s += red[w];
+  for (int w = 1; w < kThreads / 64; ++w) s += red[w];
   return s;
 }
 
@@ -243,19 +247,20 @@ __device__ __forceinline__ void ebc_tile(EbcBatch<TIn> &cur, const EbcTile<TIn> 
 // or of the next tile, are always in flight, those of the first while the table is made: a line is
 // short, and a wavefront that waited for every load would do nothing else.
 // A unit of work is a tile of lines, or (kShared) every share-th pair of its coefficient tiles.
-template <bool kShared, typename TIn, bool kUnit, bool kStore, bool kSumIn>
+template <bool kShared, typename TIn, bool kUnit, bool kStore, bool kSumIn, int kThreads = kEbcThreads>
 __device__ __forceinline__ void ebc_contract(const TIn *__restrict__ in, double *__restrict__ out,
                                              const EbcLines &L, int blk, int n_blk, double *tab,
                                              double &e_out, double &e_in) {
   const int wave = threadIdx.x >> 6;
   const int K = ebc_coefs(L.n), KT = (K + 15) / 16, share = kShared ? L.share : 1;
   const long long units = (L.lines + kEbcTileCols - 1) / kEbcTileCols * share;
-  const long long first = (long long)blk * kEbcWaves + wave, stride = (long long)n_blk * kEbcWaves;
+  constexpr int kWaves = kThreads / 64;
+  const long long first = (long long)blk * kWaves + wave, stride = (long long)n_blk * kWaves;
   auto tile_of = [&](long long u) -> long long { return kShared ? ebc_div(u, share) : u; };
   EbcTile<TIn> t = ebc_tile_at<TIn, kUnit>(in, L, tile_of(first));
   EbcBatch<TIn> cur;
   ebc_load<TIn, kUnit>(cur, t, L, 0);
-  ebc_table(L.n, tab);
+  ebc_table<kThreads>(L.n, tab);
   for (long long u = first; u < units; u += stride) {
     const EbcTile<TIn> next = ebc_tile_at<TIn, kUnit>(in, L, tile_of(u + stride));  // (past the end: no line exists)
     int kt = kShared ? 2 * (int)(u - tile_of(u) * share) : 0;
@@ -290,6 +295,28 @@ __host__ __device__ __forceinline__ unsigned *ebc_root(double *partials) {
 }
 static_assert(kEbcLeaves * kEbcTicketLine <= kEbcPartials / 2, "room of the tickets");
 
+// this thread's sum of squares of a tensor, workgroup `blk` of `n_blk`
+template <int kThreads>
+__device__ __forceinline__ double ebc_squares(const float *__restrict__ dense, long long total, int blk, int n_blk) {
+  double e_in = 0.0;
+  const long long stride = (long long)n_blk * kThreads, t0 = (long long)blk * kThreads + threadIdx.x;
+  constexpr int U = 8;  // loads in flight
+  const bool wide = (reinterpret_cast<uintptr_t>(dense) & 15u) == 0;
+  const long long quads = wide ? total / 4 : 0;
+  const float4 *dense4 = reinterpret_cast<const float4 *>(dense);
+  for (long long e = t0; e < quads; e += U * stride) {
+    float4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = e + u * stride < quads ? dense4[e + u * stride] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      e_in = fma((double)v[u].w, (double)v[u].w,
+                 fma((double)v[u].z, (double)v[u].z, fma((double)v[u].y, (double)v[u].y, fma((double)v[u].x, (double)v[u].x, e_in))));
+  }
+  for (long long e = 4 * quads + t0; e < total; e += stride) e_in = fma((double)dense[e], (double)dense[e], e_in);
+  return e_in;
+}
+
 // Workgroups [0, gx): x coefficients of err -> cx, |err|^2.  [gx, gx + gt): S_T of err.  The rest:
 // |dense|^2.  The tickets of the last launch are zeroed.
 template <bool kShared>
@@ -316,21 +343,7 @@ __global__ __launch_bounds__(kEbcThreads, 4) void ebc_first_kernel(
     if (threadIdx.x == 0) partials[1 * kEbcPartials + blk] = s;
   } else {
     blk -= gx + gt;
-    const long long stride = (long long)(gridDim.x - gx - gt) * kEbcThreads, t0 = (long long)blk * kEbcThreads + threadIdx.x;
-    constexpr int U = 8;  // loads in flight
-    const bool wide = (reinterpret_cast<uintptr_t>(dense) & 15u) == 0;
-    const long long quads = wide ? total / 4 : 0;
-    const float4 *dense4 = reinterpret_cast<const float4 *>(dense);
-    for (long long e = t0; e < quads; e += U * stride) {
-      float4 v[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) v[u] = e + u * stride < quads ? dense4[e + u * stride] : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        e_in = fma((double)v[u].w, (double)v[u].w,
-                   fma((double)v[u].z, (double)v[u].z, fma((double)v[u].y, (double)v[u].y, fma((double)v[u].x, (double)v[u].x, e_in))));
-    }
-    for (long long e = 4 * quads + t0; e < total; e += stride) e_in = fma((double)dense[e], (double)dense[e], e_in);
+    e_in = ebc_squares<kEbcThreads>(dense, total, blk, (int)gridDim.x - gx - gt);
     const double s = ebc_block_sum(e_in, red);
     if (threadIdx.x == 0) partials[4 * kEbcPartials + blk] = s;
   }
@@ -354,27 +367,8 @@ struct EbcFinish {
   double n_t, n_yx, w[4], epsilon;
 };
 
-// Ends a launch: this workgroup's sum of reduction 3 is `s` (and of reduction 2 `s_xy`, if kBoth); the workgroup that
-// draws the last ticket adds up all partial sums and writes the result.  The partial sums of this launch cross
-// workgroups of different XCDs and therefore move with device-scope stores and loads; a workgroup takes its
-// ticket after its stores are acknowledged.
-template <bool kBoth>
-__device__ __forceinline__ void ebc_finish(double s_xy, double s, double *__restrict__ partials, const EbcFinish &f,
-                                           double *__restrict__ out) {
-  __shared__ int s_last;
-  if (threadIdx.x == 0) {
-    if constexpr (kBoth)
-      __hip_atomic_store(&partials[2 * kEbcPartials + blockIdx.x], s_xy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&partials[3 * kEbcPartials + blockIdx.x], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    const int leaf = (int)(blockIdx.x % kEbcLeaves), n_leaves = min((int)gridDim.x, kEbcLeaves);
-    const unsigned members = (gridDim.x - (unsigned)leaf + kEbcLeaves - 1) / kEbcLeaves;
-    bool last = atomicAdd(ebc_leaf(partials, leaf), 1u) == members - 1;
-    if (last) last = atomicAdd(ebc_root(partials), 1u) == (unsigned)n_leaves - 1;
-    s_last = last;
-  }
-  __syncthreads();
-  if (!s_last) return;
+// The result from all partial sums, by one workgroup.  (Device-scope loads: see ebc_finish.)
+__device__ __forceinline__ void ebc_total(double *__restrict__ partials, const EbcFinish &f, double *__restrict__ out) {
   double v[kEbcSums][kEbcPartials / kEbcThreads];
 #pragma unroll
   for (int k = 0; k < kEbcSums; ++k)
@@ -410,6 +404,30 @@ __device__ __forceinline__ void ebc_finish(double s_xy, double s, double *__rest
     out[4] = hh;
     out[5] = n_tot * sums[4];
   }
+}
+
+// Ends a launch: this workgroup's sum of reduction 3 is `s` (and of reduction 2 `s_xy`, if kBoth); the workgroup that
+// draws the last ticket adds up all partial sums and writes the result.  The partial sums of this launch cross
+// workgroups of different XCDs and therefore move with device-scope stores and loads; a workgroup takes its
+// ticket after its stores are acknowledged.
+template <bool kBoth>
+__device__ __forceinline__ void ebc_finish(double s_xy, double s, double *__restrict__ partials, const EbcFinish &f,
+                                           double *__restrict__ out) {
+  __shared__ int s_last;
+  if (threadIdx.x == 0) {
+    if constexpr (kBoth)
+      __hip_atomic_store(&partials[2 * kEbcPartials + blockIdx.x], s_xy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&partials[3 * kEbcPartials + blockIdx.x], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    const int leaf = (int)(blockIdx.x % kEbcLeaves), n_leaves = min((int)gridDim.x, kEbcLeaves);
+    const unsigned members = (gridDim.x - (unsigned)leaf + kEbcLeaves - 1) / kEbcLeaves;
+    bool last = atomicAdd(ebc_leaf(partials, leaf), 1u) == members - 1;
+    if (last) last = atomicAdd(ebc_root(partials), 1u) == (unsigned)n_leaves - 1;
+    s_last = last;
+  }
+  __syncthreads();
+  if (!s_last) return;
+  ebc_total(partials, f, out);
 }
 
 // S_XYT
@@ -551,6 +569,352 @@ __global__ __launch_bounds__(kEbcThreads, SY > 8 ? 3 : 4) void ebc_plane_kernel(
   ebc_finish<true>(sum_xy, sum, partials, f, out);
 }
 
+// All contractions of short axes in one launch (a second, of one workgroup, adds up).
+// S_XY, S_XYT: a workgroup takes the planes (t) of one channel and 16 of the x coefficients, a wavefront a plane at a
+// time.  Cosines are even and sines are odd about the middle of the axis, so the coefficients of a row are those of the sums e_j +
+// e_(X-j), j <= X / 2, against cosines and of the differences against sines: half the elements, and a group of 16 coefficients is
+// of one kind.  With the plane's rows as the first operand and the table as the second, the x coefficients come out
+// as (y = lane / 16 + 4 r, k = lane % 16) in register r, which is, unchanged, the second operand of the y contraction's step r: a
+// plane goes from the tensor to its y-x coefficients in registers.  The coefficients of all planes meet in LDS, 16 *
+// (2 (Y / 4) + 1) doubles a plane, where the wavefronts contract over t.  No coefficient goes through memory; err is read once for
+// each group of 16, from the L2 of the channel's XCD, and once for S_T.  Sums and differences of two floats are as good as exact in
+// fp64 (error of the energies against a transform in 64 bits 1e-16 of their sum, as before).
+// S_T, |err|^2: a thread takes lines, sums and differences as above, on the vector units (a line has few coefficients: tiles of 16 would be
+// half empty, and the matrix units are what the planes wait for).
+// Workgroups [0, n_ch): the planes.  [n_ch, n_ch + gt): S_T and |err|^2.  The rest: |dense|^2.
+constexpr int kEbcChThreads = 512, kEbcChWaves = kEbcChThreads / 64;
+constexpr int kEbcChLds = 144 * 1024;  // of the largest sizes that take this path (T = 35, Y = 48, X = 80)
+
+// a mod n for 0 <= a < 2^16, rn = 1 / n
+__device__ __forceinline__ int ebc_mod(int a, int n, float rn) {
+  const int r = a - (int)((float)a * rn) * n;  // (the quotient may be one off)
+  return r < 0 ? r + n : r >= n ? r - n : r;
+}
+
+// sum over the wavefront in every lane, on the vector units (through LDS, as __shfl does it, three sums took 0.8 us)
+__device__ __forceinline__ double ebc_wave_sum(double v) {
+  auto halves = [](double x, uint32_t &lo, uint32_t &hi) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    lo = (uint32_t)u;
+    hi = (uint32_t)(u >> 32);
+  };
+  auto whole = [](uint32_t lo, uint32_t hi) -> double { return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo); };
+  uint32_t lo, hi;
+#define HEART_EBC_DPP(ctrl)                                                     \
+  halves(v, lo, hi);                                                            \
+  v += whole(__builtin_amdgcn_update_dpp(0u, lo, ctrl, 0xf, 0xf, false),        \
+             __builtin_amdgcn_update_dpp(0u, hi, ctrl, 0xf, 0xf, false))
+  HEART_EBC_DPP(0xB1);   // quad_perm, lane ^ 1
+  HEART_EBC_DPP(0x4E);   // quad_perm, lane ^ 2
+  HEART_EBC_DPP(0x124);  // row_ror:4
+  HEART_EBC_DPP(0x128);  // row_ror:8
+#undef HEART_EBC_DPP
+  uint32_t l0, l1, h0, h1;
+  halves(v, lo, hi);
+  swap_rows16(lo, l0, l1);
+  swap_rows16(hi, h0, h1);
+  v = whole(l0, h0) + whole(l1, h1);
+  halves(v, lo, hi);
+  swap_halves32(lo, l0, l1);
+  swap_halves32(hi, h0, h1);
+  return whole(l0, h0) + whole(l1, h1);
+}
+
+// S_T and the sum of squares of the lines of this thread; coefficients up to frequency R >= T / 4, P >= T / 2 pairs.  Behind the table
+// of T in LDS the factors of the pairs, [P][2 R + 2].  All elements of a line are asked for at once, those of the next
+// line as soon as a register is free.  (No branches: loads that may not be there are all waited for.)
+template <int R, int P>
+__device__ __forceinline__ void ebc_lines_t(const float *__restrict__ err, long long lines, int T, int inner, int blk, int n_blk,
+                                            double *tab, double &s_t, double &s_in) {
+  constexpr int K = 2 * R + 2;
+  const int r = T / 4, pairs = T / 2;  // (the middle of an even T is a pair without a second element)
+  const uint32_t bytes = (uint32_t)(4 * lines * T);
+  float e0, a[P], b[P];
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(err), 0, (int)bytes, 0x00020000);
+  uint32_t at;  // byte offset of the line
+  auto seek = [&](long long l) __attribute__((always_inline)) {
+    const uint32_t l32 = (uint32_t)min(l, lines - 1), o = l32 / (uint32_t)inner;  // (a line past the end is not counted)
+    at = 4u * (o * (uint32_t)(T * inner) + (l32 - o * (uint32_t)inner));
+  };
+  // (an element that does not exist is out of range for the descriptor and arrives as zero)
+  auto element = [&](int t, bool there) __attribute__((always_inline)) -> float {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, there ? at + (uint32_t)(4 * t * inner) : 0xffffffffu, 0, 0));
+  };
+  auto ask = [&](int u) __attribute__((always_inline)) {  // pair u: elements u + 1 and T - 1 - u
+    a[u] = element(u + 1, u < pairs);
+    b[u] = element(T - 1 - u, u < pairs && 2 * (u + 1) != T);
+  };
+  const long long stride = (long long)n_blk * kEbcChThreads;
+  long long l0 = (long long)blk * kEbcChThreads + threadIdx.x;
+  seek(l0);
+  e0 = element(0, true);
+#pragma unroll
+  for (int u = 0; u < P; ++u) ask(u);
+  ebc_table<kEbcChThreads>(T, tab);
+  // row t - 1: cosines of f = 0 .. R at t, sines of f = 1 .. R
+  double *op = tab + 2 * T;
+  for (int i = threadIdx.x; i < P * K; i += kEbcChThreads) {
+    const int t = i / K + 1, k = i % K, f = k <= R ? k : k - R;
+    op[i] = k < K - 1 && f <= r ? tab[(k <= R ? 0 : T) + ebc_mod(f * t, T, 1.f / (float)T)] : 0.0;
+  }
+  __syncthreads();
+  for (; l0 < lines; l0 += stride) {
+    double c[R + 1], sn[R], sq = (double)e0 * (double)e0;
+#pragma unroll
+    for (int f = 0; f <= R; ++f) c[f] = (double)e0;
+#pragma unroll
+    for (int f = 0; f < R; ++f) sn[f] = 0.0;
+    seek(l0 + stride);
+    e0 = element(0, true);
+    int zero = 0;
+    asm volatile("" : "+s"(zero));  // (the factors are read for each line: they are more than the registers)
+#pragma unroll
+    for (int u = 0; u < P; ++u) {
+      const double x = (double)a[u], y = (double)b[u], p = x + y, m = x - y;
+      ask(u);
+      sq = fma(x, x, fma(y, y, sq));
+      const double *w = op + zero + u * K;
+#pragma unroll
+      for (int f = 0; f <= R; ++f) c[f] = fma(p, w[f], c[f]);
+#pragma unroll
+      for (int f = 0; f < R; ++f) sn[f] = fma(m, w[R + 1 + f], sn[f]);
+      if (u % 2) __builtin_amdgcn_sched_barrier(0);
+    }
+    double q = 0.0;  // (coefficients past the last are left out, not weighted with 0: they are infinite with an infinite element)
+#pragma unroll
+    for (int f = 0; f < R; ++f)
+      if (f + 1 <= r) q = fma(c[f + 1], c[f + 1], fma(sn[f], sn[f], q));
+    s_t += fma(c[0], c[0], 2.0 * q);
+    s_in += sq;
+  }
+}
+
+template <int M, int YT, int W, int R>  // tiles of y coefficients, tiles of y, whole sixteens of folded x (up to 16 elements more are its rest), t
+__global__ __launch_bounds__(kEbcChThreads, W == 1 ? 4 : 2) void ebc_channel_kernel(
+    const float *__restrict__ err, const float *__restrict__ dense, long long total, int C, int T, int Y, int X, int n_ch, int gt,
+    double *__restrict__ partials) {
+  extern __shared__ __align__(16) double ebc_lds[];
+  __shared__ double red[kEbcChWaves][2];
+  // sums over the workgroup in a fixed order, valid in thread 0
+  auto block_sums = [&](double (&v)[2]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) v[i] = ebc_wave_sum(v[i]);
+    if ((threadIdx.x & 63) == 0)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) red[threadIdx.x >> 6][i] = v[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      v[i] = red[0][i];
+#pragma unroll
+      for (int w = 1; w < kEbcChWaves; ++w) v[i] += red[w][i];
+    }
+  };
+  int blk = blockIdx.x;
+  if (blk >= n_ch) {
+    blk -= n_ch;
+    double sums[2] = {0.0, 0.0};
+    if (blk < gt) {
+      ebc_lines_t<R, R == 5 ? 11 : 17>(err, (long long)C * Y * X, T, Y * X, blk, gt, ebc_lds, sums[0], sums[1]);
+      block_sums(sums);
+      if (threadIdx.x == 0) {
+        partials[0 * kEbcPartials + blk] = sums[1];
+        partials[1 * kEbcPartials + blk] = sums[0];
+      }
+    } else {
+      blk -= gt;
+      sums[0] = ebc_squares<kEbcChThreads>(dense, total, blk, (int)gridDim.x - n_ch - gt);
+      block_sums(sums);
+      if (threadIdx.x == 0) partials[4 * kEbcPartials + blk] = sums[0];
+    }
+    return;
+  }
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, g = lane >> 4;
+  const int KY = ebc_coefs(Y), KT = ebc_coefs(T), rx = X / 4, n_cos = rx / 16 + 1, PX = n_cos + (rx + 15) / 16;
+  const int units = (C + kNumXcd - 1) / kNumXcd * kNumXcd * PX;
+  // operands of the table for each step and lane (in registers they took 20 to 60 others to scratch memory), coef[t][ky][16]
+  constexpr int SX = 4 * W + 4, SY = 4 * M * YT, ST = R == 5 ? 6 : 9, PT = R == 5 ? 1 : 2;
+  double *tab_t = ebc_lds, *tab_y = tab_t + 2 * T, *tab_x = tab_y + 2 * Y, *op_y = tab_x + 2 * X, *op_t = op_y + 64 * SY,
+         *op_x = op_t + 64 * ST * PT, *coef = op_x + 64 * SX;
+  // (the groups of 16 x coefficients of a channel go to one XCD)
+  auto channel = [&](int u) -> int { return u / (kNumXcd * PX) * kNumXcd + u % kNumXcd; };
+  // Folded elements j = 0 .. X / 2 of row l16 of y tile yt of plane (c, t): of every whole 16 those of 4 g .. 4 g + 3, of the rest g
+  // and every fourth; e_j and e_(X-j).  Rows past the end are out of range for the descriptor and arrive as zeros; what is loaded for
+  // an element past the last, and as the mirror image of one that has none, is not used.
+  // (All steps are taken, of zeros where there are no elements: a branch a step kept the operands' reads behind it.)
+  const int folded = X / 2 + 1, whole = min(folded / 16, W);
+  const uint32_t plane = (uint32_t)(Y * X) * 4u;
+  constexpr uint32_t kNowhere = 0x7fff0000u;
+  struct Fold {
+    float at[SX], mirror[SX];
+  };
+  auto load = [&](Fold &v, int c, int t, int yt) __attribute__((always_inline)) {
+    typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+    const int y = 16 * yt + l16;
+    const bool ok = c < C && t < T;  // uniform
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(err) + (long long)(ok ? c : 0) * T * Y * X + (long long)(ok ? t : 0) * Y * X, 0, ok ? (int)plane : 0, 0x00020000);
+    const uint32_t row = y < Y ? (uint32_t)(y * X) * 4u : kNowhere;
+    // (the mirror image of j = 0 would be the element behind the row: those of 1 to 3 are loaded with the one before them)
+    const uint32_t ahead = row + 16u * g, back = row + 4u * (X - 3) - 16u * g, single = row + 4u * (16 * whole + g),
+                   single_back = row + 4u * (X - 16 * whole - g);
+#pragma unroll
+    for (int u = 0; u < W; ++u) {
+      const bool first = u == 0 && g == 0;
+      const u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, ahead + 64u * u, 0, 0);
+      const u32x4 m = __builtin_amdgcn_raw_buffer_load_b128(rs, back - 64u * u - (first ? 4u : 0u), 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        v.at[4 * u + i] = __uint_as_float(q[i]);
+        v.mirror[4 * u + i] = __uint_as_float(m[3 - i]);  // (e_(X-j), in the first lanes that of j + 1: see mirror_of)
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v.at[4 * W + i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, single + 16u * i, 0, 0));
+      v.mirror[4 * W + i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, single_back - 16u * i, 0, 0));
+    }
+  };
+  // (at its use: a selection here would wait for the loads)
+  auto mirror_of = [&](const Fold &v, int u) __attribute__((always_inline)) -> float {
+    return u > 0 && u < 4 && g == 0 ? v.mirror[u > 0 ? u - 1 : 0] : v.mirror[u];
+  };
+  Fold even, odd;
+  load(even, channel(blk), wave, 0);
+  // (tables as ebc_table's)
+  const float rt = 1.f / (float)T, ry = 1.f / (float)Y, rx1 = 1.f / (float)X;
+  for (int m = threadIdx.x; m < T + Y + X; m += kEbcChThreads) {
+    const int n = m < T ? T : m < T + Y ? Y : X, i = m < T ? m : m < T + Y ? m - T : m - T - Y;
+    double *tab = m < T ? tab_t : m < T + Y ? tab_y : tab_x;
+    double c, sn;
+    sincospi(2.0 * (double)i / (double)n, &sn, &c);
+    tab[i] = c;
+    tab[n + i] = sn;
+  }
+  __syncthreads();
+  // place of coefficient k's value at element j in a table of n: 0 the mean, then cosine and sine of each frequency (those
+  // past K are computed and dropped)
+  auto place = [&](int k, int K, int n, float rn, int j) __attribute__((always_inline)) -> int {
+    const int f = k < K ? (k + 1) >> 1 : 0;
+    return ((k & 1) == 0 && k > 0 && k < K ? n : 0) + ebc_mod(f * j, n, rn);
+  };
+  for (int i = wave; i < SY; i += kEbcChWaves) op_y[64 * i + lane] = tab_y[place(16 * (i / (4 * YT)) + l16, KY, Y, ry, 4 * (i % (4 * YT)) + g)];
+  for (int i = wave; i < ST * PT; i += kEbcChWaves) op_t[64 * i + lane] = tab_t[place(16 * (i / ST) + l16, KT, T, rt, 4 * (i % ST) + g)];
+  double s_xy = 0.0, s_xyt = 0.0;
+  for (int unit = blk; unit < units; unit += n_ch) {
+    const int c = channel(unit), q = unit / kNumXcd % PX;
+    if (c >= C) continue;  // uniform
+    const bool sine = q >= n_cos;
+    const int fx = sine ? 16 * (q - n_cos) + l16 + 1 : 16 * q + l16;  // this lane's frequency
+    const bool in_x = fx <= rx;
+    const double wx = fx > 0 ? 2.0 : 1.0, sign = sine ? -1.0 : 1.0;
+    for (int i = wave; i < SX; i += kEbcChWaves) {
+      const int j = i < 4 * whole ? 16 * (i / 4) + 4 * g + i % 4 : i < 4 * W ? 0 : 16 * whole + 4 * (i - 4 * W) + g;
+      op_x[64 * i + lane] = tab_x[(sine ? X : 0) + ebc_mod((in_x ? fx : 0) * j, X, rx1)];
+    }
+    __syncthreads();
+    // (two sets of registers in turn: a copy of what has been asked for would wait for it)
+    ebc_f64x4 acc2[M];
+#pragma unroll
+    for (int m = 0; m < M; ++m) acc2[m] = ebc_f64x4{0.0, 0.0, 0.0, 0.0};
+    int t = wave, yt = 0;
+    auto tile = [&](const Fold &v, Fold &nxt) __attribute__((always_inline)) {
+      const bool same = yt + 1 < YT;
+      const int t1 = same ? t : t + kEbcChWaves, yt1 = same ? yt + 1 : 0;
+      load(nxt, c, t1, yt1);
+      ebc_f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+      double bx[SX], ay[M][4];  // (all read before the first is used)
+#pragma unroll
+      for (int u = 0; u < SX; ++u) bx[u] = op_x[64 * u + lane];
+#pragma unroll
+      for (int m = 0; m < M; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) ay[m][r] = op_y[64 * ((m * YT + yt) * 4 + r) + lane];
+      __builtin_amdgcn_sched_barrier(0);
+      auto step = [&](int u, int j, bool there) __attribute__((always_inline)) {
+        float at = there ? v.at[u] : 0.f, mirror = there && j > 0 && 2 * j != X ? mirror_of(v, u) : 0.f;
+        asm volatile("" : "+v"(at), "+v"(mirror));  // (selections of 32 bits, not of 64)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(fma(sign, (double)mirror, (double)at), bx[u], acc, 0, 0, 0);
+      };
+#pragma unroll
+      for (int u = 0; u < W; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) step(4 * u + i, 16 * u + 4 * g + i, u < whole);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) step(4 * W + i, 16 * whole + 4 * i + g, 16 * whole + 4 * i + g < folded);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+          acc2[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(ay[m][r], acc[r], acc2[m], 0, 0, 0);
+      if (!same) {
+        double s_plane = 0.0;
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int ky = 16 * m + 4 * r + g;
+            const double x = acc2[m][r];
+            // (coefficients past the last are left out, not weighted with 0: they are infinite with an infinite element)
+            if (ky < KY) {
+              if (in_x) s_plane = fma((ky > 0 ? 2.0 : 1.0) * x, x, s_plane);
+              coef[(t * KY + ky) * 16 + l16] = x;
+            }
+            acc2[m][r] = 0.0;
+          }
+        s_xy = fma(wx, s_plane, s_xy);
+      }
+      t = t1;
+      yt = yt1;
+    };
+    while (t < T) {
+      tile(even, odd);
+      if (t < T) tile(odd, even);
+    }
+    load(even, channel(unit + n_ch), wave, 0);
+    __syncthreads();
+    // over t: a wavefront has a row of y coefficients at a time (KY is odd: the rows of two t lie in different halves of the banks)
+    for (int ky = wave; ky < KY; ky += kEbcChWaves) {
+      const double w = ky > 0 ? 2.0 * wx : wx;
+      double b[ST];
+#pragma unroll
+      for (int i = 0; i < ST; ++i) b[i] = 4 * i + g < T ? coef[((4 * i + g) * KY + ky) * 16 + l16] : 0.0;
+#pragma unroll
+      for (int p = 0; p < PT; ++p) {
+        ebc_f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int i = 0; i < ST; ++i) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(op_t[64 * (p * ST + i) + lane], b[i], acc, 0, 0, 0);
+        double s_row = 0.0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int kt = 16 * p + 4 * r + g;
+          const double v = acc[r];
+          if (in_x && kt < KT) s_row = fma((kt > 0 ? 2.0 : 1.0) * v, v, s_row);
+        }
+        s_xyt = fma(w, s_row, s_xyt);
+      }
+    }
+    __syncthreads();
+  }
+  double sums[2] = {s_xy, s_xyt};
+  block_sums(sums);
+  if (threadIdx.x == 0) {
+    partials[2 * kEbcPartials + blk] = sums[0];
+    partials[3 * kEbcPartials + blk] = sums[1];
+  }
+}
+
+__global__ __launch_bounds__(kEbcThreads) void ebc_total_kernel(double *__restrict__ partials, EbcFinish f,
+                                                                double *__restrict__ out) {
+  ebc_total(partials, f, out);
+}
+
+// a kernel as a type
+template <auto K>
+struct EbcKernel {
+  static constexpr auto k = K;
+};
+
 // the two coefficient arrays (neither larger than the tensor), the partial sums with the tickets
 static size_t ebc_workspace_doubles(long long total, int T, int Y, int X) {
   return 2 * (size_t)total + (size_t)(T + Y + X) + kEbcSums * (size_t)kEbcPartials;
@@ -581,6 +945,44 @@ int launch_ebc_band_error(long long C, int T, int Y, int X, const float *err, co
     const long long rounds = (g + most - 1) / most;
     return (int)((g + rounds - 1) / rounds);
   };
+  // One launch (ebc_channel_kernel) where its workgroups, one for 16 x coefficients of a channel, are enough and busy.  Whole call, two
+  // launches through memory -> one and the total, us: 128 x 21 x 30 x 52 33.1 -> 21.6, 128 x 11 x 19 x 57 23.0 -> 16.6, 48 x 22 x 24 x
+  // 53 20.9 -> 18.1, 64 x 9 x 20 x 40 15.2 -> 13.6, 64 x 21 x 45 x 64 38.1 -> 32.9, 128 x 33 x 45 x 80 119 -> 104, 48 x 33 x 12 x 78 26.3
+  // -> 25.3.  Not: few workgroups, each a chain of a third of the planes (16 x 21 x 30 x 52 16.4 -> 18.8, 48 x 10 x 40 x 20 14.5 -> 17.7);
+  // short x axes, whose steps are mostly padding (48 x 23 x 11 x 28 14.0 -> 16.6); and longer t or y axes with x below 64, where the
+  // registers leave no room on a CU for the workgroups of S_T (128 x 30 x 23 x 56 34.3 -> 37.1, 128 x 29 x 37 x 39 38.3 -> 45.0, 128 x 40 x
+  // 30 x 52 51.6 -> 88.6).
+  const bool low = Y < 32, wide = X >= 64;  // (2 (Y / 4) + 1 coefficients, X / 2 + 1 folded elements)
+  const int PX = X / 4 / 16 + 1 + (X / 4 + 15) / 16;
+  const int ch_steps = (wide ? 12 : 8) + (low ? 8 : 24) + (T < 24 ? 6 : 18);  // operands of the table (ebc_channel_kernel)
+  const size_t ch_lds = sizeof(double) * std::max(2 * (size_t)(T + Y + X) + 64 * (size_t)ch_steps + (size_t)T * KY * 16,
+                                                  2 * (size_t)T + (T < 24 ? 11 * 12 : 17 * 18));
+  if ((wide ? X <= 80 && T < 36 && Y <= kEbcPlaneY : X >= 32 && T < 24 && low) && C * PX >= (low ? 96 : 192) && total <= 0x3fffffff) {
+    const int units = (int)((C + kNumXcd - 1) / kNumXcd) * kNumXcd * PX, n_ch = std::min(units, kEbcPartials);
+    auto rounds = [](long long n, long long most) -> int {  // workgroups: the fewest equal rounds of no more than `most`
+      const long long r = (n + most - 1) / most;
+      return (int)((n + r - 1) / r);
+    };
+    const int gt = rounds((lt.lines + kEbcChThreads - 1) / kEbcChThreads, 160);
+    const int gd = (int)std::min<long long>((total + 16 * kEbcChThreads - 1) / (16 * kEbcChThreads), 96);
+    const EbcFinish f{{gt, gt, n_ch, n_ch, gd}, (double)T, (double)Y * X, {w[0], w[1], w[2], w[3]}, epsilon};
+    auto run = [&](auto kern) -> int {
+      static DeviceFlags attr_set;  // (per instantiation: the lambda's argument has a type of its own)
+      const int dev = current_device();
+      if (dev < 0) return fail(HEART_EHIP, "heart_ebc_band_error: cannot identify the current device");
+      if (hipError_t e = set_max_lds_once(attr_set, dev, reinterpret_cast<const void *>(kern.k), kEbcChLds))
+        return fail(HEART_EHIP, "hipFuncSetAttribute(band error LDS): %s", hipGetErrorString(e));
+      hipLaunchKernelGGL(kern.k, dim3((unsigned)(n_ch + gt + gd)), dim3(kEbcChThreads), ch_lds, st, err, dense, total, (int)C, T, Y,
+                         X, n_ch, gt, partials);
+      return HEART_OK;
+    };
+    if (int rc = !wide    ? run(EbcKernel<ebc_channel_kernel<1, 2, 1, 5>>{})
+                 : T < 24 ? (low ? run(EbcKernel<ebc_channel_kernel<1, 2, 2, 5>>{}) : run(EbcKernel<ebc_channel_kernel<2, 3, 2, 5>>{}))
+                          : (low ? run(EbcKernel<ebc_channel_kernel<1, 2, 2, 8>>{}) : run(EbcKernel<ebc_channel_kernel<2, 3, 2, 8>>{})))
+      return rc;
+    hipLaunchKernelGGL(ebc_total_kernel, dim3(1), dim3(kEbcThreads), 0, st, partials, f, out);
+    return check_launch("ebc kernels");
+  }
   const int gx = groups(lx, 384), gt = groups(lt, 400);
   const int gd = (int)std::min<long long>((total + 8 * kEbcThreads - 1) / (8 * kEbcThreads), 240);
   EbcFinish f{{gx, gt, 0, 0, gd}, (double)T, (double)Y * X, {w[0], w[1], w[2], w[3]}, epsilon};

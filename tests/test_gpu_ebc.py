@@ -166,3 +166,35 @@ def test_band_error_with_an_infinity(shape):
     assert np.isposinf(got[1]), got
     # the other bands are differences of infinite sums
     assert np.isnan(got[[0, 2, 3, 4]]).all() and np.isfinite(got[5]), got
+
+
+# the path of one launch: axes around its limits (x of 32 to 80 elements, t of 23 and 24, 35 and 36, y of 31 and 32, 48 and 49), even and
+# odd ones, whose middle pairs with itself or with its neighbour, axes of one and two elements, channels that are no multiple of 8
+@pytest.mark.parametrize("shape", [(48, 1, 1, 32), (48, 2, 31, 33), (49, 23, 30, 63), (50, 3, 5, 47), (33, 24, 31, 64), (64, 35, 48, 79),
+                                   (64, 23, 32, 80), (24, 22, 3, 65), (257, 4, 2, 77), (48, 24, 31, 63), (64, 36, 49, 64)])
+def test_band_error_in_one_launch(shape):
+    import paper_2605_14513_amd as heart
+
+    rng = np.random.default_rng(sum(shape))
+    err, dense = (rng.standard_normal(shape).astype(np.float32) for _ in range(2))
+    print("ebc", shape, flush=True)
+    got = heart.heart_ebc_band_error(np_gpu(err), np_gpu(dense)).cpu().numpy()
+    want = eo.band_energies(err)
+    # (the same bound as at the edges of the tiles)
+    assert np.abs(got[1:5] - want).max() <= 1e-13 * want.sum(), (got[1:5], want)
+    ref = shape[1] * shape[2] * shape[3] * (dense.astype(np.float64) ** 2).sum()
+    assert abs(got[5] - ref) <= 1e-13 * ref
+    assert np.array_equal(heart.heart_ebc_band_error(np_gpu(err), np_gpu(dense)).cpu().numpy(), got)
+
+
+# an infinite element leaves the same energies finite, infinite and not a number as it does where few channels take the other path
+@pytest.mark.parametrize("at", [(0, 0, 0), (3, 4, 5), (2, 10, 51), (10, 15, 26), (20, 29, 1), (0, 7, 25), (11, 0, 27)])
+def test_band_error_in_one_launch_with_an_infinite_element(at):
+    import paper_2605_14513_amd as heart
+
+    rng = np.random.default_rng(7)
+    err = np.zeros((64, 21, 30, 52), dtype=np.float32)
+    err[:3] = rng.standard_normal((3, 21, 30, 52))
+    err[1][at] = np.inf
+    got, few = (heart.heart_ebc_band_error(np_gpu(e), np_gpu(np.ones_like(e))).cpu().numpy() for e in (err, err[:3]))
+    assert np.array_equal(np.isnan(got[1:5]), np.isnan(few[1:5])) and np.array_equal(np.isinf(got[1:5]), np.isinf(few[1:5])), (got, few)
