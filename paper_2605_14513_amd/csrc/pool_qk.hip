@@ -123,10 +123,10 @@ struct PoolDriftArgs {  // what the drift stage needs beyond the token-mean argu
 
 // Mean of one block, by kPoolThreads lanes (`t` = 0 .. kPoolThreads - 1) that all call it, of a head's rows n0 ..
 // n0 + nrows - 1 (at `base`, token stride sn); contains a barrier of the workgroup.  part: LDS, kPoolPart floats.
-// kAcross: dst is read by another workgroup of this launch.  nrows <= 0: no block for these lanes.  also(): called once the
-// loads are on their way.
+// kThrough: the mean goes out with device-scope stores (dst is read by another workgroup of this launch, or see
+// pool_blocks_kernel).  nrows <= 0: no block for these lanes.  also(): called once the loads are on their way.
 constexpr int kPoolPart = kPoolThreads * 8;
-template <int D, bool kAcross, class Also>
+template <int D, bool kThrough, class Also>
 __device__ __forceinline__ void block_mean(const uint16_t *base, int n0, long long sn, int nrows, float *dst, float *part, int t,
                                            Also also) {
   constexpr int LPR = D / 8;               // lanes per token row
@@ -169,32 +169,43 @@ __device__ __forceinline__ void block_mean(const uint16_t *base, int n0, long lo
     float s = 0.f;
 #pragma unroll
     for (int r = 0; r < RPP; ++r) s += part[r * D + t];
-    if constexpr (kAcross)
+    if constexpr (kThrough)
       store_device_scope(dst + t, s / (float)nrows);
     else
       dst[t] = s / (float)nrows;
   }
 }
 
-template <int D>
+// kStream: a call whose Q and K do not stay in the chip's memory-side cache.  Read from HBM without the stores of the
+// block means, the pass ran 10 to 13 % faster although they are 1.5 % of the bytes: a plain store leaves a dirty line in
+// the L2 of an XCD, to be written back whenever the reads of the stream push it out.  There the means are therefore written
+// through (device scope), and 2^run consecutive blocks (128 KB of rows, and their means) go to one XCD.
+// (workgroup w is taken to run on XCD w % 8; what it computes does not depend on it.)
+template <int D, bool kStream>
 __global__ __launch_bounds__(kPoolThreads) void pool_blocks_kernel(
     const uint16_t *__restrict__ q, const uint16_t *__restrict__ k, long long qsb, long long qsh,
     long long qsn, long long ksb, long long ksh, long long ksn, int H, int N, int block, int Nb,
-    float *__restrict__ qblk, float *__restrict__ kblk) {
+    int run, float *__restrict__ qblk, float *__restrict__ kblk) {
   __shared__ float part[kPoolPart];
 
-  // blockIdx.x enumerates (b*H+h, tensor, block) with the block index fastest so
+  unsigned w = blockIdx.x;
+  if constexpr (kStream) {
+    const unsigned at = w >> (run + 3);                                       // which 8 * 2^run workgroups
+    if ((at + 1) << (run + 3) <= gridDim.x)                                   // (the last ones, if fewer, stay in order)
+      w = (((at << 3) + (w & 7u)) << run) + ((w >> 3) & ((1u << run) - 1u));
+  }
+  // w enumerates (b*H+h, tensor, block) with the block index fastest so
   // that consecutive workgroups stream consecutive memory.  (Divisions in 32 bits, which hold the
   // grid: 13.85 -> 13.4 us for heart_pool_drift of two items of 10 heads of 101 blocks of 64.)
-  const unsigned rest = blockIdx.x / (unsigned)Nb;  // = 2 * (b*H+h) + tensor
-  const int i = (int)(blockIdx.x - rest * (unsigned)Nb), which = (int)(rest & 1u);
+  const unsigned rest = w / (unsigned)Nb;  // = 2 * (b*H+h) + tensor
+  const int i = (int)(w - rest * (unsigned)Nb), which = (int)(rest & 1u);
   const unsigned bh = rest >> 1;
   const int b = (int)(bh / (unsigned)H), h = (int)(bh - (unsigned)b * (unsigned)H);
 
   const uint16_t *base = which ? (k + b * ksb + h * ksh) : (q + b * qsb + h * qsh);
   long long sn = which ? ksn : qsn;
   const int n0 = i * block;
-  block_mean<D, false>(base, n0, sn, min(block, N - n0),
+  block_mean<D, kStream>(base, n0, sn, min(block, N - n0),
                        (which ? kblk : qblk) + ((size_t)bh * Nb + i) * D, part, (int)threadIdx.x, [] {});
 }
 
@@ -326,6 +337,17 @@ template <int D>
 constexpr int kSmallCols = D == 64 ? 2048 : 1024;
 static_assert(kSmallNb <= kMeanThreads / (128 / 4), "at most one block a slice of the token means");
 static_assert(kSmallCols<64> <= kSmallMeans && kSmallCols<64> / 64 <= kSmallMarks, "LDS");
+// From where pool_blocks_kernel<D, true> is the better one: more bytes of Q and K than the 256 MiB of the memory-side cache.
+// heart_pool_qk with plain stores in block order -> written through in runs, us: D = 128, blocks of 128, H x N = 40 x 32760
+// 113.5 -> 107.8, 24 x 119056 250 -> 234.5 (5.8 -> 6.2 TB/s), 20 x 32760 58.2 -> 56.9; blocks of 64 116.5 -> 110.2; D = 64,
+// 80 x 32760 113.3 -> 104.4, 48 x 119056 244 -> 227.7; at the cache's size 16 x 32760 47.0 -> 46.6, and below it 13 x 32760 38.3
+// -> 39.1, 28 x 32760 of D = 64 40.1 -> 40.6 and a call of 10 heads of 101 blocks 0.5 us more (there the token means find the
+// plain stores in an L2).  Written through in block order 110.4 and 236.4; plain stores with a contiguous eighth of the
+// blocks on each XCD 110.5 and 244.
+// Runs of 64, 128, 256 KB: 110.4, 107.3, 109.4 and 242.5, 235.4, 235.8.  Rows of D = 64 between those of other heads gain
+// nothing (82.6 -> 83.1, four items of 24 heads of 20000 tokens); with D = 128 they do (115.2 -> 113.4).
+constexpr long long kStreamBytes = 256LL << 20;
+constexpr int kRunBytes = 128 * 1024;
 template <int D>
 static int launch_pool_t(const heart_shape &s, const uint16_t *qp, const uint16_t *kp, float *qblk,
                          float *kblk, float *qmean, float *kmean, const PoolDriftArgs *fused,
@@ -341,9 +363,13 @@ static int launch_pool_t(const heart_shape &s, const uint16_t *qp, const uint16_
     return check_launch("pool_drift_small_kernel");
   }
   const dim3 grid((unsigned)nwg), blk(kPoolThreads), grid2((unsigned)(2 * s.B * s.H)), blk2(kMeanThreads);
-  hipLaunchKernelGGL(pool_blocks_kernel<D>, grid, blk, 0, st, qp, kp, s.q_stride[0], s.q_stride[1],
-                     s.q_stride[2], s.k_stride[0], s.k_stride[1], s.k_stride[2], s.H, s.N, s.block,
-                     Nb, qblk, kblk);
+  const bool stream = 4LL * s.B * s.H * s.N * D > kStreamBytes &&
+                      (D == 128 || (s.q_stride[2] == D && s.k_stride[2] == D));
+  int run = 2;
+  while ((s.block * D * 2) << run < kRunBytes) ++run;
+  hipLaunchKernelGGL((stream ? pool_blocks_kernel<D, true> : pool_blocks_kernel<D, false>), grid, blk, 0, st, qp, kp,
+                     s.q_stride[0], s.q_stride[1], s.q_stride[2], s.k_stride[0], s.k_stride[1], s.k_stride[2], s.H, s.N,
+                     s.block, Nb, run, qblk, kblk);
   if (int rc = check_launch("pool_blocks_kernel")) return rc;
   if (fused) {
     hipLaunchKernelGGL(token_mean_drift_kernel<D>, grid2, blk2, 0, st, qblk, kblk, s.H, s.N, s.block,
