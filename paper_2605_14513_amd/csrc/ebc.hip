@@ -583,7 +583,7 @@ __global__ __launch_bounds__(kEbcThreads, SY > 8 ? 3 : 4) void ebc_plane_kernel(
 // half empty, and the matrix units are what the planes wait for).
 // Workgroups [0, n_ch): the planes.  [n_ch, n_ch + gt): S_T and |err|^2.  The rest: |dense|^2.
 constexpr int kEbcChThreads = 512, kEbcChWaves = kEbcChThreads / 64;
-constexpr int kEbcChLds = 144 * 1024;  // of the largest sizes that take this path (T = 35, Y = 48, X = 80)
+constexpr int kEbcChLds = 144 * 1024;  // room for the largest sizes that it holds (T = 35, Y = 48, X = 95)
 
 // a mod n for 0 <= a < 2^16, rn = 1 / n
 __device__ __forceinline__ int ebc_mod(int a, int n, float rn) {
@@ -920,6 +920,43 @@ static size_t ebc_workspace_doubles(long long total, int T, int Y, int X) {
   return 2 * (size_t)total + (size_t)(T + Y + X) + kEbcSums * (size_t)kEbcPartials;
 }
 
+// groups of 16 x coefficients of one kind (ebc_channel_kernel): cosines of the frequencies 0 .. X / 4, sines of 1 .. X / 4
+static int ebc_x_groups(int X) { return X / 4 / 16 + 1 + (X / 4 + 15) / 16; }
+
+// Whether ebc_channel_kernel is the better one.  Whole call, two launches through memory -> one and the total, us, one tensor again and
+// again (from HBM where that is another matter).  It holds 16 to 48 folded elements of x (at 95 x 48 x 35 142 of 144 KB of LDS) and y
+// and t up to its operands' tiles; of these sizes
+// - enough channels: 16 x 23 x 40 x 80 24.9 -> 30.1, 24 x 22 x 40 x 64 23.8 -> 31.9, 32 x 23 x 30 x 48 19.0 -> 21.1 against 48 x 22 x
+//   24 x 53 20.9 -> 18.1, 64 x 22 x 47 x 72 47.9 -> 38.8;
+// - all workgroups of planes at once, two a CU with x below 64, one above: 256 x 12 x 24 x 56 (512 of them) 34.8 -> 31.4, 64 x 33 x 28 x
+//   67 (192) 41.5 -> 34.3; a second and third round of them 72 x 33 x 34 x 68 (288) 55.5 -> 69.6, 160 x 21 x 22 x 72 45.9 -> 52.9,
+//   1024 x 28 x 2 x 68 69.7 -> 219;
+// - and bytes enough for what a workgroup does one after another (two planes a wavefront from t = 9, three from 17), which steps that are
+//   mostly padding (x of 32 to 43) lengthen: 48 x 21 x 6 x 32 14.3 -> 16.8, 24 x 23 x 6 x 76 17.3 -> 20.3, against 128 x 20 x 6 x 48
+//   20.9 -> 15.9 and, eight planes, 64 x 2 x 6 x 66 17.3 -> 11.6.
+// Never t of 24 to 32, which costs as much as 35 here and one tile of coefficients, not two, there (56 x 28 x 20 x 80 26.2 -> 33.4); from
+// 33 with bytes enough, 64 x 35 x 45 x 76 70.0 -> 54.9, not 80 x 34 x 17 x 66 33.2 -> 36.2.
+// More rounds where they are full and the planes tall: x of 50 to 63, two a CU, 300 x 21 x 28 x 52 54.5 -> 46.7, 1024 x 17 x 28 x 60
+// 165 -> 132, not 300 x 17 x 2 x 32 19.7 -> 27.7; above, two full ones, 128 x 33 x 45 x 80 120.4 -> 104.8 (from HBM 120.4 -> 115.5), 128 x 20
+// x 45 x 67 65.5 -> 50.3, 128 x 21 x 45 x 88 81.9 -> 70.6; not 112 x 17 x 34 x 72 (448 workgroups, 6 to 12 % slower), 128 x 33 x 32 x 72
+// (+2 to +7 %), nor t of 17 to 23 with x of 68 to 80, a fourth group of coefficients for one to four of them (128 x 23 x 45 x 80
+// 73.8 -> 73.1, from HBM 74.9 -> 82.8).
+static bool ebc_one_launch(long long C, int T, int Y, int X) {
+  const long long total = C * T * Y * X;  // (32-bit byte offsets)
+  const bool narrow = X < 64;
+  if (X < 32 || X > 95 || T > (narrow ? 23 : 35) || Y > (narrow ? 31 : kEbcPlaneY) || total > 0x3fffffff) return false;
+  const int PX = ebc_x_groups(X), units = (int)((C + kNumXcd - 1) / kNumXcd) * kNumXcd * PX;
+  if (C * PX < (Y < 32 ? 96 : 192)) return false;
+  const long long chain = T <= 8 ? 0 : X < 36 ? 1000000 : 65000LL * (T - 8);
+  if (narrow)
+    return units <= 256   ? X >= 44 || total >= chain
+           : units <= 512 ? X >= 44 && total >= 2 * chain
+                          : X >= 50 && T > 16 && Y >= 16;
+  if (units <= 256) return T < 24 ? total >= chain : T > 32 && total >= (X < 68 ? 3200000 : 4500000);
+  return Y >= 32 && units >= (X < 68 ? 384 : 481) && units <= 512 &&
+         (T < 24 ? T > 16 && (X < 68 || X > 80) : T > 32 && Y >= 44);
+}
+
 int launch_ebc_band_error(long long C, int T, int Y, int X, const float *err, const float *dense,
                           const double *w, double epsilon, double *ws, double *out,
                           hipStream_t st) {
@@ -945,19 +982,12 @@ int launch_ebc_band_error(long long C, int T, int Y, int X, const float *err, co
     const long long rounds = (g + most - 1) / most;
     return (int)((g + rounds - 1) / rounds);
   };
-  // One launch (ebc_channel_kernel) where its workgroups, one for 16 x coefficients of a channel, are enough and busy.  Whole call, two
-  // launches through memory -> one and the total, us: 128 x 21 x 30 x 52 33.1 -> 21.6, 128 x 11 x 19 x 57 23.0 -> 16.6, 48 x 22 x 24 x
-  // 53 20.9 -> 18.1, 64 x 9 x 20 x 40 15.2 -> 13.6, 64 x 21 x 45 x 64 38.1 -> 32.9, 128 x 33 x 45 x 80 119 -> 104, 48 x 33 x 12 x 78 26.3
-  // -> 25.3.  Not: few workgroups, each a chain of a third of the planes (16 x 21 x 30 x 52 16.4 -> 18.8, 48 x 10 x 40 x 20 14.5 -> 17.7);
-  // short x axes, whose steps are mostly padding (48 x 23 x 11 x 28 14.0 -> 16.6); and longer t or y axes with x below 64, where the
-  // registers leave no room on a CU for the workgroups of S_T (128 x 30 x 23 x 56 34.3 -> 37.1, 128 x 29 x 37 x 39 38.3 -> 45.0, 128 x 40 x
-  // 30 x 52 51.6 -> 88.6).
-  const bool low = Y < 32, wide = X >= 64;  // (2 (Y / 4) + 1 coefficients, X / 2 + 1 folded elements)
-  const int PX = X / 4 / 16 + 1 + (X / 4 + 15) / 16;
-  const int ch_steps = (wide ? 12 : 8) + (low ? 8 : 24) + (T < 24 ? 6 : 18);  // operands of the table (ebc_channel_kernel)
-  const size_t ch_lds = sizeof(double) * std::max(2 * (size_t)(T + Y + X) + 64 * (size_t)ch_steps + (size_t)T * KY * 16,
-                                                  2 * (size_t)T + (T < 24 ? 11 * 12 : 17 * 18));
-  if ((wide ? X <= 80 && T < 36 && Y <= kEbcPlaneY : X >= 32 && T < 24 && low) && C * PX >= (low ? 96 : 192) && total <= 0x3fffffff) {
+  if (ebc_one_launch(C, T, Y, X)) {
+    const bool low = Y < 32, wide = X >= 64;  // (2 (Y / 4) + 1 coefficients, X / 2 + 1 folded elements)
+    const int PX = ebc_x_groups(X);
+    const int ch_steps = (wide ? 12 : 8) + (low ? 8 : 24) + (T < 24 ? 6 : 18);  // operands of the table (ebc_channel_kernel)
+    const size_t ch_lds = sizeof(double) * std::max(2 * (size_t)(T + Y + X) + 64 * (size_t)ch_steps + (size_t)T * KY * 16,
+                                                    2 * (size_t)T + (T < 24 ? 11 * 12 : 17 * 18));
     const int units = (int)((C + kNumXcd - 1) / kNumXcd) * kNumXcd * PX, n_ch = std::min(units, kEbcPartials);
     auto rounds = [](long long n, long long most) -> int {  // workgroups: the fewest equal rounds of no more than `most`
       const long long r = (n + most - 1) / most;

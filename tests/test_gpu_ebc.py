@@ -10,7 +10,7 @@ import torch
 import oracle
 from oracle import ebc_oracle as eo
 from heart_synth import make_generator
-from heart_testlib import gpu, np_gpu, u16
+from heart_testlib import captured_launches, gpu, np_gpu, u16
 
 pytestmark = pytest.mark.gpu
 
@@ -198,3 +198,41 @@ def test_band_error_in_one_launch_with_an_infinite_element(at):
     err[1][at] = np.inf
     got, few = (heart.heart_ebc_band_error(np_gpu(e), np_gpu(np.ones_like(e))).cpu().numpy() for e in (err, err[:3]))
     assert np.array_equal(np.isnan(got[1:5]), np.isnan(few[1:5])) and np.array_equal(np.isinf(got[1:5]), np.isinf(few[1:5])), (got, few)
+
+
+# Which sizes go through one launch (workgroups of 512 threads, and one that adds up) and which through memory (of 256): both sides of
+# each limit of the rule.  Many channels and short chains of planes, or few bytes for long ones, took up to three times as long in one
+@pytest.mark.parametrize("shape,one", [
+    ((1024, 28, 2, 68), False), ((4096, 16, 1, 80), False), ((256, 21, 1, 68), False), ((128, 28, 1, 68), False),
+    ((160, 21, 22, 72), False), ((64, 28, 31, 64), False), ((64, 33, 31, 68), False), ((64, 33, 31, 70), True), ((80, 34, 17, 66), False),
+    ((128, 21, 30, 52), True), ((16, 21, 30, 52), False), ((48, 2, 31, 33), True), ((48, 21, 6, 32), False),
+    ((64, 22, 30, 63), True), ((64, 24, 30, 63), False), ((64, 20, 31, 60), True), ((64, 20, 32, 60), False),
+    ((256, 12, 24, 56), True), ((257, 12, 24, 56), False), ((300, 17, 16, 50), True), ((300, 17, 2, 50), False),
+    ((256, 10, 2, 44), False), ((128, 20, 1, 44), True), ((128, 20, 1, 43), False), ((128, 20, 20, 31), False),
+    ((31, 8, 5, 66), False), ((32, 8, 5, 66), True), ((64, 23, 48, 95), True), ((64, 23, 48, 96), False),
+    ((64, 23, 49, 95), False), ((64, 35, 48, 79), True), ((64, 36, 48, 79), False), ((24, 23, 6, 76), False),
+    ((128, 33, 45, 80), True), ((112, 33, 45, 80), False), ((128, 21, 45, 88), True), ((128, 21, 45, 76), False),
+    ((128, 20, 45, 67), True), ((96, 20, 45, 67), False)])
+def test_band_error_route(shape, one):
+    import paper_2605_14513_amd as heart
+
+    err = torch.zeros(shape, device="cuda")
+    ws = torch.empty(heart.heart_ebc_workspace_bytes(*shape), dtype=torch.uint8, device="cuda")
+    out = torch.empty(6, dtype=torch.float64, device="cuda")
+
+    def call():
+        heart.heart_ebc_band_error(err, err, workspace=ws, out=out)
+
+    call()  # (attributes of a kernel are set on its first call)
+    print("ebc route", shape, flush=True)
+    assert captured_launches(call)[0][1] == (512 if one else 256)
+
+
+# each instantiation of the one launch with all its tiles filled: t, y and x at the ends of what it takes, more planes than wavefronts,
+# a middle that pairs with itself and one that does not; more workgroups than a round, a second group of coefficients for a workgroup,
+# two full rounds, channels that are no multiple of 8
+@pytest.mark.parametrize("shape", [(48, 23, 31, 63), (49, 22, 30, 62), (32, 23, 31, 79), (30, 22, 31, 80), (64, 4, 2, 77), (32, 23, 31, 95),
+                                   (48, 33, 31, 67), (63, 35, 30, 94), (64, 23, 48, 95), (64, 22, 47, 67), (64, 35, 48, 95),
+                                   (64, 34, 47, 68), (300, 17, 16, 50), (523, 18, 17, 51), (128, 33, 44, 76)])
+def test_band_error_in_one_launch_with_full_tiles(shape):
+    test_band_error_in_one_launch(shape)
