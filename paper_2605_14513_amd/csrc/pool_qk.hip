@@ -337,16 +337,26 @@ template <int D>
 constexpr int kSmallCols = D == 64 ? 2048 : 1024;
 static_assert(kSmallNb <= kMeanThreads / (128 / 4), "at most one block a slice of the token means");
 static_assert(kSmallCols<64> <= kSmallMeans && kSmallCols<64> / 64 <= kSmallMarks, "LDS");
-// From where pool_blocks_kernel<D, true> is the better one: more bytes of Q and K than the 256 MiB of the memory-side cache.
-// heart_pool_qk with plain stores in block order -> written through in runs, us: D = 128, blocks of 128, H x N = 40 x 32760
-// 113.5 -> 107.8, 24 x 119056 250 -> 234.5 (5.8 -> 6.2 TB/s), 20 x 32760 58.2 -> 56.9; blocks of 64 116.5 -> 110.2; D = 64,
-// 80 x 32760 113.3 -> 104.4, 48 x 119056 244 -> 227.7; at the cache's size 16 x 32760 47.0 -> 46.6, and below it 13 x 32760 38.3
-// -> 39.1, 28 x 32760 of D = 64 40.1 -> 40.6 and a call of 10 heads of 101 blocks 0.5 us more (there the token means find the
-// plain stores in an L2).  Written through in block order 110.4 and 236.4; plain stores with a contiguous eighth of the
-// blocks on each XCD 110.5 and 244.
-// Runs of 64, 128, 256 KB: 110.4, 107.3, 109.4 and 242.5, 235.4, 235.8.  Rows of D = 64 between those of other heads gain
-// nothing (82.6 -> 83.1, four items of 24 heads of 20000 tokens); with D = 128 they do (115.2 -> 113.4).
-constexpr long long kStreamBytes = 256LL << 20;
+// Whether pool_blocks_kernel<D, true> is the better one: where Q and K are more bytes than the 256 MiB of the memory-side cache, and
+// one and a half times as many with blocks of 32 KB, which write half as many means.  heart_pool_qk with plain stores in block order ->
+// written through in runs, us: D = 128, blocks of 128, H x N = 40 x 32760 113.5 -> 107.8, 24 x 119056 250 -> 234.5 (5.8 -> 6.2 TB/s),
+// 24 x 32760 (383 MiB) 73.7 -> 72.0, but three items of 40 x 5000 (292) 60.1 -> 60.4, five of 8 x 16000 (312) 57.0 -> 57.5; blocks of 64
+// 40 x 32760 116.5 -> 110.2, 22 items of 8 x 3000 (257) 59.5 -> 57.2; D = 64, 80 x 32760 113.3 -> 104.4, 48 x 119056 244 -> 227.7, 99
+// items of 12 x 1000 (290) 60.3 -> 58.6; below the cache's size 13 x 32760 38.3 -> 39.1, 28 x 32760 of D = 64 40.1 -> 40.6 and a call of
+// 10 heads of 101 blocks 0.5 us more (there the token means find the plain stores in an L2).  Written through in block order 110.4 and
+// 236.4; plain stores with a contiguous eighth of the blocks on each XCD 110.5 and 244.
+// Runs of 64, 128, 256 KB: 110.4, 107.3, 109.4 and 242.5, 235.4, 235.8.
+// Rows between those of other heads: of D = 64 nothing is gained (82.6 -> 83.1, four items of 24 heads of 20000 tokens).  Of D = 128 long
+// heads gain from 480 MiB on (40 x 32760 116.6 -> 114.0, two items of 24 x 32760 140.8 -> 134.5; 17 x 32760 50.5 -> 51.7, two of 10 x 32760
+// 58.1 -> 59.5, eight of 40 x 3000 (468 MiB) 95.6 -> 96.2), with blocks of 64 from 256 (12 of 8 x 8191 75.2 -> 70.0, three of 24 x 8191
+// 57.3 -> 56.3).  Short heads lose more often than they gain: 105 items of 40 x 130 87.7 -> 93.5, 46 of 40 x 500 86.5 -> 91.8, 27 of 40 x
+// 500 in blocks of 64 55.1 -> 57.2, 17 of 40 x 1000 62.2 -> 63.5, against 638 of 8 x 257 144.8 -> 138.8.
+static bool pool_streams(const heart_shape &s) {
+  const long long bytes = 4LL * s.B * s.H * s.N * s.D, MiB = 1LL << 20;
+  const bool small = s.block * s.D <= 8192;
+  if (s.q_stride[2] == s.D && s.k_stride[2] == s.D) return bytes > (small ? 256 : 384) * MiB;
+  return s.D == 128 && s.N >= 2000 && bytes > (small ? 256 : 480) * MiB;
+}
 constexpr int kRunBytes = 128 * 1024;
 template <int D>
 static int launch_pool_t(const heart_shape &s, const uint16_t *qp, const uint16_t *kp, float *qblk,
@@ -363,8 +373,7 @@ static int launch_pool_t(const heart_shape &s, const uint16_t *qp, const uint16_
     return check_launch("pool_drift_small_kernel");
   }
   const dim3 grid((unsigned)nwg), blk(kPoolThreads), grid2((unsigned)(2 * s.B * s.H)), blk2(kMeanThreads);
-  const bool stream = 4LL * s.B * s.H * s.N * D > kStreamBytes &&
-                      (D == 128 || (s.q_stride[2] == D && s.k_stride[2] == D));
+  const bool stream = pool_streams(s);
   int run = 2;
   while ((s.block * D * 2) << run < kRunBytes) ++run;
   hipLaunchKernelGGL((stream ? pool_blocks_kernel<D, true> : pool_blocks_kernel<D, false>), grid, blk, 0, st, qp, kp,

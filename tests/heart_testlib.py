@@ -184,8 +184,8 @@ class OracleChain:
         return d, r
 
 
-def captured_launches(fn):
-    """(workgroups, threads of one) of every kernel that fn enqueues, in order: fn is captured, not run."""
+def _captured_kernels(fn):
+    """The launch parameters of every kernel that fn enqueues, in order: fn is captured, not run."""
     path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
     hip = ctypes.CDLL(path)  # (the one that is loaded)
 
@@ -206,5 +206,15 @@ def captured_launches(fn):
         kind, p = ctypes.c_int(-1), Params()
         assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0 and kind.value == 0  # kernels only
         assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
-        out.append((p.grid[0] * p.grid[1] * p.grid[2], p.block[0] * p.block[1] * p.block[2]))
+        out.append(p)
     return out
+
+
+def captured_launches(fn):
+    """(workgroups, threads of one) of every kernel that fn enqueues, in order: fn is captured, not run."""
+    return [(p.grid[0] * p.grid[1] * p.grid[2], p.block[0] * p.block[1] * p.block[2]) for p in _captured_kernels(fn)]
+
+
+def captured_functions(fn):
+    """Which kernels fn enqueues, in order (a value a kernel, equal for equal kernels): fn is captured, not run."""
+    return [p.func for p in _captured_kernels(fn)]
