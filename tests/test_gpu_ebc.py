@@ -124,7 +124,8 @@ def test_thresholds_calibrated_on_the_tiny_workload():
 
 
 # t and y axes that one launch contracts together, at the ends of its tiles (16 rows; 15 / 17 and 31 coefficients at 31 / 32
-# and 63 elements) and on either side of the longest axes it takes (63 and 48; up to 64 x 64 besides); more planes than wavefronts
+# and 63 elements) and on either side of the longest axes it takes (63 and 48; up to 64 x 64 besides); more planes
+# than wavefronts (300 x 3 x 5 x 62: test_band_error_route pins that it comes this way)
 @pytest.mark.parametrize("shape", [(3, 16, 63, 9), (2, 17, 32, 7), (5, 63, 63, 5), (1, 64, 63, 4), (1, 63, 64, 4),
                                    (2, 31, 31, 3), (1, 33, 1, 64), (300, 3, 5, 62),
                                    (3, 63, 48, 5), (2, 64, 48, 5), (2, 63, 49, 5), (1, 16, 47, 9)])
@@ -168,7 +169,7 @@ def test_band_error_with_an_infinity(shape):
     assert np.isnan(got[[0, 2, 3, 4]]).all() and np.isfinite(got[5]), got
 
 
-# the path of one launch: axes around its limits (x of 32 to 80 elements, t of 23 and 24, 35 and 36, y of 31 and 32, 48 and 49), even and
+# axes around the limits of the path of one launch, on either side (test_band_error_route says which take it; x of 32 to 80 elements, t of 23 and 24, 35 and 36, y of 31 and 32, 48 and 49), even and
 # odd ones, whose middle pairs with itself or with its neighbour, axes of one and two elements, channels that are no multiple of 8
 @pytest.mark.parametrize("shape", [(48, 1, 1, 32), (48, 2, 31, 33), (49, 23, 30, 63), (50, 3, 5, 47), (33, 24, 31, 64), (64, 35, 48, 79),
                                    (64, 23, 32, 80), (24, 22, 3, 65), (257, 4, 2, 77), (48, 24, 31, 63), (64, 36, 49, 64)])
@@ -212,7 +213,8 @@ def test_band_error_in_one_launch_with_an_infinite_element(at):
     ((31, 8, 5, 66), False), ((32, 8, 5, 66), True), ((64, 23, 48, 95), True), ((64, 23, 48, 96), False),
     ((64, 23, 49, 95), False), ((64, 35, 48, 79), True), ((64, 36, 48, 79), False), ((24, 23, 6, 76), False),
     ((128, 33, 45, 80), True), ((112, 33, 45, 80), False), ((128, 21, 45, 88), True), ((128, 21, 45, 76), False),
-    ((128, 20, 45, 67), True), ((96, 20, 45, 67), False)])
+    ((128, 20, 45, 67), True), ((96, 20, 45, 67), False), ((300, 3, 5, 62), False), ((700, 5, 6, 33), False),
+    ((300, 3, 33, 62), False)])
 def test_band_error_route(shape, one):
     import paper_2605_14513_amd as heart
 
@@ -236,3 +238,30 @@ def test_band_error_route(shape, one):
                                    (64, 34, 47, 68), (300, 17, 16, 50), (523, 18, 17, 51), (128, 33, 44, 76)])
 def test_band_error_in_one_launch_with_full_tiles(shape):
     test_band_error_in_one_launch(shape)
+
+
+# more planes than the 4096 wavefronts of the launch that contracts over y and t, with a second tile of y coefficients
+def test_band_error_of_many_planes_of_two_tiles():
+    test_band_error_of_planes((300, 3, 33, 62))
+
+
+# a value that is not finite leaves the same energies infinite and not a number as on the path of few channels, for each instantiation
+# of the one launch: at the ends and the middle of the axes, where folding pairs elements, and within
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("shape", [(48, 23, 31, 63), (48, 22, 30, 62), (32, 23, 31, 79), (64, 23, 48, 67), (48, 33, 31, 67), (64, 35, 48, 80)])
+def test_band_error_in_one_launch_with_a_value_that_is_not_finite(shape, value):
+    import paper_2605_14513_amd as heart
+
+    C, T, Y, X = shape
+    rng = np.random.default_rng(sum(shape))
+    base = np.zeros(shape, dtype=np.float32)
+    base[:3] = rng.standard_normal((3, T, Y, X))
+    dense = np_gpu(np.ones_like(base))
+    for at in ((0, 0, 0), (T - 1, Y - 1, X - 1), (T // 2, Y // 2, X // 2), (1, 0, X - 1), (T // 2, 3, 0), (2, Y // 2, 5)):
+        err = base.copy()
+        err[(1,) + at] = value
+        print("ebc", shape, value, at, flush=True)
+        got = heart.heart_ebc_band_error(np_gpu(err), dense).cpu().numpy()
+        few = heart.heart_ebc_band_error(np_gpu(err[:3]), dense[:3].contiguous()).cpu().numpy()
+        for same in (np.isnan, np.isposinf, np.isneginf):
+            assert np.array_equal(same(got[:5]), same(few[:5])), (at, got, few)
