@@ -18,10 +18,10 @@
 //    all that is ever computed or stored of it: no transform, no projected tensor.
 //    The contractions run on the fp64 matrix cores (v_mfma_f64_16x16x4_f64: 16 coefficients
 //    of 16 lines, four elements of the lines a step); the sums of squares are taken from the
-//    accumulators and reduced in a fixed order.  One launch and the total where there are enough channels:
+//    accumulators and reduced in a fixed order.  One launch and the total where its workgroups fill the chip once (ebc_one_launch):
 //      ebc_channel everything: a channel's planes from the tensor to S_XY and S_XYT, |err|^2 and S_T, |dense|^2 in its workgroups
 //      ebc_total  one workgroup adds up
-//    or, of few channels and short axes, two launches with the x coefficients between them:
+//    or two launches with the x coefficients between them:
 //      ebc_first  x coefficients of err with |err|^2, S_T of err, |dense|^2
 //      ebc_plane  y and t coefficients of the x coefficients with S_XY and S_XYT; its last workgroup adds everything up
 //    or, where t is longer than 63 or y than 48, in the place of the second
@@ -69,8 +69,7 @@ __device__ __forceinline__ void ebc_table(int n, double *tab) {
   __syncthreads();
 }
 
-// sum over the workgroup in a fixed order, valid in thread 0; red: a double of LDS per wavefront
-template <int kThreads = kEbcThreads>
+// sum over the workgroup in a fixed order, valid in thread 0; red: kEbcWaves doubles of LDS
 __device__ __forceinline__ double ebc_block_sum(double v, double *red) {
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
@@ -79,7 +78,7 @@ __device__ __forceinline__ double ebc_block_sum(double v, double *red) {
   __syncthreads();
   double s = red[0];
 #pragma unroll
-  for (int w = 1; w < kThreads / 64; ++w) s += red[w];
+  for (int w = 1; w < kEbcWaves; ++w) s += red[w];
   return s;
 }
 
@@ -247,20 +246,19 @@ __device__ __forceinline__ void ebc_tile(EbcBatch<TIn> &cur, const EbcTile<TIn> 
 // or of the next tile, are always in flight, those of the first while the table is made: a line is
 // short, and a wavefront that waited for every load would do nothing else.
 // A unit of work is a tile of lines, or (kShared) every share-th pair of its coefficient tiles.
-template <bool kShared, typename TIn, bool kUnit, bool kStore, bool kSumIn, int kThreads = kEbcThreads>
+template <bool kShared, typename TIn, bool kUnit, bool kStore, bool kSumIn>
 __device__ __forceinline__ void ebc_contract(const TIn *__restrict__ in, double *__restrict__ out,
                                              const EbcLines &L, int blk, int n_blk, double *tab,
                                              double &e_out, double &e_in) {
   const int wave = threadIdx.x >> 6;
   const int K = ebc_coefs(L.n), KT = (K + 15) / 16, share = kShared ? L.share : 1;
   const long long units = (L.lines + kEbcTileCols - 1) / kEbcTileCols * share;
-  constexpr int kWaves = kThreads / 64;
-  const long long first = (long long)blk * kWaves + wave, stride = (long long)n_blk * kWaves;
+  const long long first = (long long)blk * kEbcWaves + wave, stride = (long long)n_blk * kEbcWaves;
   auto tile_of = [&](long long u) -> long long { return kShared ? ebc_div(u, share) : u; };
   EbcTile<TIn> t = ebc_tile_at<TIn, kUnit>(in, L, tile_of(first));
   EbcBatch<TIn> cur;
   ebc_load<TIn, kUnit>(cur, t, L, 0);
-  ebc_table<kThreads>(L.n, tab);
+  ebc_table(L.n, tab);
   for (long long u = first; u < units; u += stride) {
     const EbcTile<TIn> next = ebc_tile_at<TIn, kUnit>(in, L, tile_of(u + stride));  // (past the end: no line exists)
     int kt = kShared ? 2 * (int)(u - tile_of(u) * share) : 0;
@@ -742,7 +740,7 @@ __global__ __launch_bounds__(kEbcChThreads, W == 1 ? 4 : 2) void ebc_channel_ker
   // and every fourth; e_j and e_(X-j).  Rows past the end are out of range for the descriptor and arrive as zeros; what is loaded for
   // an element past the last, and as the mirror image of one that has none, is not used.
   // (All steps are taken, of zeros where there are no elements: a branch a step kept the operands' reads behind it.)
-  const int folded = X / 2 + 1, whole = min(folded / 16, W);
+  const int folded = X / 2 + 1;  // (16 W <= folded <= 16 W + 16: see ebc_one_launch)
   const uint32_t plane = (uint32_t)(Y * X) * 4u;
   constexpr uint32_t kNowhere = 0x7fff0000u;
   struct Fold {
@@ -756,8 +754,8 @@ __global__ __launch_bounds__(kEbcChThreads, W == 1 ? 4 : 2) void ebc_channel_ker
         const_cast<float *>(err) + (long long)(ok ? c : 0) * T * Y * X + (long long)(ok ? t : 0) * Y * X, 0, ok ? (int)plane : 0, 0x00020000);
     const uint32_t row = y < Y ? (uint32_t)(y * X) * 4u : kNowhere;
     // (the mirror image of j = 0 would be the element behind the row: those of 1 to 3 are loaded with the one before them)
-    const uint32_t ahead = row + 16u * g, back = row + 4u * (X - 3) - 16u * g, single = row + 4u * (16 * whole + g),
-                   single_back = row + 4u * (X - 16 * whole - g);
+    const uint32_t ahead = row + 16u * g, back = row + 4u * (X - 3) - 16u * g, single = row + 4u * (16 * W + g),
+                   single_back = row + 4u * (X - 16 * W - g);
 #pragma unroll
     for (int u = 0; u < W; ++u) {
       const bool first = u == 0 && g == 0;
@@ -809,7 +807,7 @@ __global__ __launch_bounds__(kEbcChThreads, W == 1 ? 4 : 2) void ebc_channel_ker
     const bool in_x = fx <= rx;
     const double wx = fx > 0 ? 2.0 : 1.0, sign = sine ? -1.0 : 1.0;
     for (int i = wave; i < SX; i += kEbcChWaves) {
-      const int j = i < 4 * whole ? 16 * (i / 4) + 4 * g + i % 4 : i < 4 * W ? 0 : 16 * whole + 4 * (i - 4 * W) + g;
+      const int j = i < 4 * W ? 16 * (i / 4) + 4 * g + i % 4 : 16 * W + 4 * (i - 4 * W) + g;
       op_x[64 * i + lane] = tab_x[(sine ? X : 0) + ebc_mod((in_x ? fx : 0) * j, X, rx1)];
     }
     __syncthreads();
@@ -839,9 +837,9 @@ __global__ __launch_bounds__(kEbcChThreads, W == 1 ? 4 : 2) void ebc_channel_ker
 #pragma unroll
       for (int u = 0; u < W; ++u)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) step(4 * u + i, 16 * u + 4 * g + i, u < whole);
+        for (int i = 0; i < 4; ++i) step(4 * u + i, 16 * u + 4 * g + i, true);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) step(4 * W + i, 16 * whole + 4 * i + g, 16 * whole + 4 * i + g < folded);
+      for (int i = 0; i < 4; ++i) step(4 * W + i, 16 * W + 4 * i + g, 16 * W + 4 * i + g < folded);
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
