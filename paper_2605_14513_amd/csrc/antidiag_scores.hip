@@ -15,7 +15,8 @@
 // (v_mfma_f32_16x16x32_bf16), MFMA-bound, and bound by power while a full chip works: matrix instructions alone, operands N(0, 1) in
 // registers, sustain 1710 to 1800 TFLOP/s as 32x32x16 and 2020 to 2190 as 16x16x32 (half as many accumulator reads and writes a
 // FLOP), most where consecutive ones add to the same accumulator (one by one 2050, two 2165, four 2160).  With the same tiles and the
-// same operand reads estimator and selection of 40 heads of 32760 tokens take 645 us with 32x32x16 and 613 with this (the same bits).
+// same operand reads estimator and selection of 40 heads of 32760 tokens take 645 us with 32x32x16 and 613 with this (the same bits;
+// under counters 8.8 million active cycles at 1.85 GHz and 9.3 at 2.02).
 //
 // Kernel 1 (antidiag_tile): one workgroup (8 wavefronts) per 256 x 256 tile of L (128 FLOP
 //   per operand byte, which keeps the operand stream from L2 below what it delivers), or (4) per 128 x 128.  The
@@ -332,7 +333,10 @@ __global__ __launch_bounds__(2 * kTile, 2) void antidiag_tile_kernel(
     }
   } else {
     // (the same in tiles of 32: with few tiles power is not what counts, and reads and small MFMAs get in each other's way: six heads of
-    // 5000 tokens 25.5 us, 26.6 with the tiles of 16; 24 heads of 6400 37.3, 40.0)
+    // 5000 tokens 25.5 us, 26.6 with the tiles of 16; 24 heads of 6400 37.3, 40.0.  In large tiles, which short launches take too, that
+    // is next to nothing: tile kernel and combine with the tiles of 16 in place of these, one round of 144 to 256 workgroups 23.0 ->
+    // 23.3, 57.9 -> 58.1, 69.4 -> 69.4, 67.4 -> 66.3, 61.8 -> 57.6 us, two 60 of nine 137.2 -> 139.1, 8 of 64 124.1 -> 123.2, half the depth
+    // 69.5 -> 65.5, ten 612 -> 595: from 2 % more to 7 % less, and the more tiles a head has the less)
     const int l32 = lane & 31, hf = lane >> 5;
     // fragment of contraction step ks (16 elements) of tile row 32 x + l32: chunk 2 ks + hf
     uint32_t foff[4];
@@ -539,14 +543,17 @@ int launch_antidiag(const heart_shape &s, const void *q, const void *k, int stri
   if (dev < 0) return fail(HEART_EHIP, "heart_scores_antidiag: cannot identify the current device");
   // Tiles of 128 x 128, two workgroups a CU, where they fill the chip better: a round of them takes 0.5 to 0.6 of the
   // time of a round of 256 x 256, which move half the operand bytes per FLOP but come one to a CU.  Measured (tile and
-  // combine kernel, 256 -> 128): 13 heads of one tile 47 -> 22.5 us, one head of 64 tiles 49 -> 29, 14 of nine 54 -> 40,
-  // 8 of 36 62 -> 52; 20 of nine 57 -> 58, 12 of 64 182 -> 212, 40 of 64 629 -> 795.  (The same bits.)  Three rounds in the place
-  // of two: 1.16 times as fast with 16 stages, 0.96 to 1.04 with 32 (D = 128, stride 16); four of three 1.11 to 1.23.
+  // combine kernel, 256 -> 128, heads of tiles of 32 stages: D = 128, stride 16): 13 heads of one tile 44.8 -> 20.5 us, one head of 64
+  // tiles 45.2 -> 24.1, 13 of nine 45.5 -> 38.0; 20 of nine 62.9 -> 77.0, 12 of 64 184 -> 229, 40 of 64 595 -> 763.  (The same bits.)  Three
+  // rounds in the place of two are 0.92 to 1.08 times as fast with 32 stages (8 of 36 99.1 -> 106.6, 30 of nine 107.5 -> 114.9, 24 of 16
+  // 120.6 -> 120.8, 31 of nine 113.2 -> 109.6, 300 of one 168.8 -> 156.8), 0.98 to 1.08 with 16 (10 of 36 59.1 -> 60.4, 30 of nine 59.0 ->
+  // 59.6, 8 of 36 57.1 -> 53.6, 300 of one 97.1 -> 90.4), 1.01 to 1.14 with 8; four of three 0.96 to 1.09 (57 of nine 131.3 -> 137.0, 33 of 16
+  // 146.4 -> 138.3), 1.00 to 1.12 with 16.
   const int n_cu = cu_count(dev);
   if (n_cu <= 0) return fail(HEART_EHIP, "heart_scores_antidiag: cannot query the number of CUs");
   // Only the device knows how many heads `refresh` names, so small tiles then have to be the better ones for any number of
-  // them, that is for the most heads of every number of rounds of large ones (30 heads of nine tiles, of which 16 refresh: 52
-  // us, 59 with small tiles, which are better for all 30).
+  // them, that is for the most heads of every number of rounds of large ones (30 heads of nine tiles, of which 16 refresh: 59
+  // us, 73 with small tiles, at half the depth better for all 30 or as good).
   const long long large_h = (long long)MT2 * MT2, small_h = (long long)((M + 127) / 128) * MT;  // tiles of a head
   auto rounds = [](long long n, long long places) { return (n + places - 1) / places; };
   bool few = true;
