@@ -16,7 +16,7 @@
 // registers, sustain 1710 to 1800 TFLOP/s as 32x32x16 and 2020 to 2190 as 16x16x32 (half as many accumulator reads and writes a
 // FLOP), most where consecutive ones add to the same accumulator (one by one 2050, two 2165, four 2160).  With the same tiles and the
 // same operand reads estimator and selection of 40 heads of 32760 tokens take 645 us with 32x32x16 and 613 with this (the same bits;
-// under counters 8.8 million active cycles at 1.85 GHz and 9.3 at 2.02).
+// under counters the tile kernel has 1.10 million active cycles at 1.85 GHz and 1.16 at 2.02).
 //
 // Kernel 1 (antidiag_tile): one workgroup (8 wavefronts) per 256 x 256 tile of L (128 FLOP
 //   per operand byte, which keeps the operand stream from L2 below what it delivers), or (4) per 128 x 128.  The
